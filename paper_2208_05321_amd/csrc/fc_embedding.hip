@@ -441,6 +441,7 @@ static int ensure_sort(SortBufs& sb, int64_t n) {
 // radix_sort with the buffers of sb, keeping track of which of its two supertile tables is clean
 static int sort_in(SortJob& j, SortBufs& sb, hipStream_t st, const int32_t** kres, const int32_t** vres) {
     j.keysA = sb.keysA; j.valsA = sb.valsA; j.keysB = sb.keysB; j.valsB = sb.valsB; j.ghist = sb.ghist; j.dtot = sb.dtot;
+    if (sort_small_fits(j)) return sort_small(j, st, kres, vres);      // uses no tables
     int64_t dirtied = 0;
     if (sb.stot[0] && sb.stot[1] && sb.dirty[sb.zset] > 0) {     // only after a failed sort: the table to use is not known to be clean
         FC_HIP(hipMemsetAsync(sb.stot[sb.zset], 0, (size_t)SORT_STOT_WORDS * 4, st));

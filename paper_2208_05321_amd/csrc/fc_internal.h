@@ -33,6 +33,12 @@ constexpr int BWD_CHUNK = FC_BWD_CHUNK;
 // Gradient rows a row-group keeps in flight while it walks its chunk.
 constexpr int BWD_PF = FC_BWD_PF;
 
+// Small batches (fc_small.hip): one workgroup does the index work / the sort.
+constexpr int SMALL_MAX_IDS = 4096;
+constexpr int SMALL_MAX_WORDS = 32768;            // rank bitmap in LDS: up to 1,048,576 rows (128 KB)
+constexpr int SMALL_MAX_SLOTS = 65536;            // slot bitmap in LDS: 8 KB
+constexpr int SMALL_POS_BITS = 12, SMALL_KEY_BITS = 32 - SMALL_POS_BITS;
+
 // Sticky device-side flags.
 enum : uint32_t { EF_BAD_OFFSETS = 1u, EF_ID_RANGE = 2u, EF_BAD_SLOT = 4u,
                   EF_NOT_ONE_PER_BAG = 8u };   // not an error: some bag of the batch does not hold exactly its own lookup
@@ -46,12 +52,11 @@ struct Ctl {
     int32_t n_unique, n_miss, need;
 };
 
-// Host-visible (pinned, mapped) copy of the decision, written by the planning kernel.
-struct HostCtl {
-    int32_t status, n_unique, n_miss, need, hit_ids, nfree, async_flags;
-    int32_t batch_flags; // EF_NOT_ONE_PER_BAG
-    int32_t ticket;      // written last: number of the cache_prepare call this record belongs to
-};
+// Host-visible (pinned, mapped) copy of the decision, written by the planning kernel: every word carries the number of the
+// cache_prepare call it belongs to and is stored in one piece, so that the host recognises a complete record by itself and
+// the kernel need not fence (a system-scope fence in the middle of a kernel costs microseconds).
+enum HostWord { HW_STATUS = 0, HW_UNIQUE, HW_MISS, HW_NEED, HW_HITS, HW_NFREE, HW_ASYNC_FLAGS, HW_BATCH_FLAGS, HOST_REC_WORDS };
+struct HostCtl { uint64_t word[HOST_REC_WORDS]; };       // value in the low half, ticket in the high half
 
 enum ProfItem {
     P_REMAP_MARK = 0, P_RANK_COUNT, P_RANK_PLAN, P_RANK_EMIT, P_EVICT_GATHER, P_EVICT_STORE, P_FREE_COUNT, P_FREE_PICK,
@@ -373,7 +378,31 @@ struct SortJob {
 };
 int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres);
 
+// ---- small batches (fc_small.hip) ----
+bool sort_small_fits(const SortJob& j);
+int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres);
+bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags);
+// slots == nullptr: the ranks go to rbuf and the slot write-out is left to the caller
+int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
+                         int32_t* slots, int32_t ticket, const int32_t* landed_ranks, int64_t landed, int64_t landed_base,
+                         int transit_base);
+
 // ---- device helpers ----
+// bag of lookup i: the largest b with offsets[b] <= i
+__device__ __forceinline__ int bag_of(const int64_t* __restrict__ offsets, int num_bags, int i) {
+    int lo = 0, hi = num_bags;
+    while (hi - lo > 1) {
+        const int mid = (int)(((int64_t)lo + hi) >> 1);
+        if (offsets[mid] <= i) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+// the same, first guess: one lookup per bag
+__device__ __forceinline__ int bag_of_lookup(const int64_t* __restrict__ offsets, int num_bags, int i) {
+    const int g = min(i, num_bags - 1);
+    return (offsets[g] <= i && i < offsets[g + 1]) ? g : bag_of(offsets, num_bags, i);
+}
+
 template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT/64 ints */) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -395,6 +424,15 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT
     __syncthreads();
     total = tot;
     return wbase + x - v;
+}
+
+// The planning record: lanes 0 .. HOST_REC_WORDS-1 of one wavefront store one word each, 64 consecutive bytes together.
+__device__ __forceinline__ void report_to_host(HostCtl* h, int ticket, int status, int uniq, int miss, int need, int hits, int nfree,
+                                               int async_flags, int batch_flags, int lane) {
+    const int v = lane == HW_STATUS ? status : lane == HW_UNIQUE ? uniq : lane == HW_MISS ? miss : lane == HW_NEED ? need
+                : lane == HW_HITS ? hits : lane == HW_NFREE ? nfree : lane == HW_ASYNC_FLAGS ? async_flags : batch_flags;
+    if (lane < HOST_REC_WORDS)
+        __hip_atomic_store(&h->word[lane], (uint64_t)(uint32_t)v | (uint64_t)(uint32_t)ticket << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __device__ __forceinline__ int wave_sum(int x) {

@@ -256,12 +256,10 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(const int32_t* __res
         const int nf = status == FC_OK ? nfree + need - M : nfree;
         ctl->nfree = nf;
         ctl->err_flags = 0;
-        hctl->status = status; hctl->n_unique = totU; hctl->n_miss = M; hctl->need = need;
-        hctl->hit_ids = hits; hctl->nfree = nf; hctl->async_flags = (int32_t)ctl->async_flags;
-        hctl->batch_flags = (int32_t)(ef & EF_NOT_ONE_PER_BAG);
-        __threadfence_system();                       // the record first, then the ticket the host is polling for
-        *reinterpret_cast<volatile int32_t*>(&hctl->ticket) = ticket;
     }
+    if (tid < HOST_REC_WORDS)
+        report_to_host(hctl, ticket, status, totU, M, need, hits, status == FC_OK ? nfree + need - M : nfree, (int)ctl->async_flags,
+                       (int)(ef & EF_NOT_ONE_PER_BAG), tid);
 }
 
 constexpr int FREE_TILE = 1024;
@@ -644,6 +642,16 @@ static int wait_for_ticket(const volatile int32_t* ticket_word, int32_t ticket, 
     return *ticket_word == ticket ? FC_OK : FC_ERR_HIP;
 }
 
+// The planning record, word by word (see HostCtl); usually all eight words are there once the last one is.
+static int wait_for_record(const HostCtl* rec, int32_t ticket, hipStream_t st, int32_t* out) {
+    for (int k = HOST_REC_WORDS - 1; k >= 0; --k) {
+        const volatile uint64_t* word = &rec->word[k];
+        FC_TRY(wait_for_ticket(reinterpret_cast<const volatile int32_t*>(word) + 1, ticket, st));
+        out[k] = (int32_t)(uint32_t)*word;
+    }
+    return FC_OK;
+}
+
 // Index half of Algorithm 1: every decision (unique rows, misses, victims, slot assignment, both maps, the slots
 // of the batch) and no row movement.  Fills *mv with what prepare_move has to do.
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n) {
@@ -687,57 +695,65 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
         if (!c->dirty_track) c->vrank = c->vrank_buf[buf];
         transit_base = (int)(buf * c->staging_rows);
     }
-    const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
-    int64_t nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
-    if (nmark > MARK_MAX_BLOCKS) nmark = MARK_MAX_BLOCKS;
-    const int64_t per_block = cdiv(cdiv(work, nmark), MARK_THREADS) * MARK_THREADS;
-    nmark = cdiv(work, per_block);
-    const int64_t words = c->NB * RT_WORDS;
-    {
-        ProfScope ps(c, P_REMAP_MARK, st);
-        k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
-                                                              c->rbits, c->rbuf, c->ctl, c->hitpart, (int)per_block,
-                                                              (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
-    }
-    {
-        ProfScope ps(c, P_RANK_COUNT, st);
-        k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((const uint4*)c->ubits, (const uint4*)c->rbits, (const uint4*)c->pbits,
-                                                            protect_prev, c->bsum, (int)c->NB,
-                                                            c->dma_evict ? c->vrank_buf[buf] : nullptr, (int)landed,
-                                                            (int)(buf * c->staging_rows), c->rank_slot);
-    }
-    {
-        ProfScope ps(c, P_RANK_PLAN, st);
-        k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(c->bsum, (int)c->NB, (int)c->C, c->ctl, c->hctl, c->moff, c->vtake, c->voff, c->hitpart, (int)nmark, ticket);
-    }
-    // Last batch's evicted rows must have reached the host table before the victim lists and the block buffer
-    // are reused and before any of those rows could be fetched again; the kernels above do not care.
-    if (c->evict_pending) {
-        FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
-        c->evict_pending = false;
-    }
-    {
-        ProfScope ps(c, P_RANK_EMIT, st);
-        k_rank_emit<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubits, (uint4*)c->rbits, (uint4*)c->pbits, protect_prev, c->ctl,
-                                                           c->moff, c->vtake, c->voff,
-                                                           c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, (int)c->C,
-                                                           c->dirty_track ? -1 : transit_base, (int)c->staging_rows,
-                                                           c->dma_evict ? c->fill_src : nullptr);
+    const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
+    const bool small_slots = small && !defer_slots && !before_slots;     // its one kernel may write the caller's buffer, too
+    const int transit = c->dirty_track ? -1 : transit_base;
+    const int32_t* landed_ranks = c->dma_evict ? c->vrank_buf[buf] : nullptr;
+    if (small) {
+        if (c->evict_pending) {        // as below
+            FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
+            c->evict_pending = false;
+        }
+        FC_TRY(launch_prepare_small(c, st, ids, n, offsets, num_bags, small_slots ? slots : nullptr, ticket, landed_ranks, landed,
+                                    buf * c->staging_rows, transit));
+    } else {
+        const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
+        int64_t nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
+        if (nmark > MARK_MAX_BLOCKS) nmark = MARK_MAX_BLOCKS;
+        const int64_t per_block = cdiv(cdiv(work, nmark), MARK_THREADS) * MARK_THREADS;
+        nmark = cdiv(work, per_block);
+        const int64_t words = c->NB * RT_WORDS;
+        {
+            ProfScope ps(c, P_REMAP_MARK, st);
+            k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
+                                                                  c->rbits, c->rbuf, c->ctl, c->hitpart, (int)per_block,
+                                                                  (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
+        }
+        {
+            ProfScope ps(c, P_RANK_COUNT, st);
+            k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((const uint4*)c->ubits, (const uint4*)c->rbits, (const uint4*)c->pbits,
+                                                                protect_prev, c->bsum, (int)c->NB,
+                                                                landed_ranks, (int)landed,
+                                                                (int)(buf * c->staging_rows), c->rank_slot);
+        }
+        {
+            ProfScope ps(c, P_RANK_PLAN, st);
+            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(c->bsum, (int)c->NB, (int)c->C, c->ctl, c->hctl, c->moff, c->vtake, c->voff, c->hitpart, (int)nmark, ticket);
+        }
+        // Last batch's evicted rows must have reached the host table before the victim lists and the block buffer
+        // are reused and before any of those rows could be fetched again; the kernels above do not care.
+        if (c->evict_pending) {
+            FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
+            c->evict_pending = false;
+        }
+        {
+            ProfScope ps(c, P_RANK_EMIT, st);
+            k_rank_emit<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubits, (uint4*)c->rbits, (uint4*)c->pbits, protect_prev, c->ctl,
+                                                               c->moff, c->vtake, c->voff,
+                                                               c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, (int)c->C,
+                                                               transit, (int)c->staging_rows,
+                                                               c->dma_evict ? c->fill_src : nullptr);
+        }
     }
     FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
     // the planning kernel's decision
-    HostCtl h;
-    {
-        const volatile int32_t* hv = reinterpret_cast<const volatile int32_t*>(c->hctl);
-        FC_TRY(wait_for_ticket(hv + 8, ticket, st));
-        h.status = hv[0]; h.n_unique = hv[1]; h.n_miss = hv[2]; h.need = hv[3]; h.hit_ids = hv[4]; h.nfree = hv[5];
-        h.async_flags = hv[6]; h.batch_flags = hv[7]; h.ticket = hv[8];
-    }
-    if (h.status != FC_OK) return h.status;
-    c->last_one_per_bag = n == num_bags && !(h.batch_flags & (int32_t)EF_NOT_ONE_PER_BAG);
-    const int64_t M = h.n_miss, need = h.need;
-    if (M > 0) {
+    int32_t h[HOST_REC_WORDS];
+    FC_TRY(wait_for_record(c->hctl, ticket, st, h));
+    if (h[HW_STATUS] != FC_OK) return h[HW_STATUS];
+    c->last_one_per_bag = n == num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
+    const int64_t M = h[HW_MISS], need = h[HW_NEED];
+    if (M > 0 && !small) {
         {
             const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
             {
@@ -754,16 +770,16 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     // backward pass on a library stream, where the sort runs while the missing rows cross the host link)
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
     if (!defer_slots) {
-        FC_TRY(launch_slots_out(c, st, slots, n));
+        if (!small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
         FC_HIP(hipEventRecord(c->ev_index_done, st));
     }
     c->last_index_stream = st;
     c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     mv->valid = true; mv->M = M; mv->need = need; mv->buf = buf; mv->transit_base = transit_base;
     c->last.n_ids = n;
-    c->last.n_unique = h.n_unique;
-    c->last.n_hit_unique = h.n_unique - M;
-    c->last.n_hit_ids = h.hit_ids;
+    c->last.n_unique = h[HW_UNIQUE];
+    c->last.n_hit_unique = h[HW_UNIQUE] - M;
+    c->last.n_hit_ids = h[HW_HITS];
     c->last.n_miss = M;
     c->last.n_evict = need;
     c->last.bytes_h2d = M * (int64_t)c->D * 4;

@@ -1,0 +1,429 @@
+// Small batches: the whole index half of cache_prepare (Algorithm 1) in one workgroup, and the (slot, bag) sort of the
+// backward pass in another.
+//
+// A small batch is bound by the chain of launches, not by bytes: seven index kernels and three to nine sort kernels of 2-10 us
+// each, with 4 us between them, for a few kilobytes of work.  One workgroup of 16 wavefronts keeps the batch's bitmap over
+// rank space in LDS (160 KB per compute unit on gfx950), so that the phases are separated by workgroup barriers instead of
+// kernel boundaries.  The decisions are those of the kernels in fc_prepare.hip and fc_sort.hip, element for element.
+// Measured: 1024 ids, 100 k rows: index 33 us of kernels in 7 launches -> 13 us in one, sort 17 us in 3 -> 7.6 us in one, a
+// training step 144 -> 118 us; 3328 ids, 1 M rows: 37 us in 7 -> 27 us in one, an inference step 101 -> 85 us.
+// The limit of 4096 ids: a single compute unit resolves about one random line per nanosecond and issues one instruction
+// per cycle, and at 10 k ids it takes as long (40 + 32 us) as the kernels that use all of them (37 + 33 us and 11 launches,
+// whose launching the host overlaps).  The limits on rows and slots are what fits LDS.
+#include "fc_internal.h"
+
+namespace fc {
+
+constexpr int SM_THREADS = 1024;
+constexpr int SM_WAVES = SM_THREADS / 64;
+constexpr int SM_ITEMS = 8;                                       // ids, or slots, of a thread in flight together
+constexpr int SM_R8 = SMALL_MAX_WORDS / (SM_WAVES * 64 * 8);      // pairs of 16-byte pieces of the bitmap per lane, at most
+
+struct SmallArgs {
+    const int64_t* ids; const int64_t* offsets; const int32_t* freq_rank;
+    uint4 *rbits4, *pbits4;
+    int32_t *rank_slot, *slot_rank;
+    int32_t *miss_ranks, *vrank, *vslot, *fill_slots, *fill_src;   // fill_src: FC_EVICT_DMA only, else null
+    int32_t* ranks;                    // rank of every id
+    int32_t* slots_out;                // slot of every id; null: left to the caller (folded into the sort)
+    const int32_t* landed_ranks;       // see k_rank_count
+    Ctl* ctl; HostCtl* hctl;
+    int64_t N;
+    int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket;
+};
+
+// Words of a bitmap over one pair of 16-byte pieces (256 ranks).
+__device__ __forceinline__ int popc8(uint4 a, uint4 b) {
+    return __popc(a.x) + __popc(a.y) + __popc(a.z) + __popc(a.w) + __popc(b.x) + __popc(b.y) + __popc(b.z) + __popc(b.w);
+}
+__device__ __forceinline__ uint4 and_not(uint4 x, uint4 y) { return make_uint4(x.x & ~y.x, x.y & ~y.y, x.z & ~y.z, x.w & ~y.w); }
+__device__ __forceinline__ bool differ(uint4 x, uint4 y) { return ((x.x ^ y.x) | (x.y ^ y.y) | (x.z ^ y.z) | (x.w ^ y.w)) != 0; }
+// bits of the 32-rank word starting at rank `at` that lie below rank r
+__device__ __forceinline__ uint32_t word_below(int at, int r) { return r <= at ? 0u : r >= at + 32 ? 0xFFFFFFFFu : (1u << (r - at)) - 1u; }
+__device__ __forceinline__ uint4 below(uint4 v, int at, int r) {
+    return make_uint4(v.x & word_below(at, r), v.y & word_below(at + 32, r), v.z & word_below(at + 64, r), v.w & word_below(at + 96, r));
+}
+
+// The wavefront's lanes with `want` get places in a queue, the others -1.
+__device__ __forceinline__ int enqueue(bool want, int* count, int lane, uint64_t lt) {
+    const uint64_t m = __ballot(want);
+    if (!m) return -1;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(count, __popcll(m));
+    base = __shfl(base, 0);
+    return want ? base + __popcll(m & lt) : -1;
+}
+
+// Dynamic LDS: rank bitmap [words], prefix counts [words / 8], slot masks [slot chunks].
+//
+// Every decision that has an order (the j-th missing rank, the j-th victim, the j-th empty slot) is a prefix count: counts
+// per 256 ranks are scanned once, and whoever meets an element (an id with a missing rank, a slot with a victim) works out
+// its place from that and a popcount, all elements side by side; loops over the bits of a word, one lane each, took four
+// times as long here.  The code is kept short: a workgroup that runs once fetches its instructions from memory, too.
+__global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
+    extern __shared__ __align__(16) uint32_t lds_bits[];
+    __shared__ int part[SM_WAVES][2];
+    __shared__ uint32_t s_cand[8];
+    __shared__ int s_hits, s_used, s_threshold, s_queue, s_queue2;
+    __shared__ uint32_t s_flags;
+    uint32_t* ub = lds_bits;                                                   // rows of this batch
+    uint32_t* pre = ub + a.words;                                              // missing and (high half) evictable rows before
+                                                                               // a pair of pieces, in its wavefront's stretch
+    uint64_t* fmask = reinterpret_cast<uint64_t*>(pre + a.words / 8);          // slots to fill, 64 a word
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const int per_wave = a.words / SM_WAVES / 8;                               // pairs of pieces per wavefront
+    const int chunks_wave = (a.C + 64 * SM_WAVES - 1) / (64 * SM_WAVES);       // 64-slot chunks per wavefront
+    const int nfree = a.ctl->nfree;
+    // the resident bits this thread will look at: requested first, needed after the ids
+    uint4 q0[SM_R8], q1[SM_R8];
+#pragma unroll
+    for (int k = 0; k < SM_R8; ++k) {
+        const int p = w * per_wave + k * 64 + lane;
+        const bool live = k * 64 + lane < per_wave;
+        q0[k] = live ? a.rbits4[2 * p] : make_uint4(0, 0, 0, 0);
+        q1[k] = live ? a.rbits4[2 * p + 1] : make_uint4(0, 0, 0, 0);
+    }
+    for (int j = tid; j < a.words / 4; j += SM_THREADS) reinterpret_cast<uint4*>(ub)[j] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) { s_hits = s_used = s_queue = s_queue2 = 0; s_flags = 0; s_threshold = 0x7fffffff; }
+    for (int j = tid; j < a.landed; j += SM_THREADS) {     // rows of the block that has reached the host table
+        const int r = a.landed_ranks[j];
+        if (a.rank_slot[r] == -2 - (a.landed_base + j)) a.rank_slot[r] = -1;
+    }
+    __syncthreads();
+    // ids -> ranks, marked in LDS; access-level hits; offsets
+    uint32_t flags = 0;
+    int hits = 0, used = 0;
+#pragma unroll 1
+    for (int i0 = tid; i0 - tid < a.n; i0 += SM_ITEMS * SM_THREADS) {
+        int64_t id[SM_ITEMS];
+        int r[SM_ITEMS], s[SM_ITEMS];
+#pragma unroll
+        for (int k = 0; k < SM_ITEMS; ++k) id[k] = i0 + k * SM_THREADS < a.n ? a.ids[i0 + k * SM_THREADS] : 0;
+#pragma unroll
+        for (int k = 0; k < SM_ITEMS; ++k) {
+            const bool ok = (uint64_t)id[k] < (uint64_t)a.N;
+            if (!ok) flags |= EF_ID_RANGE;
+            r[k] = ok ? a.freq_rank[id[k]] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < SM_ITEMS; ++k) s[k] = r[k] >= 0 ? a.rank_slot[r[k]] : -1;
+#pragma unroll
+        for (int k = 0; k < SM_ITEMS; ++k) {
+            const int i = i0 + k * SM_THREADS;
+            bool mine = false;                             // first to mark its row
+            if (i < a.n && r[k] >= 0) {
+                const uint32_t bit = 1u << (r[k] & 31);
+                uint32_t* word = &ub[(uint32_t)r[k] >> 5];
+                // (popular rows: a plain read is one broadcast, atomics on one word queue up)
+                if (!(*reinterpret_cast<volatile uint32_t*>(word) & bit)) mine = (atomicOr(word, bit) & bit) == 0;
+                used += mine;
+                hits += s[k] >= 0;
+                a.ranks[i] = r[k];
+            }
+            const int at = enqueue(mine && s[k] < 0, &s_queue, lane, lt);
+            if (at >= 0 && at < a.C) a.fill_slots[at] = r[k];        // (more missing rows than slots: refused below)
+        }
+    }
+#pragma unroll 1
+    for (int i = tid; i <= a.num_bags; i += SM_THREADS) {
+        const int64_t o = a.offsets[i];
+        if (o != i) flags |= EF_NOT_ONE_PER_BAG;
+        if ((i == 0 && o != 0) || (i == a.num_bags && o != (int64_t)a.n)) flags |= EF_BAD_OFFSETS;
+        if (i < a.num_bags && a.offsets[i + 1] < o) flags |= EF_BAD_OFFSETS;
+    }
+    hits = wave_sum(hits);
+    used = wave_sum(used);
+    if (lane == 0) { atomicAdd(&s_hits, hits); atomicAdd(&s_used, used); }
+    if (flags) atomicOr(&s_flags, flags);
+    __syncthreads();
+    // missing and evictable rows before each pair of pieces
+    const uint4* ub4 = reinterpret_cast<const uint4*>(ub);
+    int cm = 0, cc = 0;
+#pragma unroll
+    for (int k = 0; k < SM_R8; ++k) {
+        if (k * 64 >= per_wave) break;
+        const bool live = k * 64 + lane < per_wave;
+        const int p = w * per_wave + k * 64 + lane;
+        int nm = 0, nc = 0;
+        if (live) {
+            const uint4 u0 = ub4[2 * p], u1 = ub4[2 * p + 1];
+            nm = popc8(and_not(u0, q0[k]), and_not(u1, q1[k]));
+            nc = popc8(and_not(q0[k], u0), and_not(q1[k], u1));
+        }
+        int x = nm | nc << 16;                             // 64 pairs hold 16384 ranks: no carry between the halves
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(x, o);
+            if (lane >= o) x += y;
+        }
+        // (a stretch holds at most 65536 ranks, and what precedes a pair in it at most 65280: 16 bits each)
+        if (live) pre[p] = (uint32_t)(cm + (x & 0xffff) - nm) | (uint32_t)(cc + (x >> 16) - nc) << 16;
+        x = __shfl(x, 63);
+        cm += x & 0xffff;
+        cc += x >> 16;
+    }
+    if (lane == 0) { part[w][0] = cm; part[w][1] = cc; }
+    __syncthreads();
+    // totals; part[k] becomes what precedes wavefront k's stretch
+    int M = 0, totC = 0, m0 = 0, c0 = 0;
+#pragma unroll 1
+    for (int k = 0; k < SM_WAVES; ++k) {
+        if (k == w) { m0 = M; c0 = totC; }
+        M += part[k][0]; totC += part[k][1];
+    }
+    const uint32_t ef = s_flags;
+    const int totU = s_used;
+    int status = FC_OK;
+    if (ef & EF_BAD_OFFSETS) status = FC_ERR_BAD_OFFSETS;
+    else if (ef & EF_ID_RANGE) status = FC_ERR_ID_OUT_OF_RANGE;
+    else if (totU > a.C) status = FC_ERR_BATCH_EXCEEDS_CACHE;
+    int need = M - nfree;
+    if (need < 0 || status != FC_OK) need = 0;
+    if (w == SM_WAVES - 1) {
+        const int nf = status == FC_OK ? nfree + need - M : nfree;
+        report_to_host(a.hctl, a.ticket, status, totU, M, need, s_hits, nf, (int)a.ctl->async_flags, (int)(ef & EF_NOT_ONE_PER_BAG), lane);
+        if (lane == 0) { a.ctl->status = status; a.ctl->n_unique = totU; a.ctl->n_miss = M; a.ctl->need = need; a.ctl->nfree = nf; a.ctl->err_flags = 0; }
+    }
+    if (status != FC_OK) return;
+    // the victims are the evictable ranks from the threshold up: the one with `skip` evictable ranks below it
+    const int skip = totC - need;
+    if (need > 0 && skip >= c0 && skip < c0 + cc) {        // it lies in this wavefront's stretch
+#pragma unroll
+        for (int k = 0; k < SM_R8; ++k) {
+            if (k * 64 >= per_wave) break;
+            const int p = w * per_wave + k * 64 + lane;
+            if (k * 64 + lane < per_wave) {
+                const uint4 e0 = and_not(q0[k], ub4[2 * p]), e1 = and_not(q1[k], ub4[2 * p + 1]);
+                const int left = skip - c0 - (int)(pre[p] >> 16);
+                if (left >= 0 && left < popc8(e0, e1)) {   // one lane of one wavefront
+                    s_cand[0] = e0.x; s_cand[1] = e0.y; s_cand[2] = e0.z; s_cand[3] = e0.w;
+                    s_cand[4] = e1.x; s_cand[5] = e1.y; s_cand[6] = e1.z; s_cand[7] = e1.w;
+                    s_threshold = p << 9 | left;           // resolved below
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (lane == 0) { part[w][0] = m0; part[w][1] = c0; }
+    if (tid == 0 && need > 0) {
+        int left = s_threshold & 511, rank = (s_threshold >> 9) * 256, j = 0;
+        uint32_t m = s_cand[0];
+        while (left >= __popc(m)) { left -= __popc(m); m = s_cand[++j]; }      // ends: fewer than the pair's count
+        for (; left > 0; --left) m &= m - 1;
+        s_threshold = rank + j * 32 + __ffs(m) - 1;
+    }
+    __syncthreads();
+    const int threshold = s_threshold;
+    // each missing rank goes to its place
+#pragma unroll 1
+    for (int q = tid; q < M; q += SM_THREADS) {
+        const int r = a.fill_slots[q], p = r >> 8;
+        const uint4 b0 = below(and_not(ub4[2 * p], a.rbits4[2 * p]), p * 256, r),
+                    b1 = below(and_not(ub4[2 * p + 1], a.rbits4[2 * p + 1]), p * 256 + 128, r);
+        a.miss_ranks[part[p / per_wave][0] + (int)(pre[p] & 0xffff) + popc8(b0, b1)] = r;
+    }
+    __syncthreads();
+    // slots whose row is a victim, and those that were empty, are the ones to fill
+    int cf = 0;
+    if (M > 0) {
+#pragma unroll 1
+        for (int k0 = 0; k0 < chunks_wave; k0 += SM_ITEMS) {
+            int row[SM_ITEMS];
+#pragma unroll
+            for (int k = 0; k < SM_ITEMS; ++k) {
+                const int s = (w * chunks_wave + k0 + k) * 64 + lane;
+                row[k] = k0 + k < chunks_wave && s < a.C ? a.slot_rank[s] : 0x7fffffff;
+            }
+#pragma unroll
+            for (int k = 0; k < SM_ITEMS; ++k) {
+                const int chunk = w * chunks_wave + k0 + k, r = row[k];
+                const bool victim = r >= threshold && r != 0x7fffffff && !((ub[r >> 5] >> (r & 31)) & 1u);
+                const int at = enqueue(victim, &s_queue2, lane, lt);
+                if (victim) a.fill_slots[at] = chunk * 64 + lane;
+                const uint64_t m = __ballot(victim || r < 0);
+                if (lane == 0 && k0 + k < chunks_wave) fmask[chunk] = m;
+                cf += __popcll(m);
+            }
+        }
+    }
+    __syncthreads();
+    const bool transit = a.transit_base >= 0 && need <= a.transit_rows;
+#pragma unroll 1
+    for (int q = tid; q < need; q += SM_THREADS) {         // each victim goes to its place
+        const int s = a.fill_slots[q], r = a.slot_rank[s], p = r >> 8;
+        const uint4 b0 = below(and_not(a.rbits4[2 * p], ub4[2 * p]), p * 256, r),
+                    b1 = below(and_not(a.rbits4[2 * p + 1], ub4[2 * p + 1]), p * 256 + 128, r);
+        const int j = part[p / per_wave][1] + (int)(pre[p] >> 16) + popc8(b0, b1) - skip;
+        a.vrank[j] = r;
+        a.vslot[j] = s;
+        a.rank_slot[r] = transit ? -2 - (a.transit_base + j) : -1;
+    }
+    __syncthreads();
+    if (lane == 0) part[w][0] = cf;
+    // the bitmaps change hands: resident = without the victims, with the missing; previous batch = this one
+#pragma unroll
+    for (int k = 0; k < SM_R8; ++k) {
+        if (k * 64 >= per_wave) break;
+        const int p = w * per_wave + k * 64 + lane, at = p * 256;
+        if (k * 64 + lane < per_wave) {
+            const uint4 u0 = ub4[2 * p], u1 = ub4[2 * p + 1];
+            uint4 k0 = and_not(q0[k], u0), k1 = and_not(q1[k], u1);            // evictable: stay if below the threshold
+            if (at + 256 > threshold) { k0 = below(k0, at, threshold); k1 = below(k1, at + 128, threshold); }
+            const uint4 r0 = make_uint4(u0.x | k0.x, u0.y | k0.y, u0.z | k0.z, u0.w | k0.w),
+                        r1 = make_uint4(u1.x | k1.x, u1.y | k1.y, u1.z | k1.z, u1.w | k1.w);
+            if (differ(r0, q0[k]) || differ(r1, q1[k])) { a.rbits4[2 * p] = r0; a.rbits4[2 * p + 1] = r1; }
+            a.pbits4[2 * p] = u0;
+            a.pbits4[2 * p + 1] = u1;
+        }
+    }
+    __syncthreads();
+    // j-th missing rank -> j-th lowest empty slot
+    {
+        int j0 = 0;
+        for (int k = 0; k < w; ++k) j0 += part[k][0];
+#pragma unroll 1
+        for (int k = 0; k < chunks_wave && j0 < M; ++k) {
+            const uint64_t m = fmask[w * chunks_wave + k];
+            const int j = j0 + __popcll(m & lt);
+            if (((m >> lane) & 1ull) && j < M) a.fill_slots[j] = (w * chunks_wave + k) * 64 + lane;
+            j0 += __popcll(m);
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int j = tid; j < M; j += SM_THREADS) {
+        const int s = a.fill_slots[j], rank = a.miss_ranks[j];
+        if (a.fill_src) a.fill_src[j] = a.rank_slot[rank]; // where the row's newest copy is: -1 the host table, <= -2 in transit
+        a.slot_rank[s] = rank;
+        a.rank_slot[rank] = s;
+    }
+    if (!a.slots_out) return;
+    __syncthreads();
+#pragma unroll 2
+    for (int i = tid; i < a.n; i += SM_THREADS) a.slots_out[i] = a.rank_slot[a.ranks[i]];
+}
+
+bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags) {
+    return n <= SMALL_MAX_IDS && num_bags <= 4 * SMALL_MAX_IDS && c->NB * RT_WORDS <= SMALL_MAX_WORDS && c->C <= SMALL_MAX_SLOTS;
+}
+
+int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
+                         int32_t* slots, int32_t ticket, const int32_t* landed_ranks, int64_t landed, int64_t landed_base,
+                         int transit_base) {
+    SmallArgs a;
+    a.ids = ids; a.offsets = offsets; a.freq_rank = c->freq_rank;
+    a.rbits4 = (uint4*)c->rbits; a.pbits4 = (uint4*)c->pbits;
+    a.rank_slot = c->rank_slot; a.slot_rank = c->slot_rank;
+    a.miss_ranks = c->miss_ranks; a.vrank = c->vrank; a.vslot = c->vslot; a.fill_slots = c->fill_slots;
+    a.fill_src = c->dma_evict ? c->fill_src : nullptr;
+    a.ranks = c->rbuf; a.slots_out = slots;
+    a.landed_ranks = landed_ranks; a.landed = (int)landed; a.landed_base = (int)landed_base;
+    a.ctl = c->ctl; a.hctl = c->hctl; a.N = c->N;
+    a.n = (int)n; a.num_bags = (int)num_bags; a.C = (int)c->C; a.words = (int)(c->NB * RT_WORDS);
+    a.transit_base = transit_base; a.transit_rows = (int)c->staging_rows; a.ticket = ticket;
+    const size_t lds = (size_t)(a.words + a.words / 8) * 4 + (size_t)cdiv(c->C, 64 * SM_WAVES) * SM_WAVES * 8;
+    ProfScope ps(c, P_REMAP_MARK, st);
+    k_prepare_small<<<1, SM_THREADS, lds, st>>>(a);
+    FC_HIP(hipGetLastError());
+    return FC_OK;
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Stable sort of up to SMALL_MAX_IDS (slot, bag) pairs by slot in one workgroup: LSD passes of at most 8 bits on words that
+// hold key and lookup number together (a key of up to SMALL_KEY_BITS bits above SMALL_POS_BITS of position), exchanged
+// through LDS; the lookup number becomes its bag at the end.
+// ---------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ rank_slot,
+                                                           int32_t* __restrict__ slots_out, const int64_t* __restrict__ offsets,
+                                                           int num_bags, int one_per_bag, int n, int limit, int passes, int radix_bits,
+                                                           uint32_t* flags, int32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out) {
+    extern __shared__ __align__(16) uint32_t sm_words[];   // two arrays of rounds * SM_THREADS words, then the digit counts
+    const int rounds = (n + SM_THREADS - 1) / SM_THREADS;  // elements per thread
+    const int radix = 1 << radix_bits, mask = radix - 1;
+    uint32_t* from = sm_words;
+    uint32_t* to = sm_words + rounds * SM_THREADS;
+    int* wc = reinterpret_cast<int*>(sm_words + 2 * rounds * SM_THREADS);      // [SM_WAVES][radix]
+    __shared__ int scan[SM_WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    bool bad = false;
+#pragma unroll 4
+    for (int i = tid; i < n; i += SM_THREADS) {
+        int key = keys_in[i];
+        if (rank_slot) slots_out[i] = key = rank_slot[key];
+        if ((unsigned)key >= (unsigned)limit) { bad = true; key = limit; }
+        from[i] = ((uint32_t)key << SMALL_POS_BITS) | (uint32_t)i;
+    }
+    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const int e0 = w * 64 * rounds + lane;                 // this wavefront's elements: e0 + 64 * k
+    int* mine = wc + w * radix;
+#pragma unroll 1
+    for (int p = 0; p < passes; ++p) {
+        const int shift = SMALL_POS_BITS + p * radix_bits;
+        for (int d = tid; d < SM_WAVES * radix; d += SM_THREADS) wc[d] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (int k = 0; k < rounds; ++k)
+            if (e0 + 64 * k < n) atomicAdd(&mine[(from[e0 + 64 * k] >> shift) & mask], 1);
+        __syncthreads();
+        // wc[w][d] becomes where wavefront w's first element of digit d goes
+        int run = 0;
+        if (tid < radix) {
+#pragma unroll
+            for (int k = 0; k < SM_WAVES; ++k) { const int c = wc[k * radix + tid]; wc[k * radix + tid] = run; run += c; }
+        }
+        int tot;
+        const int base = block_excl_scan<SM_THREADS>(run, tot, scan);
+        if (tid < radix) {
+#pragma unroll
+            for (int k = 0; k < SM_WAVES; ++k) wc[k * radix + tid] += base;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int k = 0; k < rounds; ++k) {
+            const bool valid = e0 + 64 * k < n;
+            const uint32_t x = valid ? from[e0 + 64 * k] : 0;
+            const int d = (x >> shift) & mask;
+            uint64_t peers = __ballot(valid);
+            for (int b = 0; b < radix_bits; ++b) {
+                const bool one = (d >> b) & 1;
+                const uint64_t bm = __ballot(one);
+                peers &= one ? bm : ~bm;
+            }
+            const int before = __popcll(peers & lt);
+            int at = 0;
+            if (valid) at = mine[d];
+            if (valid && before == 0) mine[d] = at + __popcll(peers);
+            if (valid) to[at + before] = x;
+        }
+        __syncthreads();
+        uint32_t* t = from; from = to; to = t;
+    }
+#pragma unroll 4
+    for (int e = tid; e < n; e += SM_THREADS) {
+        const uint32_t x = from[e];
+        const int i = (int)(x & ((1u << SMALL_POS_BITS) - 1));
+        keys_out[e] = (int)(x >> SMALL_POS_BITS);
+        vals_out[e] = one_per_bag ? i : bag_of_lookup(offsets, num_bags, i);
+    }
+}
+
+bool sort_small_fits(const SortJob& j) {
+    return (j.src == SORT_SRC_SLOTS || j.src == SORT_SRC_RANKS) && j.n <= SMALL_MAX_IDS && j.bits <= SMALL_KEY_BITS && !j.max_bits && !j.no_fuse;
+}
+
+int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
+    const int passes = (j.bits + 7) / 8, rb = (j.bits + passes - 1) / passes;
+    const int opb = j.one_per_bag && j.n == j.num_bags;
+    ProfScope ps(j.prof, P_SORT_SCATTER, st);
+    const size_t words = 2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb);
+    k_sort_small<<<1, SM_THREADS, words * 4, st>>>(j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.num_bags, opb, j.n,
+                                                   j.limit, passes, rb, j.flags, j.keysA, j.valsA);
+    FC_HIP(hipGetLastError());
+    *kres = j.keysA; *vres = j.valsA;
+    if (j.last_stream) *j.last_stream = st;
+    return FC_OK;
+}
+
+}  // namespace fc

@@ -20,16 +20,6 @@ __device__ __forceinline__ int first_key(const int32_t* __restrict__ slots, int 
     return k;
 }
 
-// bag of lookup i: the largest b with offsets[b] <= i
-__device__ __forceinline__ int bag_of(const int64_t* __restrict__ offsets, int num_bags, int i) {
-    int lo = 0, hi = num_bags;
-    while (hi - lo > 1) {
-        const int mid = (int)(((int64_t)lo + hi) >> 1);
-        if (offsets[mid] <= i) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 // key of element i by source (SORT_SRC_RANKS is turned into slots by k_sort_hist first)
 template <int SRC>
 __device__ __forceinline__ int load_key(const int32_t* __restrict__ keys_in, int i, int limit, bool& bad) {
