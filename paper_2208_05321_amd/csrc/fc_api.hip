@@ -87,6 +87,7 @@ static int reset_state(fc_cache* c, bool warm) {
     c->next_pending = false; c->last_pst = c->stream;
     c->planned.valid = false; c->last_index_stream = nullptr; c->move_stream[0] = c->move_stream[1] = nullptr; c->pf_dep = nullptr;
     c->quiesce_stream = nullptr;
+    c->due = 0;
     c->fetch_timed[0] = c->fetch_timed[1] = false; c->last_copy_buf = -1;
     for (bool& b : c->copy_timed) b = false;
     for (PresortRec& r : c->rec) r.valid = false;
@@ -273,7 +274,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     c->dirty_track = (flags & FC_DIRTY_TRACK) != 0;
     for (auto& set : c->lists)
         for (int k = 0; k < 7; ++k) {
-            const bool wanted = k < 3 || (k == 3 && c->dma_evict) || (k == 4 && (!c->dma_evict || c->dirty_track)) ||
+            const bool wanted = k < 4 || (k == 4 && (!c->dma_evict || c->dirty_track)) ||
                                 (k >= 5 && c->dirty_track);
             if (wanted) FC_HIP(hipMalloc((void**)&set[k], (size_t)C * 4));
         }
@@ -431,7 +432,7 @@ static int adopt_next(fc_cache* c) {
     if (c->planned.valid) {            // a batch planned ahead whose rows have not moved yet: move them now
         const MovePlan mv = c->planned;
         c->planned.valid = false;
-        FC_TRY(prepare_move(c, c->stream, mv));
+        FC_TRY(prepare_move(c, c->stream, mv, true));
     }
     if (c->next_pending || c->last_pst != c->stream) {
         FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
@@ -439,6 +440,15 @@ static int adopt_next(fc_cache* c) {
         c->last_pst = c->stream;
     }
     c->cur_ticket = c->pending_ticket;     // the batch prepared ahead of time (if any) is the current one now
+    return FC_OK;
+}
+
+// see fc_cache::due: everything the caller's stream holds by now counts as what these events stand for
+static int record_due_events(fc_cache* c) {
+    if (c->due & DUE_S_NOW) FC_HIP(hipEventRecord(c->ev_s_now, c->stream));
+    if (c->due & DUE_INDEX) FC_HIP(hipEventRecord(c->ev_index_done, c->stream));
+    for (int k = 0; k < 2; ++k) if (c->due & (DUE_MOVE << k)) FC_HIP(hipEventRecord(c->ev_move_done[k], c->stream));
+    c->due = 0;
     return FC_OK;
 }
 
@@ -498,8 +508,8 @@ int cache_prepare(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_t*
                   int32_t* slots_dev) {
     if (!c) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
-    FC_HIP(hipEventRecord(c->ev_s_now, c->stream));
     FC_TRY(adopt_next(c));
+    c->due |= DUE_S_NOW;
     const int rc = prepare_impl(c, c->stream, false, ids_dev, n, offsets_dev, num_bags, slots_dev);
     if (rc == FC_OK) c->cur_ticket = c->pending_ticket = c->ticket;
     return rc;
@@ -509,6 +519,7 @@ int cache_prepare_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int
                        int32_t* slots_dev) {
     if (!c) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
+    FC_TRY(record_due_events(c));
     // everything the caller has enqueued so far (the backward pass of the batch before the current one, and the
     // input buffers of this call) is complete before this call's row movement, or before all of it when the last
     // prepare ran on the caller's stream
@@ -529,6 +540,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     if (!c || (c->flags & FC_TRANSMIT_STAGED)) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
     if (c->planned.valid) FC_TRY(cache_advance(c));
+    FC_TRY(record_due_events(c));
     // The index half touches no rows, so it need not wait for the row movement, forward or backward work the caller
     // enqueued since the last cache_prepare / cache_advance: it is ordered behind the caller's stream as of the entry
     // of that call (which covers the backward pass whose sorted pairs this call's sort will overwrite).
@@ -581,6 +593,7 @@ int cache_advance(fc_cache* c) {
     if (!c) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
     FC_HIP(hipEventRecord(c->ev_s_now, c->stream));
+    c->due &= ~DUE_S_NOW;
     if (c->planned.valid) return adopt_next(c);
     if (c->next_pending) {
         FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));

@@ -525,25 +525,29 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     if (c->rec[k ^ 1].valid && c->rec[k ^ 1].ticket != c->cur_ticket) c->rec[k ^ 1].valid = false;
     if (!c->presort || n <= 0 || num_bags <= 0) return slots_out ? FC_ERR_INVALID_ARG : FC_OK;   // the caller then writes the slots out itself
     FC_TRY(ensure_sort(c->sb[k], n));
-    FC_HIP(hipEventRecord(c->ev_slots, c->pst));
-    FC_HIP(hipStreamWaitEvent(c->aux, c->ev_slots, 0));
+    // A small batch's sort is one short kernel: on the caller's stream it costs 8 us, on another one two waits of 10 us.
+    const hipStream_t aux = c->pst == c->stream && n <= SMALL_MAX_IDS ? c->stream : c->aux;
+    if (c->pst != aux) {
+        FC_HIP(hipEventRecord(c->ev_slots, c->pst));
+        FC_HIP(hipStreamWaitEvent(aux, c->ev_slots, 0));
+    }
     // the record's previous sort was read by a backward pass on the caller's stream, enqueued before this call
-    if (c->pst != c->stream) FC_HIP(hipStreamWaitEvent(c->aux, c->ev_s_now, 0));
+    if (c->pst != c->stream) FC_HIP(hipStreamWaitEvent(aux, c->ev_s_now, 0));
     // the record's buffers were last written by a sort that may have run on another library stream (the schedule changed)
     // (a record the caller's stream has consumed is covered by the wait for that stream above)
-    if (r.sort_stream && r.sort_stream != c->aux && !r.caller_waited) FC_HIP(hipStreamWaitEvent(c->aux, r.ev_sorted, 0));
+    if (r.sort_stream && r.sort_stream != aux && !r.caller_waited) FC_HIP(hipStreamWaitEvent(aux, r.ev_sorted, 0));
     // cache_plan_next running ahead (FC_INPUTS_READY while HBM rather than the host link binds the step):
     // the index stream is then the busiest of the schedule, and the next batch's index kernels queue behind this sort; its
     // passes after the first move to the side stream, which only carries the evicted-row block.  Where the host link binds
     // the step, that block copy fills the side stream and the sort must not delay it: measured 7% slower there, 8% faster
     // where HBM binds.
-    hipStream_t last = c->aux;
-    const bool split = slots_out && c->sort_tail_side && c->ahead_now && c->aux == c->pre &&
-                       c->side && c->side != c->aux;
-    FC_TRY(sort_pairs(c, c->sb[k], c->aux, slots, n, offsets, num_bags, &r.keys, &r.vals, slots_out, split ? c->side : nullptr, &last));
-    FC_HIP(hipEventRecord(r.ev_sorted, last));
+    hipStream_t last = aux;
+    const bool split = slots_out && c->sort_tail_side && c->ahead_now && aux == c->pre &&
+                       c->side && c->side != aux;
+    FC_TRY(sort_pairs(c, c->sb[k], aux, slots, n, offsets, num_bags, &r.keys, &r.vals, slots_out, split ? c->side : nullptr, &last));
+    if (last != c->stream) FC_HIP(hipEventRecord(r.ev_sorted, last));
     r.sort_stream = last;
-    r.caller_waited = false;
+    r.caller_waited = last == c->stream;
     r.slots = slots; r.n = n; r.offsets = offsets; r.bags = num_bags;
     r.ticket = c->ticket;
     r.one_per_bag = c->last_one_per_bag;
@@ -581,7 +585,7 @@ static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n,
 #undef FC_BWD_V
 #undef FC_BWD
     }
-    {
+    if (rblocks > 1) {             // else no run crosses a workgroup border
         ProfScope ps(prof, P_BWD_FIXUP, st);
         const BwdMeta* bm = reinterpret_cast<const BwdMeta*>(pmeta);
         const unsigned fb = (unsigned)cdiv(rblocks, 256 >> sh);

@@ -118,10 +118,13 @@ struct fc_cache {
     hipEvent_t ev_quiesce = nullptr;       // transit marks dropped by dma_quiesce on another stream than the index stream
     hipStream_t quiesce_stream = nullptr;
     hipStream_t last_index_stream = nullptr;
+    // Events of a plain cache_prepare that only work on a library stream would wait for: each costs its stream about 4 us, so
+    // they are recorded (on the caller's stream) when a call that uses such a stream comes along.
+    uint32_t due = 0;
     // The lists an index half writes and its row-movement half reads exist twice, so that the index half of the next
     // batch can run while the rows of the current one still move: lset = the set of the latest index half.
     int lset = 0;
-    int32_t* lists[2][7] = {};      // per set: miss_ranks, vslot, fill_slots, fill_src (DMA evict), vrank (unless it lives
+    int32_t* lists[2][7] = {};      // per set: miss_ranks, vslot, fill_slots, fill_src, vrank (unless it lives
                                     // with the DMA block), and with FC_DIRTY_TRACK the dirty victims' ranks and slots
     hipEvent_t ev_move_done[2] = {nullptr, nullptr};   // the row movement that read set k has finished
     hipStream_t move_stream[2] = {nullptr, nullptr};   // the stream it ran on (nullptr: none yet)
@@ -174,7 +177,8 @@ struct fc_cache {
     int32_t* vrank = nullptr;       // [C]
     int32_t* vslot = nullptr;       // [C]
     int32_t* fill_slots = nullptr;  // [C]
-    int32_t* fill_src = nullptr;    // [C]  FC_EVICT_DMA: where each missing row is read from (-1 host, <= -2 transit)
+    int32_t* fill_src = nullptr;    // [C]  FC_EVICT_DMA: where each missing row is read from (-1 host, <= -2 transit);
+                                    //      otherwise: the rank of the row that leaves the slot it is loaded into (-1: none)
     int32_t* rbuf = nullptr;        // [n_cap] rank of every input id
     int64_t n_cap = 0;
     fc::Ctl* ctl = nullptr;
@@ -269,6 +273,8 @@ struct fc_cache {
 
 namespace fc {
 
+enum : uint32_t { DUE_S_NOW = 1u, DUE_INDEX = 2u, DUE_MOVE = 4u };     // DUE_MOVE << list set
+
 // make list set k the current one (with FC_EVICT_DMA the victim ranks live with their block, not with the set)
 inline void use_list_set(fc_cache* c, int k) {
     c->lset = k;
@@ -306,7 +312,7 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots = nullptr, bool defer_slots = false);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv);
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead);
 int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                  int64_t num_bags, int32_t* slots);
 int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, float* out);
@@ -326,6 +332,9 @@ int noalloc_setup(int device);
 // dst_rows / src_rows bound the row indices on either side (rows with an index outside are skipped).
 int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, const int32_t* dst_idx, int64_t dst_rows,
                      const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks);
+// default transmitter: each slot of fill_slots gives its old row (rank fill_src[j], if any) to the host table and gets the
+// missing one, in one pass
+int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows);
 // host[slot_rank[s]] = cache[s] for every resident slot, written straight into the mapped host table.
 int launch_flush_rows(fc_cache* c, hipStream_t s);   // FC_DIRTY_TRACK: dirty rows only
 // miss fill that honours transit marks: row j comes from the host table or from a device-side evicted-row block

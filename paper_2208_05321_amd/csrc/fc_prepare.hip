@@ -339,7 +339,8 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint4* ubits4, uint4* 
                         // not resident any more; with the DMA evict transmitter the newest copy of the row is
                         // "in transit" in row j of an evicted-row block until the host threads have stored it
                         rank_slot[rank] = transit ? -2 - (transit_base + j) : -1;
-                        if ((unsigned)slot < (unsigned)C) slot_rank[slot] = -1;   // always true: the maps are inverse
+                        // empty, and whose row it still holds (every such slot is refilled below); the test is always true
+                        if ((unsigned)slot < (unsigned)C) slot_rank[slot] = -2 - rank;
                         vw[k] |= 1u << bit;
                     }
                     ++q;
@@ -369,9 +370,9 @@ __device__ __forceinline__ unsigned empty_mask(const int32_t* __restrict__ slot_
     unsigned m = 0;
     if (s0 + FREE_PER <= C) {
         const int4 v = *reinterpret_cast<const int4*>(slot_rank + s0);
-        m = (v.x == -1 ? 1u : 0u) | (v.y == -1 ? 2u : 0u) | (v.z == -1 ? 4u : 0u) | (v.w == -1 ? 8u : 0u);
+        m = (v.x < 0 ? 1u : 0u) | (v.y < 0 ? 2u : 0u) | (v.z < 0 ? 4u : 0u) | (v.w < 0 ? 8u : 0u);
     } else {
-        for (int k = 0; k < FREE_PER; ++k) if (s0 + k < C && slot_rank[s0 + k] == -1) m |= 1u << k;
+        for (int k = 0; k < FREE_PER; ++k) if (s0 + k < C && slot_rank[s0 + k] < 0) m |= 1u << k;
     }
     return m;
 }
@@ -395,7 +396,8 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_count(const int32_t* __re
 
 __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount,
                                                               int M, const int32_t* __restrict__ miss_ranks,
-                                                              int32_t* __restrict__ fill_slots, int32_t* rank_slot) {
+                                                              int32_t* __restrict__ fill_slots, int32_t* rank_slot,
+                                                              int32_t* __restrict__ old_rank) {
     __shared__ int lds[FREE_THREADS / 64];
     int part = 0;
     for (int g = threadIdx.x; g < (int)blockIdx.x; g += FREE_THREADS) part += tcount[g];
@@ -412,6 +414,7 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank
         const int s = s0 + k;
         const int r = miss_ranks[j];
         fill_slots[j] = s;
+        if (old_rank) old_rank[j] = -2 - min(slot_rank[s], -1);     // rank of the row that leaves (-1: the slot was empty)
         slot_rank[s] = r;
         rank_slot[r] = s;
         ++j;
@@ -745,7 +748,8 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
                                                                c->dma_evict ? c->fill_src : nullptr);
         }
     }
-    FC_HIP(hipEventRecord(c->ev_emit_done, st));
+    const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
+    if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
     // the planning kernel's decision
     int32_t h[HOST_REC_WORDS];
@@ -762,17 +766,18 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
             }
             ProfScope ps(c, P_FREE_PICK, st);
             k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
-                                                      c->rank_slot);
+                                                      c->rank_slot, c->dma_evict ? nullptr : c->fill_src);
         }
     }
-    FC_HIP(hipEventRecord(c->ev_assign_done, st));
+    if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));
     // every row of the batch has its slot now: write the slots out (the caller then starts sorting them for the
     // backward pass on a library stream, where the sort runs while the missing rows cross the host link)
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
     if (!defer_slots) {
         if (!small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
-        FC_HIP(hipEventRecord(c->ev_index_done, st));
+        if (!plain) FC_HIP(hipEventRecord(c->ev_index_done, st));
     }
+    if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
     c->last_index_stream = st;
     c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     mv->valid = true; mv->M = M; mv->need = need; mv->buf = buf; mv->transit_base = transit_base;
@@ -788,8 +793,19 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     return FC_OK;
 }
 
+static int move_done(fc_cache* c, hipStream_t st, bool ahead) {
+    if (st == c->stream && !ahead) c->due |= DUE_MOVE << c->lset;
+    else {
+        FC_HIP(hipEventRecord(c->ev_move_done[c->lset], st));
+        c->due &= ~(DUE_MOVE << c->lset);
+    }
+    c->move_stream[c->lset] = st;
+    return FC_OK;
+}
+
 // Row-movement half: evicted rows out (gather, then DMA block / kernel store / staged copy), missing rows in.
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv) {
+// ahead: the batch was prepared ahead of time, so the next one's index half will wait for this on a library stream.
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
@@ -819,6 +835,13 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv) {
         if (M > 0) FC_HIP(hipMemcpyAsync(c->list_pin, c->miss_ranks, (size_t)M * 4, hipMemcpyDeviceToHost, st));
         if (need > 0) FC_HIP(hipMemcpyAsync(c->list_pin + c->C, c->out_rank, (size_t)need * 4, hipMemcpyDeviceToHost, st));
         FC_HIP(hipStreamSynchronize(st));
+    }
+    // Default transmitter, rows straight from the host table: they change places with the victims in one kernel.
+    if (!staged && !c->dma_evict && !c->dirty_track && !mv.arrived) {
+        FC_TRY(launch_swap_rows(c, st, M));                        // every victim's slot is among those that are filled
+        FC_TRY(move_done(c, st, ahead));
+        c->pf_dep = c->ev_move_done[c->lset];
+        return FC_OK;
     }
     int64_t last_off = 0, last_rows = 0;
     // Rows fetched ahead of time (cache_plan_next) were read from the host table and from evicted-row blocks other
@@ -860,8 +883,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv) {
     if (last_rows > 0) FC_TRY(store_block(c, last_off, last_rows));
     if (last_rows < 0) { FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0)); c->evict_pending = false; }
     FC_HIP(hipGetLastError());
-    FC_HIP(hipEventRecord(c->ev_move_done[c->lset], st));
-    c->move_stream[c->lset] = st;
+    FC_TRY(move_done(c, st, ahead));
     // The next early fetch reads evicted-row blocks gathered up to now and host rows stored up to now: with the DMA
     // transmitter the gather just enqueued is the last thing it needs (host rows still on their way carry transit
     // marks); after a kernel store it has to wait for the whole movement.
@@ -878,7 +900,7 @@ int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     // this call (the backward pass of the batch before the current one); the index decisions did not care.
     if (n > 0) (void)presort_impl(c, slots, n, offsets, num_bags);   // on failure the backward pass sorts (and reports) itself
     if (lookahead) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
-    return prepare_move(c, st, mv);
+    return prepare_move(c, st, mv, lookahead);
 }
 
 }  // namespace fc

@@ -43,6 +43,42 @@ __global__ __launch_bounds__(256) void k_copy_rows(float* __restrict__ dst, cons
     }
 }
 
+// Rows change places (default transmitter): slot fill_slots[j] gives its row to the host table (row old_rank[j]; -1: the slot
+// was empty) and gets row miss_ranks[j] from there.  Every slot and every host row occurs once, so no row waits for another
+// and no block in between is needed.  Bound by the host link; what it replaces moved each evicted row through HBM twice more,
+// and needed a second stream with two waits of 10 us each.
+template <int VEC>
+__global__ __launch_bounds__(256) void k_swap_rows(float* __restrict__ cache, const int32_t* __restrict__ fill_slots, unsigned C,
+                                                   float* host, const int32_t* __restrict__ miss_ranks,
+                                                   const int32_t* __restrict__ old_rank, unsigned N, int rows, int D, int lpr_shift) {
+    using V = typename Vec<VEC>::T;
+    const int lpr = 1 << lpr_shift;
+    const int gpb = blockDim.x >> lpr_shift;
+    const int gl = threadIdx.x >> lpr_shift, lane = threadIdx.x & (lpr - 1);
+    const int nv = D / VEC;
+    const int stride = gridDim.x * gpb;
+    int j = blockIdx.x * gpb + gl;
+    int s = 0, r = 0, o = -1;                // the list entries of the next row are requested before this row's data
+    if (j < rows) { s = fill_slots[j]; r = miss_ranks[j]; o = old_rank[j]; }
+    while (j < rows) {
+        const int jn = j + stride;
+        int sn = 0, rn = 0, on = -1;
+        if (jn < rows) { sn = fill_slots[jn]; rn = miss_ranks[jn]; on = old_rank[jn]; }
+        if ((unsigned)s < C && (unsigned)r < N) {            // never false for lists this library builds
+            V* row = reinterpret_cast<V*>(cache + (size_t)s * D);
+            const V* in = reinterpret_cast<const V*>(host + (size_t)r * D);
+            V* out = reinterpret_cast<V*>(host + (size_t)o * D);
+            const bool leaves = (unsigned)o < N;
+            for (int cidx = lane; cidx < nv; cidx += lpr) {
+                const V v = in[cidx];
+                if (leaves) out[cidx] = nt_load_row(&row[cidx]);
+                row[cidx] = v;
+            }
+        }
+        j = jn; s = sn; r = rn; o = on;
+    }
+}
+
 // Flush: every resident slot's row (with a dirty array: every dirty one) goes to its place in the host table.
 template <int VEC>
 __global__ __launch_bounds__(256) void k_flush_rows(float* __restrict__ host, const float* __restrict__ cache,
@@ -140,6 +176,20 @@ int launch_fill_rows(fc_cache* c, hipStream_t s, int64_t rows, float* dst, int64
                                                     c->stage_dev, c->fill_src, (unsigned)(DMA_BLOCKS * c->staging_rows), (int)rows, c->D, sh, only_transit ? 1 : 0)
     switch (c->vec) { case 4: FC_FILL(4); break; case 2: FC_FILL(2); break; default: FC_FILL(1); break; }
 #undef FC_FILL
+    FC_HIP(hipGetLastError());
+    return FC_OK;
+}
+
+int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows) {
+    if (rows <= 0) return FC_OK;
+    const int sh = shift_of(c->lpr);
+    int64_t blocks = cdiv(rows, 256 >> sh);
+    if (blocks > c->fill_blocks) blocks = c->fill_blocks;
+    ProfScope ps(c, P_MISS_FILL, s);
+#define FC_SWAP(V) \
+    k_swap_rows<V><<<(unsigned)blocks, 256, 0, s>>>(c->cache, c->fill_slots, (unsigned)c->C, c->host_dev, c->miss_ranks, c->fill_src, (unsigned)c->N, (int)rows, c->D, sh)
+    switch (c->vec) { case 4: FC_SWAP(4); break; case 2: FC_SWAP(2); break; default: FC_SWAP(1); break; }
+#undef FC_SWAP
     FC_HIP(hipGetLastError());
     return FC_OK;
 }

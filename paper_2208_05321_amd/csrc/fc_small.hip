@@ -23,13 +23,14 @@ struct SmallArgs {
     const int64_t* ids; const int64_t* offsets; const int32_t* freq_rank;
     uint4 *rbits4, *pbits4;
     int32_t *rank_slot, *slot_rank;
-    int32_t *miss_ranks, *vrank, *vslot, *fill_slots, *fill_src;   // fill_src: FC_EVICT_DMA only, else null
+    int32_t *miss_ranks, *vrank, *vslot, *fill_slots, *fill_src;
     int32_t* ranks;                    // rank of every id
     int32_t* slots_out;                // slot of every id; null: left to the caller (folded into the sort)
     const int32_t* landed_ranks;       // see k_rank_count
     Ctl* ctl; HostCtl* hctl;
     int64_t N;
     int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket;
+    bool dma;
 };
 
 // Words of a bitmap over one pair of 16-byte pieces (256 ranks).
@@ -294,7 +295,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
 #pragma unroll 1
     for (int j = tid; j < M; j += SM_THREADS) {
         const int s = a.fill_slots[j], rank = a.miss_ranks[j];
-        if (a.fill_src) a.fill_src[j] = a.rank_slot[rank]; // where the row's newest copy is: -1 the host table, <= -2 in transit
+        // FC_EVICT_DMA: where the row's newest copy is (-1 the host table, <= -2 in transit); else the row that leaves the slot
+        a.fill_src[j] = a.dma ? a.rank_slot[rank] : a.slot_rank[s];
         a.slot_rank[s] = rank;
         a.rank_slot[rank] = s;
     }
@@ -316,7 +318,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
     a.rbits4 = (uint4*)c->rbits; a.pbits4 = (uint4*)c->pbits;
     a.rank_slot = c->rank_slot; a.slot_rank = c->slot_rank;
     a.miss_ranks = c->miss_ranks; a.vrank = c->vrank; a.vslot = c->vslot; a.fill_slots = c->fill_slots;
-    a.fill_src = c->dma_evict ? c->fill_src : nullptr;
+    a.fill_src = c->fill_src; a.dma = c->dma_evict;
     a.ranks = c->rbuf; a.slots_out = slots;
     a.landed_ranks = landed_ranks; a.landed = (int)landed; a.landed_base = (int)landed_base;
     a.ctl = c->ctl; a.hctl = c->hctl; a.N = c->N;
