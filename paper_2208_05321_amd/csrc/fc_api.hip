@@ -96,6 +96,7 @@ static int reset_state(fc_cache* c, bool warm) {
     k_iota_or_neg<<<1024, 256, 0, st>>>(c->rank_slot, c->N, warm ? c->C : 0);
     k_iota_or_neg<<<256, 256, 0, st>>>(c->slot_rank, c->C, warm ? c->C : 0);
     k_bits_prefix<<<256, 256, 0, st>>>(c->ubits, words, 0);
+    c->ubits_clean = true;
     k_bits_prefix<<<256, 256, 0, st>>>(c->pbits, words, 0);
     k_bits_prefix<<<256, 256, 0, st>>>(c->rbits, words, warm ? c->C : 0);
     k_set_ctl<<<1, 1, 0, st>>>(c->ctl, warm ? 0 : (int)c->C);
@@ -140,7 +141,7 @@ static void destroy(fc_cache* c) {
     for (int b = 0; b < DMA_BLOCKS; ++b)
         for (hipEvent_t e : {c->ev_copy_a[b], c->ev_copy_b[b]}) if (e) (void)hipEventDestroy(e);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
-                    (void*)c->rbits, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->moff, (void*)c->vtake, (void*)c->voff,
+                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->moff, (void*)c->vtake, (void*)c->voff,
                     (void*)c->rbuf,
                     (void*)c->ctl, (void*)c->stage_dev, (void*)c->stage_dev2, (void*)c->part, (void*)c->pmeta, (void*)c->pbits})
         if (p) (void)hipFree(p);
@@ -265,7 +266,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     FC_HIP(hipMalloc((void**)&c->rbits, words * 4));
     FC_HIP(hipMalloc((void**)&c->pbits, words * 4));
     FC_HIP(hipMalloc((void**)&c->tcount, (size_t)cdiv(C, 1024) * 4));
-    FC_HIP(hipMalloc((void**)&c->hitpart, 256 * 4));
+    FC_HIP(hipMalloc((void**)&c->hitpart, MARK_HIT_PARTS * 4));
     FC_HIP(hipMalloc((void**)&c->bsum, (size_t)c->NB * 3 * 4));
     FC_HIP(hipMalloc((void**)&c->moff, (size_t)c->NB * 4));
     FC_HIP(hipMalloc((void**)&c->vtake, (size_t)c->NB * 4));
@@ -489,6 +490,7 @@ int cache_reserve(fc_cache* c, int64_t max_ids, int32_t pipelined) {
     FC_HIP(hipSetDevice(c->device));
     FC_TRY(ensure_rbuf(c, max_ids));
     FC_TRY(reserve_bwd(c, max_ids));
+    (void)mark_bytes(c, max_ids);      // without room for them the marks stay bits
     if (pipelined && !(c->flags & FC_TRANSMIT_STAGED))
         for (int k = 0; k < 2; ++k) if (!ensure_arrival_block(c, k)) return FC_ERR_OOM_DEVICE;
     return FC_OK;

@@ -16,6 +16,8 @@ constexpr int WAVE = 64;
 // 256 threads x one uint4, i.e. 32768 ranks per tile.
 constexpr int RT_THREADS = 256;
 constexpr int RT_WORDS = RT_THREADS * 4;
+constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
+constexpr int64_t MARKB_ROWS_PER_ID = 128;        // byte marks up to this many rows per id of the batch
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;
 constexpr int RS_ITEMS = 8;                      // keys per thread
@@ -164,7 +166,10 @@ struct fc_cache {
     int32_t* rank_slot = nullptr;   // [N]  cpu_row_idx -> gpu_row_idx, -1 = not resident
     int32_t* slot_rank = nullptr;   // [C]  gpu_row_idx -> cpu_row_idx, -1 = empty
     float* cache = nullptr;         // [C][D]
-    uint32_t* ubits = nullptr;      // rank-space bitmap: rows used by the current batch (zero between calls)
+    uint32_t* ubits = nullptr;      // rank-space bitmap: rows used by the current batch (zero between calls if ubits_clean)
+    bool ubits_clean = true;
+    uint8_t* ubytes = nullptr;      // rank-space byte marks (zero between calls), allocated with the first batch that uses them
+    bool ubytes_failed = false;
     uint32_t* rbits = nullptr;      // rank-space bitmap: resident rows
     int32_t* tcount = nullptr;      // empty slots per tile of 1024 slots
     int32_t* hitpart = nullptr;     // [256] per-workgroup access-level hit counts of the marking kernel
@@ -320,6 +325,7 @@ int dma_quiesce(fc_cache* c, hipStream_t st);
 // from_ranks: the slots are not written yet; the sort's first kernel derives them from the per-id ranks and writes them
 // to `slots_out` on its way (the slot write-out folded into the sort)
 int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr);
+bool mark_bytes(fc_cache* c, int64_t n);  // byte marks for a batch of n ids (allocates them on first use)
 int ensure_rbuf(fc_cache* c, int64_t n);  // per-id rank buffer for batches of n ids
 int reserve_bwd(fc_cache* c, int64_t n);   // sort scratch of all three sets and the partial rows for batches of n lookups
 int bwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags,

@@ -13,6 +13,8 @@
 #include <omp.h>
 #include <string.h>
 
+#include <utility>
+
 namespace fc {
 
 // ---------------------------------------------------------------------------------------------------------
@@ -126,6 +128,125 @@ __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// K1, byte marks: the same, with one byte per rank in place of one bit.  Setting a byte is a plain store (every writer stores
+// the same 1, and the L2s merge bytes), so there are no atomics to queue up, no bitmap in LDS to clear and merge, and small
+// workgroups that find room beside the previous batch's forward and backward kernels; what it costs is reading N bytes
+// instead of N / 8 in K2a.  Bound by the latency of two random reads per id.
+// Measured (us, k_remap_mark + k_rank_count -> these two, in the schedules of the benchmark): 426 k ids, 10 M rows 25.6 + 6.3
+// -> 10.5 + 6.7 (plain) and 32.5 + 7.3 -> 16.6 + 11.5 (pipelined); 1.7 M ids, 100 M rows 81 + 14 -> 38 + 26.  (The bitmap
+// kernel with 256-thread workgroups and an 8 KB bitmap in LDS took 74 and 154: more of its marks are then global atomics.)
+// ---------------------------------------------------------------------------------------------------------
+constexpr int MARKB_THREADS = 256, MARKB_ITEMS = 4;
+
+__global__ __launch_bounds__(MARKB_THREADS) void k_remap_bytes(const int64_t* __restrict__ ids, int n,
+                                                               const int64_t* __restrict__ offsets, int num_bags,
+                                                               const int32_t* __restrict__ freq_rank, int64_t N,
+                                                               uint8_t* __restrict__ ubytes, const uint32_t* __restrict__ rbits,
+                                                               int32_t* __restrict__ rbuf, Ctl* ctl, int32_t* __restrict__ hitpart) {
+    __shared__ int red[MARKB_THREADS / 64];
+    const int tid = threadIdx.x;
+    const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
+    int hits = 0;
+    uint32_t flags = 0;
+    for (int64_t i0 = (int64_t)blockIdx.x * (MARKB_ITEMS * MARKB_THREADS) + tid; i0 < work; i0 += (int64_t)gridDim.x * (MARKB_ITEMS * MARKB_THREADS)) {
+        int64_t id[MARKB_ITEMS], o0[MARKB_ITEMS], o1[MARKB_ITEMS];
+        int r[MARKB_ITEMS];
+        uint32_t rb[MARKB_ITEMS];
+#pragma unroll
+        for (int k = 0; k < MARKB_ITEMS; ++k) {
+            const int64_t i = i0 + k * MARKB_THREADS;
+            id[k] = i < n ? ids[i] : 0;
+            o0[k] = i <= num_bags ? offsets[i] : 0;
+            o1[k] = i < num_bags ? offsets[i + 1] : o0[k];
+        }
+#pragma unroll
+        for (int k = 0; k < MARKB_ITEMS; ++k) {
+            const bool ok = (uint64_t)id[k] < (uint64_t)N;
+            if (!ok) flags |= EF_ID_RANGE;
+            r[k] = ok ? freq_rank[id[k]] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < MARKB_ITEMS; ++k) rb[k] = r[k] >= 0 ? rbits[(uint32_t)r[k] >> 5] : 0u;
+#pragma unroll
+        for (int k = 0; k < MARKB_ITEMS; ++k) {
+            const int64_t i = i0 + k * MARKB_THREADS;
+            if (i < n) {
+                if (r[k] >= 0) {
+                    ubytes[r[k]] = 1;
+                    hits += (rb[k] >> (r[k] & 31)) & 1u;
+                }
+                rbuf[i] = r[k];
+            }
+            if (i <= num_bags) {
+                if (o0[k] != i) flags |= EF_NOT_ONE_PER_BAG;
+                if ((i == 0 && o0[k] != 0) || (i == num_bags && o0[k] != (int64_t)n) || o1[k] < o0[k]) flags |= EF_BAD_OFFSETS;
+            }
+        }
+    }
+    hits = wave_sum(hits);
+    if ((tid & 63) == 0) red[tid >> 6] = hits;
+    __syncthreads();
+    if (tid == 0) {
+        int s = 0;
+#pragma unroll
+        for (int k = 0; k < MARKB_THREADS / 64; ++k) s += red[k];
+        hitpart[blockIdx.x] = s;
+    }
+    if (flags) atomicOr(&ctl->err_flags, flags);
+}
+
+// K2a, byte marks: the tile's 32768 bytes become its bitmap words (all of them written), the set ones are cleared, and the
+// counts are those of k_rank_count.  A lane turns 16 bytes into 16 bits with four 4-byte dot products.
+__device__ __forceinline__ uint32_t bits_of(uint4 v) {
+    const uint32_t lo = __builtin_amdgcn_udot4(v.y, 0x80402010u, __builtin_amdgcn_udot4(v.x, 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4(v.w, 0x80402010u, __builtin_amdgcn_udot4(v.z, 0x08040201u, 0u, false), false);
+    return lo | hi << 8;
+}
+
+__global__ __launch_bounds__(RT_THREADS) void k_count_bytes(uint4* ubytes16, uint16_t* __restrict__ ubits16,
+                                                            const uint16_t* __restrict__ rbits16,
+                                                            const uint16_t* __restrict__ pbits16, int protect_prev,
+                                                            int32_t* __restrict__ bsum, int NB,
+                                                            const int32_t* __restrict__ landed_ranks, int landed, int landed_base,
+                                                            int32_t* rank_slot) {
+    __shared__ int lds[3][RT_THREADS / 64];
+    for (int j = blockIdx.x * RT_THREADS + threadIdx.x; j < landed; j += gridDim.x * RT_THREADS) {
+        const int r = landed_ranks[j];
+        if (rank_slot[r] == -2 - (landed_base + j)) rank_slot[r] = -1;
+    }
+    constexpr int PER = RT_WORDS * 2 / RT_THREADS;          // 16-rank pieces per thread
+    const size_t p0 = (size_t)blockIdx.x * (RT_WORDS * 2) + threadIdx.x;
+    uint4 v[PER];
+    uint32_t q[PER], pv[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = ubytes16[p0 + k * RT_THREADS];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) q[k] = rbits16[p0 + k * RT_THREADS];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) pv[k] = protect_prev ? pbits16[p0 + k * RT_THREADS] : 0;
+    int cu = 0, cm = 0, cc = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const uint32_t u = bits_of(v[k]);
+        if (u) ubytes16[p0 + k * RT_THREADS] = make_uint4(0, 0, 0, 0);
+        ubits16[p0 + k * RT_THREADS] = (uint16_t)u;
+        cu += __popc(u);
+        cm += __popc(u & ~q[k]);
+        cc += __popc(q[k] & ~pv[k] & ~u);      // look-ahead: rows of the previously prepared batch are not evictable either
+    }
+    cu = wave_sum(cu); cm = wave_sum(cm); cc = wave_sum(cc);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) { lds[0][w] = cu; lds[1][w] = cm; lds[2][w] = cc; }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        int s = 0;
+#pragma unroll
+        for (int k = 0; k < RT_THREADS / 64; ++k) s += lds[threadIdx.x][k];
+        bsum[(size_t)threadIdx.x * NB + blockIdx.x] = s;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // K2a  per rank-space tile: rows used, rows missing, rows evictable.
 //      On the way (DMA evict transmitter): the block that this batch's victims will go to has reached the host table, so
 //      rows still marked as in transit in it become plain "not resident" (what k_clear_transit does; folded in here
@@ -183,7 +304,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(const int32_t* __res
     const int tid = threadIdx.x;
     constexpr int CH = PLAN_THREADS * PLAN_ITEMS;          // tiles per round: PLAN_ITEMS consecutive ones per thread
     int hits;
-    (void)block_excl_scan<PLAN_THREADS>(tid < nmark ? hitpart[tid] : 0, hits, lds);   // nmark <= 256
+    int mine = 0;
+    for (int k = tid; k < nmark; k += PLAN_THREADS) mine += hitpart[k];
+    (void)block_excl_scan<PLAN_THREADS>(mine, hits, lds);
     // forward: output offset of every tile's missing ranks; the totals of used and evictable rows on the way
     int carryM = 0, accU = 0, accC = 0;
     for (int base = 0; base < NB; base += CH) {
@@ -275,17 +398,18 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint4* ubits4, uint4* 
                                                           int32_t* __restrict__ miss_ranks, int32_t* __restrict__ vrank,
                                                           int32_t* __restrict__ vslot, int32_t* rank_slot,
                                                           int32_t* slot_rank, int C, int transit_base,
-                                                          int transit_rows, int32_t* __restrict__ fill_src) {
+                                                          int transit_rows, int32_t* __restrict__ fill_src, int keep_bits) {
+    // keep_bits (byte marks): the bitmap is rewritten by the next K2a and becomes pbits by a swap of pointers
     __shared__ int lds[RT_THREADS / 64];
     const size_t idx = (size_t)blockIdx.x * RT_THREADS + threadIdx.x;
     const uint4 u4 = ubits4[idx];
     const bool anyu = (u4.x | u4.y | u4.z | u4.w) != 0;
     if (ctl->status != FC_OK) {            // failed call: forget the marks, touch nothing else
-        if (anyu) ubits4[idx] = make_uint4(0, 0, 0, 0);
+        if (anyu && !keep_bits) ubits4[idx] = make_uint4(0, 0, 0, 0);
         return;
     }
     const uint4 r4 = rbits4[idx];
-    const uint4 p4 = pbits4[idx];
+    const uint4 p4 = !keep_bits || protect_prev ? pbits4[idx] : make_uint4(0, 0, 0, 0);
     const uint32_t uw[4] = {u4.x, u4.y, u4.z, u4.w};
     const uint32_t rw[4] = {r4.x, r4.y, r4.z, r4.w};
     const uint32_t pw[4] = {protect_prev ? p4.x : 0u, protect_prev ? p4.y : 0u, protect_prev ? p4.z : 0u, protect_prev ? p4.w : 0u};
@@ -352,6 +476,7 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint4* ubits4, uint4* 
     if (cm || (vw[0] | vw[1] | vw[2] | vw[3]))
         rbits4[idx] = make_uint4((rw[0] & ~vw[0]) | mw[0], (rw[1] & ~vw[1]) | mw[1], (rw[2] & ~vw[2]) | mw[2],
                                  (rw[3] & ~vw[3]) | mw[3]);
+    if (keep_bits) return;
     if (anyu) ubits4[idx] = make_uint4(0, 0, 0, 0);
     if (anyu || (p4.x | p4.y | p4.z | p4.w)) pbits4[idx] = u4;     // this batch is the "previous" one next time
 }
@@ -520,6 +645,22 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
     FC_HIP(hipMalloc((void**)&c->rbuf, (size_t)cap * 4));
     c->n_cap = cap;
     return FC_OK;
+}
+
+__global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
+
+// Byte marks cost N / 5 TB/s more in K2a, bit marks 0.04 to 0.06 ns per id in K1 (atomics), so the line lies near N = 128 n
+// (measured: see k_remap_bytes); a map that could not be allocated leaves the bits.
+bool mark_bytes(fc_cache* c, int64_t n) {
+    if (c->N > MARKB_ROWS_PER_ID * n) return false;
+    if (!c->ubytes && !c->ubytes_failed) {
+        const size_t bytes = (size_t)c->NB * RT_WORDS * 32;
+        if (hipMalloc((void**)&c->ubytes, bytes) != hipSuccess) { (void)hipGetLastError(); c->ubytes = nullptr; c->ubytes_failed = true; }
+        else if (hipMemset(c->ubytes, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError(); (void)hipFree(c->ubytes); c->ubytes = nullptr; c->ubytes_failed = true;
+        }
+    }
+    return c->ubytes != nullptr;
 }
 
 // Evicted rows, default transmitter: gather into a device block on the caller's stream (so the slots can be
@@ -702,6 +843,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     const bool small_slots = small && !defer_slots && !before_slots;     // its one kernel may write the caller's buffer, too
     const int transit = c->dirty_track ? -1 : transit_base;
     const int32_t* landed_ranks = c->dma_evict ? c->vrank_buf[buf] : nullptr;
+    bool bytes = false;                  // marks are bytes
     if (small) {
         if (c->evict_pending) {        // as below
             FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
@@ -711,18 +853,37 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
                                     buf * c->staging_rows, transit));
     } else {
         const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
-        int64_t nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
-        if (nmark > MARK_MAX_BLOCKS) nmark = MARK_MAX_BLOCKS;
-        const int64_t per_block = cdiv(cdiv(work, nmark), MARK_THREADS) * MARK_THREADS;
-        nmark = cdiv(work, per_block);
-        const int64_t words = c->NB * RT_WORDS;
-        {
-            ProfScope ps(c, P_REMAP_MARK, st);
-            k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
-                                                                  c->rbits, c->rbuf, c->ctl, c->hitpart, (int)per_block,
-                                                                  (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
-        }
-        {
+        int64_t nmark;
+        bytes = mark_bytes(c, n);
+        if (bytes) {
+            nmark = cdiv(work, MARKB_ITEMS * MARKB_THREADS);
+            if (nmark > MARK_HIT_PARTS) nmark = MARK_HIT_PARTS;
+            {
+                ProfScope ps(c, P_REMAP_MARK, st);
+                k_remap_bytes<<<(unsigned)nmark, MARKB_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubytes,
+                                                                        c->rbits, c->rbuf, c->ctl, c->hitpart);
+            }
+            ProfScope ps(c, P_RANK_COUNT, st);
+            k_count_bytes<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, (uint16_t*)c->ubits, (const uint16_t*)c->rbits,
+                                                                 (const uint16_t*)c->pbits, protect_prev, c->bsum, (int)c->NB,
+                                                                 landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot);
+            c->ubits_clean = false;
+        } else {
+            nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
+            if (nmark > MARK_MAX_BLOCKS) nmark = MARK_MAX_BLOCKS;
+            const int64_t per_block = cdiv(cdiv(work, nmark), MARK_THREADS) * MARK_THREADS;
+            nmark = cdiv(work, per_block);
+            const int64_t words = c->NB * RT_WORDS;
+            if (!c->ubits_clean) {               // left over from byte marks
+                k_zero_words<<<(unsigned)cdiv(words, 1024), 256, 0, st>>>((uint4*)c->ubits);
+                c->ubits_clean = true;
+            }
+            {
+                ProfScope ps(c, P_REMAP_MARK, st);
+                k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
+                                                                      c->rbits, c->rbuf, c->ctl, c->hitpart, (int)per_block,
+                                                                      (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
+            }
             ProfScope ps(c, P_RANK_COUNT, st);
             k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((const uint4*)c->ubits, (const uint4*)c->rbits, (const uint4*)c->pbits,
                                                                 protect_prev, c->bsum, (int)c->NB,
@@ -745,7 +906,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
                                                                c->moff, c->vtake, c->voff,
                                                                c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, (int)c->C,
                                                                transit, (int)c->staging_rows,
-                                                               c->dma_evict ? c->fill_src : nullptr);
+                                                               c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0);
         }
     }
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
@@ -755,6 +916,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     int32_t h[HOST_REC_WORDS];
     FC_TRY(wait_for_record(c->hctl, ticket, st, h));
     if (h[HW_STATUS] != FC_OK) return h[HW_STATUS];
+    if (bytes) std::swap(c->ubits, c->pbits);            // this batch is the "previous" one next time
     c->last_one_per_bag = n == num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
     const int64_t M = h[HW_MISS], need = h[HW_NEED];
     if (M > 0 && !small) {

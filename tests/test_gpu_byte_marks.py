@@ -1,0 +1,44 @@
+"""`-m gpu`: byte marks (batches of at least one id per 128 rows) against the oracle at the edges of a 32768-rank tile and of
+the rule, and batches of both kinds, and of the one-workgroup kind, in turn on one handle, in every schedule."""
+import pytest
+
+from tests.parity import run_parity, run_parity_lookahead, run_parity_planned
+from tests.tiny_workload import TinyWorkload
+
+pytestmark = pytest.mark.gpu
+
+
+class Sizes(TinyWorkload):
+    """Batch t has sizes[t % len] bags."""
+
+    def __init__(self, sizes, **kw):
+        super().__init__(bags=sizes[0], **kw)
+        self.sizes = sizes
+
+    def batch(self, t):
+        self.bags = self.sizes[t % len(self.sizes)]
+        return super().batch(t)
+
+
+@pytest.mark.parametrize("rows", [32_767, 32_768, 32_769, 65_537, 1_048_576])
+@pytest.mark.parametrize("multi_hot", [False, True])
+def test_byte_marks(rows, multi_hot):
+    w = TinyWorkload(num_rows=rows, dim=4, cache_rows=7000, seed=rows, multi_hot=multi_hot, bags=8300, max_bag=3, hot=[3, rows - 1],
+                     distinct_cap=6500)
+    run_parity(w, 3, warm=False)
+    run_parity(w, 3, warm=True, dma_evict=True)
+
+
+SIZES = [12_000, 5000, 9375, 9374, 9376, 700, 12_000, 9000]          # 1.2 M rows: bytes from 9375 ids on
+
+
+@pytest.mark.parametrize("rows", [1_200_000, 600_000])
+def test_both_kinds_of_marks_in_turn(rows):
+    w = Sizes(SIZES, num_rows=rows, dim=4, cache_rows=30_000, seed=7, multi_hot=False, distinct_cap=9000)
+    run_parity(w, 8, warm=True)
+    run_parity_planned(w, 8, warm=True, dma_evict=True, inputs_ready=True)
+    run_parity_planned(w, 8, warm=False, dma_evict=False)
+    for dma in (False, True):
+        run_parity_lookahead(w, 8, warm=True, dma_evict=dma)
+    tight = Sizes(SIZES, num_rows=rows, dim=4, cache_rows=13_000, seed=8, multi_hot=False, distinct_cap=9000)
+    run_parity_lookahead(tight, 8, warm=True)                          # some look-aheads are refused
