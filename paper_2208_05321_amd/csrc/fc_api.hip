@@ -74,10 +74,7 @@ __global__ void k_bits_prefix(uint32_t* p, int64_t words, int64_t count) {
         p[w] = v;
     }
 }
-__global__ void k_set_ctl(Ctl* ctl, int nfree) {
-    ctl->err_flags = 0; ctl->async_flags = 0; ctl->nfree = nfree;
-    ctl->status = 0; ctl->n_unique = 0; ctl->n_miss = 0; ctl->need = 0;
-}
+__global__ void k_set_ctl(Ctl* ctl) { ctl->err[0] = ctl->err[1] = 0; ctl->async_flags = 0; }
 
 static int reset_state(fc_cache* c, bool warm) {
     hipStream_t st = c->stream;
@@ -99,7 +96,8 @@ static int reset_state(fc_cache* c, bool warm) {
     c->ubits_clean = true;
     k_bits_prefix<<<256, 256, 0, st>>>(c->pbits, words, 0);
     k_bits_prefix<<<256, 256, 0, st>>>(c->rbits, words, warm ? c->C : 0);
-    k_set_ctl<<<1, 1, 0, st>>>(c->ctl, warm ? 0 : (int)c->C);
+    k_set_ctl<<<1, 1, 0, st>>>(c->ctl);
+    c->nfree = warm ? 0 : c->C;
     FC_HIP(hipGetLastError());
     if (c->dirty) FC_HIP(hipMemsetAsync(c->dirty, 0, (size_t)c->C, st));   // loaded rows equal their host copies
     if (warm) FC_HIP(hipMemcpyAsync(c->cache, c->host, (size_t)c->C * c->D * 4, hipMemcpyHostToDevice, st));
@@ -141,7 +139,7 @@ static void destroy(fc_cache* c) {
     for (int b = 0; b < DMA_BLOCKS; ++b)
         for (hipEvent_t e : {c->ev_copy_a[b], c->ev_copy_b[b]}) if (e) (void)hipEventDestroy(e);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
-                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->moff, (void*)c->vtake, (void*)c->voff,
+                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->usum, (void*)c->plan, (void*)c->tile_plan,
                     (void*)c->rbuf,
                     (void*)c->ctl, (void*)c->stage_dev, (void*)c->stage_dev2, (void*)c->part, (void*)c->pmeta, (void*)c->pbits})
         if (p) (void)hipFree(p);
@@ -239,6 +237,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     if (const char* e = getenv("FC_AHEAD_MISS_PCT")) { const float v = (float)atof(e); if (v >= 0.f) c->ahead_miss_pct = v; }
     if (const char* e = getenv("FC_FWD_BAGS")) { const int v = atoi(e); if (v == 1 || v == 2 || v == 4) c->fwd_bags = v; }
     if (const char* e = getenv("FC_MARK_IPT")) { const int v = atoi(e); if (v >= 1 && v <= 64) c->mark_ids_per_thread = v; }
+    if (const char* e = getenv("FC_PLAN_FOLD_TILES")) { const int v = atoi(e); if (v >= 0) c->plan_fold_tiles = v; }
     if (const char* e = getenv("FC_EVICT_EARLY")) c->evict_early = atoi(e);
     c->NB = cdiv(cdiv(N, 32), RT_WORDS);
     const size_t words = (size_t)c->NB * RT_WORDS;
@@ -267,10 +266,11 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     FC_HIP(hipMalloc((void**)&c->pbits, words * 4));
     FC_HIP(hipMalloc((void**)&c->tcount, (size_t)cdiv(C, 1024) * 4));
     FC_HIP(hipMalloc((void**)&c->hitpart, MARK_HIT_PARTS * 4));
-    FC_HIP(hipMalloc((void**)&c->bsum, (size_t)c->NB * 3 * 4));
-    FC_HIP(hipMalloc((void**)&c->moff, (size_t)c->NB * 4));
-    FC_HIP(hipMalloc((void**)&c->vtake, (size_t)c->NB * 4));
-    FC_HIP(hipMalloc((void**)&c->voff, (size_t)c->NB * 4));
+    FC_HIP(hipMalloc((void**)&c->bsum, (size_t)c->NB * 4));
+    FC_HIP(hipMalloc((void**)&c->ssum, (size_t)c->NB * SUB_TILES * 4));
+    FC_HIP(hipMalloc((void**)&c->usum, (size_t)c->NB * 4));
+    FC_HIP(hipMalloc((void**)&c->plan, 2 * 4));
+    FC_HIP(hipMalloc((void**)&c->tile_plan, (size_t)c->NB * sizeof(int4)));
     c->dma_evict = (flags & FC_EVICT_DMA) != 0;
     c->dirty_track = (flags & FC_DIRTY_TRACK) != 0;
     for (auto& set : c->lists)

@@ -16,6 +16,8 @@ constexpr int WAVE = 64;
 // 256 threads x one uint4, i.e. 32768 ranks per tile.
 constexpr int RT_THREADS = 256;
 constexpr int RT_WORDS = RT_THREADS * 4;
+constexpr int SUB_TILES = 8;                      // each tile's counts are also kept per eighth (4096 ranks)
+constexpr int PLAN_FOLD_TILES = 4096;             // up to this many tiles every workgroup of the emitting kernel plans for itself
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t MARKB_ROWS_PER_ID = 128;        // byte marks up to this many rows per id of the batch
 // Radix sort of (slot, bag) pairs for the backward pass.
@@ -45,13 +47,10 @@ constexpr int SMALL_POS_BITS = 12, SMALL_KEY_BITS = 32 - SMALL_POS_BITS;
 enum : uint32_t { EF_BAD_OFFSETS = 1u, EF_ID_RANGE = 2u, EF_BAD_SLOT = 4u,
                   EF_NOT_ONE_PER_BAG = 8u };   // not an error: some bag of the batch does not hold exactly its own lookup
 
-// Device-resident control block, read and written by the planning kernels.
+// Device-resident control block.
 struct Ctl {
-    uint32_t err_flags;     // EF_* raised by the current cache_prepare
+    uint32_t err[2];        // EF_* raised by the current cache_prepare, in turn
     uint32_t async_flags;   // EF_BAD_SLOT raised by fwd / bwd kernels
-    int32_t nfree;          // empty slots
-    int32_t status;         // FC_* decision of the current cache_prepare
-    int32_t n_unique, n_miss, need;
 };
 
 // Host-visible (pinned, mapped) copy of the decision, written by the planning kernel: every word carries the number of the
@@ -174,10 +173,14 @@ struct fc_cache {
     int32_t* tcount = nullptr;      // empty slots per tile of 1024 slots
     int32_t* hitpart = nullptr;     // [256] per-workgroup access-level hit counts of the marking kernel
     int64_t NB = 0;                 // rank-space tiles
-    int32_t* bsum = nullptr;        // [3][NB] per-tile counts: used, missing, evictable
-    int32_t* moff = nullptr;        // [NB] output offset of a tile's missing ranks
-    int32_t* vtake = nullptr;       // [NB] victims taken from a tile
-    int32_t* voff = nullptr;        // [NB] output offset of a tile's victims
+    uint32_t* bsum = nullptr;       // [NB] per-tile counts: missing, evictable (high half)
+    uint32_t* ssum = nullptr;       // [NB * SUB_TILES] the same per sub-tile
+    int32_t* usum = nullptr;        // [NB] per-tile counts: used
+    int32_t* plan = nullptr;        // more than PLAN_FOLD_TILES tiles: status, victims ...
+    int4* tile_plan = nullptr;      // [NB] ... and per tile: missing rows before it, evictable rows above it
+    int plan_fold_tiles = fc::PLAN_FOLD_TILES;   // (tuning: FC_PLAN_FOLD_TILES)
+    int64_t nfree = 0;              // empty slots
+    int err_set = 0;                // which of the two error words the next call uses
     int32_t* miss_ranks = nullptr;  // [C]  these five point into lists[lset] (vrank into vrank_buf with FC_EVICT_DMA)
     int32_t* vrank = nullptr;       // [C]
     int32_t* vslot = nullptr;       // [C]

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __re
                                                              const int64_t* __restrict__ offsets, int num_bags,
                                                              const int32_t* __restrict__ freq_rank, int64_t N,
                                                              uint32_t* ubits, const uint32_t* __restrict__ rbits,
-                                                             int32_t* __restrict__ rbuf, Ctl* ctl,
+                                                             int32_t* __restrict__ rbuf, uint32_t* err,
                                                              int32_t* __restrict__ hitpart, int per_block,
                                                              int lds_words) {
     __shared__ uint32_t low[MARK_LDS_WORDS];
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __re
         for (int k = 0; k < MARK_THREADS / 64; ++k) s += red[k];
         hitpart[blockIdx.x] = s;
     }
-    if (flags) atomicOr(&ctl->err_flags, flags);
+    if (flags) atomicOr(err, flags);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(MARKB_THREADS) void k_remap_bytes(const int64_t* __
                                                                const int64_t* __restrict__ offsets, int num_bags,
                                                                const int32_t* __restrict__ freq_rank, int64_t N,
                                                                uint8_t* __restrict__ ubytes, const uint32_t* __restrict__ rbits,
-                                                               int32_t* __restrict__ rbuf, Ctl* ctl, int32_t* __restrict__ hitpart) {
+                                                               int32_t* __restrict__ rbuf, uint32_t* err, int32_t* __restrict__ hitpart) {
     __shared__ int red[MARKB_THREADS / 64];
     const int tid = threadIdx.x;
     const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(MARKB_THREADS) void k_remap_bytes(const int64_t* __
         for (int k = 0; k < MARKB_THREADS / 64; ++k) s += red[k];
         hitpart[blockIdx.x] = s;
     }
-    if (flags) atomicOr(&ctl->err_flags, flags);
+    if (flags) atomicOr(err, flags);
 }
 
 // K2a, byte marks: the tile's 32768 bytes become its bitmap words (all of them written), the set ones are cleared, and the
@@ -203,13 +203,32 @@ __device__ __forceinline__ uint32_t bits_of(uint4 v) {
     return lo | hi << 8;
 }
 
+// part[w][k]: missing, and evictable in the high half, of sub-tile k as wavefront w saw them; last: used
+__device__ __forceinline__ void tile_counts(int (*part)[SUB_TILES + 1], uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum,
+                                            int32_t* __restrict__ usum, uint32_t* next_err) {
+    if (threadIdx.x >= 64) return;
+    const int k = threadIdx.x;
+    uint32_t v = 0;
+    if (k <= SUB_TILES)
+        for (int w = 0; w < RT_THREADS / 64; ++w) v += (uint32_t)part[w][k];
+    if (k < SUB_TILES) ssum[(size_t)blockIdx.x * SUB_TILES + k] = v;
+    if (k == SUB_TILES) usum[blockIdx.x] = (int)v;
+    uint32_t t = k < SUB_TILES ? v : 0;                // 32768 at most, each
+#pragma unroll
+    for (int o = SUB_TILES / 2; o > 0; o >>= 1) t += (uint32_t)__shfl_down((int)t, o);
+    if (k == 0) {
+        bsum[blockIdx.x] = t;
+        if (blockIdx.x == 0) *next_err = 0;            // the next call's error word
+    }
+}
+
 __global__ __launch_bounds__(RT_THREADS) void k_count_bytes(uint4* ubytes16, uint16_t* __restrict__ ubits16,
                                                             const uint16_t* __restrict__ rbits16,
                                                             const uint16_t* __restrict__ pbits16, int protect_prev,
-                                                            int32_t* __restrict__ bsum, int NB,
+                                                            uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int32_t* __restrict__ usum,
                                                             const int32_t* __restrict__ landed_ranks, int landed, int landed_base,
-                                                            int32_t* rank_slot) {
-    __shared__ int lds[3][RT_THREADS / 64];
+                                                            int32_t* rank_slot, uint32_t* next_err) {
+    __shared__ int part[RT_THREADS / 64][SUB_TILES + 1];
     for (int j = blockIdx.x * RT_THREADS + threadIdx.x; j < landed; j += gridDim.x * RT_THREADS) {
         const int r = landed_ranks[j];
         if (rank_slot[r] == -2 - (landed_base + j)) rank_slot[r] = -1;
@@ -224,26 +243,23 @@ __global__ __launch_bounds__(RT_THREADS) void k_count_bytes(uint4* ubytes16, uin
     for (int k = 0; k < PER; ++k) q[k] = rbits16[p0 + k * RT_THREADS];
 #pragma unroll
     for (int k = 0; k < PER; ++k) pv[k] = protect_prev ? pbits16[p0 + k * RT_THREADS] : 0;
-    int cu = 0, cm = 0, cc = 0;
+    static_assert(PER == SUB_TILES, "piece k of every thread lies in sub-tile k");
+    int cu = 0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const uint32_t u = bits_of(v[k]);
         if (u) ubytes16[p0 + k * RT_THREADS] = make_uint4(0, 0, 0, 0);
         ubits16[p0 + k * RT_THREADS] = (uint16_t)u;
         cu += __popc(u);
-        cm += __popc(u & ~q[k]);
-        cc += __popc(q[k] & ~pv[k] & ~u);      // look-ahead: rows of the previously prepared batch are not evictable either
+        // look-ahead: rows of the previously prepared batch are not evictable either
+        const int c = wave_sum(__popc(u & ~q[k]) | __popc(q[k] & ~pv[k] & ~u) << 16);
+        if (lane == 0) part[w][k] = c;
     }
-    cu = wave_sum(cu); cm = wave_sum(cm); cc = wave_sum(cc);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { lds[0][w] = cu; lds[1][w] = cm; lds[2][w] = cc; }
+    cu = wave_sum(cu);
+    if (lane == 0) part[w][SUB_TILES] = cu;
     __syncthreads();
-    if (threadIdx.x < 3) {
-        int s = 0;
-#pragma unroll
-        for (int k = 0; k < RT_THREADS / 64; ++k) s += lds[threadIdx.x][k];
-        bsum[(size_t)threadIdx.x * NB + blockIdx.x] = s;
-    }
+    tile_counts(part, bsum, ssum, usum, next_err);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -255,10 +271,10 @@ __global__ __launch_bounds__(RT_THREADS) void k_count_bytes(uint4* ubytes16, uin
 __global__ __launch_bounds__(RT_THREADS) void k_rank_count(const uint4* __restrict__ ubits4,
                                                            const uint4* __restrict__ rbits4,
                                                            const uint4* __restrict__ pbits4, int protect_prev,
-                                                           int32_t* __restrict__ bsum, int NB,
+                                                           uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int32_t* __restrict__ usum,
                                                            const int32_t* __restrict__ landed_ranks, int landed, int landed_base,
-                                                           int32_t* rank_slot) {
-    __shared__ int lds[3][RT_THREADS / 64];
+                                                           int32_t* rank_slot, uint32_t* next_err) {
+    __shared__ int part[RT_THREADS / 64][SUB_TILES + 1];
     for (int j = blockIdx.x * RT_THREADS + threadIdx.x; j < landed; j += gridDim.x * RT_THREADS) {
         const int r = landed_ranks[j];
         if (rank_slot[r] == -2 - (landed_base + j)) rank_slot[r] = -1;
@@ -272,213 +288,277 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_count(const uint4* __restri
         r.x &= ~p.x; r.y &= ~p.y; r.z &= ~p.z; r.w &= ~p.w;
     }
     int cu = __popc(u.x) + __popc(u.y) + __popc(u.z) + __popc(u.w);
-    int cm = cm0;
-    int cc = __popc(r.x & ~u.x) + __popc(r.y & ~u.y) + __popc(r.z & ~u.z) + __popc(r.w & ~u.w);
-    cu = wave_sum(cu); cm = wave_sum(cm); cc = wave_sum(cc);
+    const int cc = __popc(r.x & ~u.x) + __popc(r.y & ~u.y) + __popc(r.z & ~u.z) + __popc(r.w & ~u.w);
+    // a sub-tile is 32 threads: half a wavefront
+    static_assert(RT_THREADS / SUB_TILES == 32, "");
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { lds[0][w] = cu; lds[1][w] = cm; lds[2][w] = cc; }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        int s = 0;
+    int c = cm0 | cc << 16;
 #pragma unroll
-        for (int k = 0; k < RT_THREADS / 64; ++k) s += lds[threadIdx.x][k];
-        bsum[(size_t)threadIdx.x * NB + blockIdx.x] = s;
-    }
+    for (int o = 16; o > 0; o >>= 1) c += __shfl_down(c, o, 32);
+    if (threadIdx.x < (RT_THREADS / 64) * (SUB_TILES + 1)) part[threadIdx.x / (SUB_TILES + 1)][threadIdx.x % (SUB_TILES + 1)] = 0;
+    __syncthreads();
+    if ((lane & 31) == 0) part[w][threadIdx.x / 32] = c;
+    cu = wave_sum(cu);
+    if (lane == 0) part[w][SUB_TILES] = cu;
+    __syncthreads();
+    tile_counts(part, bsum, ssum, usum, next_err);
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// K2b  one workgroup: totals, the call's status, evict_num = numel(miss) - empty slots, output offsets of
-//      every tile's missing ranks, and which tiles give up how many victims (from the top rank down).
+// K2b  totals, the call's status, evict_num = numel(miss) - empty slots, and for a tile: where its missing ranks go in the
+//      list, how many victims it gives up (from the top rank down) and where those go.
+//
+//      All of it is a sum over the tiles' counts, one word each, so every workgroup of K2c works it out for its own tile (12 KB
+//      of reads from L2 at 100 M rows) instead of waiting for a kernel of one workgroup in between (6 us at 306 tiles, 11-14 at
+//      3052, and a launch), and the first one reports to the host before it starts on its tile.  Above PLAN_FOLD_TILES tiles
+//      (134 M rows) those reads would grow with the square of the tiles: there one workgroup plans for all.
 //      (Tried: letting the last workgroup of K2a to finish do this, found by an atomic ticket.  One ticket per tile on
 //      one address costs about 100 ns each on this part, 300 us at 3052 tiles: slower than the launch it saves.)
 // ---------------------------------------------------------------------------------------------------------
-// 256 threads: a workgroup this small finds room on a compute unit at once; a 1024-thread one waited up to 200 us for
-// sixteen free wave slots beside the previous batch's forward kernel, with the host waiting for its ticket.
-constexpr int PLAN_THREADS = 256;
-constexpr int PLAN_ITEMS = 4;
-__global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(const int32_t* __restrict__ bsum, int NB, int C, Ctl* ctl,
-                                                    HostCtl* hctl, int32_t* __restrict__ moff,
-                                                    int32_t* __restrict__ vtake, int32_t* __restrict__ voff,
-                                                    const int32_t* __restrict__ hitpart, int nmark, int ticket) {
+struct PlanArgs {
+    const uint32_t *bsum, *ssum; const int32_t* usum;    // K2a's counts
+    const uint32_t* err; const uint32_t* async_flags;
+    const int32_t* hitpart; HostCtl* hctl;
+    int NB, C, nfree, nmark, ticket, protect_prev;
+};
+struct PlanTotals { int status, used, miss, need; };
+
+__device__ __forceinline__ PlanTotals plan_totals(const PlanArgs& a, int used, int miss, int evictable) {
+    // without the look-ahead's second protected set, resident rows are either used or evictable
+    if (!a.protect_prev) used = miss + (a.C - a.nfree) - evictable;
+    const uint32_t ef = *a.err;
+    PlanTotals t{FC_OK, used, miss, miss - a.nfree};
+    if (ef & EF_BAD_OFFSETS) t.status = FC_ERR_BAD_OFFSETS;
+    else if (ef & EF_ID_RANGE) t.status = FC_ERR_ID_OUT_OF_RANGE;
+    else if (used > a.C) t.status = FC_ERR_BATCH_EXCEEDS_CACHE;
+    if (t.need < 0) t.need = 0;
+    // enough evictable rows?  (always, unless the look-ahead protects the previous batch as well)
+    if (t.status == FC_OK && t.need > evictable) t.status = FC_ERR_BATCH_EXCEEDS_CACHE;
+    if (t.status != FC_OK) t.need = 0;
+    return t;
+}
+
+template <int NT>
+__device__ __forceinline__ int block_sum(int v, int* lds /* NT / 64 ints */) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int s = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) s += lds[k];
+    __syncthreads();
+    return s;
+}
+
+template <int NT>
+__device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals& t, int* lds) {
+    int mine = 0;
+    for (int k = threadIdx.x; k < a.nmark; k += NT) mine += a.hitpart[k];
+    const int hits = block_sum<NT>(mine, lds);
+    if (threadIdx.x < HOST_REC_WORDS)
+        report_to_host(a.hctl, a.ticket, t.status, t.used, t.miss, t.need, hits, t.status == FC_OK ? a.nfree + t.need - t.miss : a.nfree,
+                       (int)*a.async_flags, (int)(*a.err & EF_NOT_ONE_PER_BAG), threadIdx.x);
+}
+
+// More than PLAN_FOLD_TILES tiles: one workgroup writes what K2c would work out.
+constexpr int PLAN_THREADS = 1024;
+__global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int32_t* __restrict__ plan, int4* __restrict__ tile_plan) {
     __shared__ int lds[PLAN_THREADS / 64];
     const int tid = threadIdx.x;
-    constexpr int CH = PLAN_THREADS * PLAN_ITEMS;          // tiles per round: PLAN_ITEMS consecutive ones per thread
-    int hits;
-    int mine = 0;
-    for (int k = tid; k < nmark; k += PLAN_THREADS) mine += hitpart[k];
-    (void)block_excl_scan<PLAN_THREADS>(mine, hits, lds);
-    // forward: output offset of every tile's missing ranks; the totals of used and evictable rows on the way
-    int carryM = 0, accU = 0, accC = 0;
-    for (int base = 0; base < NB; base += CH) {
-        const int b0 = base + tid * PLAN_ITEMS;
-        int m[PLAN_ITEMS], sum = 0;
-#pragma unroll
-        for (int k = 0; k < PLAN_ITEMS; ++k) {
-            const int b = b0 + k;
-            m[k] = b < NB ? bsum[(size_t)NB + b] : 0;
-            if (b < NB) { accU += bsum[b]; accC += bsum[(size_t)2 * NB + b]; }
-            sum += m[k];
-        }
-        int tot;
-        int run = carryM + block_excl_scan<PLAN_THREADS>(sum, tot, lds);
-#pragma unroll
-        for (int k = 0; k < PLAN_ITEMS; ++k)
-            if (b0 + k < NB) { moff[b0 + k] = run; run += m[k]; }
-        carryM += tot;
+    int mu = 0, mm = 0, mc = 0;
+    for (int b = tid; b < a.NB; b += PLAN_THREADS) {
+        const uint32_t v = a.bsum[b];
+        mu += a.usum[b]; mm += (int)(v & 0xffff); mc += (int)(v >> 16);
     }
-    int totU, totC;
-    (void)block_excl_scan<PLAN_THREADS>(accU, totU, lds);
-    (void)block_excl_scan<PLAN_THREADS>(accC, totC, lds);
-    const uint32_t ef = ctl->err_flags;
-    const int nfree = ctl->nfree;
-    int status = FC_OK;
-    if (ef & EF_BAD_OFFSETS) status = FC_ERR_BAD_OFFSETS;
-    else if (ef & EF_ID_RANGE) status = FC_ERR_ID_OUT_OF_RANGE;
-    else if (totU > C) status = FC_ERR_BATCH_EXCEEDS_CACHE;
-    const int M = carryM;
-    int need = M - nfree;
-    if (need < 0) need = 0;
-    // enough evictable rows?  (always, unless the look-ahead protects the previous batch as well)
-    if (status == FC_OK && need > totC) status = FC_ERR_BATCH_EXCEEDS_CACHE;
-    if (status != FC_OK) need = 0;
-    // Victims: walk tiles from the highest ranks down; `above` = evictable rows in tiles of larger rank.
-    int carry = 0;
-    for (int base = 0; base < NB; base += CH) {
-        const int r0 = base + tid * PLAN_ITEMS;            // position counted from the top tile
-        int cc[PLAN_ITEMS], sum = 0;
-#pragma unroll
-        for (int k = 0; k < PLAN_ITEMS; ++k) {
-            const int b = NB - 1 - (r0 + k);
-            cc[k] = b >= 0 ? bsum[(size_t)2 * NB + b] : 0;
-            sum += cc[k];
-        }
-        int tot;
-        int above = carry + block_excl_scan<PLAN_THREADS>(sum, tot, lds);
-#pragma unroll
-        for (int k = 0; k < PLAN_ITEMS; ++k) {
-            const int b = NB - 1 - (r0 + k);
-            if (b >= 0) {
-                int take = 0, off = 0;
-                if (above < need && cc[k] > 0) {
-                    take = min(cc[k], need - above);
-                    off = need - above - take;   // victims are listed in ascending rank
-                }
-                vtake[b] = take;
-                voff[b] = off;
-                above += cc[k];
-            }
-        }
-        carry += tot;
+    const int U = block_sum<PLAN_THREADS>(mu, lds), M = block_sum<PLAN_THREADS>(mm, lds), E = block_sum<PLAN_THREADS>(mc, lds);
+    const PlanTotals t = plan_totals(a, U, M, E);
+    plan_report<PLAN_THREADS>(a, t, lds);
+    if (tid == 0) { plan[0] = t.status; plan[1] = t.need; }
+    int cm = 0, cc = 0;                        // missing / evictable rows of the tiles before this round's
+    for (int base = 0; base < a.NB; base += PLAN_THREADS) {
+        const int b = base + tid;
+        const uint32_t v = b < a.NB ? a.bsum[b] : 0;
+        const int m = (int)(v & 0xffff), c = (int)(v >> 16);
+        int totm, totc;
+        const int pm = cm + block_excl_scan<PLAN_THREADS>(m, totm, lds), pc = cc + block_excl_scan<PLAN_THREADS>(c, totc, lds);
+        if (b < a.NB) tile_plan[b] = make_int4(pm, E - pc - c, 0, 0);
+        cm += totm; cc += totc;
     }
-    __syncthreads();
-    if (tid == 0) {
-        ctl->status = status;
-        ctl->n_unique = totU;
-        ctl->n_miss = M;
-        ctl->need = need;
-        const int nf = status == FC_OK ? nfree + need - M : nfree;
-        ctl->nfree = nf;
-        ctl->err_flags = 0;
-    }
-    if (tid < HOST_REC_WORDS)
-        report_to_host(hctl, ticket, status, totU, M, need, hits, status == FC_OK ? nfree + need - M : nfree, (int)ctl->async_flags,
-                       (int)(ef & EF_NOT_ONE_PER_BAG), tid);
 }
 
 constexpr int FREE_TILE = 1024;
 
 // ---------------------------------------------------------------------------------------------------------
-// K2c  per tile: write the missing ranks (ascending), pick and retire the victims, update rbits, clear ubits.
+// K2c  write the missing ranks (ascending), pick and retire the victims, update rbits, clear ubits.
+//      A thread lists its set bits in LDS; what touches memory per rank (a random read and two or three writes) is then done
+//      by all threads side by side, all random reads of a thread before the first is waited for.
+//      SPLIT workgroups share a tile.  Popularity falls off as a power, so the tiles just beyond the cached ranks hold ten
+//      times the average number of missing and evicted ranks (13,000 of each in one tile at 142 k slots of 9.4 M rows), and
+//      with a tile to a workgroup, one of those was the kernel's duration: 8 to a tile up to EMIT_SPLIT_TILES tiles; beyond,
+//      tiles are many and ranks spread thinner, and 8 times the workgroups take longer than the fullest tile.
+//      Measured (us by events, k_rank_plan + one workgroup per tile with the bits handled one by one -> this): 852 k ids, 9.4 M rows
+//      8.2 + 32 -> 16; 426 k ids, 10 M rows 7.5 + 20 -> 15 (plain), 10 + 29 -> 18 (pipelined).
 // ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint4* ubits4, uint4* rbits4, uint4* pbits4, int protect_prev,
-                                                          const Ctl* __restrict__ ctl,
-                                                          const int32_t* __restrict__ moff,
-                                                          const int32_t* __restrict__ vtake,
-                                                          const int32_t* __restrict__ voff,
+constexpr int EMIT_LIST = 4096;                // ranks of either kind listed at a time
+constexpr int EMIT_SPLIT = SUB_TILES, EMIT_SPLIT_TILES = 1024;
+
+template <int WORDS> struct Bits { uint32_t w[WORDS]; };          // the bits of a thread: 16 of one word, or four words
+__device__ __forceinline__ Bits<1> load_bits(const uint32_t* p, size_t i, Bits<1>) {
+    return Bits<1>{{reinterpret_cast<const uint16_t*>(p)[i]}};
+}
+__device__ __forceinline__ Bits<4> load_bits(const uint32_t* p, size_t i, Bits<4>) {
+    const uint4 v = reinterpret_cast<const uint4*>(p)[i];
+    return Bits<4>{{v.x, v.y, v.z, v.w}};
+}
+__device__ __forceinline__ void store_bits(uint32_t* p, size_t i, const Bits<1>& b) { reinterpret_cast<uint16_t*>(p)[i] = (uint16_t)b.w[0]; }
+__device__ __forceinline__ void store_bits(uint32_t* p, size_t i, const Bits<4>& b) {
+    reinterpret_cast<uint4*>(p)[i] = make_uint4(b.w[0], b.w[1], b.w[2], b.w[3]);
+}
+
+template <int SPLIT, bool FOLD>
+__global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint32_t* rbits, uint32_t* pbits, PlanArgs a,
+                                                          const int32_t* __restrict__ plan, const int4* __restrict__ tile_plan,
                                                           int32_t* __restrict__ miss_ranks, int32_t* __restrict__ vrank,
                                                           int32_t* __restrict__ vslot, int32_t* rank_slot,
-                                                          int32_t* slot_rank, int C, int transit_base,
+                                                          int32_t* slot_rank, int transit_base,
                                                           int transit_rows, int32_t* __restrict__ fill_src, int keep_bits) {
     // keep_bits (byte marks): the bitmap is rewritten by the next K2a and becomes pbits by a swap of pointers
+    static_assert(SPLIT == 1 || (SPLIT == 8 && RT_WORDS == 4 * RT_THREADS), "a thread holds 16 bits or four words");
+    constexpr int WORDS = SPLIT == 1 ? 4 : 1;
+    constexpr int RANKS = SPLIT == 1 ? 128 : 16;           // per thread
+    using B = Bits<WORDS>;
     __shared__ int lds[RT_THREADS / 64];
-    const size_t idx = (size_t)blockIdx.x * RT_THREADS + threadIdx.x;
-    const uint4 u4 = ubits4[idx];
-    const bool anyu = (u4.x | u4.y | u4.z | u4.w) != 0;
-    if (ctl->status != FC_OK) {            // failed call: forget the marks, touch nothing else
-        if (anyu && !keep_bits) ubits4[idx] = make_uint4(0, 0, 0, 0);
+    __shared__ uint16_t mlist[EMIT_LIST], vlist[EMIT_LIST];
+    const int tid = threadIdx.x, me = blockIdx.x / SPLIT, sub = blockIdx.x % SPLIT;
+    const size_t idx = (size_t)blockIdx.x * RT_THREADS + tid;
+    const B u = load_bits(ubits, idx, B()), r = load_bits(rbits, idx, B());
+    B p{};
+    if (!keep_bits || a.protect_prev) p = load_bits(pbits, idx, B());
+    int status, need, mbase, above;
+    if (FOLD) {
+        int mu = 0, mm = 0, mc = 0, bm = 0, ac = 0;
+#pragma unroll 4
+        for (int b = tid; b < a.NB; b += RT_THREADS) {
+            const uint32_t v = a.bsum[b];
+            const int m = (int)(v & 0xffff), c = (int)(v >> 16);
+            mm += m; mc += c;
+            if (b < me) bm += m;
+            if (b > me) ac += c;
+            if (a.protect_prev) mu += a.usum[b];
+        }
+        const int U = a.protect_prev ? block_sum<RT_THREADS>(mu, lds) : 0;
+        const int M = block_sum<RT_THREADS>(mm, lds), E = block_sum<RT_THREADS>(mc, lds);
+        mbase = block_sum<RT_THREADS>(bm, lds);
+        above = block_sum<RT_THREADS>(ac, lds);
+        const PlanTotals t = plan_totals(a, U, M, E);
+        status = t.status; need = t.need;
+        if (blockIdx.x == 0) plan_report<RT_THREADS>(a, t, lds);
+    } else {
+        status = plan[0]; need = plan[1];
+        const int4 tp = tile_plan[me];
+        mbase = tp.x; above = tp.y;
+    }
+    uint32_t anyu = 0, anyp = 0;
+#pragma unroll
+    for (int k = 0; k < WORDS; ++k) { anyu |= u.w[k]; anyp |= p.w[k]; }
+    if (status != FC_OK) {                 // failed call: forget the marks, touch nothing else
+        if (anyu && !keep_bits) store_bits(ubits, idx, B());
         return;
     }
-    const uint4 r4 = rbits4[idx];
-    const uint4 p4 = !keep_bits || protect_prev ? pbits4[idx] : make_uint4(0, 0, 0, 0);
-    const uint32_t uw[4] = {u4.x, u4.y, u4.z, u4.w};
-    const uint32_t rw[4] = {r4.x, r4.y, r4.z, r4.w};
-    const uint32_t pw[4] = {protect_prev ? p4.x : 0u, protect_prev ? p4.y : 0u, protect_prev ? p4.z : 0u, protect_prev ? p4.w : 0u};
-    uint32_t mw[4], cw[4], vw[4] = {0, 0, 0, 0};
+    const uint32_t guard = a.protect_prev ? 0xFFFFFFFFu : 0u;
+    B mw, cw, vw{};
     int cm = 0, cc = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        mw[k] = uw[k] & ~rw[k];
-        cw[k] = rw[k] & ~uw[k] & ~pw[k];
-        cm += __popc(mw[k]);
-        cc += __popc(cw[k]);
+    for (int k = 0; k < WORDS; ++k) {
+        mw.w[k] = u.w[k] & ~r.w[k];
+        cw.w[k] = r.w[k] & ~u.w[k] & ~(p.w[k] & guard);
+        cm += __popc(mw.w[k]);
+        cc += __popc(cw.w[k]);
     }
-    const int rank0 = (int)(idx * 128);
-    int totm;
-    const int pm = block_excl_scan<RT_THREADS>(cm, totm, lds);
-    if (cm) {
-        int o = moff[blockIdx.x] + pm;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            uint32_t word = mw[k];
-            while (word) {
-                const int bit = __ffs(word) - 1;
-                const int rank = rank0 + k * 32 + bit;
-                // where the row's newest copy is: -1 the host table, <= -2 an evicted-row block (in transit)
-                if (fill_src) fill_src[o] = rank_slot[rank];
-                miss_ranks[o++] = rank;
-                word &= word - 1;
-            }
+    // victims of this tile: all but its `skip` lowest evictable ranks, the tiles above it having given theirs
+    const int mine_c = (int)(a.bsum[me] >> 16);
+    const int take = max(0, min(mine_c, need - above)), v0 = need - above - take;
+    int skip = mine_c - take;              // counted from this workgroup's first evictable rank from here on
+    if (SPLIT > 1) {                       // what the workgroups before this one in the tile list
+        int bm = 0, bc = 0;
+        for (int q = 0; q < sub; ++q) {
+            const uint32_t v = a.ssum[me * SPLIT + q];
+            bm += (int)(v & 0xffff); bc += (int)(v >> 16);
         }
+        mbase += bm;
+        skip -= bc;
     }
-    const int vt = vtake[blockIdx.x];
-    if (vt > 0) {
-        int totc;
-        const int pc = block_excl_scan<RT_THREADS>(cc, totc, lds);
-        const bool transit = transit_base >= 0 && ctl->need <= transit_rows;
-        const int skip = totc - vt;          // the lowest `skip` evictable ranks of the threshold tile stay
-        const int o0 = voff[blockIdx.x];
-        int q = pc;
-        if (cc && pc + cc > skip) {
+    int both;
+    const uint32_t pre = (uint32_t)block_excl_scan<RT_THREADS>((int)((uint32_t)cm | (uint32_t)cc << 16), both, lds);
+    const int pm = (int)(pre & 0xffff), totm = (int)((uint32_t)both & 0xffff), totc = (int)((uint32_t)both >> 16);
+    const int pv = (int)(pre >> 16) - max(skip, 0);        // place among this workgroup's victims; negative: stays
+    const int vbase = v0 + max(-skip, 0), totv = max(0, totc - max(skip, 0));
+    const bool transit = transit_base >= 0 && need <= transit_rows;
+    const int rank0 = blockIdx.x * (RT_THREADS * RANKS);
+    for (int w0 = 0; w0 < totm || w0 < totv; w0 += EMIT_LIST) {        // (one round if SPLIT > 1)
+        if (cm && pm < w0 + EMIT_LIST && pm + cm > w0) {
+            int q = pm - w0;
+#pragma unroll
+            for (int k = 0; k < WORDS; ++k)
+                for (uint32_t word = mw.w[k]; word; word &= word - 1, ++q)
+                    if ((unsigned)q < (unsigned)EMIT_LIST) mlist[q] = (uint16_t)(tid * RANKS + k * 32 + __ffs(word) - 1);
+        }
+        if (cc && pv < w0 + EMIT_LIST && pv + cc > w0) {
+            int q = pv - w0;
+#pragma unroll
+            for (int k = 0; k < WORDS; ++k)
+                for (uint32_t word = cw.w[k]; word; word &= word - 1, ++q)
+                    if ((unsigned)q < (unsigned)EMIT_LIST) {
+                        vlist[q] = (uint16_t)(tid * RANKS + k * 32 + __ffs(word) - 1);
+                        vw.w[k] |= word & (0u - word);
+                    }
+        }
+        __syncthreads();
+        for (int t0 = tid; t0 < EMIT_LIST && (w0 + t0 - tid < totm || w0 + t0 - tid < totv); t0 += 4 * RT_THREADS) {
+            int mr[4], ms[4], vr[4], vs[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                uint32_t word = cw[k];
-                while (word) {
-                    const int bit = __ffs(word) - 1;
-                    if (q >= skip) {
-                        const int rank = rank0 + k * 32 + bit;
-                        const int slot = rank_slot[rank];
-                        const int j = o0 + q - skip;
-                        vrank[j] = rank;
-                        vslot[j] = slot;
-                        // not resident any more; with the DMA evict transmitter the newest copy of the row is
-                        // "in transit" in row j of an evicted-row block until the host threads have stored it
-                        rank_slot[rank] = transit ? -2 - (transit_base + j) : -1;
-                        // empty, and whose row it still holds (every such slot is refilled below); the test is always true
-                        if ((unsigned)slot < (unsigned)C) slot_rank[slot] = -2 - rank;
-                        vw[k] |= 1u << bit;
-                    }
-                    ++q;
-                    word &= word - 1;
+                const int t = t0 + k * RT_THREADS;
+                mr[k] = t < EMIT_LIST && w0 + t < totm ? rank0 + mlist[t] : -1;
+                vr[k] = t < EMIT_LIST && w0 + t < totv ? rank0 + vlist[t] : -1;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ms[k] = fill_src && mr[k] >= 0 ? rank_slot[mr[k]] : -1;
+                vs[k] = vr[k] >= 0 ? rank_slot[vr[k]] : -1;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int t = w0 + t0 + k * RT_THREADS;
+                if (mr[k] >= 0) {
+                    miss_ranks[mbase + t] = mr[k];
+                    // where the row's newest copy is: -1 the host table, <= -2 an evicted-row block (in transit)
+                    if (fill_src) fill_src[mbase + t] = ms[k];
+                }
+                if (vr[k] >= 0) {
+                    const int j = vbase + t;
+                    vrank[j] = vr[k];
+                    vslot[j] = vs[k];
+                    // not resident any more; with the DMA evict transmitter the newest copy of the row is
+                    // "in transit" in row j of an evicted-row block until the host threads have stored it
+                    rank_slot[vr[k]] = transit ? -2 - (transit_base + j) : -1;
+                    // empty, and whose row it still holds (every such slot is refilled below); the test is always true
+                    if ((unsigned)vs[k] < (unsigned)a.C) slot_rank[vs[k]] = -2 - vr[k];
                 }
             }
         }
+        __syncthreads();
     }
-    if (cm || (vw[0] | vw[1] | vw[2] | vw[3]))
-        rbits4[idx] = make_uint4((rw[0] & ~vw[0]) | mw[0], (rw[1] & ~vw[1]) | mw[1], (rw[2] & ~vw[2]) | mw[2],
-                                 (rw[3] & ~vw[3]) | mw[3]);
+    if (cm || totv > 0) {
+        uint32_t changed = 0;
+        B out;
+#pragma unroll
+        for (int k = 0; k < WORDS; ++k) { out.w[k] = (r.w[k] & ~vw.w[k]) | mw.w[k]; changed |= mw.w[k] | vw.w[k]; }
+        if (changed) store_bits(rbits, idx, out);
+    }
     if (keep_bits) return;
-    if (anyu) ubits4[idx] = make_uint4(0, 0, 0, 0);
-    if (anyu || (p4.x | p4.y | p4.z | p4.w)) pbits4[idx] = u4;     // this batch is the "previous" one next time
+    if (anyu) store_bits(ubits, idx, B());
+    if (anyu | anyp) store_bits(pbits, idx, u);            // this batch is the "previous" one next time
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -854,6 +934,9 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     } else {
         const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
         int64_t nmark;
+        // two error words in turn: a call's K2a clears the next call's
+        uint32_t *err = &c->ctl->err[c->err_set], *next_err = &c->ctl->err[c->err_set ^ 1];
+        c->err_set ^= 1;
         bytes = mark_bytes(c, n);
         if (bytes) {
             nmark = cdiv(work, MARKB_ITEMS * MARKB_THREADS);
@@ -861,12 +944,12 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
             {
                 ProfScope ps(c, P_REMAP_MARK, st);
                 k_remap_bytes<<<(unsigned)nmark, MARKB_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubytes,
-                                                                        c->rbits, c->rbuf, c->ctl, c->hitpart);
+                                                                        c->rbits, c->rbuf, err, c->hitpart);
             }
             ProfScope ps(c, P_RANK_COUNT, st);
             k_count_bytes<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, (uint16_t*)c->ubits, (const uint16_t*)c->rbits,
-                                                                 (const uint16_t*)c->pbits, protect_prev, c->bsum, (int)c->NB,
-                                                                 landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot);
+                                                                 (const uint16_t*)c->pbits, protect_prev, c->bsum, c->ssum, c->usum,
+                                                                 landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot, next_err);
             c->ubits_clean = false;
         } else {
             nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
@@ -881,18 +964,21 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
             {
                 ProfScope ps(c, P_REMAP_MARK, st);
                 k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
-                                                                      c->rbits, c->rbuf, c->ctl, c->hitpart, (int)per_block,
+                                                                      c->rbits, c->rbuf, err, c->hitpart, (int)per_block,
                                                                       (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
             }
             ProfScope ps(c, P_RANK_COUNT, st);
             k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((const uint4*)c->ubits, (const uint4*)c->rbits, (const uint4*)c->pbits,
-                                                                protect_prev, c->bsum, (int)c->NB,
+                                                                protect_prev, c->bsum, c->ssum, c->usum,
                                                                 landed_ranks, (int)landed,
-                                                                (int)(buf * c->staging_rows), c->rank_slot);
+                                                                (int)(buf * c->staging_rows), c->rank_slot, next_err);
         }
-        {
+        const PlanArgs pa{c->bsum, c->ssum, c->usum, err, &c->ctl->async_flags, c->hitpart, c->hctl, (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
+                          protect_prev};
+        const bool fold = c->NB <= c->plan_fold_tiles;
+        if (!fold) {
             ProfScope ps(c, P_RANK_PLAN, st);
-            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(c->bsum, (int)c->NB, (int)c->C, c->ctl, c->hctl, c->moff, c->vtake, c->voff, c->hitpart, (int)nmark, ticket);
+            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(pa, c->plan, c->tile_plan);
         }
         // Last batch's evicted rows must have reached the host table before the victim lists and the block buffer
         // are reused and before any of those rows could be fetched again; the kernels above do not care.
@@ -900,14 +986,17 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
             FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
             c->evict_pending = false;
         }
-        {
-            ProfScope ps(c, P_RANK_EMIT, st);
-            k_rank_emit<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubits, (uint4*)c->rbits, (uint4*)c->pbits, protect_prev, c->ctl,
-                                                               c->moff, c->vtake, c->voff,
-                                                               c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, (int)c->C,
-                                                               transit, (int)c->staging_rows,
-                                                               c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0);
-        }
+        ProfScope ps(c, P_RANK_EMIT, st);
+#define FC_EMIT(S, F) \
+        k_rank_emit<S, F><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->plan, c->tile_plan, \
+                                                                       c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, \
+                                                                       transit, (int)c->staging_rows, \
+                                                                       c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0)
+        const bool split = c->NB <= EMIT_SPLIT_TILES;
+        if (fold) { if (split) FC_EMIT(EMIT_SPLIT, true); else FC_EMIT(1, true); }
+        else if (split) FC_EMIT(EMIT_SPLIT, false);
+        else FC_EMIT(1, false);
+#undef FC_EMIT
     }
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
     if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
@@ -916,10 +1005,12 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     int32_t h[HOST_REC_WORDS];
     FC_TRY(wait_for_record(c->hctl, ticket, st, h));
     if (h[HW_STATUS] != FC_OK) return h[HW_STATUS];
+    c->nfree = h[HW_NFREE];
     if (bytes) std::swap(c->ubits, c->pbits);            // this batch is the "previous" one next time
     c->last_one_per_bag = n == num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
     const int64_t M = h[HW_MISS], need = h[HW_NEED];
     if (M > 0 && !small) {
+        int32_t* old_rank = c->dma_evict ? nullptr : c->fill_src;
         {
             const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
             {
@@ -928,7 +1019,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
             }
             ProfScope ps(c, P_FREE_PICK, st);
             k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
-                                                      c->rank_slot, c->dma_evict ? nullptr : c->fill_src);
+                                                      c->rank_slot, old_rank);
         }
     }
     if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));

@@ -27,9 +27,9 @@ struct SmallArgs {
     int32_t* ranks;                    // rank of every id
     int32_t* slots_out;                // slot of every id; null: left to the caller (folded into the sort)
     const int32_t* landed_ranks;       // see k_rank_count
-    Ctl* ctl; HostCtl* hctl;
+    const Ctl* ctl; HostCtl* hctl;
     int64_t N;
-    int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket;
+    int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket, nfree;
     bool dma;
 };
 
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     const uint64_t lt = (1ull << lane) - 1ull;
     const int per_wave = a.words / SM_WAVES / 8;                               // pairs of pieces per wavefront
     const int chunks_wave = (a.C + 64 * SM_WAVES - 1) / (64 * SM_WAVES);       // 64-slot chunks per wavefront
-    const int nfree = a.ctl->nfree;
+    const int nfree = a.nfree;
     // the resident bits this thread will look at: requested first, needed after the ids
     uint4 q0[SM_R8], q1[SM_R8];
 #pragma unroll
@@ -184,7 +184,6 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     if (w == SM_WAVES - 1) {
         const int nf = status == FC_OK ? nfree + need - M : nfree;
         report_to_host(a.hctl, a.ticket, status, totU, M, need, s_hits, nf, (int)a.ctl->async_flags, (int)(ef & EF_NOT_ONE_PER_BAG), lane);
-        if (lane == 0) { a.ctl->status = status; a.ctl->n_unique = totU; a.ctl->n_miss = M; a.ctl->need = need; a.ctl->nfree = nf; a.ctl->err_flags = 0; }
     }
     if (status != FC_OK) return;
     // the victims are the evictable ranks from the threshold up: the one with `skip` evictable ranks below it
@@ -318,7 +317,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
     a.rbits4 = (uint4*)c->rbits; a.pbits4 = (uint4*)c->pbits;
     a.rank_slot = c->rank_slot; a.slot_rank = c->slot_rank;
     a.miss_ranks = c->miss_ranks; a.vrank = c->vrank; a.vslot = c->vslot; a.fill_slots = c->fill_slots;
-    a.fill_src = c->fill_src; a.dma = c->dma_evict;
+    a.fill_src = c->fill_src; a.dma = c->dma_evict; a.nfree = (int)c->nfree;
     a.ranks = c->rbuf; a.slots_out = slots;
     a.landed_ranks = landed_ranks; a.landed = (int)landed; a.landed_base = (int)landed_base;
     a.ctl = c->ctl; a.hctl = c->hctl; a.N = c->N;

@@ -42,3 +42,15 @@ def test_both_kinds_of_marks_in_turn(rows):
         run_parity_lookahead(w, 8, warm=True, dma_evict=dma)
     tight = Sizes(SIZES, num_rows=rows, dim=4, cache_rows=13_000, seed=8, multi_hot=False, distinct_cap=9000)
     run_parity_lookahead(tight, 8, warm=True)                          # some look-aheads are refused
+
+
+@pytest.mark.parametrize("fold", ["0", "4096"])
+def test_dense_tiles_and_a_separate_plan(monkeypatch, fold):
+    """A cold cache filled by a batch that misses whole tiles (more ranks of one tile than a list in LDS holds), then
+    evictions of as many; the planning step in a kernel of its own and inside the emitting kernel."""
+    monkeypatch.setenv("FC_PLAN_FOLD_TILES", fold)
+    w = TinyWorkload(num_rows=70_000, dim=4, cache_rows=34_000, seed=9, multi_hot=False, bags=60_000, distinct_cap=33_000)
+    run_parity(w, 4, warm=False)
+    run_parity(w, 4, warm=True, dma_evict=True)
+    tight = Sizes([60_000, 8500, 30_000], num_rows=70_000, dim=4, cache_rows=34_000, seed=10, multi_hot=False, distinct_cap=16_000)
+    run_parity_lookahead(tight, 5, warm=False)
