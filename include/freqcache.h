@@ -141,7 +141,7 @@ enum {
  * Errors: INVALID_ARG, NOT_PERMUTATION, NOT_PINNED, OOM_DEVICE, OOM_PINNED, HIP.  Synchronous (it also runs a few
  * sub-millisecond test kernels on hip_stream to find library streams that run beside it).
  * Tuning knobs, read from the environment at this call (defaults suit an MI355X on a PCIe Gen5 x16 link):
- *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 1024)
+ *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256)
  *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch, fixed (default: starts at 32 and follows the
  *                         measured fetch / block-copy durations); FC_FILL_BLOCKS_EARLY_START only moves the start
  *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (transmitter without FC_EVICT_DMA)

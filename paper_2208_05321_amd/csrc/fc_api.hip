@@ -137,7 +137,7 @@ static void destroy(fc_cache* c) {
         for (hipEvent_t e : {c->ev_arrive[k], c->ev_fetch_a[k], c->ev_fetch_b[k]}) if (e) (void)hipEventDestroy(e);
     }
     for (int b = 0; b < DMA_BLOCKS; ++b)
-        for (hipEvent_t e : {c->ev_copy_a[b], c->ev_copy_b[b]}) if (e) (void)hipEventDestroy(e);
+        if (c->ev_copy_a[b]) (void)hipEventDestroy(c->ev_copy_a[b]);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
                     (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->usum, (void*)c->plan, (void*)c->tile_plan,
                     (void*)c->rbuf,
@@ -292,7 +292,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
                 hipHostMalloc((void**)&c->vrank_pin[b], (size_t)staging_rows * 4, hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError(); return FC_ERR_OOM_PINNED;
             }
-            FC_HIP(hipEventCreateWithFlags(&c->ev_d2h[b], hipEventDisableTiming | hipEventBlockingSync));
+            FC_HIP(hipEventCreateWithFlags(&c->ev_d2h[b], hipEventBlockingSync));
         }
     }
     use_list_set(c, 0);
@@ -331,7 +331,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
         FC_HIP(hipEventCreateWithFlags(e, hipEventDisableTiming));
     if (c->dma_evict) {
         for (int k = 0; k < 2; ++k) { FC_HIP(hipEventCreate(&c->ev_fetch_a[k])); FC_HIP(hipEventCreate(&c->ev_fetch_b[k])); }
-        for (int b = 0; b < DMA_BLOCKS; ++b) { FC_HIP(hipEventCreate(&c->ev_copy_a[b])); FC_HIP(hipEventCreate(&c->ev_copy_b[b])); }
+        for (int b = 0; b < DMA_BLOCKS; ++b) { FC_HIP(hipEventCreate(&c->ev_copy_a[b])); }
     } else {
         c->tune_early = false;
     }
@@ -380,7 +380,7 @@ static void tune_fetch_grid(fc_cache* c, int k) {
     if (c->last_copy_buf >= 0)
         for (int i = 0; i < DMA_BLOCKS && d_us <= 0.f; ++i) {
             const int b = (c->last_copy_buf - i + DMA_BLOCKS) % DMA_BLOCKS;
-            if (c->copy_timed[b]) d_us = elapsed_us(c->ev_copy_a[b], c->ev_copy_b[b]);
+            if (c->copy_timed[b]) d_us = elapsed_us(c->ev_copy_a[b], c->ev_d2h[b]);
         }
     const float r = d_us > 0.f ? f_us / d_us : 2.f;
     c->tune_ratio = c->tune_ratio <= 0.f ? r : 0.75f * c->tune_ratio + 0.25f * r;
@@ -408,6 +408,7 @@ static int fetch_early(fc_cache* c, int64_t M) {
         // host threads gather the rows, the DMA engine carries them; ev_arrive[k] is recorded by the thread that hands over
         // the last chunk, and cache_advance waits (on the host) for that record before it makes its stream wait for it
         FC_TRY(gather_start(c, M));
+        c->arrived_by[k] = c->ev_arrive[k];
         c->gather_pending = true;
         c->planned.arrived = true;
         return FC_OK;
@@ -420,10 +421,14 @@ static int fetch_early(fc_cache* c, int64_t M) {
         FC_TRY(launch_fill_rows(c, c->pf, M, c->arrive[k], c->staging_rows, c->fill_blocks_early));
         FC_HIP(hipEventRecord(c->ev_fetch_b[k], c->pf));
         c->fetch_timed[k] = true;
+        c->arrived_by[k] = c->ev_fetch_b[k];
     } else {
         FC_TRY(launch_copy_rows(c, c->pf, P_MISS_FILL, c->arrive[k], nullptr, c->staging_rows, c->host_dev, c->miss_ranks, c->N, M, c->fill_blocks));
     }
-    FC_HIP(hipEventRecord(c->ev_arrive[k], c->pf));
+    if (!c->dma_evict) {
+        FC_HIP(hipEventRecord(c->ev_arrive[k], c->pf));
+        c->arrived_by[k] = c->ev_arrive[k];
+    }
     c->planned.arrived = true;
     return FC_OK;
 }
@@ -439,6 +444,7 @@ static int adopt_next(fc_cache* c) {
         FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
         c->next_pending = false;
         c->last_pst = c->stream;
+        for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
     }
     c->cur_ticket = c->pending_ticket;     // the batch prepared ahead of time (if any) is the current one now
     return FC_OK;
@@ -585,7 +591,6 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
         const int rs = presort_impl(c, slots_dev, n, offsets_dev, num_bags, slots_dev);
         c->pst = c->stream;
         if (rs != FC_OK) FC_TRY(launch_slots_out(c, c->pre, slots_dev, n));     // no sort: the plain write-out
-        FC_HIP(hipEventRecord(c->ev_index_done, c->pre));
     } else if (n > 0) { c->pst = c->pre; (void)presort_impl(c, slots_dev, n, offsets_dev, num_bags); c->pst = c->stream; }
     FC_HIP(hipEventRecord(c->ev_pre_done, c->pre));
     return rc2;

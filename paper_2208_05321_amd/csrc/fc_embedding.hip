@@ -197,7 +197,7 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
     if (n == num_bags && c->fwd_sorted) {
         for (PresortRec& r : c->rec) {
             if (r.valid && r.one_per_bag && r.ticket == c->cur_ticket && r.slots == slots && r.n == n && r.offsets == offsets && r.bags == num_bags) {
-                if (!r.caller_waited) { FC_HIP(hipStreamWaitEvent(c->stream, r.ev_sorted, 0)); r.caller_waited = true; }
+                if (!r.caller_waited) { FC_HIP(hipStreamWaitEvent(c->stream, r.done, 0)); r.caller_waited = true; }
                 int64_t blocks = cdiv(n, (int64_t)gpb * FWD_ROWS);
                 if (blocks > (1 << 20)) blocks = 1 << 20;
                 ProfScope ps(c, P_BAG_FWD, c->stream);
@@ -532,10 +532,11 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
         FC_HIP(hipStreamWaitEvent(aux, c->ev_slots, 0));
     }
     // the record's previous sort was read by a backward pass on the caller's stream, enqueued before this call
-    if (c->pst != c->stream) FC_HIP(hipStreamWaitEvent(aux, c->ev_s_now, 0));
+    // (the index half has made `pre` wait already)
+    if (c->pst != c->stream && aux != c->pst) FC_HIP(hipStreamWaitEvent(aux, c->ev_s_now, 0));
     // the record's buffers were last written by a sort that may have run on another library stream (the schedule changed)
     // (a record the caller's stream has consumed is covered by the wait for that stream above)
-    if (r.sort_stream && r.sort_stream != aux && !r.caller_waited) FC_HIP(hipStreamWaitEvent(aux, r.ev_sorted, 0));
+    if (r.sort_stream && r.sort_stream != aux && !r.caller_waited) FC_HIP(hipStreamWaitEvent(aux, r.done, 0));
     // cache_plan_next running ahead (FC_INPUTS_READY while HBM rather than the host link binds the step):
     // the index stream is then the busiest of the schedule, and the next batch's index kernels queue behind this sort; its
     // passes after the first move to the side stream, which only carries the evicted-row block.  Where the host link binds
@@ -545,7 +546,9 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     const bool split = slots_out && c->sort_tail_side && c->ahead_now && aux == c->pre &&
                        c->side && c->side != aux;
     FC_TRY(sort_pairs(c, c->sb[k], aux, slots, n, offsets, num_bags, &r.keys, &r.vals, slots_out, split ? c->side : nullptr, &last));
-    if (last != c->stream) FC_HIP(hipEventRecord(r.ev_sorted, last));
+    // cache_plan_next records ev_pre_done right behind a sort that ends on `pre`
+    r.done = slots_out && last == c->pre ? c->ev_pre_done : r.ev_sorted;
+    if (last != c->stream && r.done == r.ev_sorted) FC_HIP(hipEventRecord(r.ev_sorted, last));
     r.sort_stream = last;
     r.caller_waited = last == c->stream;
     r.slots = slots; r.n = n; r.offsets = offsets; r.bags = num_bags;
@@ -619,7 +622,7 @@ int bwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
     for (PresortRec& r : c->rec) {
         // sorted ahead of time by the call that prepared the current batch, from these very buffers
         if (r.valid && r.ticket == c->cur_ticket && r.slots == slots && r.n == n && r.offsets == offsets && r.bags == num_bags) {
-            if (!r.caller_waited) FC_HIP(hipStreamWaitEvent(st, r.ev_sorted, 0));      // sorted ahead of time
+            if (!r.caller_waited) FC_HIP(hipStreamWaitEvent(st, r.done, 0));      // sorted ahead of time
             kin = r.keys; vin = r.vals;
             r.valid = false;
             break;

@@ -97,7 +97,8 @@ struct PresortRec {
     int64_t n = 0, bags = 0;
     const int32_t *keys = nullptr, *vals = nullptr;
     hipEvent_t ev_sorted = nullptr;
-    hipStream_t sort_stream = nullptr;  // where ev_sorted was last recorded (null: never)
+    hipEvent_t done = nullptr;          // the event that says so: ev_sorted, or ev_pre_done where the sort ends what is prepared ahead
+    hipStream_t sort_stream = nullptr;  // where the sort last ran (null: never)
     bool caller_waited = false;         // the caller's stream already waits for ev_sorted (forward before backward)
 };
 
@@ -135,6 +136,7 @@ struct fc_cache {
     hipStream_t pf = nullptr;
     float* arrive[2] = {nullptr, nullptr};             // [staging_rows][D] each
     hipEvent_t ev_arrive[2] = {nullptr, nullptr};
+    hipEvent_t arrived_by[2] = {nullptr, nullptr};     // the event that says the rows are there: ev_arrive or ev_fetch_b
     bool next_pending = false;
     fc::MovePlan planned;           // cache_plan_next: row movement still to be done by cache_advance
     uint32_t* pbits = nullptr;      // rank-space bitmap: rows of the previously prepared batch
@@ -150,7 +152,9 @@ struct fc_cache {
     bool last_one_per_bag = false;  // the batch of the latest index half has that shape
     int fwd_bags = 4;               // bags per row-group of the forward kernel for one-lookup-per-bag batches: 1, 2 or 4 (tuning: FC_FWD_BAGS)
     int mark_ids_per_thread = 2;    // ids per thread of the marking kernel (tuning: FC_MARK_IPT)
-    int fill_blocks = 1024;         // cap on the workgroups of the miss fill (tuning: FC_FILL_BLOCKS); 40 with FC_EVICT_DMA:
+    // cap on the workgroups of the miss fill (tuning: FC_FILL_BLOCKS).  Default transmitter, 60 k rows of 512 bytes both ways / 35 k in:
+    // 64 1216 / 460, 128 1191 / 471, 256 1201 / 452, 512 1223 / 458, 1024 1255 / 468 us a step.
+    int fill_blocks = 256;          // 40 with FC_EVICT_DMA:
                                     // ~200 KB of reads in flight fill the link and still let the DMA engine's writes through
     int fill_blocks_early = 32;     // the same for rows fetched ahead of time by cache_plan_next (tuning: FC_FILL_BLOCKS_EARLY)
     int evict_blocks = 1024;        // workgroups of the host-table store kernel (tuning: FC_EVICT_BLOCKS)
@@ -214,7 +218,8 @@ struct fc_cache {
     bool dma_evict = false;
     fc::ScatterPool* pool = nullptr;
     float* blk_pin[fc::DMA_BLOCKS] = {};          // pinned landing blocks
-    int32_t* vrank_pin[fc::DMA_BLOCKS] = {};      // pinned copies of the evicted ranks
+    int32_t* vrank_pin[fc::DMA_BLOCKS] = {};      // pinned copies of the evicted ranks, where they do not fit behind a block's rows
+    const int32_t* vrank_at[fc::DMA_BLOCKS] = {}; // where a block's ranks have landed
     int32_t* vrank_buf[fc::DMA_BLOCKS] = {};      // device lists of the evicted ranks, one per block
     int64_t blk_rows[fc::DMA_BLOCKS] = {};        // rows whose transit marks are still set, per block
     hipEvent_t ev_d2h[fc::DMA_BLOCKS] = {};
@@ -238,7 +243,7 @@ struct fc_cache {
     bool tune_early = true;
     int fill_blocks_early_max = 32;
     hipEvent_t ev_fetch_a[2] = {nullptr, nullptr}, ev_fetch_b[2] = {nullptr, nullptr};
-    hipEvent_t ev_copy_a[fc::DMA_BLOCKS] = {}, ev_copy_b[fc::DMA_BLOCKS] = {};
+    hipEvent_t ev_copy_a[fc::DMA_BLOCKS] = {};            // (the copy's end: ev_d2h)
     bool fetch_timed[2] = {false, false}, copy_timed[fc::DMA_BLOCKS] = {};
     int last_copy_buf = -1;
     float tune_ratio = 0.f;
@@ -340,7 +345,8 @@ int noalloc_setup(int device);
 // row movement (fc_rows.hip).  dst_idx / src_idx: per-row index lists in device memory, or nullptr for row j.
 // dst_rows / src_rows bound the row indices on either side (rows with an index outside are skipped).
 int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, const int32_t* dst_idx, int64_t dst_rows,
-                     const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks);
+                     const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks,
+                     int32_t* tag_out = nullptr, const int32_t* tags = nullptr);   // tag_out[j] = tags[j] on the way
 // default transmitter: each slot of fill_slots gives its old row (rank fill_src[j], if any) to the host table and gets the
 // missing one, in one pass
 int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows);

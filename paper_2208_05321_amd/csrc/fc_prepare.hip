@@ -796,17 +796,22 @@ int dma_quiesce(fc_cache* c, hipStream_t st) {
 // stream, and let the host threads scatter it once it has landed.  Nothing on the caller's stream waits for it.
 static int evict_dma(fc_cache* c, int64_t need, int buf) {
     float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
-    FC_TRY(launch_copy_rows(c, c->pst, P_EVICT_GATHER, blk, nullptr, c->staging_rows, c->cache, c->out_slot, c->C, need, 1 << 20));
+    // the ranks travel behind the rows, in one copy, where the block has room for both (a copy of their own costs the host as
+    // much as four launches)
+    const bool together = need * (int64_t)(c->D + 1) <= c->staging_rows * (int64_t)c->D;
+    FC_TRY(launch_copy_rows(c, c->pst, P_EVICT_GATHER, blk, nullptr, c->staging_rows, c->cache, c->out_slot, c->C, need, 1 << 20,
+                            together ? reinterpret_cast<int32_t*>(blk + (size_t)need * c->D) : nullptr, c->out_rank));
     FC_HIP(hipEventRecord(c->ev_gather_done, c->pst));
     FC_HIP(hipStreamWaitEvent(c->side, c->ev_gather_done, 0));
     {
         ProfScope ps(c, P_D2H_BLOCK, c->side);
         if (c->ev_copy_a[buf]) FC_HIP(hipEventRecord(c->ev_copy_a[buf], c->side));
-        FC_HIP(hipMemcpyAsync(c->vrank_pin[buf], c->out_rank, (size_t)need * 4, hipMemcpyDeviceToHost, c->side));
-        FC_HIP(hipMemcpyAsync(c->blk_pin[buf], blk, (size_t)need * c->D * 4, hipMemcpyDeviceToHost, c->side));
-        if (c->ev_copy_b[buf]) { FC_HIP(hipEventRecord(c->ev_copy_b[buf], c->side)); c->copy_timed[buf] = true; c->last_copy_buf = buf; }
+        if (!together) FC_HIP(hipMemcpyAsync(c->vrank_pin[buf], c->out_rank, (size_t)need * 4, hipMemcpyDeviceToHost, c->side));
+        FC_HIP(hipMemcpyAsync(c->blk_pin[buf], blk, (size_t)need * (c->D + (together ? 1 : 0)) * 4, hipMemcpyDeviceToHost, c->side));
     }
     FC_HIP(hipEventRecord(c->ev_d2h[buf], c->side));
+    c->vrank_at[buf] = together ? reinterpret_cast<const int32_t*>(c->blk_pin[buf] + (size_t)need * c->D) : c->vrank_pin[buf];
+    if (c->ev_copy_a[buf]) { c->copy_timed[buf] = true; c->last_copy_buf = buf; }
     c->blk_rows[buf] = need;
     pool_publish(c, buf, need);
     return FC_OK;
@@ -888,7 +893,7 @@ int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n) {
 }
 
 // before_slots: an event the slot write-out (the first kernel that writes the caller's buffer) has to wait for.
-// defer_slots: leave the slot write-out and the ev_index_done record to the caller (who folds the write-out into the sort).
+// defer_slots: leave the slot write-out to the caller (who folds it into the sort).
 int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots, bool defer_slots) {
     const int64_t LIM = ((int64_t)1 << 31) - 65536;
@@ -902,7 +907,8 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     use_list_set(c, c->lset ^ 1);
     c->have_lists = false;
     if (c->move_stream[c->lset] && c->move_stream[c->lset] != st) FC_HIP(hipStreamWaitEvent(st, c->ev_move_done[c->lset], 0));
-    if (c->last_index_stream && c->last_index_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_index_done, 0));
+    if (c->last_index_stream && c->last_index_stream != st)      // (what ran on `pre` ended with ev_pre_done)
+        FC_HIP(hipStreamWaitEvent(st, c->last_index_stream == c->pre ? c->ev_pre_done : c->ev_index_done, 0));
     if (c->quiesce_stream && c->quiesce_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_quiesce, 0));
     c->quiesce_stream = nullptr;
     const int32_t ticket = c->ticket = (c->ticket + 1) & 0x7fffffff;
@@ -1028,7 +1034,6 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
     if (!defer_slots) {
         if (!small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
-        if (!plain) FC_HIP(hipEventRecord(c->ev_index_done, st));
     }
     if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
     c->last_index_stream = st;
@@ -1112,7 +1117,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
         else {
             // more victims than one block holds (or no DMA transmitter): store by kernel, block by block; the
             // block buffer is reused from its start, so nothing may be in transit in it any more
-            if (!arrival_waited) { FC_HIP(hipStreamWaitEvent(st, c->ev_arrive[c->lset], 0)); arrival_waited = true; }
+            if (!arrival_waited) { FC_HIP(hipStreamWaitEvent(st, c->arrived_by[c->lset], 0)); arrival_waited = true; }
             FC_TRY(dma_quiesce(c, st));
             FC_TRY(evict_direct(c, need, &last_off, &last_rows));
         }
@@ -1122,7 +1127,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
             FC_TRY(store_block(c, last_off, last_rows));
             last_rows = -1;
         }
-        if (!arrival_waited) FC_HIP(hipStreamWaitEvent(st, c->ev_arrive[c->lset], 0));
+        if (!arrival_waited) FC_HIP(hipStreamWaitEvent(st, c->arrived_by[c->lset], 0));
         if (staged) FC_TRY(fill_staged(c, M, c->list_pin));
         else if (mv.arrived) {
             FC_TRY(launch_copy_rows(c, st, P_ROWS_IN, c->cache, c->fill_slots, c->C, c->arrive[c->lset], nullptr, c->staging_rows, M, 1 << 20));

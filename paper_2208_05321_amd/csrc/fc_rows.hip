@@ -25,7 +25,8 @@ template <int VEC, int KIND>
 __global__ __launch_bounds__(256) void k_copy_rows(float* __restrict__ dst, const int32_t* __restrict__ dst_idx,
                                                    unsigned dst_rows, const float* __restrict__ src,
                                                    const int32_t* __restrict__ src_idx, unsigned src_rows, int rows,
-                                                   int D, int lpr_shift) {
+                                                   int D, int lpr_shift, int32_t* __restrict__ tag_out,
+                                                   const int32_t* __restrict__ tags) {
     using V = typename Vec<VEC>::T;
     const int lpr = 1 << lpr_shift;
     const int gpb = blockDim.x >> lpr_shift;
@@ -34,6 +35,7 @@ __global__ __launch_bounds__(256) void k_copy_rows(float* __restrict__ dst, cons
     for (int j = blockIdx.x * gpb + gl; j < rows; j += gridDim.x * gpb) {
         const int di = dst_idx ? dst_idx[j] : j;
         const int si = src_idx ? src_idx[j] : j;
+        if (KIND == 0 && tag_out && lane == 0) tag_out[j] = tags[j];
         if ((unsigned)di >= dst_rows || (unsigned)si >= src_rows) continue;   // never true for lists this library builds
         const V* __restrict__ s = reinterpret_cast<const V*>(src + (size_t)si * D);
         V* __restrict__ d = reinterpret_cast<V*>(dst + (size_t)di * D);
@@ -142,7 +144,8 @@ __global__ __launch_bounds__(256) void k_fill_rows(float* __restrict__ cache, co
 static inline int shift_of(int lpr) { int s = 0; while ((1 << s) < lpr) ++s; return s; }
 
 int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, const int32_t* dst_idx, int64_t dst_rows,
-                     const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks) {
+                     const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks, int32_t* tag_out,
+                     const int32_t* tags) {
     if (rows <= 0) return FC_OK;
     const int sh = shift_of(c->lpr);
     const int gpb = 256 >> sh;
@@ -150,7 +153,7 @@ int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, cons
     if (blocks > max_blocks) blocks = max_blocks;
     ProfScope ps(c, prof_item, s);
 #define FC_LAUNCH_ROWS(V, K) \
-    k_copy_rows<V, K><<<(unsigned)blocks, 256, 0, s>>>(dst, dst_idx, (unsigned)dst_rows, src, src_idx, (unsigned)src_rows, (int)rows, c->D, sh)
+    k_copy_rows<V, K><<<(unsigned)blocks, 256, 0, s>>>(dst, dst_idx, (unsigned)dst_rows, src, src_idx, (unsigned)src_rows, (int)rows, c->D, sh, tag_out, tags)
 #define FC_LAUNCH_ROWS_V(K) \
     switch (c->vec) { case 4: FC_LAUNCH_ROWS(4, K); break; case 2: FC_LAUNCH_ROWS(2, K); break; default: FC_LAUNCH_ROWS(1, K); break; }
     if (prof_item == P_EVICT_GATHER) { FC_LAUNCH_ROWS_V(0) }

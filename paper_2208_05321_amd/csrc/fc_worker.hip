@@ -17,7 +17,7 @@ struct EvictHooks {
     void scatter(int buf, int64_t a, int64_t b) const {
         const size_t rowb = (size_t)c->D * 4;
         const float* blk = c->blk_pin[buf];
-        const int32_t* vr = c->vrank_pin[buf];
+        const int32_t* vr = c->vrank_at[buf];
         float* host = c->host;
         for (int64_t r = a; r < b; ++r) memcpy(host + (size_t)vr[r] * c->D, blk + (size_t)r * c->D, rowb);
     }
