@@ -130,7 +130,13 @@ __global__ __launch_bounds__(SC_DIG * SC_GROUPS) void k_sort_scan(int32_t* ghist
 // FUSED: `dtot` holds the per-supertile digit counts written by k_sort_hist instead of the digit totals, and `ghist` the
 // raw per-tile counts (no scan kernel has run).  OPB (SORT_SRC_SLOTS only): bag b holds exactly lookup b, as checked by
 // the caller, so the value of lookup i is i and the offsets are not read.
-template <int SRC, int ITEMS, bool FUSED, bool OPB>
+// MAXB = 9: digits of at most 9 bits; the tile is put in order in LDS first and then written run by run, so that neighbouring
+// lanes write neighbouring words (straight from the registers, every lane of a store touched a line of its own, and the
+// requests to L2 alone took 9 us at 1.7 M pairs).  MAXB = 11 (the static module's long jobs, experiments): runs of one or two
+// keys, nothing to gain, and no LDS to spare.
+// Measured per launch (us by events, before -> after): 1.7 M pairs, 7-bit digits 30-34 -> 21; 426 k pairs, 9-bit digits 17 + a scan
+// kernel of 7 -> 20.
+template <int SRC, int ITEMS, bool FUSED, bool OPB, int MAXB>
 __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __restrict__ keys_in,
                                                              const int32_t* __restrict__ vals_in,
                                                              const int64_t* __restrict__ offsets, int num_bags, int n,
@@ -139,13 +145,15 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
                                                              const int32_t* __restrict__ dtot,
                                                              int32_t* __restrict__ keys_out,
                                                              int32_t* __restrict__ vals_out) {
-    constexpr int NW = RS_THREADS / 64;
-    __shared__ int base[1 << RS_MAX_BITS];     // where this tile's run of each digit starts in the output
-    __shared__ int wc[NW][1 << RS_MAX_BITS];   // per-wavefront digit counts, then exclusive offsets
+    constexpr int NW = RS_THREADS / 64, TILE = RS_THREADS * ITEMS;
+    constexpr bool STAGE = MAXB <= 9;
+    __shared__ int base[1 << MAXB];            // where this tile's run of each digit starts in the output
+    __shared__ int wc[NW][1 << MAXB];          // per-wavefront digit counts, then exclusive offsets
     __shared__ int lds[NW];
+    __shared__ int2 stage[STAGE ? TILE : 1];
     const int radix = 1 << radix_bits, mask = radix - 1;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int tile0 = blockIdx.x * (RS_THREADS * ITEMS) + w * (64 * ITEMS);
+    const int tile0 = blockIdx.x * TILE + w * (64 * ITEMS);
     // The tile's keys and values are requested first, all together, so that their latency runs beside the digit
     // bases below.  A lane beyond n rereads element n-1 and is masked out later.
     int key[ITEMS], val[ITEMS];
@@ -165,34 +173,46 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
     }
     if (FUSED) {
         // digit totals = sum over the supertiles; this tile's offset within a digit = the supertiles before its own plus
-        // the tiles before it inside its own.  A thread owns `per` <= 2 neighbouring digits (radix <= 512).
+        // the tiles before it inside its own.  A thread owns `per` <= 2 neighbouring digits (radix <= 512); with 128 digits or
+        // fewer, `parts` threads share one and take the rows in turn.  FUSE_ROWS rows are requested together.
+        constexpr int FUSE_ROWS = 16;
         const int nsup = (nblk + SS_TILES - 1) / SS_TILES, mysup = blockIdx.x / SS_TILES;
-        const int per = (radix + RS_THREADS - 1) / RS_THREADS;
-        const int d0 = tid * per;
+        const int rows = nsup + (int)blockIdx.x - mysup * SS_TILES;
+        const int per = radix > RS_THREADS ? 2 : 1;
+        const int parts = per == 1 ? RS_THREADS / radix : 1;
+        const int d0 = (tid & (RS_THREADS / parts - 1)) * per, part = tid / (RS_THREADS / parts);
         int tot[2] = {0, 0}, bef[2] = {0, 0};
-        if (d0 < radix) {
-#pragma unroll 8
-            for (int s = 0; s < nsup; ++s) {
-                const int v0 = dtot[(size_t)s * radix + d0];
-                const int v1 = per > 1 ? dtot[(size_t)s * radix + d0 + 1] : 0;
-                tot[0] += v0; tot[1] += v1;
-                if (s < mysup) { bef[0] += v0; bef[1] += v1; }
+        for (int r0 = part; r0 < rows; r0 += FUSE_ROWS * parts) {
+            int v0[FUSE_ROWS], v1[FUSE_ROWS];
+#pragma unroll
+            for (int k = 0; k < FUSE_ROWS; ++k) {
+                const int r = r0 + k * parts;
+                const int32_t* row = r < nsup ? dtot + (size_t)r * radix : ghist + (size_t)(mysup * SS_TILES + r - nsup) * radix;
+                v0[k] = r < rows ? row[d0] : 0;
+                v1[k] = r < rows && per > 1 ? row[d0 + 1] : 0;
             }
-#pragma unroll 8
-            for (int t = mysup * SS_TILES; t < (int)blockIdx.x; ++t) {
-                bef[0] += ghist[(size_t)t * radix + d0];
-                if (per > 1) bef[1] += ghist[(size_t)t * radix + d0 + 1];
+#pragma unroll
+            for (int k = 0; k < FUSE_ROWS; ++k) {
+                const int r = r0 + k * parts;
+                if (r < nsup) { tot[0] += v0[k]; tot[1] += v1[k]; }
+                if (r < mysup || r >= nsup) { bef[0] += v0[k]; bef[1] += v1[k]; }
             }
+        }
+        if (parts > 1) {                       // join the parts (wc serves as scratch: 2 * 256 words)
+            int* scr = &wc[0][0];
+            static_assert((NW << MAXB) >= 2 * RS_THREADS, "");
+            scr[tid] = tot[0]; scr[RS_THREADS + tid] = bef[0];
+            __syncthreads();
+            tot[0] = bef[0] = 0;
+            if (tid < radix)
+                for (int k = 0; k < parts; ++k) { tot[0] += scr[k * radix + tid]; bef[0] += scr[RS_THREADS + k * radix + tid]; }
+            __syncthreads();
         }
         int total;
-        int run = block_excl_scan<RS_THREADS>(tot[0] + tot[1], total, lds);
-        if (d0 < radix) {
+        const int run = block_excl_scan<RS_THREADS>(tot[0] + tot[1], total, lds);
+        if (part == 0) {
             base[d0] = run + bef[0];
             if (per > 1) base[d0 + 1] = run + tot[0] + bef[1];
-        }
-        for (int d = tid; d < radix; d += RS_THREADS) {
-#pragma unroll
-            for (int k = 0; k < NW; ++k) wc[k][d] = 0;
         }
     } else {   // digit bases: exclusive scan of the digit totals, plus this tile's offset within the digit
         const int per = (radix + RS_THREADS - 1) / RS_THREADS;
@@ -208,10 +228,10 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
                 run += dtot[d];
             }
         }
-        for (int d = tid; d < radix; d += RS_THREADS) {
+    }
+    for (int d = tid; d < radix; d += RS_THREADS) {
 #pragma unroll
-            for (int k = 0; k < NW; ++k) wc[k][d] = 0;
-        }
+        for (int k = 0; k < NW; ++k) wc[k][d] = 0;
     }
     __syncthreads();
     if (SRC == SORT_SRC_SLOTS && !OPB) {
@@ -241,6 +261,40 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
         lrank[it] = old + before;
     }
     __syncthreads();
+    if (STAGE) {
+        // wc[k][d]: where wavefront k's first pair of digit d goes within the tile; base[d]: what that place lacks to the output's
+        const int per = (radix + RS_THREADS - 1) / RS_THREADS;     // 1 or 2
+        const int d0 = tid * per;
+        int cnt = 0;
+        if (d0 < radix)
+            for (int j = 0; j < per; ++j)
+#pragma unroll
+                for (int k = 0; k < NW; ++k) cnt += wc[k][d0 + j];
+        int total;
+        int run = block_excl_scan<RS_THREADS>(cnt, total, lds);
+        if (d0 < radix)
+            for (int j = 0; j < per; ++j) {
+                base[d0 + j] -= run;
+#pragma unroll
+                for (int k = 0; k < NW; ++k) { const int c = wc[k][d0 + j]; wc[k][d0 + j] = run; run += c; }
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (tile0 + it * 64 + lane < n) stage[wc[w][(key[it] >> shift) & mask] + lrank[it]] = make_int2(key[it], val[it]);
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int j = it * RS_THREADS + tid;
+            if (j < total) {
+                const int2 kv = stage[j];
+                const int dest = j + base[(kv.x >> shift) & mask];
+                keys_out[dest] = kv.x;
+                vals_out[dest] = kv.y;
+            }
+        }
+        return;
+    }
     for (int d = tid; d < radix; d += RS_THREADS) {
         int run = 0;
 #pragma unroll
@@ -278,8 +332,12 @@ static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, co
     // SORT_SRC_RANKS: the slots are written now, the rest of the pass reads them
     constexpr int SSRC = SRC == SORT_SRC_RANKS ? SORT_SRC_SLOTS : SRC;
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
-    k_sort_scatter<SSRC, ITEMS, FUSED, OPB><<<(unsigned)nblk, RS_THREADS, 0, st>>>(SRC == SORT_SRC_RANKS ? j.slots_out : kin, vin, j.offsets, j.num_bags,
-                                                                                  j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : j.dtot, kout, vout);
+#define FC_SCATTER(B) \
+    k_sort_scatter<SSRC, ITEMS, FUSED, OPB, B><<<(unsigned)nblk, RS_THREADS, 0, st>>>(SRC == SORT_SRC_RANKS ? j.slots_out : kin, vin, j.offsets, j.num_bags, \
+                                                                                     j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : j.dtot, kout, vout)
+    if (FUSED || rb <= 9) FC_SCATTER(9);
+    else FC_SCATTER(11);
+#undef FC_SCATTER
 }
 
 template <bool FUSED, int ITEMS>
@@ -320,17 +378,18 @@ static int run_passes(const SortJob& j, hipStream_t st, int passes, int rb, int3
 
 int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
     // Every pass is a chain of short launches bound by latency rather than by bytes.  Batches of up to FUSE_MAX_TILES
-    // tiles and more than 18 key bits take passes of at most 9 bits, each two launches (counts, then offsets and scatter in
-    // one kernel; the per-supertile counts make the scan in between unnecessary; the caller supplies their table); 7-bit digits leave runs of 16 keys per digit and tile,
-    // i.e. whole sectors to write, where 11-bit digits left single keys.  Larger jobs (the static module's ranking) keep
-    // the scan kernel: two passes up to 22 key bits, beyond that passes of at most 8 bits.
+    // tiles take passes of at most 9 bits, each two launches (counts, then offsets and scatter in one kernel; the per-supertile
+    // counts make the scan in between unnecessary; the caller supplies their table).  Up to 18 key bits that is two passes,
+    // beyond three of 7 bits, which leave runs of 16 keys per digit and tile.  (Up to 18 bits a scan kernel per pass was kept
+    // while the scatter kernel added its rows up 8 at a time; with 16 at a time the two launches it costs decide: 53 k pairs
+    // 143 -> 138 us a step, 852 k 1207 -> 1196, 426 k the same.)  Larger jobs (the static module's ranking) and callers without
+    // a table keep the scan kernel: two passes up to 22 key bits, beyond that passes of at most 8 bits.
     // (j.max_bits / j.no_fuse, from FC_SORT_BITS / FC_SORT_FUSED at cache_create, override this for experiments.)
     const int env_bits = (j.max_bits >= 4 && j.max_bits <= RS_TWO_PASS_BITS) ? j.max_bits : 0;
     const bool env_fused = !j.no_fuse;
     const int64_t nblk = cdiv(j.n, RS_TILE);
     int passes, rb;
-    // up to 18 key bits two passes with a scan kernel each are the shorter chain (measured at 426 k pairs of 18 bits)
-    bool fused = env_fused && j.stot && nblk <= FUSE_MAX_TILES && (env_bits || j.bits > 2 * FUSE_MAX_BITS);
+    bool fused = env_fused && j.stot && nblk <= FUSE_MAX_TILES;
     size_t stot_pass = 0;
     if (fused) {
         const int lim = env_bits ? (env_bits < FUSE_MAX_BITS ? env_bits : FUSE_MAX_BITS) : FUSE_MAX_BITS;
