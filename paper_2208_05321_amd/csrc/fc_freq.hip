@@ -4,6 +4,8 @@
 #include "fc_internal.h"
 
 #include <limits.h>
+#include <omp.h>
+#include <string.h>
 
 #include <new>
 #include <vector>
@@ -106,6 +108,60 @@ static int freq_init(fc_freq* f, int64_t N, void* stream) {
     return FC_OK;
 }
 
+// Result arrays on their way to the caller's ordinary memory.  The runtime's own copy into such memory moves it through a
+// staging buffer with one thread, which also takes the page faults of arrays nobody has touched yet (10 M ints: 3.9 ms, 2.4 of
+// them the copy); here chunks land in two pinned buffers in turn and several threads carry them on, faults included, while
+// the next chunk crosses the link.  10 M rows, three arrays: build 14.4 -> 6.3 ms (2 MB chunks and 8 threads 8.3, 16 threads 9.1).
+struct CopyOut {
+    static constexpr size_t CHUNK = 8u << 20;
+    char* pin[2] = {nullptr, nullptr};
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    int threads = 1;
+    bool ok = false;
+
+    CopyOut() {
+        threads = omp_get_max_threads();
+        if (threads > 16) threads = 16;
+        ok = true;
+        for (int k = 0; k < 2 && ok; ++k)
+            ok = hipHostMalloc((void**)&pin[k], CHUNK, hipHostMallocDefault) == hipSuccess &&
+                 hipEventCreateWithFlags(&ev[k], hipEventDisableTiming) == hipSuccess;
+        if (!ok) (void)hipGetLastError();
+    }
+    ~CopyOut() {
+        for (int k = 0; k < 2; ++k) {
+            if (ev[k]) (void)hipEventDestroy(ev[k]);
+            if (pin[k]) (void)hipHostFree(pin[k]);
+        }
+    }
+    CopyOut(const CopyOut&) = delete;
+    CopyOut& operator=(const CopyOut&) = delete;
+
+    // Returns once dst is complete.
+    int copy(void* dst, const void* src, size_t bytes, hipStream_t st) {
+        const size_t chunks = (bytes + CHUNK - 1) / CHUNK;
+        for (size_t i = 0; i <= chunks; ++i) {
+            if (i < chunks) {
+                const size_t off = i * CHUNK, len = bytes - off < CHUNK ? bytes - off : CHUNK;
+                FC_HIP(hipMemcpyAsync(pin[i & 1], (const char*)src + off, len, hipMemcpyDeviceToHost, st));
+                FC_HIP(hipEventRecord(ev[i & 1], st));
+            }
+            if (i > 0) {
+                const size_t off = (i - 1) * CHUNK, len = bytes - off < CHUNK ? bytes - off : CHUNK;
+                FC_HIP(hipEventSynchronize(ev[(i - 1) & 1]));
+                char* d = (char*)dst + off; const char* p = pin[(i - 1) & 1];
+#pragma omp parallel for schedule(static) num_threads(threads)
+                for (int t = 0; t < threads; ++t) {
+                    const size_t a = len * t / threads, b = len * (t + 1) / threads;
+                    memcpy(d + a, p + a, b - a);
+                }
+            }
+        }
+        return FC_OK;
+    }
+};
+constexpr size_t COPY_OUT_MIN = 8u << 20;      // 2 M rows: 2.2 -> 1.9 ms; below, setting the buffers up costs what they save
+
 static int freq_build_impl(fc_freq* f, int32_t* freq_rank_host, int32_t* inv_rank_host, int32_t* counts_host) {
     const int64_t N = f->N;
     hipStream_t st = f->stream;
@@ -141,9 +197,17 @@ static int freq_build_impl(fc_freq* f, int32_t* freq_rank_host, int32_t* inv_ran
         FC_TRY(radix_sort(j, st, &ks, &vs));       // stable: equal counts keep ascending id order
         k_rank_of<<<(unsigned)cdiv(N, 256), 256, 0, st>>>(vs, N, rank);
         FC_HIP(hipGetLastError());
-        if (freq_rank_host) FC_HIP(hipMemcpyAsync(freq_rank_host, rank, (size_t)N * 4, hipMemcpyDeviceToHost, st));
-        if (inv_rank_host) FC_HIP(hipMemcpyAsync(inv_rank_host, vs, (size_t)N * 4, hipMemcpyDeviceToHost, st));
-        if (counts_host) FC_HIP(hipMemcpyAsync(counts_host, f->counts, (size_t)N * 4, hipMemcpyDeviceToHost, st));
+        const struct { int32_t* dst; const int32_t* src; } outs[3] = {{freq_rank_host, rank}, {inv_rank_host, vs}, {counts_host, f->counts}};
+        const size_t bytes = (size_t)N * 4;
+        if (bytes >= COPY_OUT_MIN) {
+            CopyOut out;                           // set up beside the kernels above
+            if (out.ok) {
+                for (const auto& o : outs) if (o.dst) FC_TRY(out.copy(o.dst, o.src, bytes, st));
+                FC_HIP(hipStreamSynchronize(st));
+                return FC_OK;
+            }
+        }
+        for (const auto& o : outs) if (o.dst) FC_HIP(hipMemcpyAsync(o.dst, o.src, bytes, hipMemcpyDeviceToHost, st));
         FC_HIP(hipStreamSynchronize(st));
         return FC_OK;
     };
