@@ -139,7 +139,7 @@ static void destroy(fc_cache* c) {
     for (int b = 0; b < DMA_BLOCKS; ++b)
         if (c->ev_copy_a[b]) (void)hipEventDestroy(c->ev_copy_a[b]);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
-                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->usum, (void*)c->plan, (void*)c->tile_plan,
+                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->usum, (void*)c->plan[0], (void*)c->plan[1], (void*)c->tile_plan,
                     (void*)c->rbuf,
                     (void*)c->ctl, (void*)c->stage_dev, (void*)c->stage_dev2, (void*)c->part, (void*)c->pmeta, (void*)c->pbits})
         if (p) (void)hipFree(p);
@@ -269,7 +269,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     FC_HIP(hipMalloc((void**)&c->bsum, (size_t)c->NB * 4));
     FC_HIP(hipMalloc((void**)&c->ssum, (size_t)c->NB * SUB_TILES * 4));
     FC_HIP(hipMalloc((void**)&c->usum, (size_t)c->NB * 4));
-    FC_HIP(hipMalloc((void**)&c->plan, 2 * 4));
+    for (int32_t*& p : c->plan) FC_HIP(hipMalloc((void**)&p, PLAN_WORDS * 4));
     FC_HIP(hipMalloc((void**)&c->tile_plan, (size_t)c->NB * sizeof(int4)));
     c->dma_evict = (flags & FC_EVICT_DMA) != 0;
     c->dirty_track = (flags & FC_DIRTY_TRACK) != 0;
@@ -401,6 +401,7 @@ static bool ensure_arrival_block(fc_cache* c, int k) {
 }
 
 // cache_plan_next: the planned batch's missing rows into the arrival block of its list set, on the stream pf
+// M < 0: the host does not know the number of rows yet, the kernel reads it (DMA evict transmitter, rows fetched by kernel)
 static int fetch_early(fc_cache* c, int64_t M) {
     const int k = c->lset;
     if (!ensure_arrival_block(c, k)) return FC_OK;   // no room for the block: the rows are fetched at cache_advance instead
@@ -418,7 +419,8 @@ static int fetch_early(fc_cache* c, int64_t M) {
     if (c->pf_dep) FC_HIP(hipStreamWaitEvent(c->pf, c->pf_dep, 0));
     if (c->dma_evict) {
         FC_HIP(hipEventRecord(c->ev_fetch_a[k], c->pf));
-        FC_TRY(launch_fill_rows(c, c->pf, M, c->arrive[k], c->staging_rows, c->fill_blocks_early));
+        FC_TRY(launch_fill_rows(c, c->pf, M < 0 ? c->staging_rows : M, c->arrive[k], c->staging_rows, c->fill_blocks_early, false,
+                                M < 0 ? c->plan[k] : nullptr));
         FC_HIP(hipEventRecord(c->ev_fetch_b[k], c->pf));
         c->fetch_timed[k] = true;
         c->arrived_by[k] = c->ev_fetch_b[k];
@@ -457,6 +459,57 @@ static int record_due_events(fc_cache* c) {
     for (int k = 0; k < 2; ++k) if (c->due & (DUE_MOVE << k)) FC_HIP(hipEventRecord(c->ev_move_done[k], c->stream));
     c->due = 0;
     return FC_OK;
+}
+
+// cache_plan_next with nothing waited for until everything is enqueued.
+static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots, bool early) {
+    const hipStream_t st = c->pre;
+    IndexRun run;
+    MovePlan mv;
+    int rc = index_launch(c, st, false, ids, n, offsets, num_bags, slots, false, &run);
+    c->last_pst = st;
+    c->next_pending = true;
+    int fetched = FC_OK, sorted = FC_ERR_INVALID_ARG;
+    const bool guess = c->last_one_per_bag && n == num_bags;       // most likely the shape of the batch before
+    const int rec = c->rec_next;
+    if (rc == FC_OK) rc = index_assign(c, st, run, -1);
+    if (rc == FC_OK) {
+        FC_HIP(hipEventRecord(c->ev_assign_done, st));
+        c->due &= ~DUE_INDEX;
+        c->last_index_stream = st;
+        c->aux = st;
+        c->planned.arrived = false;
+        fetched = fetch_early(c, -1);
+        if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
+        c->last_one_per_bag = guess;
+        c->pst = st;
+        sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
+        rc = index_result(c, st, run, &mv);
+    }
+    c->pst = c->stream;
+    const bool arrived = c->planned.arrived;
+    c->planned = MovePlan();
+    if (rc != FC_OK) {
+        c->rec[rec].valid = false;
+        c->rec_next = rec;             // the other record is the current batch's
+        c->fetch_timed[c->lset] = false;
+        FC_HIP(hipEventRecord(c->ev_pre_done, st));
+        return rc;
+    }
+    mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= c->staging_rows;
+    c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
+    c->planned = mv;
+    c->pending_ticket = c->ticket;
+    if (sorted == FC_OK && guess && !c->last_one_per_bag) {        // its values are not the bags: once more
+        c->rec_next = rec;
+        c->pst = st;
+        sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
+        c->pst = c->stream;
+    }
+    c->rec[rec].one_per_bag = c->last_one_per_bag;
+    if (sorted != FC_OK) FC_TRY(launch_slots_out(c, st, slots, n));        // no sort: the plain write-out
+    FC_HIP(hipEventRecord(c->ev_pre_done, st));
+    return fetched;
 }
 
 extern "C" {
@@ -568,6 +621,12 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     // FC_DIRTY_TRACK: which victims of the current batch are in transit is only marked by its row movement
     if (c->dirty_track && c->move_stream[c->lset]) FC_HIP(hipStreamWaitEvent(c->pre, c->ev_move_done[c->lset], 0));
     MovePlan mv;
+    // The common form: everything that depends on the decisions is enqueued before the host has seen them (the kernels read
+    // status and counts from device memory, and do nothing if the call is refused), so that neither the GPU waits for the host
+    // to hear of them nor the host for the GPU to get there while it could be enqueueing.  What it needs: a sort to fold the
+    // slot write-out into, and rows fetched by a kernel that can read their number.
+    if (c->presort && n > 0 && num_bags > 0 && c->dma_evict && !c->miss_dma)
+        return plan_enqueued(c, ids_dev, n, offsets_dev, num_bags, slots_dev, early);
     // the slot write-out is folded into the first kernel of the sort (one launch and one pass over the ranks fewer)
     const bool fold = c->presort && n > 0 && num_bags > 0;
     const int rc = prepare_index(c, c->pre, false, ids_dev, n, offsets_dev, num_bags, slots_dev, &mv, early ? c->ev_s_now : nullptr, fold);

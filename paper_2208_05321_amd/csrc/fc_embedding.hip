@@ -495,7 +495,7 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
     while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
     SortJob j;
     j.src = SORT_SRC_SLOTS; j.keys_in = slots; j.offsets = offsets; j.num_bags = (int)num_bags; j.n = (int)n;
-    if (slots_out) { j.src = SORT_SRC_RANKS; j.keys_in = c->rbuf; j.rank_slot = c->rank_slot; j.slots_out = slots_out; }
+    if (slots_out) { j.src = SORT_SRC_RANKS; j.keys_in = c->rbuf; j.rank_slot = c->rank_slot; j.slots_out = slots_out; j.status = &c->plan[c->lset][PL_STATUS]; }
     j.limit = (int)c->C; j.bits = bits; j.flags = &c->ctl->async_flags;
     j.one_per_bag = c->last_one_per_bag;      // sort_pairs serves the batch the last index half looked at
     j.tail_stream = tail; j.tail_event = c->ev_sort_tail; j.last_stream = last;

@@ -56,6 +56,7 @@ struct Ctl {
 // Host-visible (pinned, mapped) copy of the decision, written by the planning kernel: every word carries the number of the
 // cache_prepare call it belongs to and is stored in one piece, so that the host recognises a complete record by itself and
 // the kernel need not fence (a system-scope fence in the middle of a kernel costs microseconds).
+enum PlanWord { PL_STATUS = 0, PL_NEED, PL_MISS, PLAN_WORDS };
 enum HostWord { HW_STATUS = 0, HW_UNIQUE, HW_MISS, HW_NEED, HW_HITS, HW_NFREE, HW_ASYNC_FLAGS, HW_BATCH_FLAGS, HOST_REC_WORDS };
 struct HostCtl { uint64_t word[HOST_REC_WORDS]; };       // value in the low half, ticket in the high half
 
@@ -89,6 +90,13 @@ constexpr int64_t SORT_STOT_WORDS = 131072;
 #endif
 constexpr int DMA_BLOCKS = FC_DMA_BLOCKS;
 struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, transit_base = -1; bool arrived = false; };
+// An index half that has been enqueued and whose decisions the host has not read yet.
+struct IndexRun {
+    int32_t ticket = 0;
+    int64_t n = 0, num_bags = 0;
+    bool small = false, small_slots = false, bytes = false;
+    int buf = 0, transit_base = -1;
+};
 struct PresortRec {
     bool valid = false;
     int32_t ticket = 0;                 // number of the cache_prepare / _next / plan_next call whose slots it sorted
@@ -180,8 +188,8 @@ struct fc_cache {
     uint32_t* bsum = nullptr;       // [NB] per-tile counts: missing, evictable (high half)
     uint32_t* ssum = nullptr;       // [NB * SUB_TILES] the same per sub-tile
     int32_t* usum = nullptr;        // [NB] per-tile counts: used
-    int32_t* plan = nullptr;        // more than PLAN_FOLD_TILES tiles: status, victims ...
-    int4* tile_plan = nullptr;      // [NB] ... and per tile: missing rows before it, evictable rows above it
+    int32_t* plan[2] = {nullptr, nullptr};   // per list set, PL_*: the decision as kernels enqueued behind it read it
+    int4* tile_plan = nullptr;      // [NB] more than PLAN_FOLD_TILES tiles: missing rows before a tile, evictable rows above it
     int plan_fold_tiles = fc::PLAN_FOLD_TILES;   // (tuning: FC_PLAN_FOLD_TILES)
     int64_t nfree = 0;              // empty slots
     int err_set = 0;                // which of the two error words the next call uses
@@ -324,6 +332,10 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // entry points implemented across the sources
 int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots = nullptr, bool defer_slots = false);
+int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
+                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run);
+int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M);
+int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
 int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead);
 int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
@@ -356,7 +368,7 @@ int launch_flush_rows(fc_cache* c, hipStream_t s);   // FC_DIRTY_TRACK: dirty ro
 // dst == nullptr: into the cache slots fill_slots[j]; else into row j of the block dst (of dst_rows rows)
 // only_transit: rows whose newest copy is in the host table are skipped (the DMA miss path has brought them)
 int launch_fill_rows(fc_cache* c, hipStream_t s, int64_t rows, float* dst = nullptr, int64_t dst_rows = 0, int max_blocks = 0,
-                     bool only_transit = false);
+                     bool only_transit = false, const int32_t* plan = nullptr);   // plan: rows = the missing rows it states, if at most `rows`
 
 // gather pool of the DMA miss path (fc_gather.hip)
 int gather_create(fc_cache* c, int threads);
@@ -388,6 +400,7 @@ struct SortJob {
     int n = 0, limit = 0, bits = 1;
     int max_bits = 0; bool no_fuse = false;    // experiments: most bits per pass (0 = the default policy), never skip the scan kernel
     uint32_t* flags = nullptr;                 // device word for EF_BAD_SLOT, may be null
+    const int32_t* status = nullptr;           // SORT_SRC_RANKS, may be null: raise no flag unless this device word is FC_OK
     int32_t *keysA = nullptr, *valsA = nullptr, *keysB = nullptr, *valsB = nullptr;   // n ints each
     int32_t *ghist = nullptr, *dtot = nullptr; // (tiles << RS_MAX_BITS) ints, (1 << RS_MAX_BITS) ints
     // scan-free passes (optional): a clean table of stot_cap ints to accumulate into; the first kernel also clears the first

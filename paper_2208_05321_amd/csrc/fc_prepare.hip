@@ -319,6 +319,7 @@ struct PlanArgs {
     const uint32_t *bsum, *ssum; const int32_t* usum;    // K2a's counts
     const uint32_t* err; const uint32_t* async_flags;
     const int32_t* hitpart; HostCtl* hctl;
+    int32_t* plan;                                   // status, victims, missing rows: the decision for kernels enqueued behind
     int NB, C, nfree, nmark, ticket, protect_prev;
 };
 struct PlanTotals { int status, used, miss, need; };
@@ -355,6 +356,7 @@ __device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals&
     int mine = 0;
     for (int k = threadIdx.x; k < a.nmark; k += NT) mine += a.hitpart[k];
     const int hits = block_sum<NT>(mine, lds);
+    if (threadIdx.x == 0) { a.plan[PL_STATUS] = t.status; a.plan[PL_NEED] = t.need; a.plan[PL_MISS] = t.miss; }
     if (threadIdx.x < HOST_REC_WORDS)
         report_to_host(a.hctl, a.ticket, t.status, t.used, t.miss, t.need, hits, t.status == FC_OK ? a.nfree + t.need - t.miss : a.nfree,
                        (int)*a.async_flags, (int)(*a.err & EF_NOT_ONE_PER_BAG), threadIdx.x);
@@ -362,7 +364,7 @@ __device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals&
 
 // More than PLAN_FOLD_TILES tiles: one workgroup writes what K2c would work out.
 constexpr int PLAN_THREADS = 1024;
-__global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int32_t* __restrict__ plan, int4* __restrict__ tile_plan) {
+__global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int4* __restrict__ tile_plan) {
     __shared__ int lds[PLAN_THREADS / 64];
     const int tid = threadIdx.x;
     int mu = 0, mm = 0, mc = 0;
@@ -373,7 +375,6 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int32_t*
     const int U = block_sum<PLAN_THREADS>(mu, lds), M = block_sum<PLAN_THREADS>(mm, lds), E = block_sum<PLAN_THREADS>(mc, lds);
     const PlanTotals t = plan_totals(a, U, M, E);
     plan_report<PLAN_THREADS>(a, t, lds);
-    if (tid == 0) { plan[0] = t.status; plan[1] = t.need; }
     int cm = 0, cc = 0;                        // missing / evictable rows of the tiles before this round's
     for (int base = 0; base < a.NB; base += PLAN_THREADS) {
         const int b = base + tid;
@@ -417,7 +418,7 @@ __device__ __forceinline__ void store_bits(uint32_t* p, size_t i, const Bits<4>&
 
 template <int SPLIT, bool FOLD>
 __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint32_t* rbits, uint32_t* pbits, PlanArgs a,
-                                                          const int32_t* __restrict__ plan, const int4* __restrict__ tile_plan,
+                                                          const int4* __restrict__ tile_plan,
                                                           int32_t* __restrict__ miss_ranks, int32_t* __restrict__ vrank,
                                                           int32_t* __restrict__ vslot, int32_t* rank_slot,
                                                           int32_t* slot_rank, int transit_base,
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint3
         status = t.status; need = t.need;
         if (blockIdx.x == 0) plan_report<RT_THREADS>(a, t, lds);
     } else {
-        status = plan[0]; need = plan[1];
+        status = a.plan[PL_STATUS]; need = a.plan[PL_NEED];
         const int4 tp = tile_plan[me];
         mbase = tp.x; above = tp.y;
     }
@@ -602,7 +603,9 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_count(const int32_t* __re
 __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount,
                                                               int M, const int32_t* __restrict__ miss_ranks,
                                                               int32_t* __restrict__ fill_slots, int32_t* rank_slot,
-                                                              int32_t* __restrict__ old_rank) {
+                                                              int32_t* __restrict__ old_rank, const int32_t* __restrict__ plan) {
+    // plan: the number of missing rows as the device knows it (the host has not seen it yet)
+    if (plan) M = plan[PL_STATUS] == FC_OK ? plan[PL_MISS] : 0;
     __shared__ int lds[FREE_THREADS / 64];
     int part = 0;
     for (int g = threadIdx.x; g < (int)blockIdx.x; g += FREE_THREADS) part += tcount[g];
@@ -892,10 +895,9 @@ int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n) {
     return FC_OK;
 }
 
-// before_slots: an event the slot write-out (the first kernel that writes the caller's buffer) has to wait for.
-// defer_slots: leave the slot write-out to the caller (who folds it into the sort).
-int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
-                  int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots, bool defer_slots) {
+// Everything up to the decisions (the emitting kernel), enqueued.  write_slots: a small batch's one kernel writes them, too.
+int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
+                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run) {
     const int64_t LIM = ((int64_t)1 << 31) - 65536;
     if (!c || n < 0 || num_bags < 0 || n >= LIM || num_bags >= LIM || !offsets || (n > 0 && (!ids || !slots)))
         return FC_ERR_INVALID_ARG;
@@ -926,7 +928,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
         transit_base = (int)(buf * c->staging_rows);
     }
     const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
-    const bool small_slots = small && !defer_slots && !before_slots;     // its one kernel may write the caller's buffer, too
+    const bool small_slots = small && write_slots;
     const int transit = c->dirty_track ? -1 : transit_base;
     const int32_t* landed_ranks = c->dma_evict ? c->vrank_buf[buf] : nullptr;
     bool bytes = false;                  // marks are bytes
@@ -979,12 +981,12 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
                                                                 landed_ranks, (int)landed,
                                                                 (int)(buf * c->staging_rows), c->rank_slot, next_err);
         }
-        const PlanArgs pa{c->bsum, c->ssum, c->usum, err, &c->ctl->async_flags, c->hitpart, c->hctl, (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
+        const PlanArgs pa{c->bsum, c->ssum, c->usum, err, &c->ctl->async_flags, c->hitpart, c->hctl, c->plan[c->lset], (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
                           protect_prev};
         const bool fold = c->NB <= c->plan_fold_tiles;
         if (!fold) {
             ProfScope ps(c, P_RANK_PLAN, st);
-            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(pa, c->plan, c->tile_plan);
+            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(pa, c->tile_plan);
         }
         // Last batch's evicted rows must have reached the host table before the victim lists and the block buffer
         // are reused and before any of those rows could be fetched again; the kernels above do not care.
@@ -994,7 +996,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
         }
         ProfScope ps(c, P_RANK_EMIT, st);
 #define FC_EMIT(S, F) \
-        k_rank_emit<S, F><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->plan, c->tile_plan, \
+        k_rank_emit<S, F><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->tile_plan, \
                                                                        c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, \
                                                                        transit, (int)c->staging_rows, \
                                                                        c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0)
@@ -1007,39 +1009,38 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
     if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
-    // the planning kernel's decision
+    run->ticket = ticket; run->n = n; run->num_bags = num_bags;
+    run->small = small; run->small_slots = small_slots; run->bytes = bytes; run->buf = buf; run->transit_base = transit_base;
+    return FC_OK;
+}
+
+// j-th missing rank -> j-th empty slot.  M < 0: the host does not know yet how many there are.
+int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M) {
+    if (M == 0 || run.small) return FC_OK;
+    int32_t* old_rank = c->dma_evict ? nullptr : c->fill_src;
+    const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
+    {
+        ProfScope ps(c, P_FREE_COUNT, st);
+        k_free_count<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount);
+    }
+    ProfScope ps(c, P_FREE_PICK, st);
+    k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
+                                              c->rank_slot, old_rank, M < 0 ? c->plan[c->lset] : nullptr);
+    FC_HIP(hipGetLastError());
+    return FC_OK;
+}
+
+// Wait for the decisions (status, counts) and take them over.
+int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv) {
     int32_t h[HOST_REC_WORDS];
-    FC_TRY(wait_for_record(c->hctl, ticket, st, h));
+    FC_TRY(wait_for_record(c->hctl, run.ticket, st, h));
     if (h[HW_STATUS] != FC_OK) return h[HW_STATUS];
     c->nfree = h[HW_NFREE];
-    if (bytes) std::swap(c->ubits, c->pbits);            // this batch is the "previous" one next time
-    c->last_one_per_bag = n == num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
+    if (run.bytes) std::swap(c->ubits, c->pbits);        // this batch is the "previous" one next time
+    c->last_one_per_bag = run.n == run.num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
     const int64_t M = h[HW_MISS], need = h[HW_NEED];
-    if (M > 0 && !small) {
-        int32_t* old_rank = c->dma_evict ? nullptr : c->fill_src;
-        {
-            const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
-            {
-                ProfScope ps(c, P_FREE_COUNT, st);
-                k_free_count<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount);
-            }
-            ProfScope ps(c, P_FREE_PICK, st);
-            k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
-                                                      c->rank_slot, old_rank);
-        }
-    }
-    if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));
-    // every row of the batch has its slot now: write the slots out (the caller then starts sorting them for the
-    // backward pass on a library stream, where the sort runs while the missing rows cross the host link)
-    if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
-    if (!defer_slots) {
-        if (!small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
-    }
-    if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
-    c->last_index_stream = st;
-    c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
-    mv->valid = true; mv->M = M; mv->need = need; mv->buf = buf; mv->transit_base = transit_base;
-    c->last.n_ids = n;
+    mv->valid = true; mv->M = M; mv->need = need; mv->buf = run.buf; mv->transit_base = run.transit_base;
+    c->last.n_ids = run.n;
     c->last.n_unique = h[HW_UNIQUE];
     c->last.n_hit_unique = h[HW_UNIQUE] - M;
     c->last.n_hit_ids = h[HW_HITS];
@@ -1048,6 +1049,28 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     c->last.bytes_h2d = M * (int64_t)c->D * 4;
     c->last.bytes_d2h = need * (int64_t)c->D * 4;
     c->have_lists = true;
+    return FC_OK;
+}
+
+// before_slots: an event the slot write-out (the first kernel that writes the caller's buffer) has to wait for.
+// defer_slots: leave the slot write-out to the caller (who folds it into the sort).
+int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
+                  int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots, bool defer_slots) {
+    IndexRun run;
+    const bool plain = st == c->stream;
+    FC_TRY(index_launch(c, st, lookahead, ids, n, offsets, num_bags, slots, !defer_slots && !before_slots, &run));
+    FC_TRY(index_result(c, st, run, mv));
+    FC_TRY(index_assign(c, st, run, mv->M));
+    if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));
+    // every row of the batch has its slot now: write the slots out (the caller then starts sorting them for the
+    // backward pass on a library stream, where the sort runs while the missing rows cross the host link)
+    if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
+    if (!defer_slots) {
+        if (!run.small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
+    }
+    if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
+    c->last_index_stream = st;
+    c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     return FC_OK;
 }
 

@@ -27,7 +27,7 @@ struct SmallArgs {
     int32_t* ranks;                    // rank of every id
     int32_t* slots_out;                // slot of every id; null: left to the caller (folded into the sort)
     const int32_t* landed_ranks;       // see k_rank_count
-    const Ctl* ctl; HostCtl* hctl;
+    const Ctl* ctl; HostCtl* hctl; int32_t* plan;
     int64_t N;
     int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket, nfree;
     bool dma;
@@ -120,8 +120,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
                 if (!(*reinterpret_cast<volatile uint32_t*>(word) & bit)) mine = (atomicOr(word, bit) & bit) == 0;
                 used += mine;
                 hits += s[k] >= 0;
-                a.ranks[i] = r[k];
             }
+            if (i < a.n) a.ranks[i] = r[k];
             const int at = enqueue(mine && s[k] < 0, &s_queue, lane, lt);
             if (at >= 0 && at < a.C) a.fill_slots[at] = r[k];        // (more missing rows than slots: refused below)
         }
@@ -182,6 +182,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     int need = M - nfree;
     if (need < 0 || status != FC_OK) need = 0;
     if (w == SM_WAVES - 1) {
+        if (lane == 0) { a.plan[PL_STATUS] = status; a.plan[PL_NEED] = need; a.plan[PL_MISS] = M; }
         const int nf = status == FC_OK ? nfree + need - M : nfree;
         report_to_host(a.hctl, a.ticket, status, totU, M, need, s_hits, nf, (int)a.ctl->async_flags, (int)(ef & EF_NOT_ONE_PER_BAG), lane);
     }
@@ -320,7 +321,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
     a.fill_src = c->fill_src; a.dma = c->dma_evict; a.nfree = (int)c->nfree;
     a.ranks = c->rbuf; a.slots_out = slots;
     a.landed_ranks = landed_ranks; a.landed = (int)landed; a.landed_base = (int)landed_base;
-    a.ctl = c->ctl; a.hctl = c->hctl; a.N = c->N;
+    a.ctl = c->ctl; a.hctl = c->hctl; a.plan = c->plan[c->lset]; a.N = c->N;
     a.n = (int)n; a.num_bags = (int)num_bags; a.C = (int)c->C; a.words = (int)(c->NB * RT_WORDS);
     a.transit_base = transit_base; a.transit_rows = (int)c->staging_rows; a.ticket = ticket;
     const size_t lds = (size_t)(a.words + a.words / 8) * 4 + (size_t)cdiv(c->C, 64 * SM_WAVES) * SM_WAVES * 8;
@@ -338,7 +339,8 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ rank_slot,
                                                            int32_t* __restrict__ slots_out, const int64_t* __restrict__ offsets,
                                                            int num_bags, int one_per_bag, int n, int limit, int passes, int radix_bits,
-                                                           uint32_t* flags, int32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out) {
+                                                           uint32_t* flags, const int32_t* __restrict__ status, int32_t* __restrict__ keys_out,
+                                                           int32_t* __restrict__ vals_out) {
     extern __shared__ __align__(16) uint32_t sm_words[];   // two arrays of rounds * SM_THREADS words, then the digit counts
     const int rounds = (n + SM_THREADS - 1) / SM_THREADS;  // elements per thread
     const int radix = 1 << radix_bits, mask = radix - 1;
@@ -351,11 +353,11 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
 #pragma unroll 4
     for (int i = tid; i < n; i += SM_THREADS) {
         int key = keys_in[i];
-        if (rank_slot) slots_out[i] = key = rank_slot[key];
+        if (rank_slot) slots_out[i] = key = key >= 0 ? rank_slot[key] : -1;     // (-1: an id out of range, the call is refused)
         if ((unsigned)key >= (unsigned)limit) { bad = true; key = limit; }
         from[i] = ((uint32_t)key << SMALL_POS_BITS) | (uint32_t)i;
     }
-    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
+    if (bad && flags && (!status || *status == FC_OK)) atomicOr(flags, EF_BAD_SLOT);
     const uint64_t lt = (1ull << lane) - 1ull;
     const int e0 = w * 64 * rounds + lane;                 // this wavefront's elements: e0 + 64 * k
     int* mine = wc + w * radix;
@@ -420,7 +422,7 @@ int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
     const size_t words = 2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb);
     k_sort_small<<<1, SM_THREADS, words * 4, st>>>(j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.num_bags, opb, j.n,
-                                                   j.limit, passes, rb, j.flags, j.keysA, j.valsA);
+                                                   j.limit, passes, rb, j.flags, j.status, j.keysA, j.valsA);
     FC_HIP(hipGetLastError());
     *kres = j.keysA; *vres = j.valsA;
     if (j.last_stream) *j.last_stream = st;

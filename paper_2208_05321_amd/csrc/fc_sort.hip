@@ -34,7 +34,8 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
                                                           int32_t* __restrict__ stot,
                                                           uint32_t* flags, const int32_t* __restrict__ rank_slot,
                                                           int32_t* __restrict__ slots_out,
-                                                          int32_t* __restrict__ zero_ptr, int zero_words) {
+                                                          int32_t* __restrict__ zero_ptr, int zero_words,
+                                                          const int32_t* __restrict__ status) {
     __shared__ int h[1 << RS_MAX_BITS];
     if (zero_ptr) {     // what the previous sort left in the other set of supertile tables, a slice per workgroup
         const int per = (zero_words + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -52,7 +53,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) r[it] = keys_in[min(tile0 + it * RS_THREADS + (int)threadIdx.x, n - 1)];
 #pragma unroll
-        for (int it = 0; it < ITEMS; ++it) key[it] = rank_slot[r[it]];
+        for (int it = 0; it < ITEMS; ++it) key[it] = r[it] >= 0 ? rank_slot[r[it]] : -1;     // (-1: an id out of range, the call is refused)
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             const int i = tile0 + it * RS_THREADS + (int)threadIdx.x;
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
         // offsets from these and from the counts of the few tiles before it, and no scan kernel runs in between
         if (stot && cnt) atomicAdd(&stot[(size_t)(blockIdx.x / SS_TILES) * radix + d], cnt);
     }
-    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
+    if (bad && flags && (!status || *status == FC_OK)) atomicOr(flags, EF_BAD_SLOT);
 }
 
 // Exclusive scan, per digit, of the per-tile counts over the tiles, in place; the digit totals go to dtot.
@@ -323,7 +324,7 @@ static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, co
         const bool first = shift == 0 && j.stot_other && j.other_dirty > 0;
         k_sort_hist<SRC, ITEMS><<<(unsigned)nblk, RS_THREADS, 0, st>>>(kin, j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : nullptr,
                                                                      j.flags, j.rank_slot, j.slots_out,
-                                                                     first ? j.stot_other : nullptr, first ? (int)j.other_dirty : 0);
+                                                                     first ? j.stot_other : nullptr, first ? (int)j.other_dirty : 0, j.status);
     }
     if (!FUSED) {
         ProfScope ps(j.prof, P_SORT_SCAN, st);
