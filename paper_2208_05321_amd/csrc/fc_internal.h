@@ -41,7 +41,8 @@ constexpr int BWD_PF = FC_BWD_PF;
 constexpr int SMALL_MAX_IDS = 4096;
 constexpr int SMALL_MAX_WORDS = 32768;            // rank bitmap in LDS: up to 1,048,576 rows (128 KB)
 constexpr int SMALL_MAX_SLOTS = 65536;            // slot bitmap in LDS: 8 KB
-constexpr int SMALL_POS_BITS = 12, SMALL_KEY_BITS = 32 - SMALL_POS_BITS;
+constexpr int SMALL_SORT_IDS = 10240;             // the one-workgroup sort
+constexpr int SMALL_POS_BITS = 14, SMALL_KEY_BITS = 32 - SMALL_POS_BITS;
 
 // Sticky device-side flags.
 enum : uint32_t { EF_BAD_OFFSETS = 1u, EF_ID_RANGE = 2u, EF_BAD_SLOT = 4u,

@@ -20,7 +20,7 @@ def test_small_batches(rows, cache, bags, multi_hot, dma, warm):
         run_parity_planned(w, 4, warm=warm, dma_evict=True, inputs_ready=multi_hot)
 
 
-@pytest.mark.parametrize("cache,bags", [(1, 4097), (2, 6144), (3, 6145), (127, 8191), (128, 8193), (255, 4100), (256, 70_000), (511, 5000), (512, 2048 * 33 + 1)])
+@pytest.mark.parametrize("cache,bags", [(1, 4097), (40, 10_239), (300, 10_240), (300, 10_241), (2, 6144), (3, 6145), (127, 8191), (128, 8193), (255, 4100), (256, 70_000), (511, 5000), (512, 2048 * 33 + 1)])
 def test_sort_digit_widths(cache, bags):
     """Batches past the one-workgroup sort with digits of 1 to 9 bits and ragged last tiles, one and several supertiles."""
     w = TinyWorkload(num_rows=700, dim=4, cache_rows=cache, seed=cache, multi_hot=False, bags=bags, distinct_cap=cache)
