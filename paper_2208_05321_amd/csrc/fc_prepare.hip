@@ -311,7 +311,8 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_count(const uint4* __restri
 //      All of it is a sum over the tiles' counts, one word each, so every workgroup of K2c works it out for its own tile (12 KB
 //      of reads from L2 at 100 M rows) instead of waiting for a kernel of one workgroup in between (6 us at 306 tiles, 11-14 at
 //      3052, and a launch), and the first one reports to the host before it starts on its tile.  Above PLAN_FOLD_TILES tiles
-//      (134 M rows) those reads would grow with the square of the tiles: there one workgroup plans for all.
+//      (33 M rows) those reads grow with the square of the tiles (3052 tiles, beside forward and backward: 104 us against
+//      18 + 29 with a plan of its own): there one workgroup plans for all.
 //      (Tried: letting the last workgroup of K2a to finish do this, found by an atomic ticket.  One ticket per tile on
 //      one address costs about 100 ns each on this part, 300 us at 3052 tiles: slower than the launch it saves.)
 // ---------------------------------------------------------------------------------------------------------
@@ -363,7 +364,7 @@ __device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals&
 }
 
 // More than PLAN_FOLD_TILES tiles: one workgroup writes what K2c would work out.
-constexpr int PLAN_THREADS = 1024;
+constexpr int PLAN_THREADS = 256;      // finds room beside the previous batch's forward kernel at once; 1024 threads waited for it
 __global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int4* __restrict__ tile_plan) {
     __shared__ int lds[PLAN_THREADS / 64];
     const int tid = threadIdx.x;

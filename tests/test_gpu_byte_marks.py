@@ -44,7 +44,7 @@ def test_both_kinds_of_marks_in_turn(rows):
     run_parity_lookahead(tight, 8, warm=True)                          # some look-aheads are refused
 
 
-@pytest.mark.parametrize("fold", ["0", "4096"])
+@pytest.mark.parametrize("fold", ["0", "1024"])
 def test_dense_tiles_and_a_separate_plan(monkeypatch, fold):
     """A cold cache filled by a batch that misses whole tiles (more ranks of one tile than a list in LDS holds), then
     evictions of as many; the planning step in a kernel of its own and inside the emitting kernel."""
