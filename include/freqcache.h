@@ -166,7 +166,7 @@ int cache_create(int64_t num_rows, int32_t dim, int64_t cache_rows, const int32_
                  float* host_weight, int64_t staging_rows, int32_t flags, void* hip_stream, fc_cache** out);
 
 /* Allocate now everything the per-batch calls would otherwise allocate when they first meet a batch of that size:
- * the per-id rank buffer of cache_prepare and its byte marks (num_rows bytes, if max_ids is at least num_rows / 128), the
+ * the per-id rank buffer of cache_prepare and its byte marks (num_rows bytes, if max_ids is at least num_rows / 32), the
  * sort scratch and partial-sum rows of embedding_bag_bwd_sgd for batches of up to max_ids lookups (three sort sets of 16 * max_ids bytes), and, if pipelined != 0, the two arrival blocks of
  * cache_plan_next (staging_rows * dim * 4 bytes each).  The transmitter's memory stays bounded by staging_rows
  * (Section 4.3); this call only moves the allocations out of the training loop.  Optional: without it (or for a larger

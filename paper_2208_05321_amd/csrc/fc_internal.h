@@ -20,7 +20,7 @@ constexpr int SUB_TILES = 8;                      // each tile's counts are also
 constexpr int PLAN_FOLD_TILES = 1024;             // up to this many tiles every workgroup of the emitting kernel plans for itself
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size
-constexpr int64_t MARKB_ROWS_PER_ID = 128;        // byte marks up to this many rows per id of the batch
+constexpr int64_t MARKB_ROWS_PER_ID = 32;         // byte marks up to this many rows per id of the batch
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;
 constexpr int RS_ITEMS = 8;                      // keys per thread

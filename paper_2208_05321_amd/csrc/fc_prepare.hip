@@ -733,7 +733,7 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
 
 __global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
 
-// Byte marks cost N / 5 TB/s more in K2a, bit marks 0.04 to 0.06 ns per id in K1 (atomics), so the line lies near N = 128 n
+// Byte marks cost N / 5 TB/s more in K2a, bit marks 0.04 to 0.06 ns per id in K1 (atomics), so the line lies at N = 32 n
 // (measured: see k_remap_bytes); a map that could not be allocated leaves the bits.
 bool mark_bytes(fc_cache* c, int64_t n) {
     if (c->N > MARKB_ROWS_PER_ID * n) return false;
