@@ -371,17 +371,22 @@ static float elapsed_us(hipEvent_t a, hipEvent_t b) {
 }
 
 // One step of the controller described at fc_cache::tune_early: the fetch that last used list set k against the newest
-// finished block copy (no copy at all: the fetch has the link to itself and may take what it can use).
+// block copy that is done with (no copy at all: the fetch has the link to itself and may take what it can use).
 static void tune_fetch_grid(fc_cache* c, int k) {
     if (!c->fetch_timed[k]) return;
     const float f_us = elapsed_us(c->ev_fetch_a[k], c->ev_fetch_b[k]);
     if (f_us <= 0.f) return;
     float d_us = -1.f;
-    if (c->last_copy_buf >= 0)
+    // Only blocks that have reached the host table are looked at: while a scatter thread waits for ev_d2h, a query of that event
+    // waits with it, i.e. until the copy has landed and the thread has woken up (config 4: the fetch and the sort left the host
+    // 280 us late, 0.57 -> 0.67 ms a step).
+    if (c->last_copy_buf >= 0) {
+        const uint64_t done = pool_completed(c);
         for (int i = 0; i < DMA_BLOCKS && d_us <= 0.f; ++i) {
             const int b = (c->last_copy_buf - i + DMA_BLOCKS) % DMA_BLOCKS;
-            if (c->copy_timed[b]) d_us = elapsed_us(c->ev_copy_a[b], c->ev_d2h[b]);
+            if (c->copy_timed[b] && c->copy_seq[b] <= done) d_us = elapsed_us(c->ev_copy_a[b], c->ev_d2h[b]);
         }
+    }
     const float r = d_us > 0.f ? f_us / d_us : 2.f;
     c->tune_ratio = c->tune_ratio <= 0.f ? r : 0.75f * c->tune_ratio + 0.25f * r;
     if (++c->tune_count < 6) return;

@@ -255,6 +255,7 @@ struct fc_cache {
     hipEvent_t ev_fetch_a[2] = {nullptr, nullptr}, ev_fetch_b[2] = {nullptr, nullptr};
     hipEvent_t ev_copy_a[fc::DMA_BLOCKS] = {};            // (the copy's end: ev_d2h)
     bool fetch_timed[2] = {false, false}, copy_timed[fc::DMA_BLOCKS] = {};
+    uint64_t copy_seq[fc::DMA_BLOCKS] = {};               // number of the block the copy carried
     int last_copy_buf = -1;
     float tune_ratio = 0.f;
     int tune_count = 0;
@@ -381,9 +382,10 @@ int gather_wait(fc_cache* c);
 // scatter pool (fc_worker.hip)
 int pool_create(fc_cache* c, int threads);
 void pool_destroy(fc_cache* c);
-void pool_publish(fc_cache* c, int buf, int64_t rows);   // block `buf` holds `rows` rows once ev_d2h[buf] fires
+uint64_t pool_publish(fc_cache* c, int buf, int64_t rows);   // block `buf` holds `rows` rows once ev_d2h[buf] fires; its number
 void pool_wait(fc_cache* c, uint64_t seq);               // until block number `seq` (1-based) is in the host table
 uint64_t pool_published(fc_cache* c);
+uint64_t pool_completed(fc_cache* c);                    // the last block that is in the host table
 
 // ---- radix sort (fc_sort.hip) ----
 enum SortSrc {

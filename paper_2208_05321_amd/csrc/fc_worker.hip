@@ -42,12 +42,14 @@ void pool_destroy(fc_cache* c) {
     c->pool = nullptr;
 }
 
-void pool_publish(fc_cache* c, int buf, int64_t rows) { (void)c->pool->publish(buf, rows); }
+uint64_t pool_publish(fc_cache* c, int buf, int64_t rows) { return c->pool->publish(buf, rows); }
 
 void pool_wait(fc_cache* c, uint64_t seq) {
     if (c->pool) c->pool->wait(seq);
 }
 
 uint64_t pool_published(fc_cache* c) { return c->pool ? c->pool->published() : 0; }
+
+uint64_t pool_completed(fc_cache* c) { return c->pool ? c->pool->completed() : 0; }
 
 }  // namespace fc

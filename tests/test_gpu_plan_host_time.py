@@ -1,0 +1,39 @@
+"""`-m gpu`: what cache_plan_next makes the host wait for: its own planning kernels, and nothing that moves rows or trains."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+IDS, CACHE, DIM = 35_000, 40_000, 1024
+
+
+def test_a_block_on_its_way_does_not_hold_up_the_next_plan():
+    """The controller of the early fetch reads the durations of finished block copies; asking about the one that the scatter
+    threads are still waiting for makes the caller wait with them."""
+    import torch
+    from paper_2208_05321_amd import FreqCache
+    rows = 4 * IDS
+    gpu = FreqCache(rows, DIM, CACHE, np.arange(rows, dtype=np.int32), dma_evict=True, inputs_ready=True)
+    gpu.host_weight()[:] = 1.0
+    gpu.warm()
+    gpu.reserve(IDS, pipelined=True)
+    off = torch.arange(IDS + 1, device="cuda")
+    ids = [torch.arange(k * IDS, (k + 1) * IDS, device="cuda") for k in range(4)]       # every batch replaces most of the cache
+    slots = [torch.empty(IDS, dtype=torch.int32, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    gpu.prepare(ids[0], off, out=slots[0])
+    took = []
+    for t in range(1, 13, 2):
+        gpu.plan_next(ids[t % 4], off, out=slots[t & 1])
+        gpu.advance()                                     # its evicted rows set out
+        least = gpu.stats()["n_evict"] * DIM * 4 / 64e9   # seconds they need on the link
+        time.sleep(0.0003)                                # the scatter threads wait for them by now
+        a = time.perf_counter()
+        gpu.plan_next(ids[(t + 1) % 4], off, out=slots[(t + 1) & 1])
+        took.append((time.perf_counter() - a) / least)
+        gpu.check()                                       # everything has arrived
+    gpu.close()
+    assert least > 1.8e-3
+    assert min(took[2:]) < 0.4, took
