@@ -627,7 +627,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     if (c->dirty_track && c->move_stream[c->lset]) FC_HIP(hipStreamWaitEvent(c->pre, c->ev_move_done[c->lset], 0));
     MovePlan mv;
     // The common form: everything that depends on the decisions is enqueued before the host has seen them (the kernels read
-    // status and counts from device memory, and do nothing if the call is refused), so that neither the GPU waits for the host
+    // status and counts from device memory; if the call is refused they touch neither the cache nor a buffer of the caller's), so that neither the GPU waits for the host
     // to hear of them nor the host for the GPU to get there while it could be enqueueing.  What it needs: a sort to fold the
     // slot write-out into, and rows fetched by a kernel that can read their number.
     // (After a batch without a miss the next one most likely has none either, and the kernels that depend on there being some

@@ -404,7 +404,7 @@ struct SortJob {
     int n = 0, limit = 0, bits = 1;
     int max_bits = 0; bool no_fuse = false;    // experiments: most bits per pass (0 = the default policy), never skip the scan kernel
     uint32_t* flags = nullptr;                 // device word for EF_BAD_SLOT, may be null
-    const int32_t* status = nullptr;           // SORT_SRC_RANKS, may be null: raise no flag unless this device word is FC_OK
+    const int32_t* status = nullptr;           // SORT_SRC_RANKS, may be null: unless this device word is FC_OK, touch no buffer of the caller's and raise no flag
     int32_t *keysA = nullptr, *valsA = nullptr, *keysB = nullptr, *valsB = nullptr;   // n ints each
     int32_t *ghist = nullptr, *dtot = nullptr; // (tiles << RS_MAX_BITS) ints, (1 << RS_MAX_BITS) ints
     // scan-free passes (optional): a clean table of stot_cap ints to accumulate into; the first kernel also clears the first

@@ -353,14 +353,19 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
     __shared__ int scan[SM_WAVES];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     bool bad = false;
+    const bool refused = status && *status != FC_OK;       // neither slots nor offsets are touched then
 #pragma unroll 4
     for (int i = tid; i < n; i += SM_THREADS) {
         int key = keys_in[i];
-        if (rank_slot) slots_out[i] = key = key >= 0 ? rank_slot[key] : -1;     // (-1: an id out of range, the call is refused)
+        if (rank_slot) {
+            key = key >= 0 ? rank_slot[key] : -1;          // (-1: an id out of range, the call is refused)
+            if (!refused) slots_out[i] = key;
+        }
         if ((unsigned)key >= (unsigned)limit) { bad = true; key = limit; }
         from[i] = ((uint32_t)key << SMALL_POS_BITS) | (uint32_t)i;
     }
-    if (bad && flags && (!status || *status == FC_OK)) atomicOr(flags, EF_BAD_SLOT);
+    if (refused) return;
+    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
     const uint64_t lt = (1ull << lane) - 1ull;
     const int e0 = w * 64 * rounds + lane;                 // this wavefront's elements: e0 + 64 * k
     int* mine = wc + w * radix;

@@ -1,4 +1,6 @@
 // Stable LSD radix sort of (key, value) int32 pairs, 64-wide wavefronts, tiles of RS_TILE keys per workgroup.
+// With SortJob::status the first pass of a refused batch does nothing; the later ones then order whatever the scratch holds (a
+// pass is in bounds for any keys, and by the time those on the side stream run, the word may belong to a later batch).
 // Used by the backward pass and the slot-order forward (sort lookups by slot, value = bag) and by the static-module
 // build (sort ids by descending count).  Keys come from one of four sources, see SortSrc.  A pass is either
 // count -> scan -> scatter (up to RS_MAX_BITS bits per digit) or, for batch-sized jobs with many key bits, count -> scatter
@@ -54,6 +56,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
         for (int it = 0; it < ITEMS; ++it) r[it] = keys_in[min(tile0 + it * RS_THREADS + (int)threadIdx.x, n - 1)];
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) key[it] = r[it] >= 0 ? rank_slot[r[it]] : -1;     // (-1: an id out of range, the call is refused)
+        if (status && *status != FC_OK) return;    // refused: the caller's buffer is his own again
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
             const int i = tile0 + it * RS_THREADS + (int)threadIdx.x;
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
         // offsets from these and from the counts of the few tiles before it, and no scan kernel runs in between
         if (stot && cnt) atomicAdd(&stot[(size_t)(blockIdx.x / SS_TILES) * radix + d], cnt);
     }
-    if (bad && flags && (!status || *status == FC_OK)) atomicOr(flags, EF_BAD_SLOT);
+    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
 }
 
 // Exclusive scan, per digit, of the per-tile counts over the tiles, in place; the digit totals go to dtot.
@@ -145,7 +148,8 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
                                                              const int32_t* __restrict__ ghist,
                                                              const int32_t* __restrict__ dtot,
                                                              int32_t* __restrict__ keys_out,
-                                                             int32_t* __restrict__ vals_out) {
+                                                             int32_t* __restrict__ vals_out, const int32_t* __restrict__ status) {
+    if (SRC == SORT_SRC_SLOTS && status && *status != FC_OK) return;      // refused: neither slots nor offsets may be read any more
     constexpr int NW = RS_THREADS / 64, TILE = RS_THREADS * ITEMS;
     constexpr bool STAGE = MAXB <= 9;
     __shared__ int base[1 << MAXB];            // where this tile's run of each digit starts in the output
@@ -335,7 +339,7 @@ static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, co
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
 #define FC_SCATTER(B) \
     k_sort_scatter<SSRC, ITEMS, FUSED, OPB, B><<<(unsigned)nblk, RS_THREADS, 0, st>>>(SRC == SORT_SRC_RANKS ? j.slots_out : kin, vin, j.offsets, j.num_bags, \
-                                                                                     j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : j.dtot, kout, vout)
+                                                                                     j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : j.dtot, kout, vout, SRC == SORT_SRC_RANKS ? j.status : nullptr)
     if (FUSED || rb <= 9) FC_SCATTER(9);
     else FC_SCATTER(11);
 #undef FC_SCATTER
