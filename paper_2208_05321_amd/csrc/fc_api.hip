@@ -82,8 +82,8 @@ static int reset_state(fc_cache* c, bool warm) {
     c->gather_pending = false;
     for (hipStream_t x : {c->pre, c->pf, c->side}) if (x) FC_HIP(hipStreamSynchronize(x));
     c->next_pending = false; c->last_pst = c->stream;
-    c->planned.valid = false; c->last_index_stream = nullptr; c->move_stream[0] = c->move_stream[1] = nullptr; c->pf_dep = nullptr;
-    c->quiesce_stream = nullptr;
+    c->planned.valid = false; c->last_index_stream = no_stream(); c->move_stream[0] = c->move_stream[1] = no_stream(); c->pf_dep = nullptr;
+    c->quiesce_stream = no_stream();
     c->due = 0;
     c->fetch_timed[0] = c->fetch_timed[1] = false; c->last_copy_buf = -1;
     for (bool& b : c->copy_timed) b = false;
@@ -624,7 +624,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     c->ahead_now = early;
     if (!early) FC_HIP(hipStreamWaitEvent(c->pre, c->ev_s_now, 0));
     // FC_DIRTY_TRACK: which victims of the current batch are in transit is only marked by its row movement
-    if (c->dirty_track && c->move_stream[c->lset]) FC_HIP(hipStreamWaitEvent(c->pre, c->ev_move_done[c->lset], 0));
+    if (c->dirty_track && c->move_stream[c->lset] != no_stream()) FC_HIP(hipStreamWaitEvent(c->pre, c->ev_move_done[c->lset], 0));
     MovePlan mv;
     // The common form: everything that depends on the decisions is enqueued before the host has seen them (the kernels read
     // status and counts from device memory; if the call is refused they touch neither the cache nor a buffer of the caller's), so that neither the GPU waits for the host

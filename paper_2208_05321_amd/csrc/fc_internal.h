@@ -85,6 +85,8 @@ struct SortBufs {
     int64_t dirty[2] = {0, 0};
 };
 constexpr int64_t SORT_STOT_WORDS = 131072;
+// "On no stream yet", where work is remembered by the stream it ran on: a null stream is the caller's default one.
+inline hipStream_t no_stream() { return reinterpret_cast<hipStream_t>(~(uintptr_t)0); }
 // What the row-movement half of a cache_prepare has to do (decided by the index half).
 // evicted-row blocks of the DMA evict transmitter that may be on their way at once
 #ifndef FC_DMA_BLOCKS
@@ -128,8 +130,8 @@ struct fc_cache {
     hipEvent_t ev_assign_done = nullptr;   // index half: every decision taken (all but the slot write-out)
     hipEvent_t ev_emit_done = nullptr;     // index half: the missing rows and where their newest copies are: the early fetch may start
     hipEvent_t ev_quiesce = nullptr;       // transit marks dropped by dma_quiesce on another stream than the index stream
-    hipStream_t quiesce_stream = nullptr;
-    hipStream_t last_index_stream = nullptr;
+    hipStream_t quiesce_stream = fc::no_stream();
+    hipStream_t last_index_stream = fc::no_stream();
     // Events of a plain cache_prepare that only work on a library stream would wait for: each costs its stream about 4 us, so
     // they are recorded (on the caller's stream) when a call that uses such a stream comes along.
     uint32_t due = 0;
@@ -139,7 +141,7 @@ struct fc_cache {
     int32_t* lists[2][7] = {};      // per set: miss_ranks, vslot, fill_slots, fill_src, vrank (unless it lives
                                     // with the DMA block), and with FC_DIRTY_TRACK the dirty victims' ranks and slots
     hipEvent_t ev_move_done[2] = {nullptr, nullptr};   // the row movement that read set k has finished
-    hipStream_t move_stream[2] = {nullptr, nullptr};   // the stream it ran on (nullptr: none yet)
+    hipStream_t move_stream[2] = {fc::no_stream(), fc::no_stream()};   // the stream it ran on
     // cache_plan_next also fetches the planned batch's missing rows ahead of time, on the stream `pf`, into the
     // arrival block of its list set (row j of the block = j-th missing rank); cache_advance then only copies them
     // from HBM into their slots.  Allocated by the first cache_plan_next.

@@ -909,11 +909,11 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     // batches back, possibly on another stream
     use_list_set(c, c->lset ^ 1);
     c->have_lists = false;
-    if (c->move_stream[c->lset] && c->move_stream[c->lset] != st) FC_HIP(hipStreamWaitEvent(st, c->ev_move_done[c->lset], 0));
-    if (c->last_index_stream && c->last_index_stream != st)      // (what ran on `pre` ended with ev_pre_done)
+    if (c->move_stream[c->lset] != no_stream() && c->move_stream[c->lset] != st) FC_HIP(hipStreamWaitEvent(st, c->ev_move_done[c->lset], 0));
+    if (c->last_index_stream != no_stream() && c->last_index_stream != st)      // (what ran on `pre` ended with ev_pre_done)
         FC_HIP(hipStreamWaitEvent(st, c->last_index_stream == c->pre ? c->ev_pre_done : c->ev_index_done, 0));
-    if (c->quiesce_stream && c->quiesce_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_quiesce, 0));
-    c->quiesce_stream = nullptr;
+    if (c->quiesce_stream != no_stream() && c->quiesce_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_quiesce, 0));
+    c->quiesce_stream = no_stream();
     const int32_t ticket = c->ticket = (c->ticket + 1) & 0x7fffffff;
     const int protect_prev = lookahead ? 1 : 0;
     int transit_base = -1, buf = 0;
