@@ -84,6 +84,7 @@ static int reset_state(fc_cache* c, bool warm) {
     c->next_pending = false; c->last_pst = c->stream;
     c->planned.valid = false; c->last_index_stream = no_stream(); c->move_stream[0] = c->move_stream[1] = no_stream(); c->pf_dep = nullptr;
     c->quiesce_stream = no_stream();
+    c->vrank_kept = false;
     c->due = 0;
     c->fetch_timed[0] = c->fetch_timed[1] = false; c->last_copy_buf = -1;
     for (bool& b : c->copy_timed) b = false;

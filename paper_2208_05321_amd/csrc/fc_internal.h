@@ -235,6 +235,7 @@ struct fc_cache {
     int32_t* vrank_buf[fc::DMA_BLOCKS] = {};      // device lists of the evicted ranks, one per block
     int64_t blk_rows[fc::DMA_BLOCKS] = {};        // rows whose transit marks are still set, per block
     hipEvent_t ev_d2h[fc::DMA_BLOCKS] = {};
+    bool vrank_kept = false;                      // the latest row movement stored its victims by kernel: its rank list has no block of its own
     hipEvent_t pf_dep = nullptr;                  // what the next early fetch of missing rows has to wait for
     // DMA miss path (FC_MISS_DMA): cache_plan_next's missing rows are gathered by host threads into a pinned block and
     // copied into the arrival block by hipMemcpyAsync on the fetch stream, instead of being read by a kernel.

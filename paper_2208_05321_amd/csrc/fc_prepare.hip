@@ -926,6 +926,8 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         landed = c->blk_rows[buf];            // cleared by k_rank_count below, before anything reads rank_slot or rewrites the list
         c->blk_rows[buf] = 0;
         if (!c->dirty_track) c->vrank = c->vrank_buf[buf];
+        // after more victims than a block holds no block was handed over, so this is the list that movement reads
+        if (c->vrank_kept && c->move_stream[c->lset ^ 1] != st) FC_HIP(hipStreamWaitEvent(st, c->ev_move_done[c->lset ^ 1], 0));
         transit_base = (int)(buf * c->staging_rows);
     }
     const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
@@ -1166,6 +1168,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     if (last_rows < 0) { FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0)); c->evict_pending = false; }
     FC_HIP(hipGetLastError());
     FC_TRY(move_done(c, st, ahead));
+    c->vrank_kept = c->dma_evict && !c->dirty_track && !dma_path;
     // The next early fetch reads evicted-row blocks gathered up to now and host rows stored up to now: with the DMA
     // transmitter the gather just enqueued is the last thing it needs (host rows still on their way carry transit
     // marks); after a kernel store it has to wait for the whole movement.

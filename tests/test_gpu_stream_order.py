@@ -15,7 +15,8 @@ def stream_of(kind):
 @pytest.mark.parametrize("dma", [False, True])
 def test_lists_outlive_the_row_movement_that_reads_them(kind, dma, monkeypatch):
     """Row movements of milliseconds (more rows than the block holds, so they all cross the link at cache_advance), plans of
-    100 us: the lists that a movement reads are rewritten two plans later."""
+    100 us: the lists that a movement reads are rewritten two plans later, the victims' ranks of a cache with blocks (which are
+    kept per block, and no block is handed over here) by the very next one."""
     import torch
     from paper_2208_05321_amd import FreqCache
     monkeypatch.setenv("FC_AHEAD_MISS_PCT", "1000000")          # always ahead of the caller's stream
