@@ -1142,7 +1142,8 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
         else if (c->dma_evict && mv.need <= c->staging_rows) { FC_TRY(evict_dma(c, need, mv.buf)); dma_path = true; }
         else {
             // more victims than one block holds (or no DMA transmitter): store by kernel, block by block; the
-            // block buffer is reused from its start, so nothing may be in transit in it any more
+            // block buffer is reused from its start, so nothing may be in transit in it any more: every missing row, also one
+            // that was in transit when the batch was indexed, comes from the host table below
             if (!arrival_waited) { FC_HIP(hipStreamWaitEvent(st, c->arrived_by[c->lset], 0)); arrival_waited = true; }
             FC_TRY(dma_quiesce(c, st));
             FC_TRY(evict_direct(c, need, &last_off, &last_rows));
@@ -1161,7 +1162,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
             // gathered by earlier batches (this stream has run those gathers)
             if (via_dma && c->dma_evict) FC_TRY(launch_fill_rows(c, st, M, nullptr, 0, 0, true));
         }
-        else if (c->dma_evict) FC_TRY(launch_fill_rows(c, st, M));
+        else if (dma_path) FC_TRY(launch_fill_rows(c, st, M));
         else FC_TRY(launch_copy_rows(c, st, P_MISS_FILL, c->cache, c->fill_slots, c->C, c->host_dev, c->miss_ranks, c->N, M, c->fill_blocks));
     }
     if (last_rows > 0) FC_TRY(store_block(c, last_off, last_rows));
