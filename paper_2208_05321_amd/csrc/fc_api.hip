@@ -481,8 +481,6 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     if (rc == FC_OK) rc = index_assign(c, st, run, -1);
     if (rc == FC_OK) {
         FC_HIP(hipEventRecord(c->ev_assign_done, st));
-        c->due &= ~DUE_INDEX;
-        c->last_index_stream = st;
         c->aux = st;
         c->planned.arrived = false;
         fetched = fetch_early(c, -1);

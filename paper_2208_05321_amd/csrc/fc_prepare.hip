@@ -1012,6 +1012,10 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
     if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
+    // whatever the decision is: the host hears of a refusal while workgroups of the emitting kernel still clear marks and read the
+    // counts and the error word, which the next batch's first kernels write
+    if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
+    c->last_index_stream = st;
     run->ticket = ticket; run->n = n; run->num_bags = num_bags;
     run->small = small; run->small_slots = small_slots; run->bytes = bytes; run->buf = buf; run->transit_base = transit_base;
     return FC_OK;
@@ -1071,8 +1075,6 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     if (!defer_slots) {
         if (!run.small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
     }
-    if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
-    c->last_index_stream = st;
     c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     return FC_OK;
 }

@@ -80,3 +80,46 @@ def test_rows_in_transit_when_a_batch_has_more_victims_than_a_block(planned):
     gpu.flush()
     assert np.array_equal(host, np.broadcast_to(np.arange(rows, dtype=np.float32)[:, None], host.shape))
     gpu.close()
+
+
+@pytest.mark.parametrize("kind", ["own", "default"])
+@pytest.mark.parametrize("dma", [False, True])
+@pytest.mark.parametrize("bags", [5000, 100_000])              # bit marks, byte marks
+def test_plans_right_behind_refused_plain_calls(kind, dma, bags, monkeypatch):
+    """A plain call that is refused returns while its last kernel still runs: it clears the marks and reads the counts."""
+    import torch
+    from oracle import Oracle
+    from paper_2208_05321_amd import FreqCache, FreqCacheError
+    from tests.parity import compare_prepare
+    from tests.tiny_workload import TinyWorkload
+    monkeypatch.setenv("FC_AHEAD_MISS_PCT", "1000000")
+    rows = 3_000_000
+    w = TinyWorkload(num_rows=rows, dim=4, cache_rows=90_000, seed=bags, multi_hot=False, bags=bags, distinct_cap=80_000)
+    st = stream_of(kind)
+    with torch.cuda.stream(st):
+        gpu = FreqCache(rows, 4, w.cache_rows, w.freq_rank, dma_evict=dma, inputs_ready=True)
+        host = gpu.host_weight()
+        w.host_table(out=host)
+        gpu.warm()
+        gpu.reserve(200_000, pipelined=True)
+        orc = Oracle(w.freq_rank, host.copy(), w.cache_rows, warm=True)
+        good = [w.batch(t) for t in range(6)]
+        on_gpu = [[torch.from_numpy(a).cuda() for a in b] for b in good]
+        far = on_gpu[0][0].clone()
+        far[7] = rows
+        much = torch.arange(100_000, device="cuda") * 29
+        much_off = torch.arange(100_001, device="cuda")
+        torch.cuda.synchronize()
+        for t in range(6):
+            for ids, off, name in ((far, on_gpu[0][1], "ID_OUT_OF_RANGE"), (much, much_off, "BATCH_EXCEEDS_CACHE")):
+                with pytest.raises(FreqCacheError) as e:
+                    gpu.prepare(ids, off)
+                assert e.value.name == name
+                if name == ("ID_OUT_OF_RANGE" if t % 2 else "BATCH_EXCEEDS_CACHE"):
+                    break
+            slots = gpu.plan_next(*on_gpu[t])
+            gpu.advance()
+            compare_prepare(gpu, orc, slots.cpu().numpy(), orc.prepare(*good[t]), t)
+        gpu.check()
+        gpu.close()
+        orc.close()
