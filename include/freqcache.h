@@ -167,7 +167,7 @@ int cache_create(int64_t num_rows, int32_t dim, int64_t cache_rows, const int32_
 
 /* Allocate now everything the per-batch calls would otherwise allocate when they first meet a batch of that size:
  * the per-id rank buffer of cache_prepare and its byte marks (num_rows bytes, if max_ids is at least num_rows / 32), the
- * sort scratch and partial-sum rows of embedding_bag_bwd_sgd for batches of up to max_ids lookups (three sort sets of 16 * max_ids bytes), and, if pipelined != 0, the two arrival blocks of
+ * sort scratch and partial-sum rows of embedding_bag_bwd_sgd for batches of up to max_ids lookups (three sort sets of 16 * max_ids bytes), and, if pipelined != 0 (a handle that will plan ahead), the two arrival blocks of
  * cache_plan_next (staging_rows * dim * 4 bytes each).  The transmitter's memory stays bounded by staging_rows
  * (Section 4.3); this call only moves the allocations out of the training loop.  Optional: without it (or for a larger
  * batch later) the buffers grow on demand, which costs a hipMalloc and a device-wide synchronisation in that step.
@@ -219,7 +219,8 @@ int cache_prepare_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int
  * cache_prepare / cache_advance call, not as of this call.  ids_dev / offsets_dev must therefore be complete by then (written by work
  * enqueued on the caller's stream before that call, or finished altogether) and stay untouched until cache_advance;
  * slots_dev must not be the buffer the current batch's forward / backward read.  cache_copy_rows / cache_host_weight
- * reflect the planned batch only after cache_advance.
+ * reflect the planned batch only after cache_advance.  (The first call of this kind on a handle, unless cache_reserve has announced
+ * it with pipelined != 0, is ordered behind everything on the caller's stream instead: until then plain calls mark no place there.)
  * Usage:  cache_prepare(batch 0);  loop { fwd(t); bwd(t); cache_plan_next(batch t+1, slots_next); cache_advance(); }
  * (forward / backward are asynchronous and best enqueued first, since this call waits on the host for its planning
  * kernels; those do not wait for them.  Calling it before them is equally correct.)

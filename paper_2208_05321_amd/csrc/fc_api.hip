@@ -554,6 +554,7 @@ int cache_reserve(fc_cache* c, int64_t max_ids, int32_t pipelined) {
     FC_TRY(ensure_rbuf(c, max_ids));
     FC_TRY(reserve_bwd(c, max_ids));
     (void)mark_bytes(c, max_ids);      // without room for them the marks stay bits
+    c->plans_ahead |= pipelined != 0;
     if (pipelined && !(c->flags & FC_TRANSMIT_STAGED))
         for (int k = 0; k < 2; ++k) if (!ensure_arrival_block(c, k)) return FC_ERR_OOM_DEVICE;
     return FC_OK;
@@ -573,8 +574,9 @@ int cache_prepare(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_t*
                   int32_t* slots_dev) {
     if (!c) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
+    if (c->plans_ahead) { FC_HIP(hipEventRecord(c->ev_s_now, c->stream)); c->due &= ~DUE_S_NOW; }
+    else c->due |= DUE_S_NOW;
     FC_TRY(adopt_next(c));
-    c->due |= DUE_S_NOW;
     const int rc = prepare_impl(c, c->stream, false, ids_dev, n, offsets_dev, num_bags, slots_dev);
     if (rc == FC_OK) c->cur_ticket = c->pending_ticket = c->ticket;
     return rc;
@@ -584,6 +586,7 @@ int cache_prepare_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int
                        int32_t* slots_dev) {
     if (!c) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
+    c->plans_ahead = true;
     FC_TRY(record_due_events(c));
     // everything the caller has enqueued so far (the backward pass of the batch before the current one, and the
     // input buffers of this call) is complete before this call's row movement, or before all of it when the last
@@ -605,6 +608,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     if (!c || (c->flags & FC_TRANSMIT_STAGED)) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
     if (c->planned.valid) FC_TRY(cache_advance(c));
+    c->plans_ahead = true;
     FC_TRY(record_due_events(c));
     // The index half touches no rows, so it need not wait for the row movement, forward or backward work the caller
     // enqueued since the last cache_prepare / cache_advance: it is ordered behind the caller's stream as of the entry

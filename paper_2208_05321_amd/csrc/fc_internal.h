@@ -133,8 +133,11 @@ struct fc_cache {
     hipStream_t quiesce_stream = fc::no_stream();
     hipStream_t last_index_stream = fc::no_stream();
     // Events of a plain cache_prepare that only work on a library stream would wait for: each costs its stream about 4 us, so
-    // they are recorded (on the caller's stream) when a call that uses such a stream comes along.
+    // they are recorded (on the caller's stream) when a call that uses such a stream comes along.  They then stand for more than
+    // they should, forward and backward of the current batch included; a handle that has made such calls, or announced them
+    // (cache_reserve), records them in their place.
     uint32_t due = 0;
+    bool plans_ahead = false;
     // The lists an index half writes and its row-movement half reads exist twice, so that the index half of the next
     // batch can run while the rows of the current one still move: lset = the set of the latest index half.
     int lset = 0;

@@ -1075,12 +1075,16 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     if (!defer_slots) {
         if (!run.small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
     }
+    if (plain && c->plans_ahead) {
+        FC_HIP(hipEventRecord(c->ev_index_done, st));
+        c->due &= ~DUE_INDEX;
+    }
     c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     return FC_OK;
 }
 
 static int move_done(fc_cache* c, hipStream_t st, bool ahead) {
-    if (st == c->stream && !ahead) c->due |= DUE_MOVE << c->lset;
+    if (st == c->stream && !ahead && !c->plans_ahead) c->due |= DUE_MOVE << c->lset;
     else {
         FC_HIP(hipEventRecord(c->ev_move_done[c->lset], st));
         c->due &= ~(DUE_MOVE << c->lset);
