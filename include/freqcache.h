@@ -157,8 +157,8 @@ enum {
  *                         scan kernel); FC_SORT_FUSED=0 keeps the scan kernel
  *   FC_FETCH_CU_MASK      experiment: number of compute units the early fetch's stream may use (default: all)
  *   FC_MARK_IPT           ids per thread of the marking kernel that sets bits (2)
- *   FC_PLAN_FOLD_TILES    most tiles of 32768 ranks for which the emitting kernel's workgroups plan for themselves (1024); 0: a
- *                         planning kernel of its own always
+ *   FC_PLAN_FOLD_TILES    most tiles of 32768 ranks for which the emitting kernel's workgroups plan for themselves, eight to a tile
+ *                         (1024); 0: always a planning kernel of its own and one workgroup to a tile
  *   FC_TUNE_REPORT        if set, cache_destroy prints where the early-fetch workgroup count settled
  *   FC_TIMELINE           file that receives, whenever profiling totals are collected, one line "name start_us end_us"
  *                         per timed kernel or copy (read at every collection, not here) */

@@ -17,7 +17,7 @@ constexpr int WAVE = 64;
 constexpr int RT_THREADS = 256;
 constexpr int RT_WORDS = RT_THREADS * 4;
 constexpr int SUB_TILES = 8;                      // each tile's counts are also kept per eighth (4096 ranks)
-constexpr int PLAN_FOLD_TILES = 1024;             // up to this many tiles every workgroup of the emitting kernel plans for itself
+constexpr int PLAN_FOLD_TILES = 1024;             // up to this many tiles the emitting kernel plans for itself, with SUB_TILES workgroups to a tile
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size
 constexpr int64_t MARKB_ROWS_PER_ID = 32;         // byte marks up to this many rows per id of the batch

@@ -396,13 +396,13 @@ constexpr int FREE_TILE = 1024;
 //      by all threads side by side, all random reads of a thread before the first is waited for.
 //      SPLIT workgroups share a tile.  Popularity falls off as a power, so the tiles just beyond the cached ranks hold ten
 //      times the average number of missing and evicted ranks (13,000 of each in one tile at 142 k slots of 9.4 M rows), and
-//      with a tile to a workgroup, one of those was the kernel's duration: 8 to a tile up to EMIT_SPLIT_TILES tiles; beyond,
-//      tiles are many and ranks spread thinner, and 8 times the workgroups take longer than the fullest tile.
+//      with a tile to a workgroup, one of those was the kernel's duration: 8 to a tile where every workgroup plans for itself;
+//      beyond, tiles are many and ranks spread thinner, and 8 times the workgroups take longer than the fullest tile.
 //      Measured (us by events, k_rank_plan + one workgroup per tile with the bits handled one by one -> this): 852 k ids, 9.4 M rows
 //      8.2 + 32 -> 16; 426 k ids, 10 M rows 7.5 + 20 -> 15 (plain), 10 + 29 -> 18 (pipelined).
 // ---------------------------------------------------------------------------------------------------------
 constexpr int EMIT_LIST = 4096;                // ranks of either kind listed at a time
-constexpr int EMIT_SPLIT = SUB_TILES, EMIT_SPLIT_TILES = 1024;
+constexpr int EMIT_SPLIT = SUB_TILES;
 
 template <int WORDS> struct Bits { uint32_t w[WORDS]; };          // the bits of a thread: 16 of one word, or four words
 __device__ __forceinline__ Bits<1> load_bits(const uint32_t* p, size_t i, Bits<1>) {
@@ -417,7 +417,7 @@ __device__ __forceinline__ void store_bits(uint32_t* p, size_t i, const Bits<4>&
     reinterpret_cast<uint4*>(p)[i] = make_uint4(b.w[0], b.w[1], b.w[2], b.w[3]);
 }
 
-template <int SPLIT, bool FOLD>
+template <int SPLIT>
 __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint32_t* rbits, uint32_t* pbits, PlanArgs a,
                                                           const int4* __restrict__ tile_plan,
                                                           int32_t* __restrict__ miss_ranks, int32_t* __restrict__ vrank,
@@ -428,6 +428,7 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint3
     static_assert(SPLIT == 1 || (SPLIT == 8 && RT_WORDS == 4 * RT_THREADS), "a thread holds 16 bits or four words");
     constexpr int WORDS = SPLIT == 1 ? 4 : 1;
     constexpr int RANKS = SPLIT == 1 ? 128 : 16;           // per thread
+    constexpr bool FOLD = SPLIT > 1;                       // no k_rank_plan has run
     using B = Bits<WORDS>;
     __shared__ int lds[RT_THREADS / 64];
     __shared__ uint16_t mlist[EMIT_LIST], vlist[EMIT_LIST];
@@ -998,15 +999,12 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
             c->evict_pending = false;
         }
         ProfScope ps(c, P_RANK_EMIT, st);
-#define FC_EMIT(S, F) \
-        k_rank_emit<S, F><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->tile_plan, \
+#define FC_EMIT(S) \
+        k_rank_emit<S><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->tile_plan, \
                                                                        c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, \
                                                                        transit, (int)c->staging_rows, \
                                                                        c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0)
-        const bool split = c->NB <= EMIT_SPLIT_TILES;
-        if (fold) { if (split) FC_EMIT(EMIT_SPLIT, true); else FC_EMIT(1, true); }
-        else if (split) FC_EMIT(EMIT_SPLIT, false);
-        else FC_EMIT(1, false);
+        if (fold) FC_EMIT(EMIT_SPLIT); else FC_EMIT(1);
 #undef FC_EMIT
     }
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so

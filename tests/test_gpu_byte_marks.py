@@ -46,8 +46,9 @@ def test_both_kinds_of_marks_in_turn(rows):
 
 @pytest.mark.parametrize("fold", ["0", "1024"])
 def test_dense_tiles_and_a_separate_plan(monkeypatch, fold):
-    """A cold cache filled by a batch that misses whole tiles (more ranks of one tile than a list in LDS holds), then
-    evictions of as many; the planning step in a kernel of its own and inside the emitting kernel."""
+    """A cold cache filled by a batch that misses half of every tile, then evictions of as many.  0: the planning step in a
+    kernel of its own and a tile to a workgroup (15,000 ranks of one tile in a list of 4096, round by round); 1024: planned
+    inside the emitting kernel, eight workgroups to a tile."""
     monkeypatch.setenv("FC_PLAN_FOLD_TILES", fold)
     w = TinyWorkload(num_rows=70_000, dim=4, cache_rows=34_000, seed=9, multi_hot=False, bags=60_000, distinct_cap=33_000)
     run_parity(w, 4, warm=False)
