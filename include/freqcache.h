@@ -159,6 +159,7 @@ enum {
  *   FC_MARK_IPT           ids per thread of the marking kernel that sets bits (2)
  *   FC_PLAN_FOLD_TILES    most tiles of 32768 ranks for which the emitting kernel's workgroups plan for themselves, eight to a tile
  *                         (1024); 0: always a planning kernel of its own and one workgroup to a tile
+ *   FC_SMALL_INDEX        0: small batches (up to 4096 ids, 2^20 rows, 2^16 slots) are indexed by the general kernels, too
  *   FC_TUNE_REPORT        if set, cache_destroy prints where the early-fetch workgroup count settled
  *   FC_TIMELINE           file that receives, whenever profiling totals are collected, one line "name start_us end_us"
  *                         per timed kernel or copy (read at every collection, not here) */

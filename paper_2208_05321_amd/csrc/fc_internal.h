@@ -198,6 +198,7 @@ struct fc_cache {
     int32_t* plan[2] = {nullptr, nullptr};   // per list set, PL_*: the decision as kernels enqueued behind it read it
     int4* tile_plan = nullptr;      // [NB] more than PLAN_FOLD_TILES tiles: missing rows before a tile, evictable rows above it
     int plan_fold_tiles = fc::PLAN_FOLD_TILES;   // (tuning: FC_PLAN_FOLD_TILES)
+    bool small_index = true;        // one workgroup indexes a small batch (tuning: FC_SMALL_INDEX=0)
     int64_t nfree = 0;              // empty slots
     int err_set = 0;                // which of the two error words the next call uses
     int32_t* miss_ranks = nullptr;  // [C]  these five point into lists[lset] (vrank into vrank_buf with FC_EVICT_DMA)

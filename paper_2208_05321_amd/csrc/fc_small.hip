@@ -307,7 +307,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
 }
 
 bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags) {
-    return n <= SMALL_MAX_IDS && num_bags <= 4 * SMALL_MAX_IDS && c->NB * RT_WORDS <= SMALL_MAX_WORDS && c->C <= SMALL_MAX_SLOTS;
+    return c->small_index && n <= SMALL_MAX_IDS && num_bags <= 4 * SMALL_MAX_IDS && c->NB * RT_WORDS <= SMALL_MAX_WORDS && c->C <= SMALL_MAX_SLOTS;
 }
 
 int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
