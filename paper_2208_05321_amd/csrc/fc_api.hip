@@ -4,6 +4,7 @@
 
 #include <stdio.h>
 
+#include <chrono>
 #include <new>
 #include <stdlib.h>
 #include <string.h>
@@ -374,21 +375,23 @@ static float elapsed_us(hipEvent_t a, hipEvent_t b) {
 
 // One step of the controller described at fc_cache::tune_early: the fetch that last used list set k against the newest
 // block copy that is done with (no copy at all: the fetch has the link to itself and may take what it can use).
-static void tune_fetch_grid(fc_cache* c, int k) {
+// landed: the newest copy has.
+static void tune_fetch_grid(fc_cache* c, int k, bool landed) {
     if (!c->fetch_timed[k]) return;
     const float f_us = elapsed_us(c->ev_fetch_a[k], c->ev_fetch_b[k]);
     if (f_us <= 0.f) return;
     float d_us = -1.f;
-    // Only blocks that have reached the host table are looked at: while a scatter thread waits for ev_d2h, a query of that event
+    // Only copies that are known to have landed are looked at: while a scatter thread waits for ev_d2h, a query of that event
     // waits with it, i.e. until the copy has landed and the thread has woken up (config 4: the fetch and the sort left the host
     // 280 us late, 0.57 -> 0.67 ms a step).
     if (c->last_copy_buf >= 0) {
         const uint64_t done = pool_completed(c);
         for (int i = 0; i < DMA_BLOCKS && d_us <= 0.f; ++i) {
             const int b = (c->last_copy_buf - i + DMA_BLOCKS) % DMA_BLOCKS;
-            if (c->copy_timed[b] && c->copy_seq[b] <= done) d_us = elapsed_us(c->ev_copy_a[b], c->ev_d2h[b]);
+            if (c->copy_timed[b] && ((landed && i == 0) || c->copy_seq[b] <= done)) d_us = elapsed_us(c->ev_copy_a[b], c->ev_d2h[b]);
         }
     }
+    if (d_us > 0.f) c->copy_us = d_us;
     const float r = d_us > 0.f ? f_us / d_us : 2.f;
     c->tune_ratio = c->tune_ratio <= 0.f ? r : 0.75f * c->tune_ratio + 0.25f * r;
     if (++c->tune_count < 6) return;
@@ -407,6 +410,24 @@ static bool ensure_arrival_block(fc_cache* c, int k) {
     return true;
 }
 
+// Several handles in turn (tables, or states of one) let the host get several steps ahead of the link: as many fetches and block
+// copies are then in flight at once and slow each other down.  A block of this handle that was handed over a while ago, measured by
+// how long its copy takes, and still has not landed says so, and the host waits for it.  One handle comes back within 70 to 100 us
+// and must not wait: its fetch would set out only when its own last block has left.  (A handle that runs ahead of the caller's stream
+// never waits: there HBM binds.)  us a step, never waiting / this / always waiting: three handles in turn, 35 k rows of 128 columns
+// 417-440 and for hundreds of steps 1100 / 388-399 / 391-405, 12 k of 256 columns 280-307 and 600-880 / 262-290 / 305-344; one handle,
+// 35 k rows of 128 columns 498-526 / 501-517 / 558-568, 32 columns 190-197 / 193-197 / 252-260.
+static int wait_if_far_ahead(fc_cache* c, bool* landed) {
+    const int b = c->last_copy_buf;
+    *landed = false;
+    if (c->ahead_now || b < 0 || !c->copy_timed[b]) return FC_OK;
+    const float ago = std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - c->copy_at).count();
+    if (ago < FAR_AHEAD_US || ago < 0.5f * c->copy_us) return FC_OK;
+    FC_HIP(hipEventSynchronize(c->ev_d2h[b]));
+    *landed = true;
+    return FC_OK;
+}
+
 // cache_plan_next: the planned batch's missing rows into the arrival block of its list set, on the stream pf
 // M < 0: the host does not know the number of rows yet, the kernel reads it (DMA evict transmitter, rows fetched by kernel)
 static int fetch_early(fc_cache* c, int64_t M) {
@@ -421,7 +442,9 @@ static int fetch_early(fc_cache* c, int64_t M) {
         c->planned.arrived = true;
         return FC_OK;
     }
-    if (c->tune_early) tune_fetch_grid(c, k);
+    bool landed;
+    FC_TRY(wait_if_far_ahead(c, &landed));
+    if (c->tune_early) tune_fetch_grid(c, k, landed);
     FC_HIP(hipStreamWaitEvent(c->pf, c->ev_emit_done, 0));       // which rows are missing and where their newest copies are
     if (c->pf_dep) FC_HIP(hipStreamWaitEvent(c->pf, c->pf_dep, 0));
     if (c->dma_evict) {

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdio.h>
+#include <chrono>
 #include <string>
 #include <vector>
 
@@ -20,6 +21,7 @@ constexpr int SUB_TILES = 8;                      // each tile's counts are also
 constexpr int PLAN_FOLD_TILES = 1024;             // up to this many tiles the emitting kernel plans for itself, with SUB_TILES workgroups to a tile
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size
+constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead
 constexpr int64_t MARKB_ROWS_PER_ID = 32;         // byte marks up to this many rows per id of the batch
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;
@@ -263,6 +265,8 @@ struct fc_cache {
     hipEvent_t ev_copy_a[fc::DMA_BLOCKS] = {};            // (the copy's end: ev_d2h)
     bool fetch_timed[2] = {false, false}, copy_timed[fc::DMA_BLOCKS] = {};
     uint64_t copy_seq[fc::DMA_BLOCKS] = {};               // number of the block the copy carried
+    std::chrono::steady_clock::time_point copy_at;        // when the newest block was handed over
+    float copy_us = 0.f;                                  // how long the newest copy looked at took
     int last_copy_buf = -1;
     float tune_ratio = 0.f;
     int tune_count = 0;

@@ -818,6 +818,7 @@ static int evict_dma(fc_cache* c, int64_t need, int buf) {
     c->vrank_at[buf] = together ? reinterpret_cast<const int32_t*>(c->blk_pin[buf] + (size_t)need * c->D) : c->vrank_pin[buf];
     if (c->ev_copy_a[buf]) { c->copy_timed[buf] = true; c->last_copy_buf = buf; }
     c->blk_rows[buf] = need;
+    c->copy_at = std::chrono::steady_clock::now();
     c->copy_seq[buf] = pool_publish(c, buf, need);
     return FC_OK;
 }

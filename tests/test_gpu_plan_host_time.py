@@ -9,11 +9,13 @@ pytestmark = pytest.mark.gpu
 IDS, CACHE, DIM = 35_000, 40_000, 1024
 
 
-def test_a_block_on_its_way_does_not_hold_up_the_next_plan():
+def test_a_block_on_its_way_does_not_hold_up_the_next_plan(monkeypatch):
     """The controller of the early fetch reads the durations of finished block copies; asking about the one that the scatter
-    threads are still waiting for makes the caller wait with them."""
+    threads are still waiting for makes the caller wait with them.  (On a handle that runs ahead of the caller's stream; one that
+    does not may wait for a block, but only for an old one.)"""
     import torch
     from paper_2208_05321_amd import FreqCache
+    monkeypatch.setenv("FC_AHEAD_MISS_PCT", "1000000")
     rows = 4 * IDS
     gpu = FreqCache(rows, DIM, CACHE, np.arange(rows, dtype=np.int32), dma_evict=True, inputs_ready=True)
     gpu.host_weight()[:] = 1.0
