@@ -411,17 +411,18 @@ static bool ensure_arrival_block(fc_cache* c, int k) {
 }
 
 // Several handles in turn (tables, or states of one) let the host get several steps ahead of the link: as many fetches and block
-// copies are then in flight at once and slow each other down.  A block of this handle that was handed over a while ago, measured by
-// how long its copy takes, and still has not landed says so, and the host waits for it.  One handle comes back within 70 to 100 us
-// and must not wait: its fetch would set out only when its own last block has left.  (A handle that runs ahead of the caller's stream
-// never waits: there HBM binds.)  us a step, never waiting / this / always waiting: three handles in turn, 35 k rows of 128 columns
-// 417-440 and for hundreds of steps 1100 / 388-399 / 391-405, 12 k of 256 columns 280-307 and 600-880 / 262-290 / 305-344; one handle,
-// 35 k rows of 128 columns 498-526 / 501-517 / 558-568, 32 columns 190-197 / 193-197 / 252-260.
+// copies are then in flight at once and slow each other down.  A block of this handle that had been handed over a while, measured by
+// how long its copy takes, when the call came and still has not landed says so, and the host waits for it.  One handle comes back
+// within 70 to 100 us and must not wait: its fetch would set out only when its own last block has left.  (A handle that runs ahead
+// of the caller's stream never waits: there HBM binds.)  us a step, never waiting / this / always waiting: three handles in turn,
+// 35 k rows of 128 columns 417-440 and for hundreds of steps 1100 / 388-399 / 391-405, 12 k of 256 columns 280-307 and 600-880 /
+// 258-290 / 305-344; one handle, 35 k rows of 128 columns 498-526 / 501-517 / 558-568, 49 k of 128 (1.7 M lookups) - / 784-791 / 918,
+// 32 columns 190-197 / 190-197 / 252-260.
 static int wait_if_far_ahead(fc_cache* c, bool* landed) {
     const int b = c->last_copy_buf;
     *landed = false;
     if (c->ahead_now || b < 0 || !c->copy_timed[b]) return FC_OK;
-    const float ago = std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - c->copy_at).count();
+    const float ago = std::chrono::duration<float, std::micro>(c->plan_at - c->copy_at).count();
     if (ago < FAR_AHEAD_US || ago < 0.5f * c->copy_us) return FC_OK;
     FC_HIP(hipEventSynchronize(c->ev_d2h[b]));
     *landed = true;
@@ -631,6 +632,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
                     int32_t* slots_dev) {
     if (!c || (c->flags & FC_TRANSMIT_STAGED)) return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
+    c->plan_at = std::chrono::steady_clock::now();
     if (c->planned.valid) FC_TRY(cache_advance(c));
     c->plans_ahead = true;
     FC_TRY(record_due_events(c));

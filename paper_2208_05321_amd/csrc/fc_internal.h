@@ -265,7 +265,7 @@ struct fc_cache {
     hipEvent_t ev_copy_a[fc::DMA_BLOCKS] = {};            // (the copy's end: ev_d2h)
     bool fetch_timed[2] = {false, false}, copy_timed[fc::DMA_BLOCKS] = {};
     uint64_t copy_seq[fc::DMA_BLOCKS] = {};               // number of the block the copy carried
-    std::chrono::steady_clock::time_point copy_at;        // when the newest block was handed over
+    std::chrono::steady_clock::time_point copy_at, plan_at;   // when the newest block was handed over, cache_plan_next called
     float copy_us = 0.f;                                  // how long the newest copy looked at took
     int last_copy_buf = -1;
     float tune_ratio = 0.f;
