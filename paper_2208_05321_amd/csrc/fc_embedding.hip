@@ -487,26 +487,19 @@ static int ensure_part(fc_cache* c, int64_t groups) {
     return FC_OK;
 }
 
-// The sort of a batch of n lookups by slot, as far as the handle and n decide it.
-static SortJob slot_job(const fc_cache* c, int64_t n) {
-    int bits = 1;
-    while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
-    SortJob j;
-    j.src = SORT_SRC_SLOTS; j.n = (int)n; j.limit = (int)c->C; j.bits = bits;
-    j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
-    return j;
-}
-
 // Stable sort of the batch's (slot, bag) pairs by slot on stream `st`; *kres / *vres receive the sorted arrays.
 static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* slots, int64_t n, const int64_t* offsets,
                       int64_t num_bags, const int32_t** kres, const int32_t** vres, int32_t* slots_out = nullptr,
                       hipStream_t tail = nullptr, hipStream_t* last = nullptr) {
-    SortJob j = slot_job(c, n);
-    j.keys_in = slots; j.offsets = offsets; j.num_bags = (int)num_bags;
+    int bits = 1;
+    while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
+    SortJob j;
+    j.src = SORT_SRC_SLOTS; j.keys_in = slots; j.offsets = offsets; j.num_bags = (int)num_bags; j.n = (int)n;
     if (slots_out) { j.src = SORT_SRC_RANKS; j.keys_in = c->rbuf; j.rank_slot = c->rank_slot; j.slots_out = slots_out; j.status = &c->plan[c->lset][PL_STATUS]; }
-    j.flags = &c->ctl->async_flags;
+    j.limit = (int)c->C; j.bits = bits; j.flags = &c->ctl->async_flags;
     j.one_per_bag = c->last_one_per_bag;      // sort_pairs serves the batch the last index half looked at
     j.tail_stream = tail; j.tail_event = c->ev_sort_tail; j.last_stream = last;
+    j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
     j.prof = c;
     return sort_in(j, sb, st, kres, vres);
 }
@@ -532,9 +525,8 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     if (c->rec[k ^ 1].valid && c->rec[k ^ 1].ticket != c->cur_ticket) c->rec[k ^ 1].valid = false;
     if (!c->presort || n <= 0 || num_bags <= 0) return slots_out ? FC_ERR_INVALID_ARG : FC_OK;   // the caller then writes the slots out itself
     FC_TRY(ensure_sort(c->sb[k], n));
-    // A small batch's sort is one short kernel: on the caller's stream it costs 8 us, on another one two waits of 10 us.  (With too
-    // many slots for that kernel it is six launches: those stay beside the row movement.)
-    const hipStream_t aux = c->pst == c->stream && n <= SMALL_MAX_IDS && sort_small_fits(slot_job(c, n)) ? c->stream : c->aux;
+    // A small batch's sort is one short kernel: on the caller's stream it costs 8 us, on another one two waits of 10 us.
+    const hipStream_t aux = c->pst == c->stream && n <= SMALL_MAX_IDS ? c->stream : c->aux;
     if (c->pst != aux) {
         FC_HIP(hipEventRecord(c->ev_slots, c->pst));
         FC_HIP(hipStreamWaitEvent(aux, c->ev_slots, 0));
@@ -574,9 +566,12 @@ static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n,
     int rthreads; int64_t rblocks; size_t lds;
     bwd_geometry(c, n, &rthreads, &rblocks, &lds);
     if (!kin) {
-        SortJob j = slot_job(c, n);
-        j.keys_in = slots; j.offsets = offsets; j.num_bags = (int)num_bags;
-        j.flags = &c->ctl->async_flags;
+        int bits = 1;
+        while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
+        SortJob j;
+        j.src = SORT_SRC_SLOTS; j.keys_in = slots; j.offsets = offsets; j.num_bags = (int)num_bags; j.n = (int)n;
+        j.limit = (int)c->C; j.bits = bits; j.flags = &c->ctl->async_flags;
+        j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
         j.prof = prof;
         FC_TRY(sort_in(j, sb, st, &kin, &vin));      // the scratch of the entry point that allocates nothing has no supertile tables: scan kernels there
     }

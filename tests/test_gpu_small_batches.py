@@ -25,32 +25,3 @@ def test_sort_digit_widths(cache, bags):
     """Batches past the one-workgroup sort with digits of 1 to 9 bits and ragged last tiles, one and several supertiles."""
     w = TinyWorkload(num_rows=700, dim=4, cache_rows=cache, seed=cache, multi_hot=False, bags=bags, distinct_cap=cache)
     run_parity(w, 2, warm=True)
-
-
-@pytest.mark.parametrize("cache,beside", [((1 << 18) - 1, False), (1 << 18, True)])
-def test_a_small_batch_with_many_slots_is_sorted_beside_its_row_movement(cache, beside, tmp_path, monkeypatch):
-    """The one-workgroup sort takes keys of up to 18 bits (2^18 is the key of a slot out of range); its place is the caller's
-    stream.  Beyond that the sort is a chain of kernels, which runs on a library stream while the rows cross the link."""
-    import numpy as np
-    import torch
-    from paper_2208_05321_amd import FreqCache
-    from tests.timeline_file import load_first_collection
-    rows, n = 2 * cache + 20_000, 4000
-    gpu = FreqCache(rows, 256, cache, np.arange(rows, dtype=np.int32))
-    gpu.warm()
-    off = torch.arange(n + 1, device="cuda")
-    ids = [torch.arange(k, k + n, device="cuda") for k in (0, cache, cache + n)]
-    for i in ids[:2]:
-        gpu.prepare(i, off)
-    path = tmp_path / "timeline.txt"
-    monkeypatch.setenv("FC_TIMELINE", str(path))
-    gpu.profile(True)
-    gpu.prepare(ids[2], off)
-    gpu.profile_report()
-    monkeypatch.delenv("FC_TIMELINE")
-    gpu.profile(False)
-    gpu.close()
-    spans = load_first_collection(str(path))
-    sorted_by = max(b for a, b, name in spans if name == "sort_scatter")
-    moved_from = min(a for a, b, name in spans if name == "miss_fill")
-    assert (sorted_by > moved_from) == beside
