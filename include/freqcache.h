@@ -144,7 +144,8 @@ enum {
  *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256)
  *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch, fixed (default: starts at 32 and follows the
  *                         measured fetch / block-copy durations); FC_FILL_BLOCKS_EARLY_START only moves the start
- *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (transmitter without FC_EVICT_DMA)
+ *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (without FC_EVICT_DMA: after cache_plan_next
+ *                         or with FC_DIRTY_TRACK, otherwise rows change places in the miss fill; with it: more victims than staging_rows)
  *   FC_SCATTER_THREADS    host threads of FC_EVICT_DMA (8)
  *   FC_GATHER_THREADS     host threads of FC_MISS_DMA (6)
  *   FC_AHEAD_MISS_PCT     threshold of FC_INPUTS_READY (see there); 0 = never run ahead, 100 = always
@@ -224,7 +225,8 @@ int cache_prepare_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int
  * it with pipelined != 0, is ordered behind everything on the caller's stream instead: until then plain calls mark no place there.)
  * Usage:  cache_prepare(batch 0);  loop { fwd(t); bwd(t); cache_plan_next(batch t+1, slots_next); cache_advance(); }
  * (forward / backward are asynchronous and best enqueued first, since this call waits on the host for its planning
- * kernels; those do not wait for them.  Calling it before them is equally correct.)
+ * kernels; those do not wait for them.  Calling it before them is equally correct.  With FC_EVICT_DMA it also waits for the last
+ * evicted block if that is long overdue, which keeps a program with several handles from getting many steps ahead of the link.)
  * The call also starts fetching the planned batch's missing rows, on another library-owned stream, into a block in
  * device memory (allocated on first use, staging_rows rows per list set); cache_advance then writes the evicted
  * rows out and copies the fetched rows into their slots. */

@@ -174,7 +174,7 @@ struct fc_cache {
     int fill_blocks = 256;          // 40 with FC_EVICT_DMA:
                                     // ~200 KB of reads in flight fill the link and still let the DMA engine's writes through
     int fill_blocks_early = 32;     // the same for rows fetched ahead of time by cache_plan_next (tuning: FC_FILL_BLOCKS_EARLY)
-    int evict_blocks = 1024;        // workgroups of the host-table store kernel (tuning: FC_EVICT_BLOCKS)
+    int evict_blocks = 1024;        // workgroups of the host-table store kernel (store_block) (tuning: FC_EVICT_BLOCKS)
     int evict_early = 2;            // when that kernel starts (tuning: FC_EVICT_EARLY): 0 after the miss fill, under
                                     // forward/backward; 1 right after the gather; 2 together with the miss fill
 
@@ -192,7 +192,7 @@ struct fc_cache {
     bool ubytes_failed = false;
     uint32_t* rbits = nullptr;      // rank-space bitmap: resident rows
     int32_t* tcount = nullptr;      // empty slots per tile of 1024 slots
-    int32_t* hitpart = nullptr;     // [256] per-workgroup access-level hit counts of the marking kernel
+    int32_t* hitpart = nullptr;     // [MARK_HIT_PARTS] per-workgroup access-level hit counts of the marking kernel
     int64_t NB = 0;                 // rank-space tiles
     uint32_t* bsum = nullptr;       // [NB] per-tile counts: missing, evictable (high half)
     uint32_t* ssum = nullptr;       // [NB * SUB_TILES] the same per sub-tile

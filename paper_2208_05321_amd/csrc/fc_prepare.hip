@@ -133,8 +133,9 @@ __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __re
 // workgroups that find room beside the previous batch's forward and backward kernels; what it costs is reading N bytes
 // instead of N / 8 in K2a.  Bound by the latency of two random reads per id.
 // Measured (us, k_remap_mark + k_rank_count -> these two, in the schedules of the benchmark): 426 k ids, 10 M rows 25.6 + 6.3
-// -> 10.5 + 6.7 (plain) and 32.5 + 7.3 -> 16.6 + 11.5 (pipelined); 1.7 M ids, 100 M rows 81 + 14 -> 38 + 26.  (The bitmap
-// kernel with 256-thread workgroups and an 8 KB bitmap in LDS took 74 and 154: more of its marks are then global atomics.)
+// -> 10.5 + 6.7 (plain) and 32.5 + 7.3 -> 16.6 + 11.5 (pipelined); 1.7 M ids, 100 M rows 81 + 14 -> 38 + 26 (a batch that keeps
+// its bits all the same, for the bytes: mark_bytes).  (The bitmap kernel with 256-thread workgroups and an 8 KB bitmap in LDS took
+// 74 and 154: more of its marks are then global atomics.)
 // ---------------------------------------------------------------------------------------------------------
 constexpr int MARKB_THREADS = 256, MARKB_ITEMS = 4;
 
@@ -308,8 +309,8 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_count(const uint4* __restri
 // K2b  totals, the call's status, evict_num = numel(miss) - empty slots, and for a tile: where its missing ranks go in the
 //      list, how many victims it gives up (from the top rank down) and where those go.
 //
-//      All of it is a sum over the tiles' counts, one word each, so every workgroup of K2c works it out for its own tile (12 KB
-//      of reads from L2 at 100 M rows) instead of waiting for a kernel of one workgroup in between (6 us at 306 tiles, 11-14 at
+//      All of it is a sum over the tiles' counts, one word each, so every workgroup of K2c works it out for its own tile (at most
+//      4 KB of reads from L2, 8 KB with the look-ahead) instead of waiting for a kernel of one workgroup in between (6 us at 306 tiles, 11-14 at
 //      3052, and a launch), and the first one reports to the host before it starts on its tile.  Above PLAN_FOLD_TILES tiles
 //      (33 M rows) those reads grow with the square of the tiles (3052 tiles, beside forward and backward: 104 us against
 //      18 + 29 with a plan of its own): there one workgroup plans for all.
@@ -734,8 +735,11 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
 
 __global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
 
-// Byte marks cost N / 5 TB/s more in K2a, bit marks 0.04 to 0.06 ns per id in K1 (atomics), so the line lies at N = 32 n
-// (measured: see k_remap_bytes); a map that could not be allocated leaves the bits.
+// Byte marks make the two kernels of a batch shorter (above), but K2a then reads N bytes beside forward and backward, and where HBM binds the step that costs more than the shorter chain gives.  The line is a measured one and lies
+// between the two batches below; width of the rows and schedule, on which the second effect depends, do not enter it.
+// us a step, planned, bits / bytes, several runs each: 24 rows per id (426 k ids, 10 M rows) 128 columns 507-516 / 503-512, 32
+// columns 199-203 / 190-194; 59 rows per id (1.7 M ids, 100 M rows) 128 columns 548-570 / 578-579, 16 columns 286-328 / 283-310.
+// A map that could not be allocated leaves the bits.
 bool mark_bytes(fc_cache* c, int64_t n) {
     if (c->N > MARKB_ROWS_PER_ID * n) return false;
     if (!c->ubytes && !c->ubytes_failed) {
@@ -748,8 +752,10 @@ bool mark_bytes(fc_cache* c, int64_t n) {
     return c->ubytes != nullptr;
 }
 
-// Evicted rows, default transmitter: gather into a device block on the caller's stream (so the slots can be
-// refilled at once); the block is stored into the mapped host table by a kernel on the side stream.
+// Evicted rows stored by kernel: gather into a device block on the caller's stream (so the slots can be refilled at once); the block
+// is stored into the mapped host table by a kernel on the side stream.  This is how victims leave where the exchange of
+// k_swap_rows does not apply: default transmitter with missing rows that were fetched ahead of time or with FC_DIRTY_TRACK, and
+// FC_EVICT_DMA with more victims than a block holds.
 // Measured on MI355X: zero-copy stores that saturate the host link stall the other memory operations of the
 // compute units they run on and starve reads in the other direction, so such a store must not run under small
 // latency-bound kernels (they wait for it to end) nor under the forward / backward kernels (they slow down
