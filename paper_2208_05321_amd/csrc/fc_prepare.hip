@@ -735,8 +735,9 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
 
 __global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
 
-// Byte marks make the two kernels of a batch shorter (above), but K2a then reads N bytes beside forward and backward, and where HBM binds the step that costs more than the shorter chain gives.  The line is a measured one and lies
-// between the two batches below; width of the rows and schedule, on which the second effect depends, do not enter it.
+// Byte marks make the two kernels of a batch shorter (above), but K2a then reads N bytes beside forward and backward, and where HBM
+// binds the step that costs more than the shorter chain gives.  The line is a measured one and lies between the two batches below;
+// width of the rows and schedule, on which the second effect depends, do not enter it.
 // us a step, planned, bits / bytes, several runs each: 24 rows per id (426 k ids, 10 M rows) 128 columns 507-516 / 503-512, 32
 // columns 199-203 / 190-194; 59 rows per id (1.7 M ids, 100 M rows) 128 columns 548-570 / 578-579, 16 columns 286-328 / 283-310.
 // A map that could not be allocated leaves the bits.
