@@ -4,10 +4,12 @@
 //
 // Forward: one row-group of lanes per bag, rows added in position order.
 // Backward: lookups are stably radix-sorted by slot (payload = bag index), so each slot's gradients form
-// one contiguous, position-ordered run; fixed chunks of BWD_CHUNK consecutive sorted lookups are reduced by
+// one contiguous, position-ordered run; fixed chunks of consecutive sorted lookups are reduced by
 // one row-group each (perfectly balanced however skewed the ids are), runs that cross chunk borders are
 // finished by a second small kernel in chunk order.  No floating-point atomics: results are reproducible.
 #include "fc_internal.h"
+
+#include <algorithm>
 
 // Scratch of embedding_bag_bwd_sgd_noalloc: sort buffers, radix histograms and the partial rows of the reduction for
 // batches of up to FC_NOALLOC_MAX_IDS lookups live here instead of in memory the library allocates.  Every GPU the
@@ -231,7 +233,7 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
 // ---------------------------------------------------------------------------------------------------------
 // backward, step 2: chunked segmented reduction + SGD
 // ---------------------------------------------------------------------------------------------------------
-// A row-group owns BWD_CHUNK consecutive sorted lookups; a workgroup owns gpb such chunks in a row.
+// A row-group owns CHUNK consecutive sorted lookups; a workgroup owns gpb such chunks in a row.
 // Runs (lookups of one slot) that lie inside a chunk are applied to the cached row at once.  Pieces of runs that
 // cross chunk borders meet in LDS and are joined in chunk order by the group where the run starts inside the
 // workgroup; only pieces of runs that cross WORKGROUP borders go to global memory (two rows per workgroup) and are
@@ -240,8 +242,9 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
 struct BwdMeta { int first_kind, has_head, head_slot, pad; };
 
 // STREAM: every gradient row is read exactly once (one lookup per bag) -> non-temporal loads
-template <int VEC, bool STREAM>
-__global__ __launch_bounds__(256) void k_bwd_reduce(const int32_t* __restrict__ keys, const int32_t* __restrict__ vals,
+// CHUNK: see bwd_geometry
+template <int VEC, bool STREAM, int CHUNK>
+__global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(const int32_t* __restrict__ keys, const int32_t* __restrict__ vals,
                                                     int n, int C, const float* __restrict__ grad, float* cache, int D,
                                                     int lpr_shift, float lr, float* __restrict__ part,
                                                     BwdMeta* __restrict__ bmeta) {
@@ -253,13 +256,13 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(const int32_t* __restrict__ 
     const int nv = D / VEC;
     // LDS: keys[gpb*CHUNK], vals[gpb*CHUNK], meta[gpb], pieces[gpb][2][D]
     int* skeys = reinterpret_cast<int*>(smem);
-    int* svals = skeys + gpb * BWD_CHUNK;
-    BwdMeta* smeta = reinterpret_cast<BwdMeta*>(svals + gpb * BWD_CHUNK);
+    int* svals = skeys + gpb * CHUNK;
+    BwdMeta* smeta = reinterpret_cast<BwdMeta*>(svals + gpb * CHUNK);
     float* spiece = reinterpret_cast<float*>(smeta + gpb);
     __shared__ BwdMeta blockmeta;
 
-    const int64_t blk0 = (int64_t)blockIdx.x * gpb * BWD_CHUNK;
-    for (int t = threadIdx.x; t < gpb * BWD_CHUNK; t += blockDim.x) {
+    const int64_t blk0 = (int64_t)blockIdx.x * gpb * CHUNK;
+    for (int t = threadIdx.x; t < gpb * CHUNK; t += blockDim.x) {
         const int64_t e = blk0 + t;
         skeys[t] = e < n ? keys[e] : -1;
         svals[t] = e < n ? vals[e] : 0;
@@ -267,16 +270,16 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(const int32_t* __restrict__ 
     if (threadIdx.x == 0) blockmeta = BwdMeta{0, 0, -1, 0};
     __syncthreads();
 
-    const int64_t beg = blk0 + (int64_t)gl * BWD_CHUNK;
-    const int cnt = beg >= n ? 0 : (int)(beg + BWD_CHUNK <= n ? BWD_CHUNK : n - beg);
-    const int* mk = skeys + gl * BWD_CHUNK;
-    const int* mv = svals + gl * BWD_CHUNK;
+    const int64_t beg = blk0 + (int64_t)gl * CHUNK;
+    const int cnt = beg >= n ? 0 : (int)(beg + CHUNK <= n ? CHUNK : n - beg);
+    const int* mk = skeys + gl * CHUNK;
+    const int* mv = svals + gl * CHUNK;
     V* __restrict__ pfirst = reinterpret_cast<V*>(spiece + (size_t)(gl * 2) * D);
     V* __restrict__ plast = reinterpret_cast<V*>(spiece + (size_t)(gl * 2 + 1) * D);
     int first_kind = 0, has_head = 0, head_slot = -1;
     if (cnt > 0) {
         const int prevk = gl > 0 ? mk[-1] : (beg > 0 ? keys[beg - 1] : -1);
-        const int nextk = beg + cnt < n ? (gl + 1 < gpb ? mk[BWD_CHUNK] : keys[beg + cnt]) : -2;
+        const int nextk = beg + cnt < n ? (gl + 1 < gpb ? mk[CHUNK] : keys[beg + cnt]) : -2;
         for (int cidx = lane; cidx < nv; cidx += lpr) {
             bool open_left = prevk == mk[0];
             first_kind = 0; has_head = 0; head_slot = -1;
@@ -463,14 +466,12 @@ static int sort_in(SortJob& j, SortBufs& sb, hipStream_t st, const int32_t** kre
 }
 
 static int ensure_part(fc_cache* c, int64_t groups);
-static inline void bwd_geometry(const fc_cache* c, int64_t n, int* rthreads, int64_t* rblocks, size_t* lds);
+static inline int64_t bwd_blocks_most(const fc_cache* c, int64_t n);
 
 int reserve_bwd(fc_cache* c, int64_t n) {
     if (n <= 0) return FC_OK;
     for (SortBufs& sb : c->sb) FC_TRY(ensure_sort(sb, n));
-    int rthreads; int64_t rblocks; size_t lds;
-    bwd_geometry(c, n, &rthreads, &rblocks, &lds);
-    return ensure_part(c, rblocks);
+    return ensure_part(c, bwd_blocks_most(c, n));
 }
 
 static int ensure_part(fc_cache* c, int64_t groups) {
@@ -504,11 +505,40 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
     return sort_in(j, sb, st, kres, vres);
 }
 
-static inline void bwd_geometry(const fc_cache* c, int64_t n, int* rthreads, int64_t* rblocks, size_t* lds) {
-    *rthreads = bwd_threads(c->lpr);
-    const int rgpb = *rthreads / c->lpr;                      // chunks per workgroup of the reduction
-    *rblocks = cdiv(n, (int64_t)rgpb * BWD_CHUNK);
-    *lds = (size_t)rgpb * BWD_CHUNK * 8 + (size_t)rgpb * sizeof(BwdMeta) + (size_t)rgpb * 2 * c->D * 4;
+// Launch of the reduction.  A row-group walks its chunk in steps of BWD_PF lookups, each a round of loads, so a chunk of
+// BWD_CHUNK = 32 is four rounds one after the other, whatever the batch: with few workgroups that chain is the kernel's
+// duration.  Batches of up to BWD_SMALL_BLOCKS workgroups' worth of chunks of 8 are cut into those: one round, four times the
+// workgroups.  Where all chunks fit one workgroup of 1024 threads they form one, and no run crosses a workgroup border
+// (k_bwd_fixup is then not launched).
+// Measured, chunks of 32 -> of 8 (us by events, reduction + fixup): 1024 lookups of 16 columns 19.8 -> 10.4, 53 k of 64 columns
+// 23.5 + 7.2 -> 12.5 + 7; 426 k of 32 columns (1664 workgroups) 32.5 + 8.3 -> 26.3 + 8.8.  Beyond, the chip is full either way and
+// k_bwd_fixup gets the longer: 1.7 M of 16 columns (6656 workgroups) 66.8 + 9.6 -> 57.6 + 18.8, 426 k of 128 columns (6656)
+// 64.6 + 8.2 -> 59.1 + 13.8, 328 k of 256 columns (10240) 65.5 + 16.6 -> 66.4 + 44.7.  The limit on floats keeps the partial
+// rows within what embedding_bag_bwd_sgd_noalloc has for them.
+constexpr int BWD_SMALL_CHUNK = BWD_PF;
+constexpr int64_t BWD_SMALL_BLOCKS = 2048, BWD_SMALL_FLOATS = 1 << 20;      // floats: blocks * D
+struct BwdGeom { int threads = 0, chunk = 0; int64_t blocks = 0; size_t lds = 0; };
+
+// most workgroups that chunks of 8 are used for
+static inline int64_t bwd_small_blocks(const fc_cache* c) { return std::min(BWD_SMALL_BLOCKS, BWD_SMALL_FLOATS / c->D); }
+
+static inline BwdGeom bwd_geometry(const fc_cache* c, int64_t n) {
+    BwdGeom g;
+    g.threads = bwd_threads(c->lpr);
+    g.chunk = BWD_SMALL_CHUNK;
+    const int64_t lanes = cdiv(n, BWD_SMALL_CHUNK) * c->lpr;
+    if (lanes <= 1024) g.threads = (int)cdiv(lanes, WAVE) * WAVE;
+    else if (cdiv(n, (int64_t)(g.threads / c->lpr) * BWD_SMALL_CHUNK) > bwd_small_blocks(c)) g.chunk = BWD_CHUNK;
+    const int gpb = g.threads / c->lpr;                       // chunks per workgroup
+    g.blocks = cdiv(n, (int64_t)gpb * g.chunk);
+    g.lds = (size_t)gpb * g.chunk * 8 + (size_t)gpb * sizeof(BwdMeta) + (size_t)gpb * 2 * c->D * 4;
+    return g;
+}
+
+// the most workgroups that a batch of at most n lookups takes
+static inline int64_t bwd_blocks_most(const fc_cache* c, int64_t n) {
+    const int64_t gpb = bwd_threads(c->lpr) / c->lpr;
+    return std::max(std::min(cdiv(n, gpb * BWD_SMALL_CHUNK), bwd_small_blocks(c)), cdiv(n, gpb * BWD_CHUNK));
 }
 
 // Called by cache_prepare / cache_prepare_next / cache_plan_next once the slots of the batch are on their way: the
@@ -565,8 +595,7 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
 static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags,
                    const float* grad, float lr, const int32_t* kin, const int32_t* vin, SortBufs& sb, float* part,
                    int32_t* pmeta, fc_cache* prof) {
-    int rthreads; int64_t rblocks; size_t lds;
-    bwd_geometry(c, n, &rthreads, &rblocks, &lds);
+    const BwdGeom g = bwd_geometry(c, n);
     if (!kin) {
         int bits = 1;
         while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
@@ -582,22 +611,23 @@ static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n,
     {
         ProfScope ps(prof, P_BWD_REDUCE, st);
         BwdMeta* bm = reinterpret_cast<BwdMeta*>(pmeta);
-#define FC_BWD(V, S) \
-        k_bwd_reduce<V, S><<<(unsigned)rblocks, rthreads, lds, st>>>(kin, vin, (int)n, (int)c->C, grad, c->cache, c->D, sh, lr, part, bm)
-#define FC_BWD_V(S) \
-        switch (c->vec) { case 4: FC_BWD(4, S); break; case 2: FC_BWD(2, S); break; default: FC_BWD(1, S); break; }
-        if (n == num_bags) { FC_BWD_V(true) } else { FC_BWD_V(false) }
+#define FC_BWD(V, S, H) \
+        k_bwd_reduce<V, S, H><<<(unsigned)g.blocks, g.threads, g.lds, st>>>(kin, vin, (int)n, (int)c->C, grad, c->cache, c->D, sh, lr, part, bm)
+#define FC_BWD_V(S, H) \
+        switch (c->vec) { case 4: FC_BWD(4, S, H); break; case 2: FC_BWD(2, S, H); break; default: FC_BWD(1, S, H); break; }
+        if (g.chunk == BWD_SMALL_CHUNK) { if (n == num_bags) { FC_BWD_V(true, BWD_SMALL_CHUNK) } else { FC_BWD_V(false, BWD_SMALL_CHUNK) } }
+        else if (n == num_bags) { FC_BWD_V(true, BWD_CHUNK) } else { FC_BWD_V(false, BWD_CHUNK) }
 #undef FC_BWD_V
 #undef FC_BWD
     }
-    if (rblocks > 1) {             // else no run crosses a workgroup border
+    if (g.blocks > 1) {            // else no run crosses a workgroup border
         ProfScope ps(prof, P_BWD_FIXUP, st);
         const BwdMeta* bm = reinterpret_cast<const BwdMeta*>(pmeta);
-        const unsigned fb = (unsigned)cdiv(rblocks, 256 >> sh);
+        const unsigned fb = (unsigned)cdiv(g.blocks, 256 >> sh);
         switch (c->vec) {
-            case 4: k_bwd_fixup<4><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)rblocks); break;
-            case 2: k_bwd_fixup<2><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)rblocks); break;
-            default: k_bwd_fixup<1><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)rblocks); break;
+            case 4: k_bwd_fixup<4><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
+            case 2: k_bwd_fixup<2><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
+            default: k_bwd_fixup<1><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
         }
     }
     FC_HIP(hipGetLastError());
@@ -617,9 +647,7 @@ int bwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
     if (n == 0) return FC_OK;
     FC_HIP(hipSetDevice(c->device));
     hipStream_t st = c->stream;
-    int rthreads; int64_t rblocks; size_t lds;
-    bwd_geometry(c, n, &rthreads, &rblocks, &lds);
-    FC_TRY(ensure_part(c, rblocks));
+    FC_TRY(ensure_part(c, bwd_geometry(c, n).blocks));
     const int32_t* kin = nullptr; const int32_t* vin = nullptr;
     for (PresortRec& r : c->rec) {
         // sorted ahead of time by the call that prepared the current batch, from these very buffers
@@ -642,8 +670,7 @@ int bwd_noalloc_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t
                      const float* grad, float lr) {
     FC_TRY(bwd_check_args(c, slots, n, offsets, num_bags, grad));
     if (n > FC_NOALLOC_MAX_IDS) return FC_ERR_SCRATCH_EXCEEDED;
-    int rthreads; int64_t rblocks; size_t lds;
-    bwd_geometry(c, n > 0 ? n : 1, &rthreads, &rblocks, &lds);
+    const int64_t rblocks = bwd_geometry(c, n > 0 ? n : 1).blocks;
     const size_t a256 = 255;
     const size_t pair_bytes = ((size_t)FC_NOALLOC_MAX_IDS * 4 + a256) & ~a256;
     const size_t ghist_bytes = ((size_t)(cdiv(FC_NOALLOC_MAX_IDS, RS_TILE) << RS_MAX_BITS) * 4 + a256) & ~a256;
