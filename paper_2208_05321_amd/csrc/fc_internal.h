@@ -455,6 +455,21 @@ __device__ __forceinline__ int bag_of_lookup(const int64_t* __restrict__ offsets
     return (offsets[g] <= i && i < offsets[g + 1]) ? g : bag_of(offsets, num_bags, i);
 }
 
+// The lanes among `lanes` whose digit (at most MAXB bits, radix_bits of them in use) is this lane's.
+template <int MAXB>
+__device__ __forceinline__ uint64_t same_digit(int d, int radix_bits, uint64_t lanes) {
+    uint32_t lo = (uint32_t)lanes, hi = (uint32_t)(lanes >> 32);
+#pragma unroll
+    for (int b = 0; b < MAXB; ++b) {
+        if (b >= 7 && b >= radix_bits) break;               // (unused bits are zero in every lane)
+        const int one = __builtin_amdgcn_sbfe(d, b, 1);     // 0 or -1
+        const uint64_t m = __ballot(one != 0);
+        lo &= ~((uint32_t)m ^ (uint32_t)one);
+        hi &= ~((uint32_t)(m >> 32) ^ (uint32_t)one);
+    }
+    return (uint64_t)hi << 32 | lo;
+}
+
 template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT/64 ints */) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;

@@ -338,31 +338,52 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 // Against the kernels of fc_sort.hip (us a training step, three schedules: backward sorts itself / plain / prepared ahead):
 // 5200 lookups 91, 112, 145 -> 81, 100, 99; 10101 97, 114, 141 -> 97, 100, 127; 15600 99, 117, 139 -> 122, 120, 131, hence
 // the limit: one compute unit orders about 400 pairs per microsecond and pass.
+// (Those figures are from before a wavefront's match of a digit came down to four instructions a bit and served for both counting
+// and placing, with no atomics on popular digits: 10101 lookups, 14-bit keys 35 -> 22 us.)
 // ---------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ rank_slot,
                                                            int32_t* __restrict__ slots_out, const int64_t* __restrict__ offsets,
                                                            int num_bags, int one_per_bag, int n, int limit, int passes, int radix_bits,
                                                            uint32_t* flags, const int32_t* __restrict__ status, int32_t* __restrict__ keys_out,
                                                            int32_t* __restrict__ vals_out) {
-    extern __shared__ __align__(16) uint32_t sm_words[];   // two arrays of rounds * SM_THREADS words, then the digit counts
+    // two arrays of rounds * SM_THREADS words, the digit counts, and each element's place within its wavefront and digit
+    extern __shared__ __align__(16) uint32_t sm_words[];
     const int rounds = (n + SM_THREADS - 1) / SM_THREADS;  // elements per thread
     const int radix = 1 << radix_bits, mask = radix - 1;
     uint32_t* from = sm_words;
     uint32_t* to = sm_words + rounds * SM_THREADS;
     int* wc = reinterpret_cast<int*>(sm_words + 2 * rounds * SM_THREADS);      // [SM_WAVES][radix]
+    uint16_t* place = reinterpret_cast<uint16_t*>(wc + SM_WAVES * radix);
     __shared__ int scan[SM_WAVES];
+    __shared__ int s_other;                                // some bag does not hold just its own lookup
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    bool bad = false;
+    bool bad = false, other = false;
     const bool refused = status && *status != FC_OK;       // neither slots nor offsets are touched then
-#pragma unroll 4
-    for (int i = tid; i < n; i += SM_THREADS) {
-        int key = keys_in[i];
+    // with as many lookups as bags, most likely bag i holds lookup i: seen here, in order, rather than looked up in sorted order below
+    const bool check = !one_per_bag && !refused && n == num_bags;
+    if (tid == 0) s_other = check ? offsets[n] != (int64_t)n : !one_per_bag;
+    constexpr int BATCH = 5;                               // elements of a thread in flight together
+#pragma unroll 1
+    for (int i0 = tid; i0 - tid < n; i0 += BATCH * SM_THREADS) {
+        int key[BATCH];
+        int64_t off[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) key[k] = keys_in[min(i0 + k * SM_THREADS, n - 1)];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) off[k] = check ? offsets[min(i0 + k * SM_THREADS, n - 1)] : 0;
         if (rank_slot) {
-            key = key >= 0 ? rank_slot[key] : -1;          // (-1: an id out of range, the call is refused)
-            if (!refused) slots_out[i] = key;
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) key[k] = key[k] >= 0 ? rank_slot[key[k]] : -1;     // (-1: an id out of range, the call is refused)
         }
-        if ((unsigned)key >= (unsigned)limit) { bad = true; key = limit; }
-        from[i] = ((uint32_t)key << SMALL_POS_BITS) | (uint32_t)i;
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            const int i = i0 + k * SM_THREADS;
+            if (i >= n) break;
+            if (rank_slot && !refused) slots_out[i] = key[k];
+            if ((unsigned)key[k] >= (unsigned)limit) { bad = true; key[k] = limit; }
+            other |= check && off[k] != i;
+            from[i] = ((uint32_t)key[k] << SMALL_POS_BITS) | (uint32_t)i;
+        }
     }
     if (refused) return;
     if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
@@ -374,9 +395,20 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
         const int shift = SMALL_POS_BITS + p * radix_bits;
         for (int d = tid; d < SM_WAVES * radix; d += SM_THREADS) wc[d] = 0;
         __syncthreads();
+        if (p == 0 && other) s_other = 1;
 #pragma unroll 1
-        for (int k = 0; k < rounds; ++k)
-            if (e0 + 64 * k < n) atomicAdd(&mine[(from[e0 + 64 * k] >> shift) & mask], 1);
+        for (int k = 0; k < rounds; ++k) {
+            const int e = e0 + 64 * k;
+            const bool valid = e < n;
+            const int d = ((valid ? from[e] : 0) >> shift) & mask;
+            const uint64_t peers = same_digit<8>(d, radix_bits, __ballot(valid));
+            const int before = __popcll(peers & lt);
+            if (valid) {
+                const int at = mine[d];
+                if (before == 0) mine[d] = at + __popcll(peers);
+                place[e] = (uint16_t)(at + before);
+            }
+        }
         __syncthreads();
         // wc[w][d] becomes where wavefront w's first element of digit d goes
         int run = 0;
@@ -391,32 +423,24 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
             for (int k = 0; k < SM_WAVES; ++k) wc[k * radix + tid] += base;
         }
         __syncthreads();
-#pragma unroll 1
+#pragma unroll 2
         for (int k = 0; k < rounds; ++k) {
-            const bool valid = e0 + 64 * k < n;
-            const uint32_t x = valid ? from[e0 + 64 * k] : 0;
-            const int d = (x >> shift) & mask;
-            uint64_t peers = __ballot(valid);
-            for (int b = 0; b < radix_bits; ++b) {
-                const bool one = (d >> b) & 1;
-                const uint64_t bm = __ballot(one);
-                peers &= one ? bm : ~bm;
+            const int e = e0 + 64 * k;
+            if (e < n) {
+                const uint32_t x = from[e];
+                to[mine[(x >> shift) & mask] + place[e]] = x;
             }
-            const int before = __popcll(peers & lt);
-            int at = 0;
-            if (valid) at = mine[d];
-            if (valid && before == 0) mine[d] = at + __popcll(peers);
-            if (valid) to[at + before] = x;
         }
         __syncthreads();
         uint32_t* t = from; from = to; to = t;
     }
+    const bool opb = s_other == 0;
 #pragma unroll 4
     for (int e = tid; e < n; e += SM_THREADS) {
         const uint32_t x = from[e];
         const int i = (int)(x & ((1u << SMALL_POS_BITS) - 1));
         keys_out[e] = (int)(x >> SMALL_POS_BITS);
-        vals_out[e] = one_per_bag ? i : bag_of_lookup(offsets, num_bags, i);
+        vals_out[e] = opb ? i : bag_of_lookup(offsets, num_bags, i);
     }
 }
 
@@ -430,7 +454,7 @@ int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int
     const int passes = (j.bits + 7) / 8, rb = (j.bits + passes - 1) / passes;
     const int opb = j.one_per_bag && j.n == j.num_bags;
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
-    const size_t words = 2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb);
+    const size_t words = 2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb) + (size_t)cdiv(j.n, 2);
     k_sort_small<<<1, SM_THREADS, words * 4, st>>>(j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.num_bags, opb, j.n,
                                                    j.limit, passes, rb, j.flags, j.status, j.keysA, j.valsA);
     FC_HIP(hipGetLastError());

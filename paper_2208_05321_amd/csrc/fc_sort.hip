@@ -30,7 +30,7 @@ __device__ __forceinline__ int load_key(const int32_t* __restrict__ keys_in, int
     return keys_in[i];
 }
 
-template <int SRC, int ITEMS>
+template <int SRC>
 __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restrict__ keys_in, int n, int limit, int shift,
                                                           int radix_bits, int nblk, int32_t* __restrict__ ghist,
                                                           int32_t* __restrict__ stot,
@@ -38,6 +38,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
                                                           int32_t* __restrict__ slots_out,
                                                           int32_t* __restrict__ zero_ptr, int zero_words,
                                                           const int32_t* __restrict__ status) {
+    constexpr int ITEMS = RS_ITEMS;
     __shared__ int h[1 << RS_MAX_BITS];
     if (zero_ptr) {     // what the previous sort left in the other set of supertile tables, a slice per workgroup
         const int per = (zero_words + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -138,19 +139,22 @@ __global__ __launch_bounds__(SC_DIG * SC_GROUPS) void k_sort_scan(int32_t* ghist
 // lanes write neighbouring words (straight from the registers, every lane of a store touched a line of its own, and the
 // requests to L2 alone took 9 us at 1.7 M pairs).  MAXB = 11 (the static module's long jobs, experiments): runs of one or two
 // keys, nothing to gain, and no LDS to spare.
-// Measured per launch (us by events, before -> after): 1.7 M pairs, 7-bit digits 30-34 -> 21; 426 k pairs, 9-bit digits 17 + a scan
-// kernel of 7 -> 20.
-template <int SRC, int ITEMS, bool FUSED, bool OPB, int MAXB>
-__global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __restrict__ keys_in,
-                                                             const int32_t* __restrict__ vals_in,
-                                                             const int64_t* __restrict__ offsets, int num_bags, int n,
-                                                             int limit, int shift, int radix_bits, int nblk,
-                                                             const int32_t* __restrict__ ghist,
-                                                             const int32_t* __restrict__ dtot,
-                                                             int32_t* __restrict__ keys_out,
-                                                             int32_t* __restrict__ vals_out, const int32_t* __restrict__ status) {
+// A batch has one tile for a compute unit or a few, so a tile's time is that of its wavefronts' instruction chains, not of its
+// bytes: NT = 512 threads of four pairs each rather than 256 of eight, a digit to a thread, addresses of the count rows by a
+// shift, matches of a digit in four instructions a bit.
+// us a launch, 256 threads of eight pairs and a loop over the bits -> this: 53 k pairs, 8-bit digits 11.4 -> 7.0; 426 k, 9 bits 16.1 and
+// 13.8 -> 12.7 and 10.6; 1.7 M, 7 bits 18.3 -> 13.6.
+template <int SRC, int NT, bool FUSED, bool OPB, int MAXB>
+__global__ __launch_bounds__(NT) void k_sort_scatter(const int32_t* __restrict__ keys_in,
+                                                     const int32_t* __restrict__ vals_in,
+                                                     const int64_t* __restrict__ offsets, int num_bags, int n,
+                                                     int limit, int shift, int radix_bits, int nblk,
+                                                     const int32_t* __restrict__ ghist,
+                                                     const int32_t* __restrict__ dtot,
+                                                     int32_t* __restrict__ keys_out,
+                                                     int32_t* __restrict__ vals_out, const int32_t* __restrict__ status) {
     if (SRC == SORT_SRC_SLOTS && status && *status != FC_OK) return;      // refused: neither slots nor offsets may be read any more
-    constexpr int NW = RS_THREADS / 64, TILE = RS_THREADS * ITEMS;
+    constexpr int NW = NT / 64, TILE = RS_TILE, ITEMS = TILE / NT;
     constexpr bool STAGE = MAXB <= 9;
     __shared__ int base[1 << MAXB];            // where this tile's run of each digit starts in the output
     __shared__ int wc[NW][1 << MAXB];          // per-wavefront digit counts, then exclusive offsets
@@ -176,56 +180,51 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
         } else if (SRC == SORT_SRC_COUNTS) val[it] = i;
         else val[it] = vals_in[i];
     }
-    if (FUSED) {
+    if constexpr (FUSED) {
         // digit totals = sum over the supertiles; this tile's offset within a digit = the supertiles before its own plus
-        // the tiles before it inside its own.  A thread owns `per` <= 2 neighbouring digits (radix <= 512); with 128 digits or
-        // fewer, `parts` threads share one and take the rows in turn.  FUSE_ROWS rows are requested together.
-        constexpr int FUSE_ROWS = 16;
-        const int nsup = (nblk + SS_TILES - 1) / SS_TILES, mysup = blockIdx.x / SS_TILES;
-        const int rows = nsup + (int)blockIdx.x - mysup * SS_TILES;
-        const int per = radix > RS_THREADS ? 2 : 1;
-        const int parts = per == 1 ? RS_THREADS / radix : 1;
-        const int d0 = (tid & (RS_THREADS / parts - 1)) * per, part = tid / (RS_THREADS / parts);
-        int tot[2] = {0, 0}, bef[2] = {0, 0};
-        for (int r0 = part; r0 < rows; r0 += FUSE_ROWS * parts) {
+        // the tiles before it inside its own.  A digit belongs to NT / radix threads, which take the rows in turn; a thread
+        // requests FUSE_ROWS rows of either kind together (rows past the last reread it, unused).
+        static_assert((1 << MAXB) <= NT, "a thread holds one digit");
+        constexpr int FUSE_ROWS = 8;
+        const int nsup = (nblk + SS_TILES - 1) / SS_TILES, mysup = blockIdx.x / SS_TILES, before = blockIdx.x - mysup * SS_TILES;
+        const int parts = NT >> radix_bits, part = tid >> radix_bits, d = tid & mask;
+        const int32_t* __restrict__ mine = ghist + ((size_t)mysup * SS_TILES << radix_bits);
+        int tot = 0, bef = 0;
+        for (int r0 = part; r0 < nsup || r0 < before; r0 += FUSE_ROWS * parts) {
             int v0[FUSE_ROWS], v1[FUSE_ROWS];
 #pragma unroll
             for (int k = 0; k < FUSE_ROWS; ++k) {
                 const int r = r0 + k * parts;
-                const int32_t* row = r < nsup ? dtot + (size_t)r * radix : ghist + (size_t)(mysup * SS_TILES + r - nsup) * radix;
-                v0[k] = r < rows ? row[d0] : 0;
-                v1[k] = r < rows && per > 1 ? row[d0 + 1] : 0;
+                v0[k] = dtot[((unsigned)min(r, nsup - 1) << radix_bits) + d];
+                v1[k] = mine[((unsigned)min(r, before) << radix_bits) + d];
             }
 #pragma unroll
             for (int k = 0; k < FUSE_ROWS; ++k) {
                 const int r = r0 + k * parts;
-                if (r < nsup) { tot[0] += v0[k]; tot[1] += v1[k]; }
-                if (r < mysup || r >= nsup) { bef[0] += v0[k]; bef[1] += v1[k]; }
+                tot += r < nsup ? v0[k] : 0;
+                bef += (r < mysup ? v0[k] : 0) + (r < before ? v1[k] : 0);
             }
         }
-        if (parts > 1) {                       // join the parts (wc serves as scratch: 2 * 256 words)
+        if (parts > 1) {                       // join the parts (wc serves as scratch)
             int* scr = &wc[0][0];
-            static_assert((NW << MAXB) >= 2 * RS_THREADS, "");
-            scr[tid] = tot[0]; scr[RS_THREADS + tid] = bef[0];
+            static_assert((NW << MAXB) >= 2 * NT, "");
+            scr[tid] = tot; scr[NT + tid] = bef;
             __syncthreads();
-            tot[0] = bef[0] = 0;
+            tot = bef = 0;
             if (tid < radix)
-                for (int k = 0; k < parts; ++k) { tot[0] += scr[k * radix + tid]; bef[0] += scr[RS_THREADS + k * radix + tid]; }
+                for (int k = 0; k < parts; ++k) { tot += scr[(k << radix_bits) + tid]; bef += scr[NT + (k << radix_bits) + tid]; }
             __syncthreads();
         }
         int total;
-        const int run = block_excl_scan<RS_THREADS>(tot[0] + tot[1], total, lds);
-        if (part == 0) {
-            base[d0] = run + bef[0];
-            if (per > 1) base[d0 + 1] = run + tot[0] + bef[1];
-        }
+        const int run = block_excl_scan<NT>(tot, total, lds);
+        if (part == 0) base[d] = run + bef;
     } else {   // digit bases: exclusive scan of the digit totals, plus this tile's offset within the digit
-        const int per = (radix + RS_THREADS - 1) / RS_THREADS;
+        const int per = (radix + NT - 1) / NT;
         const int d0 = tid * per;
         int local = 0;
         for (int k = 0; k < per; ++k) if (d0 + k < radix) local += dtot[d0 + k];
         int tot;
-        int run = block_excl_scan<RS_THREADS>(local, tot, lds);
+        int run = block_excl_scan<NT>(local, tot, lds);
         for (int k = 0; k < per; ++k) {
             const int d = d0 + k;
             if (d < radix) {
@@ -234,7 +233,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
             }
         }
     }
-    for (int d = tid; d < radix; d += RS_THREADS) {
+    for (int d = tid; d < radix; d += NT) {
 #pragma unroll
         for (int k = 0; k < NW; ++k) wc[k][d] = 0;
     }
@@ -248,41 +247,36 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
         }
     }
     const uint64_t lt = (1ull << lane) - 1ull;
+    uint64_t peers[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        peers[it] = same_digit<MAXB>((key[it] >> shift) & mask, radix_bits, __ballot(tile0 + it * 64 + lane < n));
     int lrank[ITEMS];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const bool valid = tile0 + it * 64 + lane < n;
         const int d = (key[it] >> shift) & mask;
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < radix_bits; ++b) {
-            const bool one = (d >> b) & 1;
-            const uint64_t bm = __ballot(one);
-            peers &= one ? bm : ~bm;
-        }
-        const int before = __popcll(peers & lt);
+        const int before = __popcll(peers[it] & lt);
         int old = 0;
         if (valid) old = wc[w][d];
-        if (valid && before == 0) wc[w][d] = old + __popcll(peers);
+        if (valid && before == 0) wc[w][d] = old + __popcll(peers[it]);
         lrank[it] = old + before;
     }
     __syncthreads();
     if (STAGE) {
         // wc[k][d]: where wavefront k's first pair of digit d goes within the tile; base[d]: what that place lacks to the output's
-        const int per = (radix + RS_THREADS - 1) / RS_THREADS;     // 1 or 2
-        const int d0 = tid * per;
+        static_assert(!STAGE || (1 << MAXB) <= NT, "a thread holds one digit");
         int cnt = 0;
-        if (d0 < radix)
-            for (int j = 0; j < per; ++j)
+        if (tid < radix)
 #pragma unroll
-                for (int k = 0; k < NW; ++k) cnt += wc[k][d0 + j];
+            for (int k = 0; k < NW; ++k) cnt += wc[k][tid];
         int total;
-        int run = block_excl_scan<RS_THREADS>(cnt, total, lds);
-        if (d0 < radix)
-            for (int j = 0; j < per; ++j) {
-                base[d0 + j] -= run;
+        int run = block_excl_scan<NT>(cnt, total, lds);
+        if (tid < radix) {
+            base[tid] -= run;
 #pragma unroll
-                for (int k = 0; k < NW; ++k) { const int c = wc[k][d0 + j]; wc[k][d0 + j] = run; run += c; }
-            }
+            for (int k = 0; k < NW; ++k) { const int c = wc[k][tid]; wc[k][tid] = run; run += c; }
+        }
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it)
@@ -290,7 +284,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {
-            const int j = it * RS_THREADS + tid;
+            const int j = it * NT + tid;
             if (j < total) {
                 const int2 kv = stage[j];
                 const int dest = j + base[(kv.x >> shift) & mask];
@@ -300,7 +294,7 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
         }
         return;
     }
-    for (int d = tid; d < radix; d += RS_THREADS) {
+    for (int d = tid; d < radix; d += NT) {
         int run = 0;
 #pragma unroll
         for (int k = 0; k < NW; ++k) { const int cnt = wc[k][d]; wc[k][d] = run; run += cnt; }
@@ -318,15 +312,15 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_scatter(const int32_t* __re
 }
 
 
-template <int SRC, bool FUSED, bool OPB, int ITEMS = RS_ITEMS>
+template <int SRC, bool FUSED, bool OPB>
 static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, const int32_t* vin, int32_t* kout, int32_t* vout,
                         int shift, int rb, int32_t* stot) {
     const int radix = 1 << rb;
-    const int nblk = (int)cdiv(j.n, RS_THREADS * ITEMS);
+    const int nblk = (int)cdiv(j.n, RS_TILE);
     {
         ProfScope ps(j.prof, P_SORT_HIST, st);
         const bool first = shift == 0 && j.stot_other && j.other_dirty > 0;
-        k_sort_hist<SRC, ITEMS><<<(unsigned)nblk, RS_THREADS, 0, st>>>(kin, j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : nullptr,
+        k_sort_hist<SRC><<<(unsigned)nblk, RS_THREADS, 0, st>>>(kin, j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : nullptr,
                                                                      j.flags, j.rank_slot, j.slots_out,
                                                                      first ? j.stot_other : nullptr, first ? (int)j.other_dirty : 0, j.status);
     }
@@ -337,29 +331,29 @@ static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, co
     // SORT_SRC_RANKS: the slots are written now, the rest of the pass reads them
     constexpr int SSRC = SRC == SORT_SRC_RANKS ? SORT_SRC_SLOTS : SRC;
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
-#define FC_SCATTER(B) \
-    k_sort_scatter<SSRC, ITEMS, FUSED, OPB, B><<<(unsigned)nblk, RS_THREADS, 0, st>>>(SRC == SORT_SRC_RANKS ? j.slots_out : kin, vin, j.offsets, j.num_bags, \
+#define FC_SCATTER(NT, F, B) \
+    k_sort_scatter<SSRC, NT, F, OPB, B><<<(unsigned)nblk, NT, 0, st>>>(SRC == SORT_SRC_RANKS ? j.slots_out : kin, vin, j.offsets, j.num_bags, \
                                                                                      j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : j.dtot, kout, vout, SRC == SORT_SRC_RANKS ? j.status : nullptr)
-    if (FUSED || rb <= 9) FC_SCATTER(9);
-    else FC_SCATTER(11);
+    if (FUSED || rb <= 9) FC_SCATTER(512, FUSED, 9);
+    else FC_SCATTER(256, false, 11);
 #undef FC_SCATTER
 }
 
-template <bool FUSED, int ITEMS>
+template <bool FUSED>
 static void first_pass(const SortJob& j, hipStream_t st, int32_t* kout, int32_t* vout, int rb, int32_t* stot) {
     const bool opb = j.one_per_bag && j.n == j.num_bags;
-    if (j.src == SORT_SRC_PAIRS) launch_pass<SORT_SRC_PAIRS, FUSED, false, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
-    else if (j.src == SORT_SRC_COUNTS) launch_pass<SORT_SRC_COUNTS, FUSED, false, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+    if (j.src == SORT_SRC_PAIRS) launch_pass<SORT_SRC_PAIRS, FUSED, false>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+    else if (j.src == SORT_SRC_COUNTS) launch_pass<SORT_SRC_COUNTS, FUSED, false>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
     else if (j.src == SORT_SRC_SLOTS) {
-        if (opb) launch_pass<SORT_SRC_SLOTS, FUSED, true, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
-        else launch_pass<SORT_SRC_SLOTS, FUSED, false, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+        if (opb) launch_pass<SORT_SRC_SLOTS, FUSED, true>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+        else launch_pass<SORT_SRC_SLOTS, FUSED, false>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
     } else {
-        if (opb) launch_pass<SORT_SRC_RANKS, FUSED, true, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
-        else launch_pass<SORT_SRC_RANKS, FUSED, false, ITEMS>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+        if (opb) launch_pass<SORT_SRC_RANKS, FUSED, true>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
+        else launch_pass<SORT_SRC_RANKS, FUSED, false>(j, st, j.keys_in, j.vals_in, kout, vout, 0, rb, stot);
     }
 }
 
-template <bool FUSED, int ITEMS>
+template <bool FUSED>
 static int run_passes(const SortJob& j, hipStream_t st, int passes, int rb, int32_t* stot, size_t stot_pass,
                       const int32_t** kres, const int32_t** vres) {
     const int32_t* kin = j.keys_in; const int32_t* vin = j.vals_in;
@@ -371,8 +365,8 @@ static int run_passes(const SortJob& j, hipStream_t st, int passes, int rb, int3
             FC_HIP(hipStreamWaitEvent(j.tail_stream, j.tail_event, 0));
             st = j.tail_stream;
         }
-        if (p == 0) first_pass<FUSED, ITEMS>(j, st, kout, vout, rb, sp);
-        else launch_pass<SORT_SRC_PAIRS, FUSED, false, ITEMS>(j, st, kin, vin, kout, vout, p * rb, rb, sp);
+        if (p == 0) first_pass<FUSED>(j, st, kout, vout, rb, sp);
+        else launch_pass<SORT_SRC_PAIRS, FUSED, false>(j, st, kin, vin, kout, vout, p * rb, rb, sp);
         kin = kout; vin = vout;
         if (kout == j.keysA) { kout = j.keysB; vout = j.valsB; } else { kout = j.keysA; vout = j.valsA; }
     }
@@ -410,8 +404,8 @@ int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int
     }
     int32_t* stot = fused ? j.stot : nullptr;
     if (j.dirtied) *j.dirtied = fused ? (int64_t)(stot_pass * passes) : 0;
-    if (fused) FC_TRY((run_passes<true, RS_ITEMS>(j, st, passes, rb, stot, stot_pass, kres, vres)));
-    else FC_TRY((run_passes<false, RS_ITEMS>(j, st, passes, rb, stot, stot_pass, kres, vres)));
+    if (fused) FC_TRY((run_passes<true>(j, st, passes, rb, stot, stot_pass, kres, vres)));
+    else FC_TRY((run_passes<false>(j, st, passes, rb, stot, stot_pass, kres, vres)));
     FC_HIP(hipGetLastError());
     return FC_OK;
 }
