@@ -15,7 +15,7 @@ namespace fc {
 
 // ---- profiling ----
 static const char* const kProfNames[P_COUNT] = {
-    "remap_mark", "rank_count", "rank_plan", "rank_emit", "evict_gather", "evict_store", "free_count", "free_assign",
+    "remap_mark", "rank_count", "rank_emit", "evict_gather", "evict_store", "free_count", "free_assign",
     "miss_fill", "slots_out", "bag_fwd", "sort_hist", "sort_scan", "sort_scatter", "bwd_reduce", "bwd_fixup",
     "h2d_block", "d2h_block", "flush_rows", "rows_in"};
 
@@ -95,7 +95,6 @@ static int reset_state(fc_cache* c, bool warm) {
     k_iota_or_neg<<<1024, 256, 0, st>>>(c->rank_slot, c->N, warm ? c->C : 0);
     k_iota_or_neg<<<256, 256, 0, st>>>(c->slot_rank, c->C, warm ? c->C : 0);
     k_bits_prefix<<<256, 256, 0, st>>>(c->ubits, words, 0);
-    c->ubits_clean = true;
     k_bits_prefix<<<256, 256, 0, st>>>(c->pbits, words, 0);
     k_bits_prefix<<<256, 256, 0, st>>>(c->rbits, words, warm ? c->C : 0);
     k_set_ctl<<<1, 1, 0, st>>>(c->ctl);
@@ -141,7 +140,7 @@ static void destroy(fc_cache* c) {
     for (int b = 0; b < DMA_BLOCKS; ++b)
         if (c->ev_copy_a[b]) (void)hipEventDestroy(c->ev_copy_a[b]);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
-                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->usum, (void*)c->plan[0], (void*)c->plan[1], (void*)c->tile_plan,
+                    (void*)c->rbits, (void*)c->ubytes, (void*)c->uchunks, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->gsum, (void*)c->plan[0], (void*)c->plan[1],
                     (void*)c->rbuf,
                     (void*)c->ctl, (void*)c->stage_dev, (void*)c->stage_dev2, (void*)c->part, (void*)c->pmeta, (void*)c->pbits})
         if (p) (void)hipFree(p);
@@ -238,9 +237,9 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     if (const char* e = getenv("FC_SORT_FUSED")) c->sort_no_fuse = atoi(e) == 0;
     if (const char* e = getenv("FC_AHEAD_MISS_PCT")) { const float v = (float)atof(e); if (v >= 0.f) c->ahead_miss_pct = v; }
     if (const char* e = getenv("FC_FWD_BAGS")) { const int v = atoi(e); if (v == 1 || v == 2 || v == 4) c->fwd_bags = v; }
-    if (const char* e = getenv("FC_MARK_IPT")) { const int v = atoi(e); if (v >= 1 && v <= 64) c->mark_ids_per_thread = v; }
+    if (const char* e = getenv("FC_MARK_DENSE")) { const int v = atoi(e); if (v >= 0 && v <= 4096) c->mark_dense = v; }
     if (const char* e = getenv("FC_SMALL_INDEX")) c->small_index = atoi(e) != 0;
-    if (const char* e = getenv("FC_PLAN_FOLD_TILES")) { const int v = atoi(e); if (v >= 0) c->plan_fold_tiles = v; }
+    if (const char* e = getenv("FC_PLAN_FOLD_TILES")) { const int v = atoi(e); if (v >= 0) c->split_tiles = v; }
     if (const char* e = getenv("FC_EVICT_EARLY")) c->evict_early = atoi(e);
     c->NB = cdiv(cdiv(N, 32), RT_WORDS);
     const size_t words = (size_t)c->NB * RT_WORDS;
@@ -271,9 +270,8 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     FC_HIP(hipMalloc((void**)&c->hitpart, MARK_HIT_PARTS * 4));
     FC_HIP(hipMalloc((void**)&c->bsum, (size_t)c->NB * 4));
     FC_HIP(hipMalloc((void**)&c->ssum, (size_t)c->NB * SUB_TILES * 4));
-    FC_HIP(hipMalloc((void**)&c->usum, (size_t)c->NB * 4));
+    FC_HIP(hipMalloc((void**)&c->gsum, (size_t)cdiv(c->NB, GROUP_TILES) * sizeof(int4)));
     for (int32_t*& p : c->plan) FC_HIP(hipMalloc((void**)&p, PLAN_WORDS * 4));
-    FC_HIP(hipMalloc((void**)&c->tile_plan, (size_t)c->NB * sizeof(int4)));
     c->dma_evict = (flags & FC_EVICT_DMA) != 0;
     c->dirty_track = (flags & FC_DIRTY_TRACK) != 0;
     for (auto& set : c->lists)
@@ -578,7 +576,7 @@ int cache_reserve(fc_cache* c, int64_t max_ids, int32_t pipelined) {
     FC_HIP(hipSetDevice(c->device));
     FC_TRY(ensure_rbuf(c, max_ids));
     FC_TRY(reserve_bwd(c, max_ids));
-    (void)mark_bytes(c, max_ids);      // without room for them the marks stay bits
+    FC_TRY(ensure_marks(c));
     c->plans_ahead |= pipelined != 0;
     if (pipelined && !(c->flags & FC_TRANSMIT_STAGED))
         for (int k = 0; k < 2; ++k) if (!ensure_arrival_block(c, k)) return FC_ERR_OOM_DEVICE;

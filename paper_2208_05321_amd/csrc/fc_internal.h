@@ -18,11 +18,11 @@ constexpr int WAVE = 64;
 constexpr int RT_THREADS = 256;
 constexpr int RT_WORDS = RT_THREADS * 4;
 constexpr int SUB_TILES = 8;                      // each tile's counts are also kept per eighth (4096 ranks)
-constexpr int PLAN_FOLD_TILES = 1024;             // up to this many tiles the emitting kernel plans for itself, with SUB_TILES workgroups to a tile
+constexpr int SPLIT_TILES = 1024;                 // up to this many tiles the emitting kernel has SUB_TILES workgroups to a tile
+constexpr int GROUP_TILES = 16;                   // tiles whose counts are added up
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size
 constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead
-constexpr int64_t MARKB_ROWS_PER_ID = 32;         // byte marks up to this many rows per id of the batch
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;
 constexpr int RS_ITEMS = 8;                      // keys per thread
@@ -65,7 +65,7 @@ enum HostWord { HW_STATUS = 0, HW_UNIQUE, HW_MISS, HW_NEED, HW_HITS, HW_NFREE, H
 struct HostCtl { uint64_t word[HOST_REC_WORDS]; };       // value in the low half, ticket in the high half
 
 enum ProfItem {
-    P_REMAP_MARK = 0, P_RANK_COUNT, P_RANK_PLAN, P_RANK_EMIT, P_EVICT_GATHER, P_EVICT_STORE, P_FREE_COUNT, P_FREE_PICK,
+    P_REMAP_MARK = 0, P_RANK_COUNT, P_RANK_EMIT, P_EVICT_GATHER, P_EVICT_STORE, P_FREE_COUNT, P_FREE_PICK,
     P_MISS_FILL, P_SLOTS_OUT, P_BAG_FWD, P_SORT_HIST, P_SORT_SCAN, P_SORT_SCATTER, P_BWD_REDUCE, P_BWD_FIXUP,
     P_H2D_BLOCK, P_D2H_BLOCK, P_FLUSH_ROWS, P_ROWS_IN, P_COUNT
 };
@@ -100,7 +100,7 @@ struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, tran
 struct IndexRun {
     int32_t ticket = 0;
     int64_t n = 0, num_bags = 0;
-    bool small = false, small_slots = false, bytes = false;
+    bool small = false, small_slots = false;
     int buf = 0, transit_base = -1;
 };
 struct PresortRec {
@@ -168,7 +168,7 @@ struct fc_cache {
     bool fwd_sorted = true;         // one-lookup-per-bag batches: forward in slot order when the pairs are sorted ahead of time (tuning: FC_FWD_SORTED=0)
     bool last_one_per_bag = false;  // the batch of the latest index half has that shape
     int fwd_bags = 4;               // bags per row-group of the forward kernel for one-lookup-per-bag batches: 1, 2 or 4 (tuning: FC_FWD_BAGS)
-    int mark_ids_per_thread = 2;    // ids per thread of the marking kernel (tuning: FC_MARK_IPT)
+    int mark_dense = 4;             // the marks of this many ranks per id of a batch are read one and all (tuning: FC_MARK_DENSE)
     // cap on the workgroups of the miss fill (tuning: FC_FILL_BLOCKS).  Default transmitter, 60 k rows of 512 bytes both ways / 35 k in:
     // 64 1216 / 460, 128 1191 / 471, 256 1201 / 452, 512 1223 / 458, 1024 1255 / 468 us a step.
     int fill_blocks = 256;          // 40 with FC_EVICT_DMA:
@@ -186,20 +186,18 @@ struct fc_cache {
     int32_t* rank_slot = nullptr;   // [N]  cpu_row_idx -> gpu_row_idx, -1 = not resident
     int32_t* slot_rank = nullptr;   // [C]  gpu_row_idx -> cpu_row_idx, -1 = empty
     float* cache = nullptr;         // [C][D]
-    uint32_t* ubits = nullptr;      // rank-space bitmap: rows used by the current batch (zero between calls if ubits_clean)
-    bool ubits_clean = true;
-    uint8_t* ubytes = nullptr;      // rank-space byte marks (zero between calls), allocated with the first batch that uses them
-    bool ubytes_failed = false;
+    uint32_t* ubits = nullptr;      // rank-space bitmap: rows used by the current batch
+    uint8_t* ubytes = nullptr;      // the same as a byte per rank, and per chunk of ranks that has any (zero between calls); allocated
+    uint8_t* uchunks = nullptr;     // with the first batch that uses them
     uint32_t* rbits = nullptr;      // rank-space bitmap: resident rows
     int32_t* tcount = nullptr;      // empty slots per tile of 1024 slots
     int32_t* hitpart = nullptr;     // [MARK_HIT_PARTS] per-workgroup access-level hit counts of the marking kernel
     int64_t NB = 0;                 // rank-space tiles
     uint32_t* bsum = nullptr;       // [NB] per-tile counts: missing, evictable (high half)
     uint32_t* ssum = nullptr;       // [NB * SUB_TILES] the same per sub-tile
-    int32_t* usum = nullptr;        // [NB] per-tile counts: used
+    int4* gsum = nullptr;           // [NB / GROUP_TILES] per group of tiles: missing, evictable, used (look-ahead)
     int32_t* plan[2] = {nullptr, nullptr};   // per list set, PL_*: the decision as kernels enqueued behind it read it
-    int4* tile_plan = nullptr;      // [NB] more than PLAN_FOLD_TILES tiles: missing rows before a tile, evictable rows above it
-    int plan_fold_tiles = fc::PLAN_FOLD_TILES;   // (tuning: FC_PLAN_FOLD_TILES)
+    int split_tiles = fc::SPLIT_TILES;           // (tuning: FC_PLAN_FOLD_TILES)
     bool small_index = true;        // one workgroup indexes a small batch (tuning: FC_SMALL_INDEX=0)
     int64_t nfree = 0;              // empty slots
     int err_set = 0;                // which of the two error words the next call uses
@@ -359,7 +357,7 @@ int dma_quiesce(fc_cache* c, hipStream_t st);
 // from_ranks: the slots are not written yet; the sort's first kernel derives them from the per-id ranks and writes them
 // to `slots_out` on its way (the slot write-out folded into the sort)
 int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr);
-bool mark_bytes(fc_cache* c, int64_t n);  // byte marks for a batch of n ids (allocates them on first use)
+int ensure_marks(fc_cache* c);             // byte marks
 int ensure_rbuf(fc_cache* c, int64_t n);  // per-id rank buffer for batches of n ids
 int reserve_bwd(fc_cache* c, int64_t n);   // sort scratch of all three sets and the partial rows for batches of n lookups
 int bwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags,
@@ -470,6 +468,12 @@ __device__ __forceinline__ uint64_t same_digit(int d, int radix_bits, uint64_t l
     return (uint64_t)hi << 32 | lo;
 }
 
+__device__ __forceinline__ int wave_sum(int x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o);
+    return x;  // valid in lane 0
+}
+
 template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT/64 ints */) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -500,12 +504,6 @@ __device__ __forceinline__ void report_to_host(HostCtl* h, int ticket, int statu
                 : lane == HW_HITS ? hits : lane == HW_NFREE ? nfree : lane == HW_ASYNC_FLAGS ? async_flags : batch_flags;
     if (lane < HOST_REC_WORDS)
         __hip_atomic_store(&h->word[lane], (uint64_t)(uint32_t)v | (uint64_t)(uint32_t)ticket << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o);
-    return x;  // valid in lane 0
 }
 
 }  // namespace fc

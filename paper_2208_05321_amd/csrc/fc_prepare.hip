@@ -13,167 +13,66 @@
 #include <omp.h>
 #include <string.h>
 
+#include <algorithm>
 #include <utility>
 
 namespace fc {
 
 // ---------------------------------------------------------------------------------------------------------
-// K1  ids -> frequency rank (idx_map lookup), mark the rank in ubits, count access-level hits, check offsets.
+// K1  ids -> frequency rank (idx_map lookup), mark the rank, count access-level hits, check offsets.
 //
-// Frequent ids are by construction the LOW ranks, and they are the ones repeated thousands of times in a
-// batch.  Device-scope atomics on one address serialise at the memory side (~100 ns each on this part), so
-// the low end of rank space is first marked in a per-workgroup LDS bitmap (fast LDS atomics) and merged into
-// the global bitmap once per workgroup; only the long tail of rare ranks goes to global atomics directly.
-// At most MARK_MAX_BLOCKS workgroups run, so a hot word sees at most that many global atomics.
+// A mark is a byte per rank, set by a plain store (every writer stores the same 1, and the L2s merge bytes): no atomics to queue up
+// on popular rows, nothing in LDS to clear and merge, and small workgroups that find room beside the previous batch's forward and
+// backward kernels.  Frequent ids are by construction the LOW ranks, so below `dense` ranks K2a reads every byte; above, marks
+// are few, and a second byte says which MARK_CHUNK ranks hold any, so that K2a reads those alone (and a batch whose popular
+// rows have moved to high ranks costs no more than the reads).  Bound by the latency of two random reads per id.
+// Measured (us, a bitmap set by atomics, popular ranks in LDS first, and its count -> these two): 426 k ids, 10 M rows 25.6 + 6.3 ->
+// 8.8 + 6.4; 53 k ids, 4 M rows 14.0 + 3.7 -> 7.0 + 5.2; 1.7 M ids, 100 M rows, beside backward 66-74 + 5.8 -> 41-46 + 13.  `dense` at
+// 2 / 4 / 8 / 32 ranks per id, K2a alone: 12.7 / 13.1 / 12.8 / 17.2 at 100 M rows, 5.5 / 5.9 / 5.7 / 6.3 at 10 M; without the chunks (all of the
+// 100 M bytes read) 26.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int MARK_THREADS = 1024;
-constexpr int MARK_LDS_WORDS = 12288;      // 48 KB: ranks below 393,216
-constexpr int MARK_MAX_BLOCKS = 256;
+constexpr int MARK_THREADS = 256, MARK_ITEMS = 4;
+constexpr int MARK_CHUNK = 256;
 
 __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __restrict__ ids, int n,
-                                                             const int64_t* __restrict__ offsets, int num_bags,
-                                                             const int32_t* __restrict__ freq_rank, int64_t N,
-                                                             uint32_t* ubits, const uint32_t* __restrict__ rbits,
-                                                             int32_t* __restrict__ rbuf, uint32_t* err,
-                                                             int32_t* __restrict__ hitpart, int per_block,
-                                                             int lds_words) {
-    __shared__ uint32_t low[MARK_LDS_WORDS];
-    __shared__ int red[MARK_THREADS / 64];
-    const int tid = threadIdx.x;
-    for (int w = tid; w < lds_words; w += MARK_THREADS) low[w] = 0;
-    __syncthreads();
-    const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
-    const int64_t begin = (int64_t)blockIdx.x * per_block;
-    const int64_t end = begin + per_block < work ? begin + per_block : work;
-    int hits = 0;
-    uint32_t flags = 0;
-    // four ids per thread and round: all loads of a stage are issued before any of them is waited for
-    for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * MARK_THREADS) {
-        int64_t id[4];
-        int r[4];
-        uint32_t rb[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = i0 + (int64_t)k * MARK_THREADS;
-            id[k] = (i < end && i < n) ? ids[i] : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = i0 + (int64_t)k * MARK_THREADS;
-            r[k] = -1;
-            if (i < end && i < n) {
-                if (id[k] < 0 || id[k] >= N) flags |= EF_ID_RANGE;
-                else r[k] = freq_rank[id[k]];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) rb[k] = r[k] >= 0 ? rbits[(uint32_t)r[k] >> 5] : 0u;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = i0 + (int64_t)k * MARK_THREADS;
-            if (i < end && i < n) {
-                if (r[k] >= 0) {
-                    const uint32_t w = (uint32_t)r[k] >> 5, bit = 1u << (r[k] & 31);
-                    if (w < (uint32_t)lds_words) atomicOr(&low[w], bit);
-                    // rare ranks: bits are only ever set during this kernel, so a read that sees the bit is final
-                    else if (!(ubits[w] & bit)) atomicOr(&ubits[w], bit);
-                    hits += (rb[k] & bit) != 0;
-                }
-                rbuf[i] = r[k];
-            }
-            if (i < end && i <= num_bags) {
-                const int64_t o = offsets[i];
-                if (o != i) flags |= EF_NOT_ONE_PER_BAG;
-                if (i == 0 && o != 0) flags |= EF_BAD_OFFSETS;
-                if (i == num_bags && o != (int64_t)n) flags |= EF_BAD_OFFSETS;
-                if (i < num_bags && offsets[i + 1] < o) flags |= EF_BAD_OFFSETS;
-            }
-        }
-    }
-    __syncthreads();
-    // Merge into the global bitmap: LDS words first, then all global reads at once, then the atomics still needed.
-    // Every workgroup holds the hottest words, so each starts at a different word: by the time most of them reach a
-    // hot word its bits are already set and the (coherent) read spares the atomic.
-    const int rot = (int)(((int64_t)blockIdx.x * lds_words) / gridDim.x);
-    constexpr int FL = MARK_LDS_WORDS / MARK_THREADS;
-    uint32_t v[FL], g[FL];
-    int wi[FL];
-#pragma unroll
-    for (int k = 0; k < FL; ++k) {
-        int w = k * MARK_THREADS + tid;
-        v[k] = 0;
-        if (w < lds_words) {
-            w += rot;
-            if (w >= lds_words) w -= lds_words;
-            v[k] = low[w];
-        }
-        wi[k] = w;
-    }
-#pragma unroll
-    for (int k = 0; k < FL; ++k)
-        g[k] = v[k] ? __hip_atomic_load(&ubits[wi[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0xFFFFFFFFu;
-#pragma unroll
-    for (int k = 0; k < FL; ++k)
-        if (v[k] & ~g[k]) atomicOr(&ubits[wi[k]], v[k]);
-    hits = wave_sum(hits);
-    if ((tid & 63) == 0) red[tid >> 6] = hits;
-    __syncthreads();
-    if (tid == 0) {
-        int s = 0;
-#pragma unroll
-        for (int k = 0; k < MARK_THREADS / 64; ++k) s += red[k];
-        hitpart[blockIdx.x] = s;
-    }
-    if (flags) atomicOr(err, flags);
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// K1, byte marks: the same, with one byte per rank in place of one bit.  Setting a byte is a plain store (every writer stores
-// the same 1, and the L2s merge bytes), so there are no atomics to queue up, no bitmap in LDS to clear and merge, and small
-// workgroups that find room beside the previous batch's forward and backward kernels; what it costs is reading N bytes
-// instead of N / 8 in K2a.  Bound by the latency of two random reads per id.
-// Measured (us, k_remap_mark + k_rank_count -> these two, in the schedules of the benchmark): 426 k ids, 10 M rows 25.6 + 6.3
-// -> 10.5 + 6.7 (plain) and 32.5 + 7.3 -> 16.6 + 11.5 (pipelined); 1.7 M ids, 100 M rows 81 + 14 -> 38 + 26 (a batch that keeps
-// its bits all the same, for the bytes: mark_bytes).  (The bitmap kernel with 256-thread workgroups and an 8 KB bitmap in LDS took
-// 74 and 154: more of its marks are then global atomics.)
-// ---------------------------------------------------------------------------------------------------------
-constexpr int MARKB_THREADS = 256, MARKB_ITEMS = 4;
-
-__global__ __launch_bounds__(MARKB_THREADS) void k_remap_bytes(const int64_t* __restrict__ ids, int n,
                                                                const int64_t* __restrict__ offsets, int num_bags,
                                                                const int32_t* __restrict__ freq_rank, int64_t N,
-                                                               uint8_t* __restrict__ ubytes, const uint32_t* __restrict__ rbits,
-                                                               int32_t* __restrict__ rbuf, uint32_t* err, int32_t* __restrict__ hitpart) {
-    __shared__ int red[MARKB_THREADS / 64];
+                                                               uint8_t* __restrict__ ubytes, uint8_t* __restrict__ uchunks, int dense,
+                                                               const uint32_t* __restrict__ rbits,
+                                                               int32_t* __restrict__ rbuf, uint32_t* err, int32_t* __restrict__ hitpart,
+                                                               int4* __restrict__ gsum, int groups) {
+    __shared__ int red[MARK_THREADS / 64];
     const int tid = threadIdx.x;
+    for (int g = blockIdx.x * MARK_THREADS + tid; g < groups; g += gridDim.x * MARK_THREADS) gsum[g] = make_int4(0, 0, 0, 0);      // for K2a
     const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
     int hits = 0;
     uint32_t flags = 0;
-    for (int64_t i0 = (int64_t)blockIdx.x * (MARKB_ITEMS * MARKB_THREADS) + tid; i0 < work; i0 += (int64_t)gridDim.x * (MARKB_ITEMS * MARKB_THREADS)) {
-        int64_t id[MARKB_ITEMS], o0[MARKB_ITEMS], o1[MARKB_ITEMS];
-        int r[MARKB_ITEMS];
-        uint32_t rb[MARKB_ITEMS];
+    for (int64_t i0 = (int64_t)blockIdx.x * (MARK_ITEMS * MARK_THREADS) + tid; i0 < work; i0 += (int64_t)gridDim.x * (MARK_ITEMS * MARK_THREADS)) {
+        int64_t id[MARK_ITEMS], o0[MARK_ITEMS], o1[MARK_ITEMS];
+        int r[MARK_ITEMS];
+        uint32_t rb[MARK_ITEMS];
 #pragma unroll
-        for (int k = 0; k < MARKB_ITEMS; ++k) {
-            const int64_t i = i0 + k * MARKB_THREADS;
+        for (int k = 0; k < MARK_ITEMS; ++k) {
+            const int64_t i = i0 + k * MARK_THREADS;
             id[k] = i < n ? ids[i] : 0;
             o0[k] = i <= num_bags ? offsets[i] : 0;
             o1[k] = i < num_bags ? offsets[i + 1] : o0[k];
         }
 #pragma unroll
-        for (int k = 0; k < MARKB_ITEMS; ++k) {
+        for (int k = 0; k < MARK_ITEMS; ++k) {
             const bool ok = (uint64_t)id[k] < (uint64_t)N;
             if (!ok) flags |= EF_ID_RANGE;
             r[k] = ok ? freq_rank[id[k]] : -1;
         }
 #pragma unroll
-        for (int k = 0; k < MARKB_ITEMS; ++k) rb[k] = r[k] >= 0 ? rbits[(uint32_t)r[k] >> 5] : 0u;
+        for (int k = 0; k < MARK_ITEMS; ++k) rb[k] = r[k] >= 0 ? rbits[(uint32_t)r[k] >> 5] : 0u;
 #pragma unroll
-        for (int k = 0; k < MARKB_ITEMS; ++k) {
-            const int64_t i = i0 + k * MARKB_THREADS;
+        for (int k = 0; k < MARK_ITEMS; ++k) {
+            const int64_t i = i0 + k * MARK_THREADS;
             if (i < n) {
                 if (r[k] >= 0) {
                     ubytes[r[k]] = 1;
+                    if (r[k] >= dense) uchunks[r[k] / MARK_CHUNK] = 1;
                     hits += (rb[k] >> (r[k] & 31)) & 1u;
                 }
                 rbuf[i] = r[k];
@@ -190,135 +89,113 @@ __global__ __launch_bounds__(MARKB_THREADS) void k_remap_bytes(const int64_t* __
     if (tid == 0) {
         int s = 0;
 #pragma unroll
-        for (int k = 0; k < MARKB_THREADS / 64; ++k) s += red[k];
+        for (int k = 0; k < MARK_THREADS / 64; ++k) s += red[k];
         hitpart[blockIdx.x] = s;
     }
     if (flags) atomicOr(err, flags);
 }
 
-// K2a, byte marks: the tile's 32768 bytes become its bitmap words (all of them written), the set ones are cleared, and the
-// counts are those of k_rank_count.  A lane turns 16 bytes into 16 bits with four 4-byte dot products.
+// ---------------------------------------------------------------------------------------------------------
+// K2a  per rank-space tile: rows used, rows missing, rows evictable.  The tile's 32768 marks become its bitmap words (all of
+//      them written) and the set ones are cleared.  A lane turns 16 bytes into 16 bits with four 4-byte dot products.
+//      On the way (DMA evict transmitter): the block that this batch's victims will go to has reached the host table, so
+//      rows still marked as in transit in it become plain "not resident" (what k_clear_transit does; folded in here
+//      because nothing before K2c reads rank_slot, and a launch of its own lengthened the index chain).
+// ---------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t bits_of(uint4 v) {
     const uint32_t lo = __builtin_amdgcn_udot4(v.y, 0x80402010u, __builtin_amdgcn_udot4(v.x, 0x08040201u, 0u, false), false);
     const uint32_t hi = __builtin_amdgcn_udot4(v.w, 0x80402010u, __builtin_amdgcn_udot4(v.z, 0x08040201u, 0u, false), false);
     return lo | hi << 8;
 }
 
-// part[w][k]: missing, and evictable in the high half, of sub-tile k as wavefront w saw them; last: used
-__device__ __forceinline__ void tile_counts(int (*part)[SUB_TILES + 1], uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum,
-                                            int32_t* __restrict__ usum, uint32_t* next_err) {
-    if (threadIdx.x >= 64) return;
-    const int k = threadIdx.x;
-    uint32_t v = 0;
-    if (k <= SUB_TILES)
-        for (int w = 0; w < RT_THREADS / 64; ++w) v += (uint32_t)part[w][k];
-    if (k < SUB_TILES) ssum[(size_t)blockIdx.x * SUB_TILES + k] = v;
-    if (k == SUB_TILES) usum[blockIdx.x] = (int)v;
-    uint32_t t = k < SUB_TILES ? v : 0;                // 32768 at most, each
-#pragma unroll
-    for (int o = SUB_TILES / 2; o > 0; o >>= 1) t += (uint32_t)__shfl_down((int)t, o);
-    if (k == 0) {
-        bsum[blockIdx.x] = t;
-        if (blockIdx.x == 0) *next_err = 0;            // the next call's error word
-    }
-}
+// A wavefront counts SUB_TILES / 4 sub-tiles of 4096 ranks, a lane 64 neighbouring ranks of each: four lanes share a chunk.
+constexpr int WAVE_SUBS = SUB_TILES / (RT_THREADS / 64);
 
-__global__ __launch_bounds__(RT_THREADS) void k_count_bytes(uint4* ubytes16, uint16_t* __restrict__ ubits16,
-                                                            const uint16_t* __restrict__ rbits16,
-                                                            const uint16_t* __restrict__ pbits16, int protect_prev,
-                                                            uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int32_t* __restrict__ usum,
-                                                            const int32_t* __restrict__ landed_ranks, int landed, int landed_base,
-                                                            int32_t* rank_slot, uint32_t* next_err) {
-    __shared__ int part[RT_THREADS / 64][SUB_TILES + 1];
-    for (int j = blockIdx.x * RT_THREADS + threadIdx.x; j < landed; j += gridDim.x * RT_THREADS) {
-        const int r = landed_ranks[j];
-        if (rank_slot[r] == -2 - (landed_base + j)) rank_slot[r] = -1;
-    }
-    constexpr int PER = RT_WORDS * 2 / RT_THREADS;          // 16-rank pieces per thread
-    const size_t p0 = (size_t)blockIdx.x * (RT_WORDS * 2) + threadIdx.x;
-    uint4 v[PER];
-    uint32_t q[PER], pv[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) v[k] = ubytes16[p0 + k * RT_THREADS];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) q[k] = rbits16[p0 + k * RT_THREADS];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) pv[k] = protect_prev ? pbits16[p0 + k * RT_THREADS] : 0;
-    static_assert(PER == SUB_TILES, "piece k of every thread lies in sub-tile k");
-    int cu = 0;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const uint32_t u = bits_of(v[k]);
-        if (u) ubytes16[p0 + k * RT_THREADS] = make_uint4(0, 0, 0, 0);
-        ubits16[p0 + k * RT_THREADS] = (uint16_t)u;
-        cu += __popc(u);
-        // look-ahead: rows of the previously prepared batch are not evictable either
-        const int c = wave_sum(__popc(u & ~q[k]) | __popc(q[k] & ~pv[k] & ~u) << 16);
-        if (lane == 0) part[w][k] = c;
-    }
-    cu = wave_sum(cu);
-    if (lane == 0) part[w][SUB_TILES] = cu;
-    __syncthreads();
-    tile_counts(part, bsum, ssum, usum, next_err);
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// K2a  per rank-space tile: rows used, rows missing, rows evictable.
-//      On the way (DMA evict transmitter): the block that this batch's victims will go to has reached the host table, so
-//      rows still marked as in transit in it become plain "not resident" (what k_clear_transit does; folded in here
-//      because nothing before K3 reads rank_slot, and a launch of its own lengthened the index chain).
-// ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(RT_THREADS) void k_rank_count(const uint4* __restrict__ ubits4,
-                                                           const uint4* __restrict__ rbits4,
-                                                           const uint4* __restrict__ pbits4, int protect_prev,
-                                                           uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int32_t* __restrict__ usum,
+__global__ __launch_bounds__(RT_THREADS) void k_rank_count(uint4* ubytes16, uint8_t* uchunks, int dense_tiles, uint2* __restrict__ ubits64,
+                                                           const uint2* __restrict__ rbits64, const uint2* __restrict__ pbits64, int protect_prev,
+                                                           uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int4* gsum,
                                                            const int32_t* __restrict__ landed_ranks, int landed, int landed_base,
                                                            int32_t* rank_slot, uint32_t* next_err) {
-    __shared__ int part[RT_THREADS / 64][SUB_TILES + 1];
+    static_assert(SUB_TILES * 64 * 64 == RT_WORDS * 32 && MARK_CHUNK == 4 * 64, "");
+    __shared__ int part[SUB_TILES], upart[RT_THREADS / 64];
     for (int j = blockIdx.x * RT_THREADS + threadIdx.x; j < landed; j += gridDim.x * RT_THREADS) {
         const int r = landed_ranks[j];
         if (rank_slot[r] == -2 - (landed_base + j)) rank_slot[r] = -1;
     }
-    const size_t idx = (size_t)blockIdx.x * RT_THREADS + threadIdx.x;
-    const uint4 u = ubits4[idx];
-    uint4 r = rbits4[idx];
-    const int cm0 = __popc(u.x & ~r.x) + __popc(u.y & ~r.y) + __popc(u.z & ~r.z) + __popc(u.w & ~r.w);
-    if (protect_prev) {        // look-ahead: rows of the previously prepared batch are not evictable either
-        const uint4 p = pbits4[idx];
-        r.x &= ~p.x; r.y &= ~p.y; r.z &= ~p.z; r.w &= ~p.w;
-    }
-    int cu = __popc(u.x) + __popc(u.y) + __popc(u.z) + __popc(u.w);
-    const int cc = __popc(r.x & ~u.x) + __popc(r.y & ~u.y) + __popc(r.z & ~u.z) + __popc(r.w & ~u.w);
-    // a sub-tile is 32 threads: half a wavefront
-    static_assert(RT_THREADS / SUB_TILES == 32, "");
+    const bool dense = (int)blockIdx.x < dense_tiles;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int c = cm0 | cc << 16;
+    const size_t p0 = (size_t)blockIdx.x * (RT_WORDS / 2) + w * (WAVE_SUBS * 64) + lane;      // 64-rank pieces
+    uint4 v[WAVE_SUBS][4];
+    uint2 q[WAVE_SUBS], pv[WAVE_SUBS];
+    uint32_t any[WAVE_SUBS];
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) c += __shfl_down(c, o, 32);
-    if (threadIdx.x < (RT_THREADS / 64) * (SUB_TILES + 1)) part[threadIdx.x / (SUB_TILES + 1)][threadIdx.x % (SUB_TILES + 1)] = 0;
-    __syncthreads();
-    if ((lane & 31) == 0) part[w][threadIdx.x / 32] = c;
+    for (int k = 0; k < WAVE_SUBS; ++k) any[k] = dense ? 1u : uchunks[(p0 + k * 64) / 4];
+#pragma unroll
+    for (int k = 0; k < WAVE_SUBS; ++k) q[k] = rbits64[p0 + k * 64];
+#pragma unroll
+    for (int k = 0; k < WAVE_SUBS; ++k) pv[k] = protect_prev ? pbits64[p0 + k * 64] : make_uint2(0, 0);
+#pragma unroll
+    for (int k = 0; k < WAVE_SUBS; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[k][j] = make_uint4(0, 0, 0, 0);
+        if (any[k]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[k][j] = ubytes16[(p0 + k * 64) * 4 + j];
+        }
+    }
+    int cu = 0;
+#pragma unroll
+    for (int k = 0; k < WAVE_SUBS; ++k) {
+        uint32_t u[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            u[j] = bits_of(v[k][j]);
+            if (u[j]) ubytes16[(p0 + k * 64) * 4 + j] = make_uint4(0, 0, 0, 0);
+        }
+        if (!dense && any[k] && (lane & 3) == 0) uchunks[(p0 + k * 64) / 4] = 0;       // its four lanes have read it, in one instruction
+        const uint2 uu = make_uint2(u[0] | u[1] << 16, u[2] | u[3] << 16);
+        ubits64[p0 + k * 64] = uu;
+        cu += __popc(uu.x) + __popc(uu.y);
+        // look-ahead: rows of the previously prepared batch are not evictable either
+        const int miss = __popc(uu.x & ~q[k].x) + __popc(uu.y & ~q[k].y);
+        const int evictable = __popc(q[k].x & ~pv[k].x & ~uu.x) + __popc(q[k].y & ~pv[k].y & ~uu.y);
+        const int c = wave_sum(miss | evictable << 16);
+        if (lane == 0) part[w * WAVE_SUBS + k] = c;
+    }
     cu = wave_sum(cu);
-    if (lane == 0) part[w][SUB_TILES] = cu;
+    if (lane == 0) upart[w] = cu;
     __syncthreads();
-    tile_counts(part, bsum, ssum, usum, next_err);
+    if (threadIdx.x < SUB_TILES) ssum[(size_t)blockIdx.x * SUB_TILES + threadIdx.x] = (uint32_t)part[threadIdx.x];
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;                        // 32768 at most in either half
+        int used = 0;
+#pragma unroll
+        for (int k = 0; k < SUB_TILES; ++k) t += (uint32_t)part[k];
+#pragma unroll
+        for (int k = 0; k < RT_THREADS / 64; ++k) used += upart[k];
+        bsum[blockIdx.x] = t;
+        // (cleared by K1; most tiles of a large table have nothing to add)
+        int* g = reinterpret_cast<int*>(&gsum[blockIdx.x / GROUP_TILES]);
+        if (t & 0xffff) atomicAdd(&g[0], (int)(t & 0xffff));
+        if (t >> 16) atomicAdd(&g[1], (int)(t >> 16));
+        if (protect_prev && used) atomicAdd(&g[2], used);
+        if (blockIdx.x == 0) *next_err = 0;    // the next call's error word
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------
 // K2b  totals, the call's status, evict_num = numel(miss) - empty slots, and for a tile: where its missing ranks go in the
 //      list, how many victims it gives up (from the top rank down) and where those go.
 //
-//      All of it is a sum over the tiles' counts, one word each, so every workgroup of K2c works it out for its own tile (at most
-//      4 KB of reads from L2, 8 KB with the look-ahead) instead of waiting for a kernel of one workgroup in between (6 us at 306 tiles, 11-14 at
-//      3052, and a launch), and the first one reports to the host before it starts on its tile.  Above PLAN_FOLD_TILES tiles
-//      (33 M rows) those reads grow with the square of the tiles (3052 tiles, beside forward and backward: 104 us against
-//      18 + 29 with a plan of its own): there one workgroup plans for all.
+//      All of it is a sum over the tiles' counts.  K2a adds those of GROUP_TILES neighbours up (its atomics meet at most that often
+//      on a word), so every workgroup of K2c works it out for its own tile from the sums of the groups and the counts of its own
+//      group, and the first one reports to the host before it starts on its tile; a kernel of one workgroup in between took 6 us at
+//      306 tiles and 11-16 at 3052, and a launch (3052 tiles, planning + emitting: 15.7 + 12.6 -> 20).
 //      (Tried: letting the last workgroup of K2a to finish do this, found by an atomic ticket.  One ticket per tile on
 //      one address costs about 100 ns each on this part, 300 us at 3052 tiles: slower than the launch it saves.)
 // ---------------------------------------------------------------------------------------------------------
 struct PlanArgs {
-    const uint32_t *bsum, *ssum; const int32_t* usum;    // K2a's counts
+    const uint32_t *bsum, *ssum; const int4* gsum;       // K2a's counts: per tile, sub-tile and group of tiles
     const uint32_t* err; const uint32_t* async_flags;
     const int32_t* hitpart; HostCtl* hctl;
     int32_t* plan;                                   // status, victims, missing rows: the decision for kernels enqueued behind
@@ -341,52 +218,34 @@ __device__ __forceinline__ PlanTotals plan_totals(const PlanArgs& a, int used, i
     return t;
 }
 
-template <int NT>
-__device__ __forceinline__ int block_sum(int v, int* lds /* NT / 64 ints */) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int s = 0;
+// K sums at once
+template <int NT, int K>
+__device__ __forceinline__ void block_sums(int (&v)[K], int* lds /* K * NT / 64 ints */) {
 #pragma unroll
-    for (int k = 0; k < NT / 64; ++k) s += lds[k];
+    for (int j = 0; j < K; ++j) {
+        v[j] = wave_sum(v[j]);
+        if ((threadIdx.x & 63) == 0) lds[j * (NT / 64) + (threadIdx.x >> 6)] = v[j];
+    }
     __syncthreads();
-    return s;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        v[j] = 0;
+#pragma unroll
+        for (int k = 0; k < NT / 64; ++k) v[j] += lds[j * (NT / 64) + k];
+    }
+    __syncthreads();
 }
 
 template <int NT>
 __device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals& t, int* lds) {
-    int mine = 0;
-    for (int k = threadIdx.x; k < a.nmark; k += NT) mine += a.hitpart[k];
-    const int hits = block_sum<NT>(mine, lds);
+    int sum[1] = {0};
+    for (int k = threadIdx.x; k < a.nmark; k += NT) sum[0] += a.hitpart[k];
+    block_sums<NT, 1>(sum, lds);
+    const int hits = sum[0];
     if (threadIdx.x == 0) { a.plan[PL_STATUS] = t.status; a.plan[PL_NEED] = t.need; a.plan[PL_MISS] = t.miss; }
     if (threadIdx.x < HOST_REC_WORDS)
         report_to_host(a.hctl, a.ticket, t.status, t.used, t.miss, t.need, hits, t.status == FC_OK ? a.nfree + t.need - t.miss : a.nfree,
                        (int)*a.async_flags, (int)(*a.err & EF_NOT_ONE_PER_BAG), threadIdx.x);
-}
-
-// More than PLAN_FOLD_TILES tiles: one workgroup writes what K2c would work out.
-constexpr int PLAN_THREADS = 256;      // finds room beside the previous batch's forward kernel at once; 1024 threads waited for it
-__global__ __launch_bounds__(PLAN_THREADS) void k_rank_plan(PlanArgs a, int4* __restrict__ tile_plan) {
-    __shared__ int lds[PLAN_THREADS / 64];
-    const int tid = threadIdx.x;
-    int mu = 0, mm = 0, mc = 0;
-    for (int b = tid; b < a.NB; b += PLAN_THREADS) {
-        const uint32_t v = a.bsum[b];
-        mu += a.usum[b]; mm += (int)(v & 0xffff); mc += (int)(v >> 16);
-    }
-    const int U = block_sum<PLAN_THREADS>(mu, lds), M = block_sum<PLAN_THREADS>(mm, lds), E = block_sum<PLAN_THREADS>(mc, lds);
-    const PlanTotals t = plan_totals(a, U, M, E);
-    plan_report<PLAN_THREADS>(a, t, lds);
-    int cm = 0, cc = 0;                        // missing / evictable rows of the tiles before this round's
-    for (int base = 0; base < a.NB; base += PLAN_THREADS) {
-        const int b = base + tid;
-        const uint32_t v = b < a.NB ? a.bsum[b] : 0;
-        const int m = (int)(v & 0xffff), c = (int)(v >> 16);
-        int totm, totc;
-        const int pm = cm + block_excl_scan<PLAN_THREADS>(m, totm, lds), pc = cc + block_excl_scan<PLAN_THREADS>(c, totc, lds);
-        if (b < a.NB) tile_plan[b] = make_int4(pm, E - pc - c, 0, 0);
-        cm += totm; cc += totc;
-    }
 }
 
 constexpr int FREE_TILE = 1024;
@@ -397,7 +256,7 @@ constexpr int FREE_TILE = 1024;
 //      by all threads side by side, all random reads of a thread before the first is waited for.
 //      SPLIT workgroups share a tile.  Popularity falls off as a power, so the tiles just beyond the cached ranks hold ten
 //      times the average number of missing and evicted ranks (13,000 of each in one tile at 142 k slots of 9.4 M rows), and
-//      with a tile to a workgroup, one of those was the kernel's duration: 8 to a tile where every workgroup plans for itself;
+//      with a tile to a workgroup, one of those was the kernel's duration: 8 to a tile up to SPLIT_TILES tiles (33 M rows);
 //      beyond, tiles are many and ranks spread thinner, and 8 times the workgroups take longer than the fullest tile.
 //      Measured (us by events, k_rank_plan + one workgroup per tile with the bits handled one by one -> this): 852 k ids, 9.4 M rows
 //      8.2 + 32 -> 16; 426 k ids, 10 M rows 7.5 + 20 -> 15 (plain), 10 + 29 -> 18 (pipelined).
@@ -419,79 +278,64 @@ __device__ __forceinline__ void store_bits(uint32_t* p, size_t i, const Bits<4>&
 }
 
 template <int SPLIT>
-__global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint32_t* rbits, uint32_t* pbits, PlanArgs a,
-                                                          const int4* __restrict__ tile_plan,
+__global__ __launch_bounds__(RT_THREADS) void k_rank_emit(const uint32_t* __restrict__ ubits, uint32_t* rbits, const uint32_t* __restrict__ pbits, PlanArgs a,
                                                           int32_t* __restrict__ miss_ranks, int32_t* __restrict__ vrank,
                                                           int32_t* __restrict__ vslot, int32_t* rank_slot,
                                                           int32_t* slot_rank, int transit_base,
-                                                          int transit_rows, int32_t* __restrict__ fill_src, int keep_bits) {
-    // keep_bits (byte marks): the bitmap is rewritten by the next K2a and becomes pbits by a swap of pointers
+                                                          int transit_rows, int32_t* __restrict__ fill_src) {
+    // (ubits is rewritten by a later K2a in full and becomes pbits by a swap of pointers)
     static_assert(SPLIT == 1 || (SPLIT == 8 && RT_WORDS == 4 * RT_THREADS), "a thread holds 16 bits or four words");
     constexpr int WORDS = SPLIT == 1 ? 4 : 1;
     constexpr int RANKS = SPLIT == 1 ? 128 : 16;           // per thread
-    constexpr bool FOLD = SPLIT > 1;                       // no k_rank_plan has run
     using B = Bits<WORDS>;
-    __shared__ int lds[RT_THREADS / 64];
+    __shared__ int lds[7 * RT_THREADS / 64];
     __shared__ uint16_t mlist[EMIT_LIST], vlist[EMIT_LIST];
     const int tid = threadIdx.x, me = blockIdx.x / SPLIT, sub = blockIdx.x % SPLIT;
     const size_t idx = (size_t)blockIdx.x * RT_THREADS + tid;
     const B u = load_bits(ubits, idx, B()), r = load_bits(rbits, idx, B());
     B p{};
-    if (!keep_bits || a.protect_prev) p = load_bits(pbits, idx, B());
-    int status, need, mbase, above;
-    if (FOLD) {
-        int mu = 0, mm = 0, mc = 0, bm = 0, ac = 0;
-#pragma unroll 4
-        for (int b = tid; b < a.NB; b += RT_THREADS) {
-            const uint32_t v = a.bsum[b];
-            const int m = (int)(v & 0xffff), c = (int)(v >> 16);
-            mm += m; mc += c;
-            if (b < me) bm += m;
-            if (b > me) ac += c;
-            if (a.protect_prev) mu += a.usum[b];
-        }
-        const int U = a.protect_prev ? block_sum<RT_THREADS>(mu, lds) : 0;
-        const int M = block_sum<RT_THREADS>(mm, lds), E = block_sum<RT_THREADS>(mc, lds);
-        mbase = block_sum<RT_THREADS>(bm, lds);
-        above = block_sum<RT_THREADS>(ac, lds);
-        const PlanTotals t = plan_totals(a, U, M, E);
-        status = t.status; need = t.need;
-        if (blockIdx.x == 0) plan_report<RT_THREADS>(a, t, lds);
-    } else {
-        status = a.plan[PL_STATUS]; need = a.plan[PL_NEED];
-        const int4 tp = tile_plan[me];
-        mbase = tp.x; above = tp.y;
+    if (a.protect_prev) p = load_bits(pbits, idx, B());
+    // missing, evictable, used in all; missing before and evictable above this tile; both before this workgroup in the tile; bits here
+    int sum[7] = {0, 0, 0, 0, 0, 0, 0};
+    const int groups = (a.NB + GROUP_TILES - 1) / GROUP_TILES, mine = me / GROUP_TILES;
+    for (int g = tid; g < groups; g += RT_THREADS) {
+        const int4 v = a.gsum[g];
+        sum[0] += v.x; sum[1] += v.y; sum[2] += v.z;
+        if (g < mine) sum[3] += v.x;
+        if (g > mine) sum[4] += v.y;
     }
-    uint32_t anyu = 0, anyp = 0;
+    const int nb = mine * GROUP_TILES + tid;
+    if (tid < GROUP_TILES && nb < a.NB) {
+        const uint32_t v = a.bsum[nb];
+        if (nb < me) sum[3] += (int)(v & 0xffff);
+        if (nb > me) sum[4] += (int)(v >> 16);
+    }
+    if (SPLIT > 1 && tid >= 64 && tid < 64 + sub) {
+        const uint32_t v = a.ssum[me * SPLIT + tid - 64];
+        sum[3] += (int)(v & 0xffff);
+        sum[5] = (int)(v >> 16);
+    }
 #pragma unroll
-    for (int k = 0; k < WORDS; ++k) { anyu |= u.w[k]; anyp |= p.w[k]; }
-    if (status != FC_OK) {                 // failed call: forget the marks, touch nothing else
-        if (anyu && !keep_bits) store_bits(ubits, idx, B());
-        return;
-    }
-    const uint32_t guard = a.protect_prev ? 0xFFFFFFFFu : 0u;
+    for (int k = 0; k < WORDS; ++k) sum[6] |= (u.w[k] | r.w[k]) != 0;
+    block_sums<RT_THREADS, 7>(sum, lds);
+    const PlanTotals totals = plan_totals(a, sum[2], sum[0], sum[1]);
+    if (blockIdx.x == 0) plan_report<RT_THREADS>(a, totals, lds);
+    const int status = totals.status, need = totals.need, mbase = sum[3], above = sum[4];
+    if (status != FC_OK) return;           // failed call: K2a has cleared the marks, nothing else is touched
+    if (!sum[6]) return;                   // neither used nor resident rows here
     B mw, cw, vw{};
     int cm = 0, cc = 0;
 #pragma unroll
     for (int k = 0; k < WORDS; ++k) {
         mw.w[k] = u.w[k] & ~r.w[k];
-        cw.w[k] = r.w[k] & ~u.w[k] & ~(p.w[k] & guard);
+        cw.w[k] = r.w[k] & ~u.w[k] & ~p.w[k];
         cm += __popc(mw.w[k]);
         cc += __popc(cw.w[k]);
     }
     // victims of this tile: all but its `skip` lowest evictable ranks, the tiles above it having given theirs
     const int mine_c = (int)(a.bsum[me] >> 16);
     const int take = max(0, min(mine_c, need - above)), v0 = need - above - take;
-    int skip = mine_c - take;              // counted from this workgroup's first evictable rank from here on
-    if (SPLIT > 1) {                       // what the workgroups before this one in the tile list
-        int bm = 0, bc = 0;
-        for (int q = 0; q < sub; ++q) {
-            const uint32_t v = a.ssum[me * SPLIT + q];
-            bm += (int)(v & 0xffff); bc += (int)(v >> 16);
-        }
-        mbase += bm;
-        skip -= bc;
-    }
+    const int skip = mine_c - take - sum[5];   // counted from this workgroup's first evictable rank
     int both;
     const uint32_t pre = (uint32_t)block_excl_scan<RT_THREADS>((int)((uint32_t)cm | (uint32_t)cc << 16), both, lds);
     const int pm = (int)(pre & 0xffff), totm = (int)((uint32_t)both & 0xffff), totc = (int)((uint32_t)both >> 16);
@@ -560,9 +404,6 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_emit(uint32_t* ubits, uint3
         for (int k = 0; k < WORDS; ++k) { out.w[k] = (r.w[k] & ~vw.w[k]) | mw.w[k]; changed |= mw.w[k] | vw.w[k]; }
         if (changed) store_bits(rbits, idx, out);
     }
-    if (keep_bits) return;
-    if (anyu) store_bits(ubits, idx, B());
-    if (anyu | anyp) store_bits(pbits, idx, u);            // this batch is the "previous" one next time
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -733,24 +574,18 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
     return FC_OK;
 }
 
-__global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
-
-// Byte marks make the two kernels of a batch shorter (above), but K2a then reads N bytes beside forward and backward, and where HBM
-// binds the step that costs more than the shorter chain gives.  The line is a measured one and lies between the two batches below;
-// width of the rows and schedule, on which the second effect depends, do not enter it.
-// us a step, planned, bits / bytes, several runs each: 24 rows per id (426 k ids, 10 M rows) 128 columns 507-516 / 503-512, 32
-// columns 199-203 / 190-194; 59 rows per id (1.7 M ids, 100 M rows) 128 columns 548-570 / 578-579, 16 columns 286-328 / 283-310.
-// A map that could not be allocated leaves the bits.
-bool mark_bytes(fc_cache* c, int64_t n) {
-    if (c->N > MARKB_ROWS_PER_ID * n) return false;
-    if (!c->ubytes && !c->ubytes_failed) {
-        const size_t bytes = (size_t)c->NB * RT_WORDS * 32;
-        if (hipMalloc((void**)&c->ubytes, bytes) != hipSuccess) { (void)hipGetLastError(); c->ubytes = nullptr; c->ubytes_failed = true; }
-        else if (hipMemset(c->ubytes, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-            (void)hipGetLastError(); (void)hipFree(c->ubytes); c->ubytes = nullptr; c->ubytes_failed = true;
-        }
-    }
-    return c->ubytes != nullptr;
+// The mark bytes (zero between calls), with the first batch that needs them.
+int ensure_marks(fc_cache* c) {
+    if (c->ubytes) return FC_OK;
+    const size_t ranks = (size_t)c->NB * RT_WORDS * 32;
+    FC_HIP(hipMalloc((void**)&c->uchunks, ranks / MARK_CHUNK));
+    FC_HIP(hipMemset(c->uchunks, 0, ranks / MARK_CHUNK));
+    FC_HIP(hipMalloc((void**)&c->ubytes, ranks));
+    hipError_t e = hipMemset(c->ubytes, 0, ranks);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) { (void)hipFree(c->ubytes); c->ubytes = nullptr; }
+    FC_HIP(e);
+    return FC_OK;
 }
 
 // Evicted rows stored by kernel: gather into a device block on the caller's stream (so the slots can be refilled at once); the block
@@ -943,7 +778,6 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     const bool small_slots = small && write_slots;
     const int transit = c->dirty_track ? -1 : transit_base;
     const int32_t* landed_ranks = c->dma_evict ? c->vrank_buf[buf] : nullptr;
-    bool bytes = false;                  // marks are bytes
     if (small) {
         if (c->evict_pending) {        // as below
             FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0));
@@ -957,49 +791,23 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         // two error words in turn: a call's K2a clears the next call's
         uint32_t *err = &c->ctl->err[c->err_set], *next_err = &c->ctl->err[c->err_set ^ 1];
         c->err_set ^= 1;
-        bytes = mark_bytes(c, n);
-        if (bytes) {
-            nmark = cdiv(work, MARKB_ITEMS * MARKB_THREADS);
-            if (nmark > MARK_HIT_PARTS) nmark = MARK_HIT_PARTS;
-            {
-                ProfScope ps(c, P_REMAP_MARK, st);
-                k_remap_bytes<<<(unsigned)nmark, MARKB_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubytes,
-                                                                        c->rbits, c->rbuf, err, c->hitpart);
-            }
-            ProfScope ps(c, P_RANK_COUNT, st);
-            k_count_bytes<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, (uint16_t*)c->ubits, (const uint16_t*)c->rbits,
-                                                                 (const uint16_t*)c->pbits, protect_prev, c->bsum, c->ssum, c->usum,
-                                                                 landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot, next_err);
-            c->ubits_clean = false;
-        } else {
-            nmark = cdiv(work, (int64_t)c->mark_ids_per_thread * MARK_THREADS);
-            if (nmark > MARK_MAX_BLOCKS) nmark = MARK_MAX_BLOCKS;
-            const int64_t per_block = cdiv(cdiv(work, nmark), MARK_THREADS) * MARK_THREADS;
-            nmark = cdiv(work, per_block);
-            const int64_t words = c->NB * RT_WORDS;
-            if (!c->ubits_clean) {               // left over from byte marks
-                k_zero_words<<<(unsigned)cdiv(words, 1024), 256, 0, st>>>((uint4*)c->ubits);
-                c->ubits_clean = true;
-            }
-            {
-                ProfScope ps(c, P_REMAP_MARK, st);
-                k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits,
-                                                                      c->rbits, c->rbuf, err, c->hitpart, (int)per_block,
-                                                                      (int)(words < MARK_LDS_WORDS ? words : MARK_LDS_WORDS));
-            }
-            ProfScope ps(c, P_RANK_COUNT, st);
-            k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((const uint4*)c->ubits, (const uint4*)c->rbits, (const uint4*)c->pbits,
-                                                                protect_prev, c->bsum, c->ssum, c->usum,
-                                                                landed_ranks, (int)landed,
-                                                                (int)(buf * c->staging_rows), c->rank_slot, next_err);
+        FC_TRY(ensure_marks(c));
+        nmark = cdiv(work, MARK_ITEMS * MARK_THREADS);
+        if (nmark > MARK_HIT_PARTS) nmark = MARK_HIT_PARTS;
+        const int64_t dense_tiles = std::min(c->NB, cdiv(n * c->mark_dense, RT_WORDS * 32));
+        {
+            ProfScope ps(c, P_REMAP_MARK, st);
+            k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubytes, c->uchunks,
+                                                                  (int)std::min(dense_tiles * RT_WORDS * 32, c->N), c->rbits, c->rbuf, err, c->hitpart, c->gsum, (int)cdiv(c->NB, GROUP_TILES));
         }
-        const PlanArgs pa{c->bsum, c->ssum, c->usum, err, &c->ctl->async_flags, c->hitpart, c->hctl, c->plan[c->lset], (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
+        {
+            ProfScope ps(c, P_RANK_COUNT, st);
+            k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, c->uchunks, (int)dense_tiles, (uint2*)c->ubits, (const uint2*)c->rbits,
+                                                                (const uint2*)c->pbits, protect_prev, c->bsum, c->ssum, c->gsum,
+                                                                landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot, next_err);
+        }
+        const PlanArgs pa{c->bsum, c->ssum, c->gsum, err, &c->ctl->async_flags, c->hitpart, c->hctl, c->plan[c->lset], (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
                           protect_prev};
-        const bool fold = c->NB <= c->plan_fold_tiles;
-        if (!fold) {
-            ProfScope ps(c, P_RANK_PLAN, st);
-            k_rank_plan<<<1, PLAN_THREADS, 0, st>>>(pa, c->tile_plan);
-        }
         // Last batch's evicted rows must have reached the host table before the victim lists and the block buffer
         // are reused and before any of those rows could be fetched again; the kernels above do not care.
         if (c->evict_pending) {
@@ -1008,11 +816,11 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         }
         ProfScope ps(c, P_RANK_EMIT, st);
 #define FC_EMIT(S) \
-        k_rank_emit<S><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, c->tile_plan, \
+        k_rank_emit<S><<<(unsigned)(c->NB * S), RT_THREADS, 0, st>>>(c->ubits, c->rbits, c->pbits, pa, \
                                                                        c->miss_ranks, c->vrank, c->vslot, c->rank_slot, c->slot_rank, \
                                                                        transit, (int)c->staging_rows, \
-                                                                       c->dma_evict ? c->fill_src : nullptr, bytes ? 1 : 0)
-        if (fold) FC_EMIT(EMIT_SPLIT); else FC_EMIT(1);
+                                                                       c->dma_evict ? c->fill_src : nullptr)
+        if (c->NB <= c->split_tiles) FC_EMIT(EMIT_SPLIT); else FC_EMIT(1);
 #undef FC_EMIT
     }
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
@@ -1023,7 +831,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
     c->last_index_stream = st;
     run->ticket = ticket; run->n = n; run->num_bags = num_bags;
-    run->small = small; run->small_slots = small_slots; run->bytes = bytes; run->buf = buf; run->transit_base = transit_base;
+    run->small = small; run->small_slots = small_slots; run->buf = buf; run->transit_base = transit_base;
     return FC_OK;
 }
 
@@ -1049,7 +857,7 @@ int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv)
     FC_TRY(wait_for_record(c->hctl, run.ticket, st, h));
     if (h[HW_STATUS] != FC_OK) return h[HW_STATUS];
     c->nfree = h[HW_NFREE];
-    if (run.bytes) std::swap(c->ubits, c->pbits);        // this batch is the "previous" one next time
+    if (!run.small) std::swap(c->ubits, c->pbits);        // this batch is the "previous" one next time
     c->last_one_per_bag = run.n == run.num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
     const int64_t M = h[HW_MISS], need = h[HW_NEED];
     mv->valid = true; mv->M = M; mv->need = need; mv->buf = run.buf; mv->transit_base = run.transit_base;

@@ -1,0 +1,21 @@
+"""`-m gpu`: marks read chunk by chunk and counts added up over groups of tiles, against the oracle: tables that end at the edge of a
+group of 16 tiles of 32768 ranks, popular rows among the highest ranks, none, a few and all of the marks read one and all."""
+import pytest
+
+from tests.parity import run_parity, run_parity_lookahead, run_parity_planned
+from tests.tiny_workload import TinyWorkload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [524_288, 524_289, 1_048_577])
+@pytest.mark.parametrize("dense", ["0", "4", "4096"])
+@pytest.mark.parametrize("split_tiles", ["0", "1024"])
+def test_mark_chunks(monkeypatch, rows, dense, split_tiles):
+    monkeypatch.setenv("FC_MARK_DENSE", dense)
+    monkeypatch.setenv("FC_PLAN_FOLD_TILES", split_tiles)
+    w = TinyWorkload(num_rows=rows, dim=4, cache_rows=9000, seed=rows, multi_hot=False, bags=5000,
+                     hot=[0, 255, 256, rows // 2, rows - 257, rows - 256, rows - 1], distinct_cap=4000)
+    run_parity(w, 3, warm=False)
+    run_parity_planned(w, 4, warm=True, dma_evict=True, inputs_ready=True)
+    run_parity_lookahead(w, 4, warm=True)
