@@ -468,21 +468,25 @@ __device__ __forceinline__ uint64_t same_digit(int d, int radix_bits, uint64_t l
     return (uint64_t)hi << 32 | lo;
 }
 
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o);
-    return x;  // valid in lane 0
+// Inclusive sum over the wavefront's lanes, all of them active: six adds on neighbouring lanes' registers (within rows of 16
+// lanes, then across them) where a shuffle through LDS costs each step its latency.
+// us a launch, shuffles -> this: emitting kernel 12.7 -> 9.6 (306 tiles), 20.8 -> 17.0 (3052); count 13.1 -> 11.7 (3052).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int add_lane(int x) { return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int wave_scan(int x) {
+    x = add_lane<0x111, 0xf>(x);               // row_shr 1, 2, 4, 8
+    x = add_lane<0x112, 0xf>(x);
+    x = add_lane<0x114, 0xf>(x);
+    x = add_lane<0x118, 0xf>(x);
+    x = add_lane<0x142, 0xa>(x);               // row_bcast 15: a row's total to the next, for rows 1 and 3
+    return add_lane<0x143, 0xc>(x);            // row_bcast 31: that of the first half to the second
 }
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_scan(x), 63); }
 
 template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT/64 ints */) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
+    const int x = wave_scan(v);
     if (lane == 63) lds[w] = x;
     __syncthreads();
     int wbase = 0, tot = 0;

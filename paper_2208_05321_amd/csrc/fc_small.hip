@@ -51,7 +51,7 @@ __device__ __forceinline__ int enqueue(bool want, int* count, int lane, uint64_t
     if (!m) return -1;
     int base = 0;
     if (lane == 0) base = atomicAdd(count, __popcll(m));
-    base = __shfl(base, 0);
+    base = __builtin_amdgcn_readfirstlane(base);
     return want ? base + __popcll(m & lt) : -1;
 }
 
@@ -152,15 +152,10 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
             nm = popc8(and_not(u0, q0[k]), and_not(u1, q1[k]));
             nc = popc8(and_not(q0[k], u0), and_not(q1[k], u1));
         }
-        int x = nm | nc << 16;                             // 64 pairs hold 16384 ranks: no carry between the halves
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(x, o);
-            if (lane >= o) x += y;
-        }
+        int x = wave_scan(nm | nc << 16);                  // 64 pairs hold 16384 ranks: no carry between the halves
         // (a stretch holds at most 65536 ranks, and what precedes a pair in it at most 65280: 16 bits each)
         if (live) pre[p] = (uint32_t)(cm + (x & 0xffff) - nm) | (uint32_t)(cc + (x >> 16) - nc) << 16;
-        x = __shfl(x, 63);
+        x = __builtin_amdgcn_readlane(x, 63);
         cm += x & 0xffff;
         cc += x >> 16;
     }
