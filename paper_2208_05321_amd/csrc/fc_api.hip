@@ -466,17 +466,22 @@ static int fetch_early(fc_cache* c, int64_t M) {
 
 // the caller's stream takes over from the look-ahead stream: everything cache_prepare_next enqueued comes first
 static int adopt_next(fc_cache* c) {
+    const auto wait_for_prepared = [c]() -> int {
+        if (c->next_pending || c->last_pst != c->stream) {
+            FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
+            c->next_pending = false;
+            c->last_pst = c->stream;
+            for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
+        }
+        return FC_OK;
+    };
     if (c->planned.valid) {            // a batch planned ahead whose rows have not moved yet: move them now
         const MovePlan mv = c->planned;
         c->planned.valid = false;
+        if (mv.one_wait) FC_TRY(wait_for_prepared());
         FC_TRY(prepare_move(c, c->stream, mv, true));
     }
-    if (c->next_pending || c->last_pst != c->stream) {
-        FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
-        c->next_pending = false;
-        c->last_pst = c->stream;
-        for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
-    }
+    FC_TRY(wait_for_prepared());
     c->cur_ticket = c->pending_ticket;     // the batch prepared ahead of time (if any) is the current one now
     return FC_OK;
 }
@@ -506,11 +511,13 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         FC_HIP(hipEventRecord(c->ev_assign_done, st));
         c->aux = st;
         c->planned.arrived = false;
-        fetched = fetch_early(c, -1);
         if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         c->last_one_per_bag = guess;
         c->pst = st;
         sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
+        // Last, although it could start first: making a stream wait for an event that has not happened yet costs the host 10-15 us, for
+        // one that has 0.4, and by now the emitting kernel is through wherever it is the host that binds the step.
+        fetched = fetch_early(c, -1);
         rc = index_result(c, st, run, &mv);
     }
     c->pst = c->stream;
@@ -524,6 +531,7 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         return rc;
     }
     mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= c->staging_rows;
+    mv.one_wait = !early;
     c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
     c->planned = mv;
     c->pending_ticket = c->ticket;

@@ -639,16 +639,22 @@ int dma_quiesce(fc_cache* c, hipStream_t st) {
     return FC_OK;
 }
 
-// DMA evict transmitter: gather into block `buf`, hand the block and its rank list to the DMA engine on the side
-// stream, and let the host threads scatter it once it has landed.  Nothing on the caller's stream waits for it.
-static int evict_dma(fc_cache* c, int64_t need, int buf) {
+// DMA evict transmitter: gather into block `buf` ...
+static bool ranks_travel_along(const fc_cache* c, int64_t need) { return need * (int64_t)(c->D + 1) <= c->staging_rows * (int64_t)c->D; }
+static int gather_block(fc_cache* c, int64_t need, int buf) {
     float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
     // the ranks travel behind the rows, in one copy, where the block has room for both (a copy of their own costs the host as
     // much as four launches)
-    const bool together = need * (int64_t)(c->D + 1) <= c->staging_rows * (int64_t)c->D;
     FC_TRY(launch_copy_rows(c, c->pst, P_EVICT_GATHER, blk, nullptr, c->staging_rows, c->cache, c->out_slot, c->C, need, 1 << 20,
-                            together ? reinterpret_cast<int32_t*>(blk + (size_t)need * c->D) : nullptr, c->out_rank));
+                            ranks_travel_along(c, need) ? reinterpret_cast<int32_t*>(blk + (size_t)need * c->D) : nullptr, c->out_rank));
     FC_HIP(hipEventRecord(c->ev_gather_done, c->pst));
+    return FC_OK;
+}
+// ... and hand the block and its rank list to the DMA engine on the side stream, and let the host threads scatter it once it has
+// landed.  Nothing on the caller's stream waits for it.
+static int send_block(fc_cache* c, int64_t need, int buf) {
+    const float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
+    const bool together = ranks_travel_along(c, need);
     FC_HIP(hipStreamWaitEvent(c->side, c->ev_gather_done, 0));
     {
         ProfScope ps(c, P_D2H_BLOCK, c->side);
@@ -913,7 +919,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
-    if (c->last_index_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_assign_done, 0));
+    if (c->last_index_stream != st && !mv.one_wait) FC_HIP(hipStreamWaitEvent(st, c->ev_assign_done, 0));
     const int64_t M = mv.M;
     int64_t need = mv.need;                    // victims to write back
     const bool staged = (c->flags & FC_TRANSMIT_STAGED) != 0;
@@ -952,14 +958,14 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     // than the one this batch's victims go to (its marks were dropped before this batch was indexed), so the
     // victims need not wait for them; a kernel-store evict reuses the block buffer from its start and has to.
     bool arrival_waited = !mv.arrived;
-    bool dma_path = false;
+    bool dma_path = false, send = false;
     // DMA miss path: ev_arrive of this list set is recorded by a gather thread once it has handed the last chunk to the
     // DMA engine; the host waits here until that has happened (the GPU meanwhile works through the current batch)
     const bool via_dma = mv.arrived && c->gather_pending;
     if (via_dma) { FC_TRY(gather_wait(c)); c->gather_pending = false; }
     if (need > 0) {
         if (staged) FC_TRY(evict_staged(c, need, c->list_pin + c->C));
-        else if (c->dma_evict && mv.need <= c->staging_rows) { FC_TRY(evict_dma(c, need, mv.buf)); dma_path = true; }
+        else if (c->dma_evict && mv.need <= c->staging_rows) { FC_TRY(gather_block(c, need, mv.buf)); dma_path = send = true; }
         else {
             // more victims than one block holds (or no DMA transmitter): store by kernel, block by block; the
             // block buffer is reused from its start, so nothing may be in transit in it any more: every missing row, also one
@@ -989,6 +995,8 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     if (last_rows < 0) { FC_HIP(hipStreamWaitEvent(st, c->ev_evict_done, 0)); c->evict_pending = false; }
     FC_HIP(hipGetLastError());
     FC_TRY(move_done(c, st, ahead));
+    // (after the rows that come in: by then the gather may be through, and the side stream's wait for it costs the host next to nothing)
+    if (send) FC_TRY(send_block(c, need, mv.buf));
     c->vrank_kept = c->dma_evict && !c->dirty_track && !dma_path;
     // The next early fetch reads evicted-row blocks gathered up to now and host rows stored up to now: with the DMA
     // transmitter the gather just enqueued is the last thing it needs (host rows still on their way carry transit
