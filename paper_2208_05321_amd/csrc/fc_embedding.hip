@@ -515,7 +515,9 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
 // k_bwd_fixup gets the longer: 1.7 M of 16 columns (6656 workgroups) 66.8 + 9.6 -> 57.6 + 18.8, 426 k of 128 columns (6656)
 // 64.6 + 8.2 -> 59.1 + 13.8, 328 k of 256 columns (10240) 65.5 + 16.6 -> 66.4 + 44.7.  The limit on floats keeps the partial
 // rows within what embedding_bag_bwd_sgd_noalloc has for them.
-constexpr int BWD_SMALL_CHUNK = BWD_PF;
+// Rows of fewer than 8 columns keep chunks of 32 and with them the order of their sums: where a row is hardly more than one element,
+// nothing beside it hides what another order leaves of a sum that cancels.
+constexpr int BWD_SMALL_CHUNK = BWD_PF, BWD_SMALL_MIN_D = 8;
 constexpr int64_t BWD_SMALL_BLOCKS = 2048, BWD_SMALL_FLOATS = 1 << 20;      // floats: blocks * D
 struct BwdGeom { int threads = 0, chunk = 0; int64_t blocks = 0; size_t lds = 0; };
 
@@ -527,7 +529,8 @@ static inline BwdGeom bwd_geometry(const fc_cache* c, int64_t n) {
     g.threads = bwd_threads(c->lpr);
     g.chunk = BWD_SMALL_CHUNK;
     const int64_t lanes = cdiv(n, BWD_SMALL_CHUNK) * c->lpr;
-    if (lanes <= 1024) g.threads = (int)cdiv(lanes, WAVE) * WAVE;
+    if (c->D < BWD_SMALL_MIN_D) g.chunk = BWD_CHUNK;
+    else if (lanes <= 1024) g.threads = (int)cdiv(lanes, WAVE) * WAVE;
     else if (cdiv(n, (int64_t)(g.threads / c->lpr) * BWD_SMALL_CHUNK) > bwd_small_blocks(c)) g.chunk = BWD_CHUNK;
     const int gpb = g.threads / c->lpr;                       // chunks per workgroup
     g.blocks = cdiv(n, (int64_t)gpb * g.chunk);
