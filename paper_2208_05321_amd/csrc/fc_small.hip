@@ -6,7 +6,7 @@
 // rank space in LDS (160 KB per compute unit on gfx950), so that the phases are separated by workgroup barriers instead of
 // kernel boundaries.  The decisions are those of the kernels in fc_prepare.hip and fc_sort.hip, element for element.
 // Measured: 1024 ids, 100 k rows: index 33 us of kernels in 7 launches -> 13 us in one, sort 17 us in 3 -> 7.6 us in one, a
-// training step 144 -> 118 us; 3328 ids, 1 M rows: 37 us in 7 -> 27 us in one, an inference step 101 -> 85 us.
+// training step 144 -> 118 us; 3328 ids, 1 M rows: 37 us in 7 -> 27 us in one, an inference step 101 -> 85 us (since then: below).
 // The limit of 4096 ids: a single compute unit resolves about one random line per nanosecond and issues one instruction
 // per cycle, and at 10 k ids it takes as long (40 + 32 us) as the kernels that use all of them (37 + 33 us and 11 launches,
 // whose launching the host overlaps).  The limits on rows and slots are what fits LDS.
@@ -16,7 +16,8 @@ namespace fc {
 
 constexpr int SM_THREADS = 1024;
 constexpr int SM_WAVES = SM_THREADS / 64;
-constexpr int SM_ITEMS = 8;                                       // ids, or slots, of a thread in flight together
+constexpr int SM_ITEMS = 8;                                       // slots of a thread in flight together
+constexpr int SM_IDS = SMALL_MAX_IDS / SM_THREADS;                // ids of a thread
 constexpr int SM_R8 = SMALL_MAX_WORDS / (SM_WAVES * 64 * 8);      // pairs of 16-byte pieces of the bitmap per lane, at most
 
 struct SmallArgs {
@@ -45,25 +46,23 @@ __device__ __forceinline__ uint4 below(uint4 v, int at, int r) {
     return make_uint4(v.x & word_below(at, r), v.y & word_below(at + 32, r), v.z & word_below(at + 64, r), v.w & word_below(at + 96, r));
 }
 
-// The wavefront's lanes with `want` get places in a queue, the others -1.
-__device__ __forceinline__ int enqueue(bool want, int* count, int lane, uint64_t lt) {
-    const uint64_t m = __ballot(want);
-    if (!m) return -1;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(count, __popcll(m));
-    base = __builtin_amdgcn_readfirstlane(base);
-    return want ? base + __popcll(m & lt) : -1;
-}
+// lanes of m before this one, and whether this one is among them
+__device__ __forceinline__ int lanes_before(uint64_t m) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)); }
+__device__ __forceinline__ bool has_lane(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
-// Dynamic LDS: rank bitmap [words], prefix counts [words / 8], slot masks [slot chunks].
+// Dynamic LDS: rank bitmap [words], prefix counts [words / 8], slot masks [slot chunks], a queue [ids].
 //
 // Every decision that has an order (the j-th missing rank, the j-th victim, the j-th empty slot) is a prefix count: counts
 // per 256 ranks are scanned once, and whoever meets an element (an id with a missing rank, a slot with a victim) works out
 // its place from that and a popcount, all elements side by side; loops over the bits of a word, one lane each, took four
 // times as long here.  The code is kept short: a workgroup that runs once fetches its instructions from memory, too.
+// What bounds it is the chain of dependent reads, a microsecond each, so a thread keeps its ids' ranks and slots in registers, what
+// other threads need goes through LDS wherever it fits, and what a later phase reads is requested before the phase in between.  1024 ids, 100 k rows, 1500 slots: 16.7 -> 10.9 us; 3328 ids,
+// 1 M rows, 15 k slots: 31.4 -> 21.6 (init 2.6, ids to marks 3.6, prefix counts 1.9, threshold 0.7, missing 1.0, slots 3.9, victims and empty
+// slots 2.4, slots out 1.1, bitmaps 2.4).  A unit runs 16 wavefronts on four SIMDs, so 100 instructions for all are 0.7 us.
 __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     extern __shared__ __align__(16) uint32_t lds_bits[];
-    __shared__ int part[SM_WAVES][2];
+    __shared__ int part[SM_WAVES][2], before[SM_WAVES][2], holes[SM_WAVES];
     __shared__ uint32_t s_cand[8];
     __shared__ int s_hits, s_used, s_threshold, s_queue, s_queue2;
     __shared__ uint32_t s_flags;
@@ -72,11 +71,19 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
                                                                                // a pair of pieces, in its wavefront's stretch
     uint64_t* fmask = reinterpret_cast<uint64_t*>(pre + a.words / 8);          // slots to fill, 64 a word
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const uint64_t lt = (1ull << lane) - 1ull;
     const int per_wave = a.words / SM_WAVES / 8;                               // pairs of pieces per wavefront
-    const int chunks_wave = (a.C + 64 * SM_WAVES - 1) / (64 * SM_WAVES);       // 64-slot chunks per wavefront
+    const int chunks_wave = (a.C + 64 * SM_WAVES - 1) / (64 * SM_WAVES);       // 64-slot chunks per wavefront, at most 64
+    uint16_t* queue = reinterpret_cast<uint16_t*>(fmask + chunks_wave * SM_WAVES);
     const int nfree = a.nfree;
-    // the resident bits this thread will look at: requested first, needed after the ids
+    // ids and offsets, and the resident bits this thread will look at
+    int64_t id[SM_IDS], o0[SM_IDS], o1[SM_IDS];
+#pragma unroll
+    for (int k = 0; k < SM_IDS; ++k) {
+        const int i = tid + k * SM_THREADS;
+        id[k] = i < a.n ? a.ids[i] : 0;
+        o0[k] = i <= a.num_bags ? a.offsets[i] : i;
+        o1[k] = i < a.num_bags ? a.offsets[i + 1] : o0[k];
+    }
     uint4 q0[SM_R8], q1[SM_R8];
 #pragma unroll
     for (int k = 0; k < SM_R8; ++k) {
@@ -85,53 +92,74 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
         q0[k] = live ? a.rbits4[2 * p] : make_uint4(0, 0, 0, 0);
         q1[k] = live ? a.rbits4[2 * p + 1] : make_uint4(0, 0, 0, 0);
     }
+    const uint32_t async_flags = a.ctl->async_flags;
     for (int j = tid; j < a.words / 4; j += SM_THREADS) reinterpret_cast<uint4*>(ub)[j] = make_uint4(0, 0, 0, 0);
     if (tid == 0) { s_hits = s_used = s_queue = s_queue2 = 0; s_flags = 0; s_threshold = 0x7fffffff; }
-    for (int j = tid; j < a.landed; j += SM_THREADS) {     // rows of the block that has reached the host table
+    // rows of the block that has reached the host table (fill_src below reads what this leaves; who else reads it meanwhile asks
+    // only whether it is negative)
+    for (int j = tid; j < a.landed; j += SM_THREADS) {
         const int r = a.landed_ranks[j];
         if (a.rank_slot[r] == -2 - (a.landed_base + j)) a.rank_slot[r] = -1;
     }
     __syncthreads();
     // ids -> ranks, marked in LDS; access-level hits; offsets
     uint32_t flags = 0;
-    int hits = 0, used = 0;
-#pragma unroll 1
-    for (int i0 = tid; i0 - tid < a.n; i0 += SM_ITEMS * SM_THREADS) {
-        int64_t id[SM_ITEMS];
-        int r[SM_ITEMS], s[SM_ITEMS];
+    int r[SM_IDS], s[SM_IDS];
 #pragma unroll
-        for (int k = 0; k < SM_ITEMS; ++k) id[k] = i0 + k * SM_THREADS < a.n ? a.ids[i0 + k * SM_THREADS] : 0;
+    for (int k = 0; k < SM_IDS; ++k) {
+        const bool ok = (uint64_t)id[k] < (uint64_t)a.N;
+        if (!ok) flags |= EF_ID_RANGE;
+        r[k] = ok && tid + k * SM_THREADS < a.n ? a.freq_rank[id[k]] : -1;
+    }
 #pragma unroll
-        for (int k = 0; k < SM_ITEMS; ++k) {
-            const bool ok = (uint64_t)id[k] < (uint64_t)a.N;
-            if (!ok) flags |= EF_ID_RANGE;
-            r[k] = ok ? a.freq_rank[id[k]] : -1;
-        }
+    for (int k = 0; k < SM_IDS; ++k) s[k] = r[k] >= 0 ? a.rank_slot[r[k]] : -1;
+    int row[SM_ITEMS];                                     // rows of this lane's first slots
 #pragma unroll
-        for (int k = 0; k < SM_ITEMS; ++k) s[k] = r[k] >= 0 ? a.rank_slot[r[k]] : -1;
+    for (int k = 0; k < SM_ITEMS; ++k) {
+        const int slot = (w * chunks_wave + k) * 64 + lane;
+        row[k] = k < chunks_wave && slot < a.C ? a.slot_rank[slot] : 0x7fffffff;
+    }
 #pragma unroll
-        for (int k = 0; k < SM_ITEMS; ++k) {
-            const int i = i0 + k * SM_THREADS;
-            bool mine = false;                             // first to mark its row
-            if (i < a.n && r[k] >= 0) {
-                const uint32_t bit = 1u << (r[k] & 31);
-                uint32_t* word = &ub[(uint32_t)r[k] >> 5];
-                // (popular rows: a plain read is one broadcast, atomics on one word queue up)
-                if (!(*reinterpret_cast<volatile uint32_t*>(word) & bit)) mine = (atomicOr(word, bit) & bit) == 0;
-                used += mine;
-                hits += s[k] >= 0;
-            }
-            if (i < a.n) a.ranks[i] = r[k];
-            const int at = enqueue(mine && s[k] < 0, &s_queue, lane, lt);
-            if (at >= 0 && at < a.C) a.fill_slots[at] = r[k];        // (more missing rows than slots: refused below)
-        }
+    for (int k = 0; k < SM_IDS; ++k) {
+        const int i = tid + k * SM_THREADS;
+        if (i > a.num_bags) continue;
+        if (o0[k] != i) flags |= EF_NOT_ONE_PER_BAG;
+        if ((i == 0 && o0[k] != 0) || (i == a.num_bags && o0[k] != (int64_t)a.n) || o1[k] < o0[k]) flags |= EF_BAD_OFFSETS;
     }
 #pragma unroll 1
-    for (int i = tid; i <= a.num_bags; i += SM_THREADS) {
+    for (int i = tid + SM_IDS * SM_THREADS; i <= a.num_bags; i += SM_THREADS) {        // more bags than ids
         const int64_t o = a.offsets[i];
         if (o != i) flags |= EF_NOT_ONE_PER_BAG;
-        if ((i == 0 && o != 0) || (i == a.num_bags && o != (int64_t)a.n)) flags |= EF_BAD_OFFSETS;
+        if (i == a.num_bags && o != (int64_t)a.n) flags |= EF_BAD_OFFSETS;
         if (i < a.num_bags && a.offsets[i + 1] < o) flags |= EF_BAD_OFFSETS;
+    }
+    int hits = 0, used = 0;
+    uint64_t missing[SM_IDS];                              // lanes whose id k is the first of its row, and the row is missing
+    int misses = 0;
+#pragma unroll
+    for (int k = 0; k < SM_IDS; ++k) {
+        bool first = false;
+        if (r[k] >= 0) {
+            const uint32_t bit = 1u << (r[k] & 31);
+            uint32_t* word = &ub[(uint32_t)r[k] >> 5];
+            // (popular rows: a plain read is one broadcast, atomics on one word queue up)
+            first = !(*reinterpret_cast<volatile uint32_t*>(word) & bit) && !(atomicOr(word, bit) & bit);
+            used += first;
+            hits += s[k] >= 0;
+        }
+        missing[k] = __ballot(first && s[k] < 0);
+        misses += __popcll(missing[k]);
+        if (tid + k * SM_THREADS < a.n) a.ranks[tid + k * SM_THREADS] = r[k];
+    }
+    if (misses) {                                          // their positions in the batch are queued
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_queue, misses);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int k = 0; k < SM_IDS; ++k) {
+            if (has_lane(missing[k])) queue[at + lanes_before(missing[k])] = (uint16_t)(tid + k * SM_THREADS);
+            at += __popcll(missing[k]);
+        }
     }
     hits = wave_sum(hits);
     used = wave_sum(used);
@@ -161,13 +189,12 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     }
     if (lane == 0) { part[w][0] = cm; part[w][1] = cc; }
     __syncthreads();
-    // totals; part[k] becomes what precedes wavefront k's stretch
-    int M = 0, totC = 0, m0 = 0, c0 = 0;
-#pragma unroll 1
-    for (int k = 0; k < SM_WAVES; ++k) {
-        if (k == w) { m0 = M; c0 = totC; }
-        M += part[k][0]; totC += part[k][1];
-    }
+    // totals, and what precedes this wavefront's stretch
+    const int pm = lane < SM_WAVES ? part[lane][0] : 0, pc = lane < SM_WAVES ? part[lane][1] : 0;
+    const int sm = wave_scan(pm), sc = wave_scan(pc);
+    const int M = __builtin_amdgcn_readlane(sm, 63), totC = __builtin_amdgcn_readlane(sc, 63);
+    const int c0 = __builtin_amdgcn_readlane(sc - pc, __builtin_amdgcn_readfirstlane(w));
+    if (w == 0 && lane < SM_WAVES) { before[lane][0] = sm - pm; before[lane][1] = sc - pc; }
     const uint32_t ef = s_flags;
     const int totU = s_used;
     int status = FC_OK;
@@ -179,7 +206,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     if (w == SM_WAVES - 1) {
         if (lane == 0) { a.plan[PL_STATUS] = status; a.plan[PL_NEED] = need; a.plan[PL_MISS] = M; }
         const int nf = status == FC_OK ? nfree + need - M : nfree;
-        report_to_host(a.hctl, a.ticket, status, totU, M, need, s_hits, nf, (int)a.ctl->async_flags, (int)(ef & EF_NOT_ONE_PER_BAG), lane);
+        report_to_host(a.hctl, a.ticket, status, totU, M, need, s_hits, nf, (int)async_flags, (int)(ef & EF_NOT_ONE_PER_BAG), lane);
     }
     if (status != FC_OK) return;
     // the victims are the evictable ranks from the threshold up: the one with `skip` evictable ranks below it
@@ -201,23 +228,21 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
         }
     }
     __syncthreads();
-    if (lane == 0) { part[w][0] = m0; part[w][1] = c0; }
-    if (tid == 0 && need > 0) {
-        int left = s_threshold & 511, rank = (s_threshold >> 9) * 256, j = 0;
+    int threshold = 0x7fffffff;
+    if (need > 0) {                                        // every thread for itself
+        int left = s_threshold & 511, j = 0;
         uint32_t m = s_cand[0];
         while (left >= __popc(m)) { left -= __popc(m); m = s_cand[++j]; }      // ends: fewer than the pair's count
-        for (; left > 0; --left) m &= m - 1;
-        s_threshold = rank + j * 32 + __ffs(m) - 1;
+        const bool here = lane < 32 && ((m >> lane) & 1u) && __popc(m & ((1u << lane) - 1u)) == left;
+        threshold = (s_threshold >> 9) * 256 + j * 32 + __ffsll((unsigned long long)__ballot(here)) - 1;
     }
-    __syncthreads();
-    const int threshold = s_threshold;
     // each missing rank goes to its place
 #pragma unroll 1
     for (int q = tid; q < M; q += SM_THREADS) {
-        const int r = a.fill_slots[q], p = r >> 8;
-        const uint4 b0 = below(and_not(ub4[2 * p], a.rbits4[2 * p]), p * 256, r),
-                    b1 = below(and_not(ub4[2 * p + 1], a.rbits4[2 * p + 1]), p * 256 + 128, r);
-        a.miss_ranks[part[p / per_wave][0] + (int)(pre[p] & 0xffff) + popc8(b0, b1)] = r;
+        const int rank = a.ranks[queue[q]], p = rank >> 8;
+        const uint4 b0 = below(and_not(ub4[2 * p], a.rbits4[2 * p]), p * 256, rank),
+                    b1 = below(and_not(ub4[2 * p + 1], a.rbits4[2 * p + 1]), p * 256 + 128, rank);
+        a.miss_ranks[before[p / per_wave][0] + (int)(pre[p] & 0xffff) + popc8(b0, b1)] = rank;
     }
     __syncthreads();
     // slots whose row is a victim, and those that were empty, are the ones to fill
@@ -225,38 +250,81 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     if (M > 0) {
 #pragma unroll 1
         for (int k0 = 0; k0 < chunks_wave; k0 += SM_ITEMS) {
-            int row[SM_ITEMS];
+            int next[SM_ITEMS];
 #pragma unroll
             for (int k = 0; k < SM_ITEMS; ++k) {
-                const int s = (w * chunks_wave + k0 + k) * 64 + lane;
-                row[k] = k0 + k < chunks_wave && s < a.C ? a.slot_rank[s] : 0x7fffffff;
+                const int c = k0 + SM_ITEMS + k, slot = (w * chunks_wave + c) * 64 + lane;
+                next[k] = c < chunks_wave && slot < a.C ? a.slot_rank[slot] : 0x7fffffff;
             }
+            uint64_t vm[SM_ITEMS];
+            int victims = 0;
 #pragma unroll
             for (int k = 0; k < SM_ITEMS; ++k) {
-                const int chunk = w * chunks_wave + k0 + k, r = row[k];
-                const bool victim = r >= threshold && r != 0x7fffffff && !((ub[r >> 5] >> (r & 31)) & 1u);
-                const int at = enqueue(victim, &s_queue2, lane, lt);
-                if (victim) a.fill_slots[at] = chunk * 64 + lane;
-                const uint64_t m = __ballot(victim || r < 0);
-                if (lane == 0 && k0 + k < chunks_wave) fmask[chunk] = m;
+                const int x = row[k];
+                if (k0 + k >= chunks_wave) { vm[k] = 0; continue; }
+                const bool victim = (unsigned)x - (unsigned)threshold < 0x7fffffffu - (unsigned)threshold &&       // neither empty nor past the last slot
+                                    !((ub[x >> 5] >> (x & 31)) & 1u);
+                vm[k] = __ballot(victim);
+                victims += __popcll(vm[k]);
+                const uint64_t m = vm[k] | __ballot(x < 0);
+                if (lane == 0) fmask[w * chunks_wave + k0 + k] = m;
                 cf += __popcll(m);
             }
+            if (victims) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(&s_queue2, victims);
+                at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+                for (int k = 0; k < SM_ITEMS; ++k) {
+                    if (has_lane(vm[k])) queue[at + lanes_before(vm[k])] = (uint16_t)((w * chunks_wave + k0 + k) * 64 + lane);
+                    at += __popcll(vm[k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < SM_ITEMS; ++k) row[k] = next[k];
         }
     }
+    if (lane == 0) holes[w] = cf;
     __syncthreads();
     const bool transit = a.transit_base >= 0 && need <= a.transit_rows;
 #pragma unroll 1
     for (int q = tid; q < need; q += SM_THREADS) {         // each victim goes to its place
-        const int s = a.fill_slots[q], r = a.slot_rank[s], p = r >> 8;
-        const uint4 b0 = below(and_not(a.rbits4[2 * p], ub4[2 * p]), p * 256, r),
-                    b1 = below(and_not(a.rbits4[2 * p + 1], ub4[2 * p + 1]), p * 256 + 128, r);
-        const int j = part[p / per_wave][1] + (int)(pre[p] >> 16) + popc8(b0, b1) - skip;
-        a.vrank[j] = r;
-        a.vslot[j] = s;
-        a.rank_slot[r] = transit ? -2 - (a.transit_base + j) : -1;
+        const int slot = queue[q], rank = a.slot_rank[slot], p = rank >> 8;
+        const uint4 b0 = below(and_not(a.rbits4[2 * p], ub4[2 * p]), p * 256, rank),
+                    b1 = below(and_not(a.rbits4[2 * p + 1], ub4[2 * p + 1]), p * 256 + 128, rank);
+        const int j = before[p / per_wave][1] + (int)(pre[p] >> 16) + popc8(b0, b1) - skip;
+        a.vrank[j] = rank;
+        a.vslot[j] = slot;
+        a.rank_slot[rank] = transit ? -2 - (a.transit_base + j) : -1;
+    }
+    // the j-th lowest empty slot is the j-th missing rank's
+    {
+        const uint64_t m = lane < chunks_wave && M > 0 ? fmask[w * chunks_wave + lane] : 0;
+        int j0 = wave_sum(lane < w ? holes[lane] : 0);     // (w < 16)
+#pragma unroll 1
+        for (int k = 0; k < chunks_wave && j0 < M; ++k) {
+            const uint64_t mk = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m >> 32), k) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)m, k);
+            const int j = j0 + lanes_before(mk);
+            if (has_lane(mk) && j < M) a.fill_slots[j] = (w * chunks_wave + k) * 64 + lane;
+            j0 += __popcll(mk);
+        }
     }
     __syncthreads();
-    if (lane == 0) part[w][0] = cf;
+#pragma unroll 1
+    for (int j = tid; j < M; j += SM_THREADS) {
+        const int slot = a.fill_slots[j], rank = a.miss_ranks[j];
+        // FC_EVICT_DMA: where the row's newest copy is (-1 the host table, <= -2 in transit); else the row that leaves the slot
+        a.fill_src[j] = a.dma ? a.rank_slot[rank] : a.slot_rank[slot];
+        a.slot_rank[slot] = rank;
+        a.rank_slot[rank] = slot;
+    }
+    if (a.slots_out) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < SM_IDS; ++k) if (s[k] < 0 && r[k] >= 0) s[k] = a.rank_slot[r[k]];
+#pragma unroll
+        for (int k = 0; k < SM_IDS; ++k) if (tid + k * SM_THREADS < a.n) a.slots_out[tid + k * SM_THREADS] = s[k];
+    }
     // the bitmaps change hands: resident = without the victims, with the missing; previous batch = this one
 #pragma unroll
     for (int k = 0; k < SM_R8; ++k) {
@@ -265,7 +333,8 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
         if (k * 64 + lane < per_wave) {
             const uint4 u0 = ub4[2 * p], u1 = ub4[2 * p + 1];
             uint4 k0 = and_not(q0[k], u0), k1 = and_not(q1[k], u1);            // evictable: stay if below the threshold
-            if (at + 256 > threshold) { k0 = below(k0, at, threshold); k1 = below(k1, at + 128, threshold); }
+            if (at >= threshold) k0 = k1 = make_uint4(0, 0, 0, 0);
+            else if (at + 256 > threshold) { k0 = below(k0, at, threshold); k1 = below(k1, at + 128, threshold); }
             const uint4 r0 = make_uint4(u0.x | k0.x, u0.y | k0.y, u0.z | k0.z, u0.w | k0.w),
                         r1 = make_uint4(u1.x | k1.x, u1.y | k1.y, u1.z | k1.z, u1.w | k1.w);
             if (differ(r0, q0[k]) || differ(r1, q1[k])) { a.rbits4[2 * p] = r0; a.rbits4[2 * p + 1] = r1; }
@@ -273,36 +342,16 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
             a.pbits4[2 * p + 1] = u1;
         }
     }
-    __syncthreads();
-    // j-th missing rank -> j-th lowest empty slot
-    {
-        int j0 = 0;
-        for (int k = 0; k < w; ++k) j0 += part[k][0];
-#pragma unroll 1
-        for (int k = 0; k < chunks_wave && j0 < M; ++k) {
-            const uint64_t m = fmask[w * chunks_wave + k];
-            const int j = j0 + __popcll(m & lt);
-            if (((m >> lane) & 1ull) && j < M) a.fill_slots[j] = (w * chunks_wave + k) * 64 + lane;
-            j0 += __popcll(m);
-        }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int j = tid; j < M; j += SM_THREADS) {
-        const int s = a.fill_slots[j], rank = a.miss_ranks[j];
-        // FC_EVICT_DMA: where the row's newest copy is (-1 the host table, <= -2 in transit); else the row that leaves the slot
-        a.fill_src[j] = a.dma ? a.rank_slot[rank] : a.slot_rank[s];
-        a.slot_rank[s] = rank;
-        a.rank_slot[rank] = s;
-    }
-    if (!a.slots_out) return;
-    __syncthreads();
-#pragma unroll 2
-    for (int i = tid; i < a.n; i += SM_THREADS) a.slots_out[i] = a.rank_slot[a.ranks[i]];
+}
+
+static size_t prepare_small_lds(const fc_cache* c, int64_t n) {
+    const size_t words = (size_t)c->NB * RT_WORDS;
+    return (words + words / 8) * 4 + (size_t)cdiv(c->C, 64 * SM_WAVES) * SM_WAVES * 8 + (size_t)cdiv(n, 8) * 16;
 }
 
 bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags) {
-    return c->small_index && n <= SMALL_MAX_IDS && num_bags <= 4 * SMALL_MAX_IDS && c->NB * RT_WORDS <= SMALL_MAX_WORDS && c->C <= SMALL_MAX_SLOTS;
+    return c->small_index && n <= SMALL_MAX_IDS && num_bags <= 4 * SMALL_MAX_IDS && c->NB * RT_WORDS <= SMALL_MAX_WORDS && c->C <= SMALL_MAX_SLOTS &&
+           prepare_small_lds(c, n) <= SMALL_MAX_LDS;
 }
 
 int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
@@ -319,7 +368,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
     a.ctl = c->ctl; a.hctl = c->hctl; a.plan = c->plan[c->lset]; a.N = c->N;
     a.n = (int)n; a.num_bags = (int)num_bags; a.C = (int)c->C; a.words = (int)(c->NB * RT_WORDS);
     a.transit_base = transit_base; a.transit_rows = (int)c->staging_rows; a.ticket = ticket;
-    const size_t lds = (size_t)(a.words + a.words / 8) * 4 + (size_t)cdiv(c->C, 64 * SM_WAVES) * SM_WAVES * 8;
+    const size_t lds = prepare_small_lds(c, n);
     ProfScope ps(c, P_REMAP_MARK, st);
     k_prepare_small<<<1, SM_THREADS, lds, st>>>(a);
     FC_HIP(hipGetLastError());
