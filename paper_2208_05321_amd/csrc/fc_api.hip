@@ -4,6 +4,7 @@
 
 #include <stdio.h>
 
+#include <algorithm>
 #include <chrono>
 #include <new>
 #include <stdlib.h>
@@ -212,6 +213,27 @@ static int make_library_streams(fc_cache* c) {
     return FC_OK;
 }
 
+// The runtime opens another copy engine when a copy is handed over while one that waited for a kernel is under way, up to three more,
+// and each time the call takes 5 to 15 ms.  That belongs here and not in the middle of a training loop: blocks leave as they will
+// there, DMA_BLOCKS at most under way, each behind a short kernel.  (20 steps of 1.7 M ids of 128 columns, 11 ms, with one or two such calls
+// among them 16 to 25 ms.)  Blocks of less than 1 MB are gone before the next one comes.
+static int open_copy_engines(fc_cache* c) {
+    const size_t bytes = std::min((size_t)c->staging_rows * c->D * 4, (size_t)4 << 20);
+    if (bytes < (size_t)1 << 20) return FC_OK;
+    for (int k = 0; k < 32; ++k) {
+        const int b = k % DMA_BLOCKS;
+        if (k >= DMA_BLOCKS) FC_HIP(hipEventSynchronize(c->ev_d2h[b]));
+        k_spin<<<1, 64, 0, c->stream>>>(1000 + 500 * (k % 5), nullptr);          // 10 to 30 us
+        FC_HIP(hipEventRecord(c->ev_gather_done, c->stream));
+        FC_HIP(hipStreamWaitEvent(c->side, c->ev_gather_done, 0));
+        FC_HIP(hipEventRecord(c->ev_copy_a[b], c->side));
+        FC_HIP(hipMemcpyAsync(c->blk_pin[b], c->stage_dev, bytes, hipMemcpyDeviceToHost, c->side));
+        FC_HIP(hipEventRecord(c->ev_d2h[b], c->side));
+    }
+    FC_HIP(hipStreamSynchronize(c->side));
+    return FC_OK;
+}
+
 static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, float* host_weight, int64_t staging_rows,
                   int32_t flags, void* hip_stream, fc_cache* c) {
     FC_HIP(hipGetDevice(&c->device));
@@ -342,6 +364,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
         if (const char* e = getenv("FC_SCATTER_THREADS")) { const int v = atoi(e); if (v >= 1 && v <= 64) threads = v; }
         FC_TRY(pool_create(c, threads));
     }
+    if (c->dma_evict) FC_TRY(open_copy_engines(c));
     c->miss_dma = (flags & FC_MISS_DMA) != 0 && !c->dirty_track;
     if (c->miss_dma) {
         for (int k = 0; k < 2; ++k) {
