@@ -689,9 +689,11 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     // to hear of them nor the host for the GPU to get there while it could be enqueueing.  What it needs: a sort to fold the
     // slot write-out into, and rows fetched by a kernel that can read their number.
     // (After a batch without a miss the next one most likely has none either, and the kernels that depend on there being some
-    // are better not enqueued.  Larger batches wait: 1.7 M lookups of 128 columns, where HBM binds, 548-570 us a step waiting and
-    // 573 enqueued ahead; at 16 columns 286-328 and 287-311.)
-    if (c->presort && n > 0 && n <= ENQUEUE_MAX_IDS && num_bags > 0 && c->dma_evict && !c->miss_dma && c->last.n_miss > 0)
+    // are better not enqueued.  Large batches of wide rows wait: HBM and the link bind them, and what is enqueued ahead crowds the current
+    // batch's forward and backward.  us a step, waiting / enqueued ahead: 1.7 M lookups of 16 columns, 100 M rows 262 / 213 and, three
+    // handles in turn, 264 / 207; of 128 columns, 16 M rows 540-544 / 524-553 and, three in turn, 530-534 / 556.)
+    const bool ahead_of_decisions = n <= ENQUEUE_MAX_IDS || n * (int64_t)c->D <= ENQUEUE_MAX_FLOATS;
+    if (c->presort && n > 0 && ahead_of_decisions && num_bags > 0 && c->dma_evict && !c->miss_dma && c->last.n_miss > 0)
         return plan_enqueued(c, ids_dev, n, offsets_dev, num_bags, slots_dev, early);
     // the slot write-out is folded into the first kernel of the sort (one launch and one pass over the ranks fewer)
     const bool fold = c->presort && n > 0 && num_bags > 0;
