@@ -529,18 +529,22 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     int fetched = FC_OK, sorted = FC_ERR_INVALID_ARG;
     const bool guess = c->last_one_per_bag && n == num_bags;       // most likely the shape of the batch before
     const int rec = c->rec_next;
+    // Few rows to move: the host binds the step, and what counts is what each call costs it.  Making a stream wait for an event that has
+    // not happened yet takes 10-15 us, for one that has 0.4: the fetch comes last, when the emitting kernel is through, and the
+    // caller's stream waits once, for all that is prepared (MovePlan::one_wait).  Many: the link binds it, and fetch and block copy set
+    // out as early as they can (a first pass, 13 MB each way: 455 us, and 513 with the fetch last and the copy behind the sort).
+    const bool few = c->last.n_miss * (int64_t)c->D * 4 <= FEW_BYTES;
     if (rc == FC_OK) rc = index_assign(c, st, run, -1);
     if (rc == FC_OK) {
         FC_HIP(hipEventRecord(c->ev_assign_done, st));
         c->aux = st;
         c->planned.arrived = false;
+        if (!few) fetched = fetch_early(c, -1);
         if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         c->last_one_per_bag = guess;
         c->pst = st;
         sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
-        // Last, although it could start first: making a stream wait for an event that has not happened yet costs the host 10-15 us, for
-        // one that has 0.4, and by now the emitting kernel is through wherever it is the host that binds the step.
-        fetched = fetch_early(c, -1);
+        if (few) fetched = fetch_early(c, -1);
         rc = index_result(c, st, run, &mv);
     }
     c->pst = c->stream;
@@ -554,7 +558,7 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         return rc;
     }
     mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= c->staging_rows;
-    mv.one_wait = !early;
+    mv.one_wait = !early && few;
     c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
     c->planned = mv;
     c->pending_ticket = c->ticket;
