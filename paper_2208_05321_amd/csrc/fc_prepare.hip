@@ -652,9 +652,18 @@ static int gather_block(fc_cache* c, int64_t need, int buf) {
 }
 // ... and hand the block and its rank list to the DMA engine on the side stream, and let the host threads scatter it once it has
 // landed.  Nothing on the caller's stream waits for it.
-static int send_block(fc_cache* c, int64_t need, int buf) {
+// The host waits while this handle's last block is still on its way, if that was handed over a while ago (the rows that come in are
+// enqueued by now, and the GPU is busy with them).  With several handles in turn nothing else holds it back until each has DMA_BLOCKS
+// blocks in flight, and a dozen copies at once beside the fills take three times as long as one after the other and never catch up.
+// us a step, three handles in turn, plain schedule, without / with this: 294 k lookups of 128 columns, 22 k rows each way 715 / 262,
+// 781 k of 256 columns, 32 k rows 1645 / 616, 635 k of 107 columns, 9 k rows 485 / 484.  (`ahead_now`, as in wait_if_far_ahead: HBM binds.)
+static int send_block(fc_cache* c, int64_t need, int buf, bool ahead) {
     const float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
     const bool together = ranks_travel_along(c, need);
+    if (c->last_copy_buf >= 0 && c->copy_timed[c->last_copy_buf] && !(ahead && c->ahead_now)) {
+        const float ago = std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - c->copy_at).count();
+        if (ago > FAR_AHEAD_US) FC_HIP(hipEventSynchronize(c->ev_d2h[c->last_copy_buf]));
+    }
     FC_HIP(hipStreamWaitEvent(c->side, c->ev_gather_done, 0));
     {
         ProfScope ps(c, P_D2H_BLOCK, c->side);
@@ -996,7 +1005,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     FC_HIP(hipGetLastError());
     FC_TRY(move_done(c, st, ahead));
     // (after the rows that come in: by then the gather may be through, and the side stream's wait for it costs the host next to nothing)
-    if (send) FC_TRY(send_block(c, need, mv.buf));
+    if (send) FC_TRY(send_block(c, need, mv.buf, ahead));
     c->vrank_kept = c->dma_evict && !c->dirty_track && !dma_path;
     // The next early fetch reads evicted-row blocks gathered up to now and host rows stored up to now: with the DMA
     // transmitter the gather just enqueued is the last thing it needs (host rows still on their way carry transit
