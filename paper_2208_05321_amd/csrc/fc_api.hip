@@ -489,22 +489,17 @@ static int fetch_early(fc_cache* c, int64_t M) {
 
 // the caller's stream takes over from the look-ahead stream: everything cache_prepare_next enqueued comes first
 static int adopt_next(fc_cache* c) {
-    const auto wait_for_prepared = [c]() -> int {
-        if (c->next_pending || c->last_pst != c->stream) {
-            FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
-            c->next_pending = false;
-            c->last_pst = c->stream;
-            for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
-        }
-        return FC_OK;
-    };
     if (c->planned.valid) {            // a batch planned ahead whose rows have not moved yet: move them now
         const MovePlan mv = c->planned;
         c->planned.valid = false;
-        if (mv.one_wait) FC_TRY(wait_for_prepared());
         FC_TRY(prepare_move(c, c->stream, mv, true));
     }
-    FC_TRY(wait_for_prepared());
+    if (c->next_pending || c->last_pst != c->stream) {
+        FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
+        c->next_pending = false;
+        c->last_pst = c->stream;
+        for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
+    }
     c->cur_ticket = c->pending_ticket;     // the batch prepared ahead of time (if any) is the current one now
     return FC_OK;
 }
@@ -530,9 +525,11 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     const bool guess = c->last_one_per_bag && n == num_bags;       // most likely the shape of the batch before
     const int rec = c->rec_next;
     // Few rows to move: the host binds the step, and what counts is what each call costs it.  Making a stream wait for an event that has
-    // not happened yet takes 10-15 us, for one that has 0.4: the fetch comes last, when the emitting kernel is through, and the
-    // caller's stream waits once, for all that is prepared (MovePlan::one_wait).  Many: the link binds it, and fetch and block copy set
-    // out as early as they can (a first pass, 13 MB each way: 455 us, and 513 with the fetch last and the copy behind the sort).
+    // not happened yet takes 10-15 us, for one that has 0.4: the fetch comes last, when the emitting kernel is through.  Many: the link
+    // binds it, and fetch and block copy set out as early as they can (a first pass, 13 MB each way: 455 us, and 513 with the fetch last
+    // and the copy behind the sort).  (The rows move under the sort either way.  Behind it, with one wait of the caller's stream for both,
+    // one step of 426 k lookups of 32 columns came to 147 us rather than 154, and others to more: 229 k of 32 columns in bags 150 and
+    // 137, 53 k of 64 columns 126 and 119, and the first pass 326 and 320, 292 and 249, 198 and 181.)
     const bool few = c->last.n_miss * (int64_t)c->D * 4 <= FEW_BYTES;
     if (rc == FC_OK) rc = index_assign(c, st, run, -1);
     if (rc == FC_OK) {
@@ -558,7 +555,6 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         return rc;
     }
     mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= c->staging_rows;
-    mv.one_wait = !early && few;
     c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
     c->planned = mv;
     c->pending_ticket = c->ticket;

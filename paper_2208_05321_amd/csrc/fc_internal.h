@@ -98,9 +98,7 @@ inline hipStream_t no_stream() { return reinterpret_cast<hipStream_t>(~(uintptr_
 #define FC_DMA_BLOCKS 4
 #endif
 constexpr int DMA_BLOCKS = FC_DMA_BLOCKS;
-// one_wait: the caller's stream waits for all that was prepared, the sort included, before the rows move: moving them under the sort
-// gains 5 to 10 us on the GPU, a second wait costs the host 10 to 15, and it is the host that binds the step of most such batches.
-struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, transit_base = -1; bool arrived = false, one_wait = false; };
+struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, transit_base = -1; bool arrived = false; };
 // An index half that has been enqueued and whose decisions the host has not read yet.
 struct IndexRun {
     int32_t ticket = 0;

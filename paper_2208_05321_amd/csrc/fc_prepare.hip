@@ -928,7 +928,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
-    if (c->last_index_stream != st && !mv.one_wait) FC_HIP(hipStreamWaitEvent(st, c->ev_assign_done, 0));
+    if (c->last_index_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_assign_done, 0));
     const int64_t M = mv.M;
     int64_t need = mv.need;                    // victims to write back
     const bool staged = (c->flags & FC_TRANSMIT_STAGED) != 0;

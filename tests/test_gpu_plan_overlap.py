@@ -1,0 +1,50 @@
+"""`-m gpu`: what of a planned batch runs beside what."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def test_rows_of_a_planned_batch_move_under_its_sort(tmp_path, monkeypatch):
+    """Evicted rows are gathered as soon as the decisions are taken; a long sort (4 M lookups, few of them of missing rows) is still
+    under way then."""
+    import torch
+    from paper_2208_05321_amd import FreqCache
+    from tests.timeline_file import load_first_collection
+    n, dim, rows, cache, popular, others = 1 << 22, 16, 200_000, 150_000, 80_000, 20_000
+    path = tmp_path / "timeline.txt"
+    monkeypatch.setenv("FC_TIMELINE", str(path))
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        gpu = FreqCache(rows, dim, cache, np.arange(rows, dtype=np.int32), dma_evict=True)
+        gpu.host_weight()[:] = 1.0
+        gpu.warm()
+        gpu.reserve(n, pipelined=True)
+        off = torch.arange(n + 1, device="cuda")
+        k = torch.arange(n, device="cuda") % (popular + others)
+        # the popular rows, and in turn either of two groups of rare ones, each of which takes the other's place
+        ids = [torch.where(k < popular, k, k + rows - (1 + g) * others - popular) for g in range(2)]
+        slots = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+        gpu.prepare(ids[0], off, out=slots[0])
+        steps = 4
+        for t in range(1, 8):
+            if t == 8 - steps:
+                gpu.check()
+                gpu.profile(True)
+            gpu.plan_next(ids[t & 1], off, out=slots[t & 1])
+            gpu.advance()
+            gpu.check()                                   # everything has arrived before the next step
+            stats = gpu.stats()
+        gpu.profile_report()
+        gpu.profile(False)
+        monkeypatch.delenv("FC_TIMELINE")
+        gpu.profile(False)                                # closes the file
+        assert 0 < stats["n_evict"] * dim * 4 < 8 << 20, stats
+        gpu.close()
+    spans = load_first_collection(str(path))
+    gathers = [a for a, b, name in spans if name == "evict_gather"]
+    scatters = [b for a, b, name in spans if name == "sort_scatter"]
+    assert len(gathers) == steps and len(scatters) % steps == 0 and scatters
+    ends = scatters[len(scatters) // steps - 1::len(scatters) // steps]          # of each step's last pass
+    assert all(a < b for a, b in zip(gathers, ends)), (gathers, ends)
