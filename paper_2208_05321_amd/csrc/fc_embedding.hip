@@ -241,6 +241,33 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
 // 2 = lies wholly inside a longer run.
 struct BwdMeta { int first_kind, has_head, head_slot, pad; };
 
+// threads per workgroup of the reduction: at most 64 chunks per workgroup
+__host__ __device__ static inline int bwd_threads(int lpr) { int t = 32 * lpr; if (t > 256) t = 256; if (t < 64) t = 64; return t; }
+
+// Pieces of a run in chunks a (first) to b, added up in levels: over the chunks that make BWD_CHUNK = 32 lookups, then over as many of
+// those as a workgroup of bwd_threads takes (k_bwd_fixup does this across workgroups), then over what is left.  The rounding error of a
+// sum grows with the number of terms added in sequence, and short chunks have more pieces to add: one after the other, a popular row's
+// update was up to twice as far off as with chunks of 32 (4096 lookups in one workgroup 3.6e-7 of its size and 1.8e-7; 20,000 of 256
+// columns 4.5e-7 and 2.5e-7; in levels 1.7e-7 and 2.4e-7).
+template <int JOIN, class V, class Piece>
+__device__ __forceinline__ V join_pieces(V first, int a, int b, int lpr_shift, Piece piece) {
+    V acc = first;
+    if (JOIN == 1) {
+        for (int q = a + 1; q <= b; ++q) acc = vadd(acc, piece(q));
+        return acc;
+    }
+    const int span = (bwd_threads(1 << lpr_shift) >> lpr_shift) * JOIN;       // (powers of two, all of them)
+    V mid = vzero(V()), total = vzero(V());
+    for (int q = a + 1; q <= b; ++q) {
+        if (q % JOIN == 0) {
+            mid = vadd(mid, acc); acc = vzero(V());
+            if ((q & (span - 1)) == 0) { total = vadd(total, mid); mid = vzero(V()); }
+        }
+        acc = vadd(acc, piece(q));
+    }
+    return vadd(total, vadd(mid, acc));
+}
+
 // STREAM: every gradient row is read exactly once (one lookup per bag) -> non-temporal loads
 // CHUNK: see bwd_geometry
 template <int VEC, bool STREAM, int CHUNK>
@@ -331,9 +358,7 @@ __global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(
         // chunks 0..j carry pieces of that run; kind says whether it ended (1) or leaves the workgroup (2)
         V* __restrict__ out = reinterpret_cast<V*>(part + (size_t)(blockIdx.x * 2) * D);
         for (int cidx = lane; cidx < nv; cidx += lpr) {
-            V acc = pfirst[cidx];
-            for (int q = 1; q <= j; ++q) acc = vadd(acc, reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]);
-            out[cidx] = acc;
+            out[cidx] = join_pieces<BWD_CHUNK / CHUNK>(pfirst[cidx], 0, j, lpr_shift, [&](int q) { return reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]; });
         }
         if (lane == 0) blockmeta.first_kind = kind;
     }
@@ -343,8 +368,7 @@ __global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(
         const bool closed = kind == 1;          // ended inside the workgroup
         V* __restrict__ out = reinterpret_cast<V*>(part + (size_t)(blockIdx.x * 2 + 1) * D);
         for (int cidx = lane; cidx < nv; cidx += lpr) {
-            V acc = plast[cidx];
-            for (int q = gl + 1; q <= j; ++q) acc = vadd(acc, reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]);
+            const V acc = join_pieces<BWD_CHUNK / CHUNK>(plast[cidx], gl, j, lpr_shift, [&](int q) { return reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]; });
             if (!closed) out[cidx] = acc;
             else if (head_slot < C) {
                 V* row = reinterpret_cast<V*>(cache + (size_t)head_slot * D);
@@ -366,11 +390,12 @@ __global__ __launch_bounds__(256) void k_mark_dirty(const int32_t* __restrict__ 
     }
 }
 
-// Runs that cross workgroup borders: the workgroup where the run starts adds the later workgroups' pieces in order.
+// Runs that cross workgroup borders: the workgroup where the run starts adds the later workgroups' pieces in order, `join` neighbours
+// first (see join_pieces).
 template <int VEC>
 __global__ __launch_bounds__(256) void k_bwd_fixup(int C, float* cache, int D, int lpr_shift, float lr,
                                                    const float* __restrict__ part, const BwdMeta* __restrict__ bmeta,
-                                                   int nblocks) {
+                                                   int nblocks, int join) {
     using V = typename Vec<VEC>::T;
     const int lpr = 1 << lpr_shift;
     const int gpb = blockDim.x >> lpr_shift;
@@ -385,7 +410,7 @@ __global__ __launch_bounds__(256) void k_bwd_fixup(int C, float* cache, int D, i
     // are loaded and ignored.
     constexpr int FIX_PF = 8;
     for (int cidx = lane; cidx < nv; cidx += lpr) {
-        V acc = reinterpret_cast<const V*>(part + (size_t)(b * 2 + 1) * D)[cidx];
+        V acc = reinterpret_cast<const V*>(part + (size_t)(b * 2 + 1) * D)[cidx], total = vzero(V());
         bool done = false;
         for (int h = b + 1; h < nblocks && !done; h += FIX_PF) {
             V p[FIX_PF];
@@ -399,18 +424,16 @@ __global__ __launch_bounds__(256) void k_bwd_fixup(int C, float* cache, int D, i
 #pragma unroll
             for (int j = 0; j < FIX_PF; ++j) {
                 if (!done && h + j < nblocks) {
+                    if (((h + j) & (join - 1)) == 0) { total = vadd(total, acc); acc = vzero(V()); }
                     acc = vadd(acc, p[j]);
                     done = kind[j] != 2;
                 }
             }
         }
         V* row = reinterpret_cast<V*>(cache + (size_t)slot * D);
-        row[cidx] = vsgd(row[cidx], acc, lr);
+        row[cidx] = vsgd(row[cidx], vadd(total, acc), lr);
     }
 }
-
-// threads per workgroup of the reduction: at most 64 chunks per workgroup
-static inline int bwd_threads(int lpr) { int t = 32 * lpr; if (t > 256) t = 256; if (t < 64) t = 64; return t; }
 
 // (Re)allocation of sort scratch and of the reduction's partial rows; growth is rare and waits for the whole device.
 static int ensure_sort(SortBufs& sb, int64_t n) {
@@ -627,10 +650,11 @@ static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n,
         ProfScope ps(prof, P_BWD_FIXUP, st);
         const BwdMeta* bm = reinterpret_cast<const BwdMeta*>(pmeta);
         const unsigned fb = (unsigned)cdiv(g.blocks, 256 >> sh);
+        const int join = BWD_CHUNK / g.chunk;
         switch (c->vec) {
-            case 4: k_bwd_fixup<4><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
-            case 2: k_bwd_fixup<2><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
-            default: k_bwd_fixup<1><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks); break;
+            case 4: k_bwd_fixup<4><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks, join); break;
+            case 2: k_bwd_fixup<2><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks, join); break;
+            default: k_bwd_fixup<1><<<fb, 256, 0, st>>>((int)c->C, c->cache, c->D, sh, lr, part, bm, (int)g.blocks, join); break;
         }
     }
     FC_HIP(hipGetLastError());
