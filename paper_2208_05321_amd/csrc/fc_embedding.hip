@@ -538,8 +538,10 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
 // k_bwd_fixup gets the longer: 1.7 M of 16 columns (6656 workgroups) 66.8 + 9.6 -> 57.6 + 18.8, 426 k of 128 columns (6656)
 // 64.6 + 8.2 -> 59.1 + 13.8, 328 k of 256 columns (10240) 65.5 + 16.6 -> 66.4 + 44.7.  The limit on floats keeps the partial
 // rows within what embedding_bag_bwd_sgd_noalloc has for them.
-// Rows of fewer than 8 columns keep chunks of 32 and with them the order of their sums: where a row is hardly more than one element,
-// nothing beside it hides what another order leaves of a sum that cancels.
+// Rows of fewer than 8 columns keep chunks of 32, not for speed (1 column, chunks of 32 / of 8: 1000 lookups 20 / 9 us, 50 k 30 / 17,
+// 400 k 32 / 22): a row's lookups then mostly lie in one chunk and are added in position order, one by one, which is what a sum that
+// cancels can be held to in a row of one or a few elements, where no larger one sets the scale (tests/test_gpu_swap_rows.py, one column:
+// 1.1e-8 off with 5e-4 left of the sum).  From 8 columns on a row has larger elements beside it.
 constexpr int BWD_SMALL_CHUNK = BWD_PF, BWD_SMALL_MIN_D = 8;
 constexpr int64_t BWD_SMALL_BLOCKS = 2048, BWD_SMALL_FLOATS = 1 << 20;      // floats: blocks * D
 struct BwdGeom { int threads = 0, chunk = 0; int64_t blocks = 0; size_t lds = 0; };

@@ -23,7 +23,7 @@ def _cut(x, size):
 
 
 # dim, lookups, chunks of 32 lookups per workgroup
-@pytest.mark.parametrize("dim,n,chunks", [(8, 4096, 32), (9, 509, 16), (16, 2048, 32), (16, 20_000, 32), (64, 20_000, 16), (50, 3001, 8), (128, 20_000, 8),
+@pytest.mark.parametrize("dim,n,chunks", [(1, 4300, 64), (1, 20_000, 64), (3, 5000, 32), (8, 4096, 32), (9, 509, 16), (16, 2048, 32), (16, 20_000, 32), (64, 20_000, 16), (50, 3001, 8), (128, 20_000, 8),
                                           (256, 20_000, 4), (1024, 20_001, 4)])
 def test_error_of_a_popular_row(dim, n, chunks):
     import torch
