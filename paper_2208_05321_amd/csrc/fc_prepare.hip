@@ -762,7 +762,10 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     if (!c || n < 0 || num_bags < 0 || n >= LIM || num_bags >= LIM || !offsets || (n > 0 && (!ids || !slots)))
         return FC_ERR_INVALID_ARG;
     FC_HIP(hipSetDevice(c->device));
+    // what can run out of memory comes before any state changes: list set, error word and evicted-row block in turn, rows in transit
+    const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
     FC_TRY(ensure_rbuf(c, n));
+    if (!small) FC_TRY(ensure_marks(c));
     c->pst = st;
     // the list set this call rewrites (missing ranks, victims, fill slots) was last read by the row movement two
     // batches back, possibly on another stream
@@ -789,7 +792,6 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         if (c->vrank_kept && c->move_stream[c->lset ^ 1] != st) FC_HIP(hipStreamWaitEvent(st, c->ev_move_done[c->lset ^ 1], 0));
         transit_base = (int)(buf * c->staging_rows);
     }
-    const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
     const bool small_slots = small && write_slots;
     const int transit = c->dirty_track ? -1 : transit_base;
     const int32_t* landed_ranks = c->dma_evict ? c->vrank_buf[buf] : nullptr;
@@ -806,7 +808,6 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         // two error words in turn: a call's K2a clears the next call's
         uint32_t *err = &c->ctl->err[c->err_set], *next_err = &c->ctl->err[c->err_set ^ 1];
         c->err_set ^= 1;
-        FC_TRY(ensure_marks(c));
         nmark = cdiv(work, MARK_ITEMS * MARK_THREADS);
         if (nmark > MARK_HIT_PARTS) nmark = MARK_HIT_PARTS;
         const int64_t dense_tiles = std::min(c->NB, cdiv(n * c->mark_dense, RT_WORDS * 32));
