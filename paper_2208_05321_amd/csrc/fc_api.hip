@@ -141,7 +141,7 @@ static void destroy(fc_cache* c) {
     for (int b = 0; b < DMA_BLOCKS; ++b)
         if (c->ev_copy_a[b]) (void)hipEventDestroy(c->ev_copy_a[b]);
     for (void* p : {(void*)c->freq_rank, (void*)c->rank_slot, (void*)c->slot_rank, (void*)c->cache, (void*)c->ubits,
-                    (void*)c->rbits, (void*)c->ubytes, (void*)c->uchunks, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->gsum, (void*)c->plan[0], (void*)c->plan[1],
+                    (void*)c->rbits, (void*)c->ubytes, (void*)c->tcount, (void*)c->hitpart, (void*)c->bsum, (void*)c->ssum, (void*)c->gsum, (void*)c->plan[0], (void*)c->plan[1],
                     (void*)c->rbuf,
                     (void*)c->ctl, (void*)c->stage_dev, (void*)c->stage_dev2, (void*)c->part, (void*)c->pmeta, (void*)c->pbits})
         if (p) (void)hipFree(p);

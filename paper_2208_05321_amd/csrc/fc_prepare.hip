@@ -574,17 +574,18 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
     return FC_OK;
 }
 
-// The mark bytes (zero between calls), with the first batch that needs them.
+// The mark bytes and, in the same allocation, those of the chunks (zero between calls), with the first batch that needs them.
 int ensure_marks(fc_cache* c) {
     if (c->ubytes) return FC_OK;
-    const size_t ranks = (size_t)c->NB * RT_WORDS * 32;
-    FC_HIP(hipMalloc((void**)&c->uchunks, ranks / MARK_CHUNK));
-    FC_HIP(hipMemset(c->uchunks, 0, ranks / MARK_CHUNK));
-    FC_HIP(hipMalloc((void**)&c->ubytes, ranks));
-    hipError_t e = hipMemset(c->ubytes, 0, ranks);
+    const size_t ranks = (size_t)c->NB * RT_WORDS * 32, bytes = ranks + ranks / MARK_CHUNK;
+    uint8_t* p = nullptr;
+    FC_HIP(hipMalloc((void**)&p, bytes));
+    hipError_t e = hipMemset(p, 0, bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) { (void)hipFree(c->ubytes); c->ubytes = nullptr; }
+    if (e != hipSuccess) (void)hipFree(p);
     FC_HIP(e);
+    c->ubytes = p;
+    c->uchunks = p + ranks;
     return FC_OK;
 }
 

@@ -87,6 +87,7 @@ int main() {
     const size_t mine = 4;               // buffers of step()
     need(cache_destroy(c) == FC_OK, "destroy");
     printf("allocations left: %ld\n", (long)(live.size() - mine));
+    need(live.size() == mine, "everything is given back");
     printf("ok\n");
     return 0;
 }
