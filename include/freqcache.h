@@ -157,6 +157,7 @@ enum {
  *   FC_SORT_BITS          most key bits per pass of the backward's sort (4..11; default: passes of up to 9 bits without a
  *                         scan kernel); FC_SORT_FUSED=0 keeps the scan kernel
  *   FC_FETCH_CU_MASK      experiment: number of compute units the early fetch's stream may use (default: all)
+ *   FC_MARK_BYTES         0: marks are bits, as they are where device memory has no room for a byte per row (see cache_reserve)
  *   FC_MARK_DENSE         ranks per id of a batch whose marks are read one and all, not chunk by chunk (4)
  *   FC_PLAN_FOLD_TILES    most tiles of 32768 ranks for which the emitting kernel has eight workgroups to a tile (1024), else one
  *   FC_SMALL_INDEX        0: small batches (up to 4096 ids, 2^20 rows, 2^16 slots) are indexed by the general kernels, too
@@ -167,7 +168,9 @@ int cache_create(int64_t num_rows, int32_t dim, int64_t cache_rows, const int32_
                  float* host_weight, int64_t staging_rows, int32_t flags, void* hip_stream, fc_cache** out);
 
 /* Allocate now everything the per-batch calls would otherwise allocate when they first meet a batch of that size:
- * the per-id rank buffer of cache_prepare and its byte marks (num_rows bytes), the
+ * the per-id rank buffer of cache_prepare and its byte marks (num_rows * 257 / 256
+ * bytes, which a batch allocates that is not indexed by one workgroup; where there is no room for them the marks are bits, and no
+ * call fails for it), the
  * sort scratch and partial-sum rows of embedding_bag_bwd_sgd for batches of up to max_ids lookups (three sort sets of 16 * max_ids bytes), and, if pipelined != 0 (a handle that will plan ahead), the two arrival blocks of
  * cache_plan_next (staging_rows * dim * 4 bytes each).  The transmitter's memory stays bounded by staging_rows
  * (Section 4.3); this call only moves the allocations out of the training loop.  Optional: without it (or for a larger

@@ -260,6 +260,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     if (const char* e = getenv("FC_AHEAD_MISS_PCT")) { const float v = (float)atof(e); if (v >= 0.f) c->ahead_miss_pct = v; }
     if (const char* e = getenv("FC_FWD_BAGS")) { const int v = atoi(e); if (v == 1 || v == 2 || v == 4) c->fwd_bags = v; }
     if (const char* e = getenv("FC_MARK_DENSE")) { const int v = atoi(e); if (v >= 0 && v <= 4096) c->mark_dense = v; }
+    if (const char* e = getenv("FC_MARK_BYTES")) c->bit_marks = c->no_mark_bytes = atoi(e) == 0;
     if (const char* e = getenv("FC_SMALL_INDEX")) c->small_index = atoi(e) != 0;
     if (const char* e = getenv("FC_PLAN_FOLD_TILES")) { const int v = atoi(e); if (v >= 0) c->split_tiles = v; }
     if (const char* e = getenv("FC_EVICT_EARLY")) c->evict_early = atoi(e);
@@ -607,7 +608,8 @@ int cache_reserve(fc_cache* c, int64_t max_ids, int32_t pipelined) {
     FC_HIP(hipSetDevice(c->device));
     FC_TRY(ensure_rbuf(c, max_ids));
     FC_TRY(reserve_bwd(c, max_ids));
-    FC_TRY(ensure_marks(c));
+    c->no_mark_bytes = c->bit_marks;
+    (void)mark_bytes(c);               // without room for them the marks are bits
     c->plans_ahead |= pipelined != 0;
     if (pipelined && !(c->flags & FC_TRANSMIT_STAGED))
         for (int k = 0; k < 2; ++k) if (!ensure_arrival_block(c, k)) return FC_ERR_OOM_DEVICE;

@@ -192,6 +192,8 @@ struct fc_cache {
     uint32_t* ubits = nullptr;      // rank-space bitmap: rows used by the current batch
     uint8_t* ubytes = nullptr;      // the same as a byte per rank, and per chunk of ranks that has any (zero between calls); allocated
     uint8_t* uchunks = nullptr;     // with the first batch that uses them
+    bool no_mark_bytes = false;     // no room for them: marks are bits of ubits
+    bool bit_marks = false;         // never bytes (tuning: FC_MARK_BYTES=0)
     uint32_t* rbits = nullptr;      // rank-space bitmap: resident rows
     int32_t* tcount = nullptr;      // empty slots per tile of 1024 slots
     int32_t* hitpart = nullptr;     // [MARK_HIT_PARTS] per-workgroup access-level hit counts of the marking kernel
@@ -360,7 +362,7 @@ int dma_quiesce(fc_cache* c, hipStream_t st);
 // from_ranks: the slots are not written yet; the sort's first kernel derives them from the per-id ranks and writes them
 // to `slots_out` on its way (the slot write-out folded into the sort)
 int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr);
-int ensure_marks(fc_cache* c);             // byte marks
+bool mark_bytes(fc_cache* c);              // byte marks (allocates them on first use), else bit marks
 int ensure_rbuf(fc_cache* c, int64_t n);  // per-id rank buffer for batches of n ids
 int reserve_bwd(fc_cache* c, int64_t n);   // sort scratch of all three sets and the partial rows for batches of n lookups
 int bwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags,

@@ -96,6 +96,116 @@ __global__ __launch_bounds__(MARK_THREADS) void k_remap_mark(const int64_t* __re
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// K1 where device memory has no room for the bytes: marks are bits of ubits, cleared before.  Device-scope atomics on one address
+// serialise at the memory side (~100 ns each on this part), so the low end of rank space, the popular rows, is first marked in a
+// per-workgroup LDS bitmap and merged into the global one once per workgroup; only the long tail of rare ranks goes to global
+// atomics directly.  At most BITS_MAX_BLOCKS workgroups run, so a hot word sees at most that many global atomics.
+// us, beside forward and backward, bytes / this / global atomics alone: 53 k ids, 4 M rows 10 / 16 / 49; 426 k ids, 10 M rows 24 / 38 / 209; 1.7 M ids,
+// 100 M rows 38 / 66 / 498.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int BITS_THREADS = 1024, BITS_ITEMS = 2;
+constexpr int BITS_LDS_WORDS = 12288;      // 48 KB: ranks below 393,216
+constexpr int BITS_MAX_BLOCKS = 256;
+
+__global__ __launch_bounds__(BITS_THREADS) void k_remap_bits(const int64_t* __restrict__ ids, int n,
+                                                             const int64_t* __restrict__ offsets, int num_bags,
+                                                             const int32_t* __restrict__ freq_rank, int64_t N,
+                                                             uint32_t* ubits, const uint32_t* __restrict__ rbits,
+                                                             int32_t* __restrict__ rbuf, uint32_t* err,
+                                                             int32_t* __restrict__ hitpart, int per_block,
+                                                             int lds_words, int4* __restrict__ gsum, int groups) {
+    __shared__ uint32_t low[BITS_LDS_WORDS];
+    __shared__ int red[BITS_THREADS / 64];
+    const int tid = threadIdx.x;
+    for (int g = blockIdx.x * BITS_THREADS + tid; g < groups; g += gridDim.x * BITS_THREADS) gsum[g] = make_int4(0, 0, 0, 0);      // for K2a
+    for (int w = tid; w < lds_words; w += BITS_THREADS) low[w] = 0;
+    __syncthreads();
+    const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
+    const int64_t begin = (int64_t)blockIdx.x * per_block;
+    const int64_t end = begin + per_block < work ? begin + per_block : work;
+    int hits = 0;
+    uint32_t flags = 0;
+    // four ids per thread and round: all loads of a stage are issued before any of them is waited for
+    for (int64_t i0 = begin + tid; i0 < end; i0 += 4 * BITS_THREADS) {
+        int64_t id[4];
+        int r[4];
+        uint32_t rb[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + (int64_t)k * BITS_THREADS;
+            id[k] = (i < end && i < n) ? ids[i] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + (int64_t)k * BITS_THREADS;
+            r[k] = -1;
+            if (i < end && i < n) {
+                if (id[k] < 0 || id[k] >= N) flags |= EF_ID_RANGE;
+                else r[k] = freq_rank[id[k]];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rb[k] = r[k] >= 0 ? rbits[(uint32_t)r[k] >> 5] : 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + (int64_t)k * BITS_THREADS;
+            if (i < end && i < n) {
+                if (r[k] >= 0) {
+                    const uint32_t w = (uint32_t)r[k] >> 5, bit = 1u << (r[k] & 31);
+                    if (w < (uint32_t)lds_words) atomicOr(&low[w], bit);
+                    // rare ranks: bits are only ever set during this kernel, so a read that sees the bit is final
+                    else if (!(ubits[w] & bit)) atomicOr(&ubits[w], bit);
+                    hits += (rb[k] & bit) != 0;
+                }
+                rbuf[i] = r[k];
+            }
+            if (i < end && i <= num_bags) {
+                const int64_t o = offsets[i];
+                if (o != i) flags |= EF_NOT_ONE_PER_BAG;
+                if (i == 0 && o != 0) flags |= EF_BAD_OFFSETS;
+                if (i == num_bags && o != (int64_t)n) flags |= EF_BAD_OFFSETS;
+                if (i < num_bags && offsets[i + 1] < o) flags |= EF_BAD_OFFSETS;
+            }
+        }
+    }
+    __syncthreads();
+    // Merge into the global bitmap: LDS words first, then all global reads at once, then the atomics still needed.
+    // Every workgroup holds the hottest words, so each starts at a different word: by the time most of them reach a
+    // hot word its bits are already set and the (coherent) read spares the atomic.
+    const int rot = (int)(((int64_t)blockIdx.x * lds_words) / gridDim.x);
+    constexpr int FL = BITS_LDS_WORDS / BITS_THREADS;
+    uint32_t v[FL], g[FL];
+    int wi[FL];
+#pragma unroll
+    for (int k = 0; k < FL; ++k) {
+        int w = k * BITS_THREADS + tid;
+        v[k] = 0;
+        if (w < lds_words) {
+            w += rot;
+            if (w >= lds_words) w -= lds_words;
+            v[k] = low[w];
+        }
+        wi[k] = w;
+    }
+#pragma unroll
+    for (int k = 0; k < FL; ++k)
+        g[k] = v[k] ? __hip_atomic_load(&ubits[wi[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < FL; ++k)
+        if (v[k] & ~g[k]) atomicOr(&ubits[wi[k]], v[k]);
+    hits = wave_sum(hits);
+    if ((tid & 63) == 0) red[tid >> 6] = hits;
+    __syncthreads();
+    if (tid == 0) {
+        int s = 0;
+#pragma unroll
+        for (int k = 0; k < BITS_THREADS / 64; ++k) s += red[k];
+        hitpart[blockIdx.x] = s;
+    }
+    if (flags) atomicOr(err, flags);
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // K2a  per rank-space tile: rows used, rows missing, rows evictable.  The tile's 32768 marks become its bitmap words (all of
 //      them written) and the set ones are cleared.  A lane turns 16 bytes into 16 bits with four 4-byte dot products.
 //      On the way (DMA evict transmitter): the block that this batch's victims will go to has reached the host table, so
@@ -111,6 +221,7 @@ __device__ __forceinline__ uint32_t bits_of(uint4 v) {
 // A wavefront counts SUB_TILES / 4 sub-tiles of 4096 ranks, a lane 64 neighbouring ranks of each: four lanes share a chunk.
 constexpr int WAVE_SUBS = SUB_TILES / (RT_THREADS / 64);
 
+template <bool BYTES>
 __global__ __launch_bounds__(RT_THREADS) void k_rank_count(uint4* ubytes16, uint8_t* uchunks, int dense_tiles, uint2* __restrict__ ubits64,
                                                            const uint2* __restrict__ rbits64, const uint2* __restrict__ pbits64, int protect_prev,
                                                            uint32_t* __restrict__ bsum, uint32_t* __restrict__ ssum, int4* gsum,
@@ -129,7 +240,7 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_count(uint4* ubytes16, uint
     uint2 q[WAVE_SUBS], pv[WAVE_SUBS];
     uint32_t any[WAVE_SUBS];
 #pragma unroll
-    for (int k = 0; k < WAVE_SUBS; ++k) any[k] = dense ? 1u : uchunks[(p0 + k * 64) / 4];
+    for (int k = 0; k < WAVE_SUBS; ++k) any[k] = !BYTES ? 0u : dense ? 1u : uchunks[(p0 + k * 64) / 4];
 #pragma unroll
     for (int k = 0; k < WAVE_SUBS; ++k) q[k] = rbits64[p0 + k * 64];
 #pragma unroll
@@ -146,15 +257,18 @@ __global__ __launch_bounds__(RT_THREADS) void k_rank_count(uint4* ubytes16, uint
     int cu = 0;
 #pragma unroll
     for (int k = 0; k < WAVE_SUBS; ++k) {
-        uint32_t u[4];
+        uint2 uu;
+        if (BYTES) {
+            uint32_t u[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            u[j] = bits_of(v[k][j]);
-            if (u[j]) ubytes16[(p0 + k * 64) * 4 + j] = make_uint4(0, 0, 0, 0);
-        }
-        if (!dense && any[k] && (lane & 3) == 0) uchunks[(p0 + k * 64) / 4] = 0;       // its four lanes have read it, in one instruction
-        const uint2 uu = make_uint2(u[0] | u[1] << 16, u[2] | u[3] << 16);
-        ubits64[p0 + k * 64] = uu;
+            for (int j = 0; j < 4; ++j) {
+                u[j] = bits_of(v[k][j]);
+                if (u[j]) ubytes16[(p0 + k * 64) * 4 + j] = make_uint4(0, 0, 0, 0);
+            }
+            if (!dense && any[k] && (lane & 3) == 0) uchunks[(p0 + k * 64) / 4] = 0;       // its four lanes have read it, in one instruction
+            uu = make_uint2(u[0] | u[1] << 16, u[2] | u[3] << 16);
+            ubits64[p0 + k * 64] = uu;
+        } else uu = ubits64[p0 + k * 64];
         cu += __popc(uu.x) + __popc(uu.y);
         // look-ahead: rows of the previously prepared batch are not evictable either
         const int miss = __popc(uu.x & ~q[k].x) + __popc(uu.y & ~q[k].y);
@@ -574,19 +688,23 @@ int ensure_rbuf(fc_cache* c, int64_t n) {
     return FC_OK;
 }
 
-// The mark bytes and, in the same allocation, those of the chunks (zero between calls), with the first batch that needs them.
-int ensure_marks(fc_cache* c) {
-    if (c->ubytes) return FC_OK;
+__global__ __launch_bounds__(256) void k_zero_words(uint4* p) { p[(size_t)blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0); }
+
+// The mark bytes and, in the same allocation, those of the chunks (zero between calls), with the first batch that needs them.  Where
+// there is no room for them (num_rows bytes) marks are bits, until a cache_reserve finds room.
+bool mark_bytes(fc_cache* c) {
+    if (c->ubytes || c->no_mark_bytes) return c->ubytes != nullptr;
     const size_t ranks = (size_t)c->NB * RT_WORDS * 32, bytes = ranks + ranks / MARK_CHUNK;
     uint8_t* p = nullptr;
-    FC_HIP(hipMalloc((void**)&p, bytes));
-    hipError_t e = hipMemset(p, 0, bytes);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) (void)hipFree(p);
-    FC_HIP(e);
+    if (hipMalloc((void**)&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError();
+        if (p) (void)hipFree(p);
+        c->no_mark_bytes = true;
+        return false;
+    }
     c->ubytes = p;
     c->uchunks = p + ranks;
-    return FC_OK;
+    return true;
 }
 
 // Evicted rows stored by kernel: gather into a device block on the caller's stream (so the slots can be refilled at once); the block
@@ -766,7 +884,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     // what can run out of memory comes before any state changes: list set, error word and evicted-row block in turn, rows in transit
     const bool small = !lookahead && prepare_small_fits(c, n, num_bags);
     FC_TRY(ensure_rbuf(c, n));
-    if (!small) FC_TRY(ensure_marks(c));
+    const bool bytes = !small && mark_bytes(c);
     c->pst = st;
     // the list set this call rewrites (missing ranks, victims, fill slots) was last read by the row movement two
     // batches back, possibly on another stream
@@ -809,19 +927,30 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         // two error words in turn: a call's K2a clears the next call's
         uint32_t *err = &c->ctl->err[c->err_set], *next_err = &c->ctl->err[c->err_set ^ 1];
         c->err_set ^= 1;
-        nmark = cdiv(work, MARK_ITEMS * MARK_THREADS);
-        if (nmark > MARK_HIT_PARTS) nmark = MARK_HIT_PARTS;
+        const int groups = (int)cdiv(c->NB, GROUP_TILES);
         const int64_t dense_tiles = std::min(c->NB, cdiv(n * c->mark_dense, RT_WORDS * 32));
-        {
+        if (bytes) {
+            nmark = std::min<int64_t>(cdiv(work, MARK_ITEMS * MARK_THREADS), MARK_HIT_PARTS);
             ProfScope ps(c, P_REMAP_MARK, st);
             k_remap_mark<<<(unsigned)nmark, MARK_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubytes, c->uchunks,
-                                                                  (int)std::min(dense_tiles * RT_WORDS * 32, c->N), c->rbits, c->rbuf, err, c->hitpart, c->gsum, (int)cdiv(c->NB, GROUP_TILES));
+                                                                  (int)std::min(dense_tiles * RT_WORDS * 32, c->N), c->rbits, c->rbuf, err, c->hitpart, c->gsum, groups);
+        } else {
+            const int64_t per_block = cdiv(cdiv(work, std::min<int64_t>(cdiv(work, BITS_ITEMS * BITS_THREADS), BITS_MAX_BLOCKS)), BITS_THREADS) * BITS_THREADS;
+            const int64_t words = c->NB * RT_WORDS;
+            nmark = cdiv(work, per_block);
+            k_zero_words<<<(unsigned)(words / 1024), 256, 0, st>>>((uint4*)c->ubits);
+            ProfScope ps(c, P_REMAP_MARK, st);
+            k_remap_bits<<<(unsigned)nmark, BITS_THREADS, 0, st>>>(ids, (int)n, offsets, (int)num_bags, c->freq_rank, c->N, c->ubits, c->rbits, c->rbuf, err,
+                                                                  c->hitpart, (int)per_block, (int)std::min<int64_t>(words, BITS_LDS_WORDS), c->gsum, groups);
         }
         {
             ProfScope ps(c, P_RANK_COUNT, st);
-            k_rank_count<<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, c->uchunks, (int)dense_tiles, (uint2*)c->ubits, (const uint2*)c->rbits,
-                                                                (const uint2*)c->pbits, protect_prev, c->bsum, c->ssum, c->gsum,
-                                                                landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot, next_err);
+#define FC_COUNT(B) \
+            k_rank_count<B><<<(unsigned)c->NB, RT_THREADS, 0, st>>>((uint4*)c->ubytes, c->uchunks, (int)dense_tiles, (uint2*)c->ubits, (const uint2*)c->rbits, \
+                                                                   (const uint2*)c->pbits, protect_prev, c->bsum, c->ssum, c->gsum, \
+                                                                   landed_ranks, (int)landed, (int)(buf * c->staging_rows), c->rank_slot, next_err)
+            if (bytes) FC_COUNT(true); else FC_COUNT(false);
+#undef FC_COUNT
         }
         const PlanArgs pa{c->bsum, c->ssum, c->gsum, err, &c->ctl->async_flags, c->hitpart, c->hctl, c->plan[c->lset], (int)c->NB, (int)c->C, (int)c->nfree, (int)nmark, ticket,
                           protect_prev};

@@ -1,7 +1,7 @@
 // A program of its own around libfreqcache.so whose device allocations can be made to fail: hipMalloc and hipFree of this executable
 // come before the runtime's.  A handle with FC_EVICT_DMA takes small batches (indexed by one workgroup) until the ring of evicted-row
-// blocks has been round, then a batch that is the first to need the mark map, for which there is no room; whatever that call
-// returns, every row of every later batch has to be its own.  Row r of the table holds r.
+// blocks has been round, then batches that need the mark map, for which there is no room: they take place all the same, and every
+// row of every later batch is its own.  Row r of the table holds r.
 #include <hip/hip_runtime_api.h>
 
 #include <dlfcn.h>
@@ -71,17 +71,17 @@ int main() {
     float* host = cache_host_weight(c);
     for (int64_t i = 0; i < N * D; ++i) host[i] = (float)(i / D);
     for (int k = 0; k < 8; ++k) need(step(c, k * SMALL, SMALL) == FC_OK, "small batch");      // from the third on, 3000 rows leave with each
-    const size_t before = live.size();
-    fail_from = 1 << 18;                 // the mark map (num_rows bytes), not the small buffers of a batch
+    fail_from = N;                       // the mark map (num_rows bytes), not the smaller buffers of a batch
     for (int k = 0; k < 2; ++k) {
-        const int rc = step(c, 100 * SMALL, BIG);
-        need(rc == FC_OK || rc == FC_ERR_OOM_DEVICE, "code of the call without room");
-        printf("without room: %s\n", cache_strerror(rc));
+        need(step(c, (100 + 2 * k) * SMALL, BIG) == FC_OK, "large batch without room");
+        need(cache_reserve(c, BIG, 0) == FC_OK, "reserve without room");
     }
     need(failed > 0, "an allocation that failed");
-    printf("allocations that failed: %d, kept since: %ld\n", failed, (long)(live.size() - before));
+    printf("allocations that failed: %d\n", failed);
     fail_from = 0;
-    need(step(c, 100 * SMALL, BIG) == FC_OK, "large batch");
+    need(step(c, 104 * SMALL, BIG) == FC_OK, "large batch");
+    need(cache_reserve(c, BIG, 0) == FC_OK, "reserve");
+    need(step(c, 106 * SMALL, BIG) == FC_OK, "large batch");
     for (int k = 0; k < 8; ++k) need(step(c, k * SMALL, SMALL) == FC_OK, "small batch after it");
     need(cache_check(c) == FC_OK, "check");          // (not before: it drops the marks of rows in transit)
     const size_t mine = 4;               // buffers of step()

@@ -19,3 +19,17 @@ def test_mark_chunks(monkeypatch, rows, dense, split_tiles):
     run_parity(w, 3, warm=False)
     run_parity_planned(w, 4, warm=True, dma_evict=True, inputs_ready=True)
     run_parity_lookahead(w, 4, warm=True)
+
+
+@pytest.mark.parametrize("rows", [524_288, 524_289, 1_048_577])
+@pytest.mark.parametrize("split_tiles", ["0", "1024"])
+def test_bit_marks(monkeypatch, rows, split_tiles):
+    """Where there is no room for a byte per row."""
+    monkeypatch.setenv("FC_MARK_BYTES", "0")
+    monkeypatch.setenv("FC_PLAN_FOLD_TILES", split_tiles)
+    w = TinyWorkload(num_rows=rows, dim=4, cache_rows=9000, seed=rows + 1, multi_hot=False, bags=5000,
+                     hot=[0, 31, 32, 255, rows // 2, rows - 257, rows - 1], distinct_cap=4000)
+    run_parity(w, 3, warm=False)
+    run_parity(w, 3, warm=True, dma_evict=True)
+    run_parity_planned(w, 4, warm=True, dma_evict=True, inputs_ready=True)
+    run_parity_lookahead(w, 4, warm=True)
