@@ -139,7 +139,9 @@ enum {
  *   hip_stream      hipStream_t on which all per-batch work is enqueued (NULL = default stream).
  *   out             receives the handle.
  * Errors: INVALID_ARG, NOT_PERMUTATION, NOT_PINNED, OOM_DEVICE, OOM_PINNED, HIP.  Synchronous (it also runs a few
- * sub-millisecond test kernels on hip_stream to find library streams that run beside it).
+ * sub-millisecond test kernels on hip_stream to find library streams that run beside it; and with FC_EVICT_DMA and blocks of 1 MB or
+ * more, the first handle of a process on a device copies a few dozen blocks of up to 4 MB, about 20 ms, so that the runtime sets up
+ * its copy engines here and not among the first training steps).
  * Tuning knobs, read from the environment at this call (defaults suit an MI355X on a PCIe Gen5 x16 link):
  *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256)
  *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch, fixed (default: starts at 32 and follows the

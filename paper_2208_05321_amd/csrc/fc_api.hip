@@ -5,6 +5,7 @@
 #include <stdio.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <new>
 #include <stdlib.h>
@@ -216,10 +217,14 @@ static int make_library_streams(fc_cache* c) {
 // The runtime opens another copy engine when a copy is handed over while one that waited for a kernel is under way, up to three more,
 // and each time the call takes 5 to 15 ms.  That belongs here and not in the middle of a training loop: blocks leave as they will
 // there, DMA_BLOCKS at most under way, each behind a short kernel.  (20 steps of 1.7 M ids of 128 columns, 11 ms, with one or two such calls
-// among them 16 to 25 ms.)  Blocks of less than 1 MB are gone before the next one comes.
+// among them 16 to 25 ms.)  Blocks of less than 1 MB are gone before the next one comes.  The engines belong to the process, so the
+// first handle with such blocks on a device opens them (about 20 ms) and the others do not (3 to 4 ms each, for nothing).  This is how
+// the runtime was seen to behave, not something it promises; nothing depends on it but those milliseconds.
+static std::atomic<uint64_t> engines_open{0};       // a bit per device
 static int open_copy_engines(fc_cache* c) {
     const size_t bytes = std::min((size_t)c->staging_rows * c->D * 4, (size_t)4 << 20);
-    if (bytes < (size_t)1 << 20) return FC_OK;
+    const uint64_t mine = 1ull << (c->device & 63);
+    if (bytes < (size_t)1 << 20 || (engines_open.load(std::memory_order_relaxed) & mine)) return FC_OK;
     for (int k = 0; k < 32; ++k) {
         const int b = k % DMA_BLOCKS;
         if (k >= DMA_BLOCKS) FC_HIP(hipEventSynchronize(c->ev_d2h[b]));
@@ -231,6 +236,7 @@ static int open_copy_engines(fc_cache* c) {
         FC_HIP(hipEventRecord(c->ev_d2h[b], c->side));
     }
     FC_HIP(hipStreamSynchronize(c->side));
+    engines_open.fetch_or(mine, std::memory_order_relaxed);
     return FC_OK;
 }
 
