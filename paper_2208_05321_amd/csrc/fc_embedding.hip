@@ -251,21 +251,21 @@ __host__ __device__ static inline int bwd_threads(int lpr) { int t = 32 * lpr; i
 // columns 4.5e-7 and 2.5e-7; in levels 1.7e-7 and 2.4e-7).
 template <int JOIN, class V, class Piece>
 __device__ __forceinline__ V join_pieces(V first, int a, int b, int lpr_shift, Piece piece) {
-    V acc = first;
-    if (JOIN == 1) {
-        for (int q = a + 1; q <= b; ++q) acc = vadd(acc, piece(q));
-        return acc;
+    V mid = first, total = vzero(V());
+    int q = a + 1;
+    for (; q <= b && (JOIN == 1 || q % JOIN != 0); ++q) mid = vadd(mid, piece(q));       // to the end of the first of those
+    if (JOIN == 1) return mid;
+    const int span = (bwd_threads(1 << lpr_shift) >> lpr_shift) * JOIN;                  // (powers of two, all of them)
+    for (; q <= b; q += JOIN) {
+        V p[JOIN];
+#pragma unroll
+        for (int k = 0; k < JOIN; ++k) p[k] = q + k <= b ? piece(q + k) : vzero(V());
+#pragma unroll
+        for (int k = 1; k < JOIN; ++k) p[0] = vadd(p[0], p[k]);
+        if ((q & (span - 1)) == 0) { total = vadd(total, mid); mid = vzero(V()); }
+        mid = vadd(mid, p[0]);
     }
-    const int span = (bwd_threads(1 << lpr_shift) >> lpr_shift) * JOIN;       // (powers of two, all of them)
-    V mid = vzero(V()), total = vzero(V());
-    for (int q = a + 1; q <= b; ++q) {
-        if (q % JOIN == 0) {
-            mid = vadd(mid, acc); acc = vzero(V());
-            if ((q & (span - 1)) == 0) { total = vadd(total, mid); mid = vzero(V()); }
-        }
-        acc = vadd(acc, piece(q));
-    }
-    return vadd(total, vadd(mid, acc));
+    return vadd(total, mid);
 }
 
 // STREAM: every gradient row is read exactly once (one lookup per bag) -> non-temporal loads
@@ -700,14 +700,15 @@ int bwd_noalloc_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t
     FC_TRY(bwd_check_args(c, slots, n, offsets, num_bags, grad));
     if (n > FC_NOALLOC_MAX_IDS) return FC_ERR_SCRATCH_EXCEEDED;
     const int64_t rblocks = bwd_geometry(c, n > 0 ? n : 1).blocks;
-    const size_t a256 = 255;
-    const size_t pair_bytes = ((size_t)FC_NOALLOC_MAX_IDS * 4 + a256) & ~a256;
-    const size_t ghist_bytes = ((size_t)(cdiv(FC_NOALLOC_MAX_IDS, RS_TILE) << RS_MAX_BITS) * 4 + a256) & ~a256;
-    const size_t dtot_bytes = ((size_t)(1 << RS_MAX_BITS) * 4 + a256) & ~a256;
-    const size_t fixed = 4 * pair_bytes + ghist_bytes + dtot_bytes;
+    constexpr size_t a256 = 255;
+    constexpr size_t pair_bytes = ((size_t)FC_NOALLOC_MAX_IDS * 4 + a256) & ~a256;
+    constexpr size_t ghist_bytes = ((size_t)(((FC_NOALLOC_MAX_IDS + RS_TILE - 1) / RS_TILE) << RS_MAX_BITS) * 4 + a256) & ~a256;
+    constexpr size_t dtot_bytes = ((size_t)(1 << RS_MAX_BITS) * 4 + a256) & ~a256;
+    constexpr size_t fixed = 4 * pair_bytes + ghist_bytes + dtot_bytes;
+    // (chunks of 8 refuse nothing that chunks of 32 would take)
+    static_assert(fixed + ((BWD_SMALL_BLOCKS * sizeof(BwdMeta) + a256) & ~a256) + BWD_SMALL_FLOATS * 8 <= FC_NOALLOC_SCRATCH_BYTES, "scratch too small for chunks of 8");
     const size_t meta_bytes = ((size_t)rblocks * sizeof(BwdMeta) + a256) & ~a256;
     const size_t part_bytes = (size_t)rblocks * 2 * c->D * 4;
-    static_assert(4 * (((size_t)FC_NOALLOC_MAX_IDS * 4 + 255) & ~(size_t)255) + (1 << 20) <= FC_NOALLOC_SCRATCH_BYTES, "scratch too small for the sort");
     if (fixed + meta_bytes + part_bytes > (size_t)FC_NOALLOC_SCRATCH_BYTES) return FC_ERR_SCRATCH_EXCEEDED;   // wide rows: fewer lookups fit
     if (n == 0) return FC_OK;
     FC_HIP(hipSetDevice(c->device));
