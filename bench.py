@@ -349,7 +349,8 @@ def main():
             # algorithmic bytes per launch: what the step must move whatever the implementation (R = bytes per row)
             model = {
                 "remap_mark": n_m * (8 + 4 + 4 + 4) + (nb + 1) * 8,            # id, idx_map entry, resident bit word, rank out
-                "rank_count": nw * 4 * 2,
+                # marks of 4 ranks per id, a byte per 256 ranks beyond, resident bits in, the batch's bits out
+                "rank_count": min(4.0 * n_m, w.num_rows) + w.num_rows / 256 + nw * 4 * 2,
                 "rank_emit": nw * 4 * 2 + m_m * 4 + e_m * (8 + 4 + 4),
                 "evict_gather": e_m * (2 * R + 4),
                 "evict_store": e_m * (2 * R + 4),

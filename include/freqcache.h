@@ -253,7 +253,8 @@ int embedding_bag_fwd(fc_cache* c, const int32_t* slots_dev, int64_t n, const in
 /* Backward of the sum-bag fused with the SGD step (synchronous update, Section 2.2): for every distinct
  * slot s, g = sum over the lookups i with slots[i] == s of grad_out[bag(i), :] (a row looked up k times
  * receives k gradients), then cached_weight[s, :] -= lr * g.  Deterministic: no floating-point atomics;
- * lookups of a slot are summed in position order within fixed blocks of consecutive lookups.
+ * lookups of a slot are summed in position order within fixed blocks of consecutive lookups (8 or 32, by the size of the batch), the
+ * blocks' sums in levels.
  *   grad_out_dev fp32[num_bags*dim], device.  Asynchronous on the stream; BAD_SLOT as above. */
 int embedding_bag_bwd_sgd(fc_cache* c, const int32_t* slots_dev, int64_t n, const int64_t* offsets_dev,
                           int64_t num_bags, const float* grad_out_dev, float lr);
@@ -265,7 +266,8 @@ int embedding_bag_bwd_sgd(fc_cache* c, const int32_t* slots_dev, int64_t n, cons
  * code object (every GPU the library runs on holds one copy until the process ends; cache_create looks its address up).
  * Limits: n <= FC_NOALLOC_MAX_IDS lookups, and 10.5 MB + blocks * (16 + 8 * dim) bytes <= FC_NOALLOC_SCRATCH_BYTES, where
  * blocks = ceil(n / 256) for dim <= 128 and ceil(n * lanes / 8192) with lanes = min(64, dim / 4) for wider rows (dim 256:
- * n <= 524288; dim 1024: n <= 150000 or so); beyond them the call returns FC_ERR_SCRATCH_EXCEEDED and does nothing.
+ * n <= 524288; dim 1024: n <= 150000 or so); beyond them the call returns FC_ERR_SCRATCH_EXCEEDED and does nothing.  (Batches of up to
+ * min(2048, 2^20 / dim) blocks of a quarter of that many lookups are cut into those; they always fit.)
  * It never uses a sort started ahead of time by cache_prepare (create the handle with FC_NO_PRESORT to spare that work)
  * and is not covered by cache_profile_*.  All calls on one GPU, from any handle, share the one array: calls that overlap
  * on a GPU (two handles on different streams) race; the array keeps the previous call's contents, none of which the

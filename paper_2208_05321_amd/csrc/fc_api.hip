@@ -533,9 +533,11 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     const int rec = c->rec_next;
     // Few rows to move: the host binds the step, and what counts is what each call costs it.  Making a stream wait for an event that has
     // not happened yet takes 10-15 us, for one that has 0.4: the fetch comes last, when the emitting kernel is through.  Many: the link
-    // binds it, and fetch and block copy set out as early as they can (a first pass, 13 MB each way: 455 us, and 513 with the fetch last
-    // and the copy behind the sort).  (The rows move under the sort either way.  Behind it, with one wait of the caller's stream for both,
-    // one step of 426 k lookups of 32 columns came to 147 us rather than 154, and others to more: 229 k of 32 columns in bags 150 and
+    // binds it, and the fetch sets out as early as it can.  us a step in turn with other handles, and the first pass, fetch first / last:
+    // 426 k lookups, rows of 2 MB (16 columns) 144 / 139 and 276 / 292, 4.5 MB 155 / 154 and 310 / 325, 7 MB 171 / 166 and 413 / 427, 9 MB
+    // 207 / 207 and 398 / 392, 13 MB 294 / 295 and 552 / 546, 18 MB 389 / 381 and 609 / 621; 53 k lookups, 2 MB 127 / 122 and 183 / 178.
+    // (The caller's stream waits for the decisions and, later, for the sort, so that the rows move under it.  With one wait for both, one
+    // step of 426 k lookups of 32 columns came to 147 us rather than 154, and others to more: 229 k of 32 columns in bags 150 and
     // 137, 53 k of 64 columns 126 and 119, and the first pass 326 and 320, 292 and 249, 198 and 181.)
     const bool few = c->last.n_miss * (int64_t)c->D * 4 <= FEW_BYTES;
     if (rc == FC_OK) rc = index_assign(c, st, run, -1);
@@ -698,8 +700,10 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     // slot write-out into, and rows fetched by a kernel that can read their number.
     // (After a batch without a miss the next one most likely has none either, and the kernels that depend on there being some
     // are better not enqueued.  Large batches of wide rows wait: HBM and the link bind them, and what is enqueued ahead crowds the current
-    // batch's forward and backward.  us a step, waiting / enqueued ahead: 1.7 M lookups of 16 columns, 100 M rows 262 / 213 and, three
-    // handles in turn, 264 / 207; of 128 columns, 16 M rows 540-544 / 524-553 and, three in turn, 530-534 / 556.)
+    // batch's forward and backward.  us a step in turn with other handles, and the first pass, waiting / enqueued ahead: 1.7 M lookups, 100 M
+    // rows, 16 columns 264 / 207; 16 M rows, 32 columns 231 / 223 and 436 / 432, 64 columns 311 / 310 and 583 / 573, 96 columns 461 / 463 and
+    // 882 / 910, 128 columns 535 / 534 and 967 / 982; 1.05 M lookups of 128 columns 348 / 348 and 641 / 654, of 64 columns 217 / 213.  From
+    // 64 columns on the two are within 2% in a loop, on either side of the lines.)
     const bool ahead_of_decisions = n <= ENQUEUE_MAX_IDS || n * (int64_t)c->D <= ENQUEUE_MAX_FLOATS;
     if (c->presort && n > 0 && ahead_of_decisions && num_bags > 0 && c->dma_evict && !c->miss_dma && c->last.n_miss > 0)
         return plan_enqueued(c, ids_dev, n, offsets_dev, num_bags, slots_dev, early);

@@ -365,7 +365,7 @@ __device__ __forceinline__ void plan_report(const PlanArgs& a, const PlanTotals&
 constexpr int FREE_TILE = 1024;
 
 // ---------------------------------------------------------------------------------------------------------
-// K2c  write the missing ranks (ascending), pick and retire the victims, update rbits, clear ubits.
+// K2c  write the missing ranks (ascending), pick and retire the victims, update rbits.
 //      A thread lists its set bits in LDS; what touches memory per rank (a random read and two or three writes) is then done
 //      by all threads side by side, all random reads of a thread before the first is waited for.
 //      SPLIT workgroups share a tile.  Popularity falls off as a power, so the tiles just beyond the cached ranks hold ten
@@ -972,8 +972,8 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
     if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
-    // whatever the decision is: the host hears of a refusal while workgroups of the emitting kernel still clear marks and read the
-    // counts and the error word, which the next batch's first kernels write
+    // whatever the decision is: the host hears of a refusal while workgroups of the emitting kernel still read the bitmap, the counts (of
+    // tiles, groups and hits) and the error word, which the next batch's first kernels write
     if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
     c->last_index_stream = st;
     run->ticket = ticket; run->n = n; run->num_bags = num_bags;

@@ -380,8 +380,8 @@ int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int
     // tiles take passes of at most 9 bits, each two launches (counts, then offsets and scatter in one kernel; the per-supertile
     // counts make the scan in between unnecessary; the caller supplies their table).  Up to 18 key bits that is two passes,
     // beyond three of 7 bits, which leave runs of 16 keys per digit and tile.  (Up to 18 bits a scan kernel per pass was kept
-    // while the scatter kernel added its rows up 8 at a time; with 16 at a time the two launches it costs decide: 53 k pairs
-    // 143 -> 138 us a step, 852 k 1207 -> 1196, 426 k the same.)  Larger jobs (the static module's ranking) and callers without
+    // while a tile's 256 threads added its rows up 8 at a time; with 16 rows together, or with 8 of either kind by 512 threads as now,
+    // the two launches it costs decide: 53 k pairs 143 -> 138 us a step, 852 k 1207 -> 1196, 426 k the same.)  Larger jobs (the static module's ranking) and callers without
     // a table keep the scan kernel: two passes up to 22 key bits, beyond that passes of at most 8 bits.
     // (j.max_bits / j.no_fuse, from FC_SORT_BITS / FC_SORT_FUSED at cache_create, override this for experiments.)
     const int env_bits = (j.max_bits >= 4 && j.max_bits <= RS_TWO_PASS_BITS) ? j.max_bits : 0;

@@ -21,7 +21,7 @@ def test_random_call_sequences(seed, dma, dirty, staging_rows):
     test_gpu_sequences.test_random_call_sequences(seed, dma, dirty, staging_rows)
 
 
-@pytest.mark.parametrize("rows", [900, 9000])                   # byte marks, bit marks
+@pytest.mark.parametrize("rows", [900, 9000])
 @pytest.mark.parametrize("dma", [True, False])
 @pytest.mark.parametrize("free", [True, False])
 def test_thrashing(rows, dma, free):

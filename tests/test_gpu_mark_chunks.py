@@ -33,3 +33,11 @@ def test_bit_marks(monkeypatch, rows, split_tiles):
     run_parity(w, 3, warm=True, dma_evict=True)
     run_parity_planned(w, 4, warm=True, dma_evict=True, inputs_ready=True)
     run_parity_lookahead(w, 4, warm=True)
+
+
+@pytest.mark.parametrize("n", [(1 << 20) - 1, (1 << 20) + 1])
+@pytest.mark.parametrize("dim", [4, 65])
+def test_planned_batches_around_a_million_ids(n, dim):
+    """Enqueued ahead of the decisions up to 2^20 ids and, where ids times columns stay below 2^26, beyond (65 columns: not beyond)."""
+    w = TinyWorkload(num_rows=300_000, dim=dim, cache_rows=60_000, seed=n % 97 + dim, multi_hot=False, bags=n, distinct_cap=50_000)
+    run_parity_planned(w, 3, warm=True, dma_evict=True, inputs_ready=True)

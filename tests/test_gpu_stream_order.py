@@ -84,9 +84,9 @@ def test_rows_in_transit_when_a_batch_has_more_victims_than_a_block(planned):
 
 @pytest.mark.parametrize("kind", ["own", "default"])
 @pytest.mark.parametrize("dma", [False, True])
-@pytest.mark.parametrize("bags", [5000, 100_000])              # bit marks, byte marks
+@pytest.mark.parametrize("bags", [5000, 100_000])
 def test_plans_right_behind_refused_plain_calls(kind, dma, bags, monkeypatch):
-    """A plain call that is refused returns while its last kernel still runs: it clears the marks and reads the counts."""
+    """A plain call that is refused returns while its last kernel still runs: it reads the bitmap and the counts."""
     import torch
     from oracle import Oracle
     from paper_2208_05321_amd import FreqCache, FreqCacheError
