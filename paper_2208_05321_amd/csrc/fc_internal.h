@@ -23,7 +23,7 @@ constexpr int GROUP_TILES = 16;                   // tiles whose counts are adde
 constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking kernel, at most
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size,
 constexpr int64_t ENQUEUE_MAX_FLOATS = 1 << 26;   // and larger batches of up to this many floats of rows
-constexpr int64_t FEW_BYTES = 8 << 20;            // bytes of missing rows up to which the host binds a planned step: plan_enqueued
+constexpr int64_t FEW_BYTES = 4 << 20;            // bytes of missing rows up to which the host binds a planned step: plan_enqueued
 constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead, send_block
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;

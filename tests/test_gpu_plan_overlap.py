@@ -40,7 +40,7 @@ def test_rows_of_a_planned_batch_move_under_its_sort(tmp_path, monkeypatch):
         gpu.profile(False)
         monkeypatch.delenv("FC_TIMELINE")
         gpu.profile(False)                                # closes the file
-        assert 0 < stats["n_evict"] * dim * 4 < 8 << 20, stats
+        assert 0 < stats["n_evict"] * dim * 4 < 4 << 20, stats
         gpu.close()
     spans = load_first_collection(str(path))
     gathers = [a for a, b, name in spans if name == "evict_gather"]
