@@ -82,9 +82,9 @@ enum {
                                The host table is complete after cache_flush (or cache_check).  Number of threads:
                                environment variable FC_SCATTER_THREADS (default 8).  Not with FC_TRANSMIT_STAGED.
                                Results are identical. */
-    FC_NO_PRESORT = 8,      /* By default cache_prepare also starts, on a library-owned stream, the sort of the
-                               batch's (slot, bag) pairs that embedding_bag_bwd_sgd needs, so that it overlaps the
-                               miss fill; it reads slots_dev and offsets_dev until it is done.  Set this flag when
+    FC_NO_PRESORT = 8,      /* By default cache_prepare also enqueues the sort of the batch's (slot, bag) pairs that
+                               embedding_bag_bwd_sgd needs (cache_prepare_next and cache_plan_next on a library-owned
+                               stream); it reads slots_dev and offsets_dev until it is done.  Set this flag when
                                no backward pass follows (inference) or those buffers are reused at once. */
     FC_INPUTS_READY = 32,   /* A promise about cache_plan_next's inputs: ids_dev / offsets_dev are complete when the call is made
                                (resident batches, or uploads the caller has waited for), not merely enqueued on the caller's

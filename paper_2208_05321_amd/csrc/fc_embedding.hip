@@ -570,8 +570,8 @@ static inline int64_t bwd_blocks_most(const fc_cache* c, int64_t n) {
 }
 
 // Called by cache_prepare / cache_prepare_next / cache_plan_next once the slots of the batch are on their way: the
-// sort needs nothing but the slots and the bag offsets, so it runs on a library stream (c->aux) while the missing
-// rows are still crossing the host link.  Two records alternate, so that the sort of the next batch does not
+// sort needs nothing but the slots and the bag offsets, so that of a batch prepared ahead runs on a library stream (c->aux) while
+// the missing rows are still crossing the host link.  Two records alternate, so that the sort of the next batch does not
 // disturb the current one's.
 int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out) {
     const int k = c->rec_next;
@@ -583,10 +583,11 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     if (c->rec[k ^ 1].valid && c->rec[k ^ 1].ticket != c->cur_ticket) c->rec[k ^ 1].valid = false;
     if (!c->presort || n <= 0 || num_bags <= 0) return slots_out ? FC_ERR_INVALID_ARG : FC_OK;   // the caller then writes the slots out itself
     FC_TRY(ensure_sort(c->sb[k], n));
-    // A small batch's sort is one short kernel: on the caller's stream it costs 8 us, on another one two waits of 10 us.  With 2^18
-    // slots or more it is a chain of short ones, which beside the row movement cost more all the same (1128 lookups of 128 columns,
-    // 372 k slots: 133 us a step here, 140-153 there).
-    const hipStream_t aux = c->pst == c->stream && n <= SMALL_MAX_IDS ? c->stream : c->aux;
+    // A plain call's sort stays on the caller's stream: on another one it costs two waits for events that have not happened yet (10-15 us
+    // of the host each, and a hop between hardware queues), and what it hides beside a saturated link it takes from the link.
+    // us a step, on another stream beside the row movement / here: 14 k lookups of 128 columns 125 / 108, 54 k of 64 (FC_EVICT_DMA) 141 / 112, 266 k of 128
+    // (FC_EVICT_DMA) 191 / 172, 852 k of 128 1201 / 1172; of the tried ones only bags of 20 with 53 k missing rows of 64 columns lost (554 / 560).
+    const hipStream_t aux = c->pst == c->stream ? c->stream : c->aux;
     if (c->pst != aux) {
         FC_HIP(hipEventRecord(c->ev_slots, c->pst));
         FC_HIP(hipStreamWaitEvent(aux, c->ev_slots, 0));

@@ -354,7 +354,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
 int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M);
 int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead);
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows = nullptr);
 int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                  int64_t num_bags, int32_t* slots);
 int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, float* out);

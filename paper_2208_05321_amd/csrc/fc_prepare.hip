@@ -1029,15 +1029,10 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     FC_TRY(index_result(c, st, run, mv));
     FC_TRY(index_assign(c, st, run, mv->M));
     if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));
-    // every row of the batch has its slot now: write the slots out (the caller then starts sorting them for the
-    // backward pass on a library stream, where the sort runs while the missing rows cross the host link)
+    // every row of the batch has its slot now: write the slots out
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
     if (!defer_slots) {
         if (!run.small_slots) FC_TRY(launch_slots_out(c, st, slots, n));
-    }
-    if (plain && c->plans_ahead) {
-        FC_HIP(hipEventRecord(c->ev_index_done, st));
-        c->due &= ~DUE_INDEX;
     }
     c->aux = (st == c->pre && !lookahead) ? c->pre : c->pf;
     return FC_OK;
@@ -1055,7 +1050,8 @@ static int move_done(fc_cache* c, hipStream_t st, bool ahead) {
 
 // Row-movement half: evicted rows out (gather, then DMA block / kernel store / staged copy), missing rows in.
 // ahead: the batch was prepared ahead of time, so the next one's index half will wait for this on a library stream.
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
+// send_rows: the evicted block is not handed over here but by the caller (send_block), once it has enqueued what else it has; its rows.
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows) {
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
@@ -1136,7 +1132,8 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
     FC_HIP(hipGetLastError());
     FC_TRY(move_done(c, st, ahead));
     // (after the rows that come in: by then the gather may be through, and the side stream's wait for it costs the host next to nothing)
-    if (send) FC_TRY(send_block(c, need, mv.buf, ahead));
+    if (send && send_rows) *send_rows = need;
+    else if (send) FC_TRY(send_block(c, need, mv.buf, ahead));
     c->vrank_kept = c->dma_evict && !c->dirty_track && !dma_path;
     // The next early fetch reads evicted-row blocks gathered up to now and host rows stored up to now: with the DMA
     // transmitter the gather just enqueued is the last thing it needs (host rows still on their way carry transit
@@ -1149,12 +1146,28 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead) {
 int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                  int64_t num_bags, int32_t* slots) {
     MovePlan mv;
-    FC_TRY(prepare_index(c, st, lookahead, ids, n, offsets, num_bags, slots, &mv));
-    // Look-ahead: rows about to be evicted or overwritten may still be in use by work the caller enqueued before
-    // this call (the backward pass of the batch before the current one); the index decisions did not care.
-    if (n > 0) (void)presort_impl(c, slots, n, offsets, num_bags);   // on failure the backward pass sorts (and reports) itself
-    if (lookahead) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
-    return prepare_move(c, st, mv, lookahead);
+    // the slot write-out is folded into the first kernel of the sort, unless the index kernel of a small batch has them in registers
+    const bool fold = !lookahead && c->presort && n > 0 && num_bags > 0 && !prepare_small_fits(c, n, num_bags);
+    FC_TRY(prepare_index(c, st, lookahead, ids, n, offsets, num_bags, slots, &mv, nullptr, fold));
+    if (lookahead) {
+        if (n > 0) (void)presort_impl(c, slots, n, offsets, num_bags);   // on failure the backward pass sorts (and reports) itself
+        // Rows about to be evicted or overwritten may still be in use by work the caller enqueued before this call (the backward
+        // pass of the batch before the current one); the index decisions did not care.
+        FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
+        return prepare_move(c, st, mv, true);
+    }
+    // The rows first: while they cross the link the host gets ahead of the GPU.
+    int64_t send_rows = 0;
+    FC_TRY(prepare_move(c, st, mv, false, &send_rows));
+    const int rs = n > 0 ? presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr) : FC_OK;
+    const int rw = fold && rs != FC_OK ? launch_slots_out(c, st, slots, n) : FC_OK;
+    if (send_rows > 0) FC_TRY(send_block(c, send_rows, mv.buf, false));      // whatever else failed: its rows are marked as in transit
+    FC_TRY(rw);
+    if (c->plans_ahead) {              // the sort's first kernel reads what the next index half writes
+        FC_HIP(hipEventRecord(c->ev_index_done, st));
+        c->due &= ~DUE_INDEX;
+    }
+    return FC_OK;
 }
 
 }  // namespace fc
