@@ -514,7 +514,7 @@ static int ensure_part(fc_cache* c, int64_t groups) {
 // Stable sort of the batch's (slot, bag) pairs by slot on stream `st`; *kres / *vres receive the sorted arrays.
 static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* slots, int64_t n, const int64_t* offsets,
                       int64_t num_bags, const int32_t** kres, const int32_t** vres, int32_t* slots_out = nullptr,
-                      hipStream_t tail = nullptr, hipStream_t* last = nullptr) {
+                      hipStream_t tail = nullptr, hipStream_t* last = nullptr, SortJob* along = nullptr) {
     int bits = 1;
     while (((int64_t)1 << bits) <= c->C) ++bits;           // keys lie in [0, C] (C = out-of-range sentinel)
     SortJob j;
@@ -525,6 +525,15 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
     j.tail_stream = tail; j.tail_event = c->ev_sort_tail; j.last_stream = last;
     j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
     j.prof = c;
+    if (along) {
+        j.keysA = sb.keysA; j.valsA = sb.valsA;
+        if (sort_small_fits(j)) {
+            j.last_stream = nullptr;
+            *along = j;
+            *kres = j.keysA; *vres = j.valsA; *last = st;
+            return FC_OK;
+        }
+    }
     return sort_in(j, sb, st, kres, vres);
 }
 
@@ -573,7 +582,7 @@ static inline int64_t bwd_blocks_most(const fc_cache* c, int64_t n) {
 // sort needs nothing but the slots and the bag offsets, so that of a batch prepared ahead runs on a library stream (c->aux) while
 // the missing rows are still crossing the host link.  Two records alternate, so that the sort of the next batch does not
 // disturb the current one's.
-int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out) {
+int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out, SortJob* along) {
     const int k = c->rec_next;
     c->rec_next ^= 1;
     PresortRec& r = c->rec[k];
@@ -606,7 +615,7 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     hipStream_t last = aux;
     const bool split = slots_out && c->sort_tail_side && c->ahead_now && aux == c->pre &&
                        c->side && c->side != aux;
-    FC_TRY(sort_pairs(c, c->sb[k], aux, slots, n, offsets, num_bags, &r.keys, &r.vals, slots_out, split ? c->side : nullptr, &last));
+    FC_TRY(sort_pairs(c, c->sb[k], aux, slots, n, offsets, num_bags, &r.keys, &r.vals, slots_out, split ? c->side : nullptr, &last, along));
     // cache_plan_next records ev_pre_done right behind a sort that ends on `pre`
     r.done = slots_out && last == c->pre ? c->ev_pre_done : r.ev_sorted;
     if (last != c->stream && r.done == r.ev_sorted) FC_HIP(hipEventRecord(r.ev_sorted, last));

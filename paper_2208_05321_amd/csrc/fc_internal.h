@@ -346,6 +346,7 @@ void prof_collect(fc_cache* c);
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+struct SortJob;
 // entry points implemented across the sources
 int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots = nullptr, bool defer_slots = false);
@@ -354,14 +355,15 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
 int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M);
 int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows = nullptr);
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows = nullptr, SortJob* along = nullptr);
 int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                  int64_t num_bags, int32_t* slots);
 int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, float* out);
 int dma_quiesce(fc_cache* c, hipStream_t st);
 // from_ranks: the slots are not written yet; the sort's first kernel derives them from the per-id ranks and writes them
 // to `slots_out` on its way (the slot write-out folded into the sort)
-int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr);
+// along: a sort that one workgroup can do is not launched but left in *along (n > 0 then): it goes along with the rows, or by sort_small
+int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr, SortJob* along = nullptr);
 bool mark_bytes(fc_cache* c);              // byte marks (allocates them on first use), else bit marks
 int ensure_rbuf(fc_cache* c, int64_t n);  // per-id rank buffer for batches of n ids
 int reserve_bwd(fc_cache* c, int64_t n);   // sort scratch of all three sets and the partial rows for batches of n lookups
@@ -378,14 +380,14 @@ int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, cons
                      int32_t* tag_out = nullptr, const int32_t* tags = nullptr);   // tag_out[j] = tags[j] on the way
 // default transmitter: each slot of fill_slots gives its old row (rank fill_src[j], if any) to the host table and gets the
 // missing one, in one pass
-int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows);
+int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows, SortJob* along = nullptr);
 // host[slot_rank[s]] = cache[s] for every resident slot, written straight into the mapped host table.
 int launch_flush_rows(fc_cache* c, hipStream_t s);   // FC_DIRTY_TRACK: dirty rows only
 // miss fill that honours transit marks: row j comes from the host table or from a device-side evicted-row block
 // dst == nullptr: into the cache slots fill_slots[j]; else into row j of the block dst (of dst_rows rows)
 // only_transit: rows whose newest copy is in the host table are skipped (the DMA miss path has brought them)
 int launch_fill_rows(fc_cache* c, hipStream_t s, int64_t rows, float* dst = nullptr, int64_t dst_rows = 0, int max_blocks = 0,
-                     bool only_transit = false, const int32_t* plan = nullptr);   // plan: rows = the missing rows it states, if at most `rows`
+                     bool only_transit = false, const int32_t* plan = nullptr, SortJob* along = nullptr);   // plan: rows = the missing rows it states, if at most `rows`
 
 // gather pool of the DMA miss path (fc_gather.hip)
 int gather_create(fc_cache* c, int threads);
@@ -402,6 +404,7 @@ uint64_t pool_published(fc_cache* c);
 uint64_t pool_completed(fc_cache* c);                    // the last block that is in the host table
 
 // ---- radix sort (fc_sort.hip) ----
+struct RowArgs;
 enum SortSrc {
     SORT_SRC_PAIRS = 0,   // keys_in / vals_in as given
     SORT_SRC_SLOTS = 1,   // keys_in = slots of a batch (out-of-range -> sentinel `limit`, flag raised), value = bag of lookup i
@@ -430,12 +433,14 @@ struct SortJob {
     // of the first pass is free again sooner; *last_stream receives the stream the last pass ran on
     hipStream_t tail_stream = nullptr; hipEvent_t tail_event = nullptr; hipStream_t* last_stream = nullptr;
     fc_cache* prof = nullptr;                  // where to book per-kernel times, may be null
+    bool launched = false;                     // a job that went along with the rows (launch_rows_and_sort)
 };
 int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres);
 
 // ---- small batches (fc_small.hip) ----
 bool sort_small_fits(const SortJob& j);
 int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres);
+int launch_rows_and_sort(fc_cache* c, hipStream_t st, bool swap, const RowArgs& r, int max_blocks, SortJob* j);
 bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags);
 // slots == nullptr: the ranks go to rbuf and the slot write-out is left to the caller
 int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,

@@ -1051,7 +1051,8 @@ static int move_done(fc_cache* c, hipStream_t st, bool ahead) {
 // Row-movement half: evicted rows out (gather, then DMA block / kernel store / staged copy), missing rows in.
 // ahead: the batch was prepared ahead of time, so the next one's index half will wait for this on a library stream.
 // send_rows: the evicted block is not handed over here but by the caller (send_block), once it has enqueued what else it has; its rows.
-int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows) {
+// along: a sort to launch with the missing rows, where a kernel brings them over the link (SortJob::launched says so).
+int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows, SortJob* along) {
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
@@ -1084,7 +1085,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
     }
     // Default transmitter, rows straight from the host table: they change places with the victims in one kernel.
     if (!staged && !c->dma_evict && !c->dirty_track && !mv.arrived) {
-        FC_TRY(launch_swap_rows(c, st, M));                        // every victim's slot is among those that are filled
+        FC_TRY(launch_swap_rows(c, st, M, along));                        // every victim's slot is among those that are filled
         FC_TRY(move_done(c, st, ahead));
         c->pf_dep = c->ev_move_done[c->lset];
         return FC_OK;
@@ -1124,7 +1125,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
             // gathered by earlier batches (this stream has run those gathers)
             if (via_dma && c->dma_evict) FC_TRY(launch_fill_rows(c, st, M, nullptr, 0, 0, true));
         }
-        else if (dma_path) FC_TRY(launch_fill_rows(c, st, M));
+        else if (dma_path) FC_TRY(launch_fill_rows(c, st, M, nullptr, 0, 0, false, nullptr, along));
         else FC_TRY(launch_copy_rows(c, st, P_MISS_FILL, c->cache, c->fill_slots, c->C, c->host_dev, c->miss_ranks, c->N, M, c->fill_blocks));
     }
     if (last_rows > 0) FC_TRY(store_block(c, last_off, last_rows));
@@ -1156,10 +1157,19 @@ int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         return prepare_move(c, st, mv, true);
     }
-    // The rows first: while they cross the link the host gets ahead of the GPU.
+    // The rows first: while they cross the link the host gets ahead of the GPU.  A sort for one workgroup goes along with them.
+    SortJob along;
     int64_t send_rows = 0;
-    FC_TRY(prepare_move(c, st, mv, false, &send_rows));
-    const int rs = n > 0 ? presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr) : FC_OK;
+    const bool little = n <= SMALL_SORT_IDS;
+    int rs = FC_OK;
+    if (n > 0 && little) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr, &along);
+    FC_TRY(prepare_move(c, st, mv, false, &send_rows, along.n > 0 ? &along : nullptr));
+    if (n > 0 && !little) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr);
+    if (along.n > 0 && !along.launched) {
+        const int32_t *keys, *vals;
+        rs = sort_small(along, st, &keys, &vals);
+        if (rs != FC_OK) for (PresortRec& r : c->rec) r.valid = r.valid && r.ticket != c->ticket;
+    }
     const int rw = fold && rs != FC_OK ? launch_slots_out(c, st, slots, n) : FC_OK;
     if (send_rows > 0) FC_TRY(send_block(c, send_rows, mv.buf, false));      // whatever else failed: its rows are marked as in transit
     FC_TRY(rw);

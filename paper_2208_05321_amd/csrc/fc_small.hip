@@ -10,7 +10,9 @@
 // The limit of 4096 ids: a single compute unit resolves about one random line per nanosecond and issues one instruction
 // per cycle, and at 10 k ids it takes as long (40 + 32 us) as the kernels that use all of them (37 + 33 us and 11 launches,
 // whose launching the host overlaps).  The limits on rows and slots are what fits LDS.
-#include "fc_internal.h"
+#include "rows_device.h"
+
+#include <algorithm>
 
 namespace fc {
 
@@ -385,11 +387,20 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 // (Those figures are from before a wavefront's match of a digit came down to four instructions a bit and served for both counting
 // and placing, with no atomics on popular digits: 10101 lookups, 14-bit keys 35 -> 22 us.)
 // ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __restrict__ keys_in, const int32_t* __restrict__ rank_slot,
-                                                           int32_t* __restrict__ slots_out, const int64_t* __restrict__ offsets,
-                                                           int num_bags, int one_per_bag, int n, int limit, int passes, int radix_bits,
-                                                           uint32_t* flags, const int32_t* __restrict__ status, int32_t* __restrict__ keys_out,
-                                                           int32_t* __restrict__ vals_out) {
+struct SmallSort {
+    const int32_t *keys_in, *rank_slot; int32_t* slots_out; const int64_t* offsets; const int32_t* status; uint32_t* flags;
+    int32_t *keys_out, *vals_out;
+    int num_bags, one_per_bag, n, limit, passes, radix_bits;
+};
+
+__device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
+    const int32_t* __restrict__ keys_in = a.keys_in;
+    const int32_t* __restrict__ rank_slot = a.rank_slot;
+    const int64_t* __restrict__ offsets = a.offsets;
+    int32_t* __restrict__ slots_out = a.slots_out;
+    int32_t* __restrict__ keys_out = a.keys_out;
+    int32_t* __restrict__ vals_out = a.vals_out;
+    const int num_bags = a.num_bags, one_per_bag = a.one_per_bag, n = a.n, limit = a.limit, passes = a.passes, radix_bits = a.radix_bits;
     // two arrays of rounds * SM_THREADS words, the digit counts, and each element's place within its wavefront and digit
     extern __shared__ __align__(16) uint32_t sm_words[];
     const int rounds = (n + SM_THREADS - 1) / SM_THREADS;  // elements per thread
@@ -402,7 +413,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
     __shared__ int s_other;                                // some bag does not hold just its own lookup
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     bool bad = false, other = false;
-    const bool refused = status && *status != FC_OK;       // neither slots nor offsets are touched then
+    const bool refused = a.status && *a.status != FC_OK;       // neither slots nor offsets are touched then
     // with as many lookups as bags, most likely bag i holds lookup i: seen here, in order, rather than looked up in sorted order below
     const bool check = !one_per_bag && !refused && n == num_bags;
     if (tid == 0) s_other = check ? offsets[n] != (int64_t)n : !one_per_bag;
@@ -430,7 +441,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
         }
     }
     if (refused) return;
-    if (bad && flags) atomicOr(flags, EF_BAD_SLOT);
+    if (bad && a.flags) atomicOr(a.flags, EF_BAD_SLOT);
     const uint64_t lt = (1ull << lane) - 1ull;
     const int e0 = w * 64 * rounds + lane;                 // this wavefront's elements: e0 + 64 * k
     int* mine = wc + w * radix;
@@ -488,22 +499,54 @@ __global__ __launch_bounds__(SM_THREADS) void k_sort_small(const int32_t* __rest
     }
 }
 
+__global__ __launch_bounds__(SM_THREADS) void k_sort_small(SmallSort a) { sort_in_workgroup(a); }
+
+// The sort in the first workgroup, rows on their way in the others: neither needs the other, the sort keeps one compute unit busy and the
+// rows the link.  (Every workgroup is given the sort's LDS and with it a compute unit of its own; the rows take 64 of them at most.)
+// us a step, one launch after the other / this: 1024 lookups of 16 columns 36.5 / 32.5, 1157 of 128 columns 41.8 / 35.5, 163 of 226 columns 59 / 54.
+template <int VEC, bool SWAP>
+__global__ __launch_bounds__(SM_THREADS) void k_rows_and_sort(RowArgs r, SmallSort a) {
+    if (blockIdx.x == 0) sort_in_workgroup(a);
+    else if (SWAP) swap_rows<VEC>(r, blockIdx.x - 1, gridDim.x - 1);
+    else fill_rows<VEC>(r, blockIdx.x - 1, gridDim.x - 1);
+}
+
 static_assert(SMALL_SORT_IDS <= 1 << SMALL_POS_BITS, "a lookup's number has to fit");
 
 bool sort_small_fits(const SortJob& j) {
     return (j.src == SORT_SRC_SLOTS || j.src == SORT_SRC_RANKS) && j.n <= SMALL_SORT_IDS && j.bits <= SMALL_KEY_BITS && !j.max_bits && !j.no_fuse;
 }
 
-int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
+static SmallSort small_sort(const SortJob& j, size_t* lds) {
     const int passes = (j.bits + 7) / 8, rb = (j.bits + passes - 1) / passes;
-    const int opb = j.one_per_bag && j.n == j.num_bags;
+    *lds = 4 * (2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb) + (size_t)cdiv(j.n, 2));
+    return SmallSort{j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.status, j.flags, j.keysA, j.valsA,
+                     j.num_bags, j.one_per_bag && j.n == j.num_bags, j.n, j.limit, passes, rb};
+}
+
+int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
     ProfScope ps(j.prof, P_SORT_SCATTER, st);
-    const size_t words = 2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb) + (size_t)cdiv(j.n, 2);
-    k_sort_small<<<1, SM_THREADS, words * 4, st>>>(j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.num_bags, opb, j.n,
-                                                   j.limit, passes, rb, j.flags, j.status, j.keysA, j.valsA);
+    size_t lds;
+    const SmallSort a = small_sort(j, &lds);
+    k_sort_small<<<1, SM_THREADS, lds, st>>>(a);
     FC_HIP(hipGetLastError());
     *kres = j.keysA; *vres = j.valsA;
     if (j.last_stream) *j.last_stream = st;
+    return FC_OK;
+}
+
+int launch_rows_and_sort(fc_cache* c, hipStream_t st, bool swap, const RowArgs& r, int max_blocks, SortJob* j) {
+    size_t lds;
+    const SmallSort a = small_sort(*j, &lds);
+    // (blocks are counted in workgroups of 256 elsewhere)
+    const unsigned blocks = 1 + (unsigned)std::min<int64_t>(cdiv(r.rows, SM_THREADS >> r.lpr_shift), cdiv(max_blocks, SM_THREADS / 256));
+    ProfScope ps(c, P_MISS_FILL, st);
+#define FC_BOTH(V) \
+    if (swap) k_rows_and_sort<V, true><<<blocks, SM_THREADS, lds, st>>>(r, a); else k_rows_and_sort<V, false><<<blocks, SM_THREADS, lds, st>>>(r, a)
+    switch (c->vec) { case 4: FC_BOTH(4); break; case 2: FC_BOTH(2); break; default: FC_BOTH(1); break; }
+#undef FC_BOTH
+    FC_HIP(hipGetLastError());
+    j->launched = true;
     return FC_OK;
 }
 
