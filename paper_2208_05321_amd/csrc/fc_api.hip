@@ -814,6 +814,7 @@ int cache_check(fc_cache* c) {
     FC_HIP(hipMemcpy(&h, c->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
     if (h.async_flags) {
         FC_HIP(hipMemset(&c->ctl->async_flags, 0, 4));
+        FC_HIP(hipStreamSynchronize(nullptr));         // (returns before it is done, and later calls are on other streams)
         return FC_ERR_BAD_SLOT;
     }
     return FC_OK;

@@ -457,8 +457,16 @@ static int ensure_sort(SortBufs& sb, int64_t n) {
     if (!sb.dtot) FC_HIP(hipMalloc((void**)&sb.dtot, (size_t)(1 << RS_MAX_BITS) * 4));
     for (int k = 0; k < 2; ++k)
         if (!sb.stot[k]) {
-            FC_HIP(hipMalloc((void**)&sb.stot[k], (size_t)SORT_STOT_WORDS * 4));
-            FC_HIP(hipMemset(sb.stot[k], 0, (size_t)SORT_STOT_WORDS * 4));
+            int32_t* p = nullptr;
+            FC_HIP(hipMalloc((void**)&p, (size_t)SORT_STOT_WORDS * 4));
+            // hipMemset of device memory returns before it is done (10 us later on an idle device), and nothing orders the library's
+            // streams behind the null stream: without the wait a handle's first sort could count into a table still to be cleared.
+            if (hipMemset(p, 0, (size_t)SORT_STOT_WORDS * 4) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+                (void)hipGetLastError();
+                (void)hipFree(p);
+                return FC_ERR_HIP;
+            }
+            sb.stot[k] = p;
             sb.dirty[k] = 0;
         }
     return FC_OK;
