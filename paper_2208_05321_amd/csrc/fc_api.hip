@@ -496,13 +496,15 @@ static int fetch_early(fc_cache* c, int64_t M) {
 
 // the caller's stream takes over from the look-ahead stream: everything cache_prepare_next enqueued comes first
 static int adopt_next(fc_cache* c) {
+    bool waited = false;
     if (c->planned.valid) {            // a batch planned ahead whose rows have not moved yet: move them now
         const MovePlan mv = c->planned;
         c->planned.valid = false;
         FC_TRY(prepare_move(c, c->stream, mv, true));
+        waited = c->decided == c->ev_pre_done;
     }
     if (c->next_pending || c->last_pst != c->stream) {
-        FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
+        if (!waited) FC_HIP(hipStreamWaitEvent(c->stream, c->ev_pre_done, 0));
         c->next_pending = false;
         c->last_pst = c->stream;
         for (PresortRec& r : c->rec) if (r.done == c->ev_pre_done) r.caller_waited = true;
@@ -520,12 +522,34 @@ static int record_due_events(fc_cache* c) {
     return FC_OK;
 }
 
+// The planned batch's missing rows into the arrival block of its list set, on the index stream itself, between the slots and the sort;
+// the event of the decisions then says that they are there, too.
+static int fetch_inline(fc_cache* c, hipStream_t st, SortJob* along) {
+    const int k = c->lset;
+    if (!ensure_arrival_block(c, k)) return FC_OK;
+    bool landed;
+    FC_TRY(wait_if_far_ahead(c, &landed));
+    if (c->pf_dep) FC_HIP(hipStreamWaitEvent(st, c->pf_dep, 0));
+    FC_TRY(launch_fill_rows(c, st, c->staging_rows, c->arrive[k], c->staging_rows, c->fill_blocks, false, c->plan[k], along));
+    c->arrived_by[k] = c->decided;
+    c->fetch_timed[k] = false;
+    c->planned.arrived = true;
+    return FC_OK;
+}
+
 // cache_plan_next with nothing waited for until everything is enqueued.
 static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots, bool early) {
     const hipStream_t st = c->pre;
     IndexRun run;
     MovePlan mv;
-    int rc = index_launch(c, st, false, ids, n, offsets, num_bags, slots, false, &run);
+    // Very few rows to move: they are fetched on the index stream, between the slots and the sort.  That leaves out the fetch stream, four
+    // events and two waits, and by the time the host gets to cache_advance they have arrived.  A batch that one workgroup sorts is
+    // sorted in the launch that fetches, and one event stands for everything.  The limit is where the sort would be kept waiting:
+    // us a step and its first pass, fetched on a stream of their own / here (landing blocks as in lands_directly): 1024 lookups of 16 columns 86 and 117 / 65 and 97, 2.6 k of 32
+    // columns 107 and 156 / 70 and 120, 53 k of 64 columns (1.4 MB) 121 and 205 / 107 and 175; 53 k of 96 columns (2.1 MB) 107 and 194 / 114 and 196, 426 k of 16 columns (2.4 MB) 136 and 292 /
+    // 151 and 309.
+    const bool inlined = c->last.n_miss * (int64_t)c->D * 4 <= INLINE_BYTES;
+    int rc = index_launch(c, st, false, ids, n, offsets, num_bags, slots, false, &run, !inlined);
     c->last_pst = st;
     c->next_pending = true;
     int fetched = FC_OK, sorted = FC_ERR_INVALID_ARG;
@@ -541,16 +565,36 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     // 137, 53 k of 64 columns 126 and 119, and the first pass 326 and 320, 292 and 249, 198 and 181.)
     const bool few = c->last.n_miss * (int64_t)c->D * 4 <= FEW_BYTES;
     if (rc == FC_OK) rc = index_assign(c, st, run, -1);
-    if (rc == FC_OK) {
+    const bool at_once = inlined && n <= SMALL_SORT_IDS;
+    if (rc == FC_OK && at_once) {
+        c->planned.arrived = false;
+        c->aux = st;
+        c->decided = c->ev_pre_done;
+        if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
+        c->last_one_per_bag = guess;
+        c->pst = st;
+        SortJob along;
+        sorted = presort_impl(c, slots, n, offsets, num_bags, slots, &along);
+        fetched = fetch_inline(c, st, along.n > 0 ? &along : nullptr);
+        if (along.n > 0 && !along.launched) {
+            const int32_t *keys, *vals;
+            sorted = sort_small(along, st, &keys, &vals);
+            if (sorted != FC_OK) c->rec[rec].valid = false;
+        }
+        FC_HIP(hipEventRecord(c->ev_pre_done, st));
+        rc = index_result(c, st, run, &mv);
+    } else if (rc == FC_OK) {
+        c->planned.arrived = false;
+        c->decided = c->ev_assign_done;
+        if (inlined) fetched = fetch_inline(c, st, nullptr);
         FC_HIP(hipEventRecord(c->ev_assign_done, st));
         c->aux = st;
-        c->planned.arrived = false;
-        if (!few) fetched = fetch_early(c, -1);
+        if (!few && !inlined) fetched = fetch_early(c, -1);
         if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         c->last_one_per_bag = guess;
         c->pst = st;
         sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
-        if (few) fetched = fetch_early(c, -1);
+        if (few && !inlined) fetched = fetch_early(c, -1);
         rc = index_result(c, st, run, &mv);
     }
     c->pst = c->stream;
@@ -567,15 +611,20 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
     c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
     c->planned = mv;
     c->pending_ticket = c->ticket;
+    bool more = !at_once;                                         // work that ev_pre_done does not stand for yet
     if (sorted == FC_OK && guess && !c->last_one_per_bag) {        // its values are not the bags: once more
+        more = true;
         c->rec_next = rec;
         c->pst = st;
         sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
         c->pst = c->stream;
     }
     c->rec[rec].one_per_bag = c->last_one_per_bag;
-    if (sorted != FC_OK) FC_TRY(launch_slots_out(c, st, slots, n));        // no sort: the plain write-out
-    FC_HIP(hipEventRecord(c->ev_pre_done, st));
+    if (sorted != FC_OK) {                                        // no sort: the plain write-out
+        more = true;
+        FC_TRY(launch_slots_out(c, st, slots, n));
+    }
+    if (more) FC_HIP(hipEventRecord(c->ev_pre_done, st));
     return fetched;
 }
 

@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stdio.h>
 #include <chrono>
+#include <stdlib.h>
 #include <string>
 #include <vector>
 
@@ -24,6 +25,8 @@ constexpr int MARK_HIT_PARTS = 2048;              // workgroups of the marking k
 constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ahead of the decisions up to this batch size,
 constexpr int64_t ENQUEUE_MAX_FLOATS = 1 << 26;   // and larger batches of up to this many floats of rows
 constexpr int64_t FEW_BYTES = 4 << 20;            // bytes of missing rows up to which the host binds a planned step: plan_enqueued
+constexpr int64_t INLINE_BYTES = 3 << 19;         // bytes of missing rows up to which a planned step fetches them on the index stream: plan_enqueued
+constexpr int64_t LAND_BYTES = 1 << 18;           // bytes up to which a gathered block is stored into its landing block by the gather: lands_directly
 constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead, send_block
 // Radix sort of (slot, bag) pairs for the backward pass.
 constexpr int RS_THREADS = 256;
@@ -133,6 +136,7 @@ struct fc_cache {
     hipStream_t pre = nullptr, pst = nullptr, last_pst = nullptr;
     hipEvent_t ev_s_now = nullptr, ev_pre_done = nullptr, ev_index_done = nullptr;
     hipEvent_t ev_assign_done = nullptr;   // index half: every decision taken (all but the slot write-out)
+    hipEvent_t decided = nullptr;          // the event that says so: ev_assign_done, or ev_pre_done where all of an index half ends at once
     hipEvent_t ev_emit_done = nullptr;     // index half: the missing rows and where their newest copies are: the early fetch may start
     hipEvent_t ev_quiesce = nullptr;       // transit marks dropped by dma_quiesce on another stream than the index stream
     hipStream_t quiesce_stream = fc::no_stream();
@@ -351,7 +355,7 @@ struct SortJob;
 int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots = nullptr, bool defer_slots = false);
 int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
-                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run);
+                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run, bool mark_emitted = true);   // mark_emitted: record ev_emit_done
 int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M);
 int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
@@ -377,7 +381,8 @@ int noalloc_setup(int device);
 // dst_rows / src_rows bound the row indices on either side (rows with an index outside are skipped).
 int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, const int32_t* dst_idx, int64_t dst_rows,
                      const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks,
-                     int32_t* tag_out = nullptr, const int32_t* tags = nullptr);   // tag_out[j] = tags[j] on the way
+                     int32_t* tag_out = nullptr, const int32_t* tags = nullptr,   // tag_out[j] = tags[j] on the way
+                     float* twin = nullptr, int32_t* tag_twin = nullptr);   // and a second copy of both
 // default transmitter: each slot of fill_slots gives its old row (rank fill_src[j], if any) to the host table and gets the
 // missing one, in one pass
 int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows, SortJob* along = nullptr);

@@ -760,13 +760,27 @@ int dma_quiesce(fc_cache* c, hipStream_t st) {
 
 // DMA evict transmitter: gather into block `buf` ...
 static bool ranks_travel_along(const fc_cache* c, int64_t need) { return need * (int64_t)(c->D + 1) <= c->staging_rows * (int64_t)c->D; }
-static int gather_block(fc_cache* c, int64_t need, int buf) {
+// A small block: the gather writes its rows (and ranks) into the pinned landing block as well, and there is no copy to hand over.  The copy
+// costs the host 20-25 us (the side stream's wait for a gather that has just been enqueued 16, the copy and its events 5), the stores the
+// caller's stream what they take on the link.  On a planned step that hides behind what the host does, so the limit is where the
+// rows of the step stop being few (INLINE_BYTES); a plain one is in the way of the sort.
+// us a step, copy / this: planned, 2.6 k lookups of 32 columns (31 KB) 107 / 70, 53 k of 64 columns (1.4 MB) 121 / 107 and the first pass 205 / 175 (both with the rows
+// fetched on the index stream), of 96 columns (2.1 MB) 107 / 114, of 128 columns (2.7 MB) 124 / 132; plain, 1024 lookups of 16 columns 60 / 46, 10 k of 32 columns (134 KB)
+// 83 / 79, 18 k of 64 columns (470 KB) 82 / 85.
+static bool lands_directly(const fc_cache* c, int64_t need, bool ahead) {
+    return ranks_travel_along(c, need) && need * (int64_t)c->D * 4 <= (ahead ? INLINE_BYTES : LAND_BYTES);
+}
+static int gather_block(fc_cache* c, int64_t need, int buf, bool ahead) {
     float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
     // the ranks travel behind the rows, in one copy, where the block has room for both (a copy of their own costs the host as
     // much as four launches)
+    const bool along = ranks_travel_along(c, need), direct = lands_directly(c, need, ahead);
+    float* land = direct ? c->blk_pin[buf] : nullptr;
     FC_TRY(launch_copy_rows(c, c->pst, P_EVICT_GATHER, blk, nullptr, c->staging_rows, c->cache, c->out_slot, c->C, need, 1 << 20,
-                            ranks_travel_along(c, need) ? reinterpret_cast<int32_t*>(blk + (size_t)need * c->D) : nullptr, c->out_rank));
+                            along ? reinterpret_cast<int32_t*>(blk + (size_t)need * c->D) : nullptr, c->out_rank, land,
+                            direct ? reinterpret_cast<int32_t*>(land + (size_t)need * c->D) : nullptr));
     FC_HIP(hipEventRecord(c->ev_gather_done, c->pst));
+    if (direct) FC_HIP(hipEventRecord(c->ev_d2h[buf], c->pst));
     return FC_OK;
 }
 // ... and hand the block and its rank list to the DMA engine on the side stream, and let the host threads scatter it once it has
@@ -779,6 +793,13 @@ static int gather_block(fc_cache* c, int64_t need, int buf) {
 static int send_block(fc_cache* c, int64_t need, int buf, bool ahead) {
     const float* blk = c->stage_dev + (size_t)buf * c->staging_rows * c->D;
     const bool together = ranks_travel_along(c, need);
+    if (lands_directly(c, need, ahead)) {                // its rows are on their way, or there
+        c->vrank_at[buf] = reinterpret_cast<const int32_t*>(c->blk_pin[buf] + (size_t)need * c->D);
+        c->copy_timed[buf] = false;
+        c->blk_rows[buf] = need;
+        c->copy_seq[buf] = pool_publish(c, buf, need);
+        return FC_OK;
+    }
     if (c->last_copy_buf >= 0 && c->copy_timed[c->last_copy_buf] && !(ahead && c->ahead_now)) {
         const float ago = std::chrono::duration<float, std::micro>(std::chrono::steady_clock::now() - c->copy_at).count();
         if (ago > FAR_AHEAD_US) FC_HIP(hipEventSynchronize(c->ev_d2h[c->last_copy_buf]));
@@ -876,7 +897,7 @@ int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n) {
 
 // Everything up to the decisions (the emitting kernel), enqueued.  write_slots: a small batch's one kernel writes them, too.
 int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
-                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run) {
+                 int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run, bool mark_emitted) {
     const int64_t LIM = ((int64_t)1 << 31) - 65536;
     if (!c || n < 0 || num_bags < 0 || n >= LIM || num_bags >= LIM || !offsets || (n > 0 && (!ids || !slots)))
         return FC_ERR_INVALID_ARG;
@@ -970,7 +991,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
 #undef FC_EMIT
     }
     const bool plain = st == c->stream;         // nothing on another stream waits for the events below, until a call says so
-    if (!plain) FC_HIP(hipEventRecord(c->ev_emit_done, st));
+    if (!plain && mark_emitted) FC_HIP(hipEventRecord(c->ev_emit_done, st));
     FC_HIP(hipGetLastError());
     // whatever the decision is: the host hears of a refusal while workgroups of the emitting kernel still read the bitmap, the counts (of
     // tiles, groups and hits) and the error word, which the next batch's first kernels write
@@ -1028,7 +1049,7 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     FC_TRY(index_launch(c, st, lookahead, ids, n, offsets, num_bags, slots, !defer_slots && !before_slots, &run));
     FC_TRY(index_result(c, st, run, mv));
     FC_TRY(index_assign(c, st, run, mv->M));
-    if (!plain) FC_HIP(hipEventRecord(c->ev_assign_done, st));
+    if (!plain) { FC_HIP(hipEventRecord(c->ev_assign_done, st)); c->decided = c->ev_assign_done; }
     // every row of the batch has its slot now: write the slots out
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
     if (!defer_slots) {
@@ -1056,7 +1077,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
     c->pst = st;
     // the lists this half reads are complete once the last decision is taken; the slot write-out (and, folded into it,
     // the sort) is waited for by whoever hands the batch to the caller
-    if (c->last_index_stream != st) FC_HIP(hipStreamWaitEvent(st, c->ev_assign_done, 0));
+    if (c->last_index_stream != st) FC_HIP(hipStreamWaitEvent(st, c->decided, 0));
     const int64_t M = mv.M;
     int64_t need = mv.need;                    // victims to write back
     const bool staged = (c->flags & FC_TRANSMIT_STAGED) != 0;
@@ -1094,7 +1115,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
     // Rows fetched ahead of time (cache_plan_next) were read from the host table and from evicted-row blocks other
     // than the one this batch's victims go to (its marks were dropped before this batch was indexed), so the
     // victims need not wait for them; a kernel-store evict reuses the block buffer from its start and has to.
-    bool arrival_waited = !mv.arrived;
+    bool arrival_waited = !mv.arrived || c->arrived_by[c->lset] == c->decided;
     bool dma_path = false, send = false;
     // DMA miss path: ev_arrive of this list set is recorded by a gather thread once it has handed the last chunk to the
     // DMA engine; the host waits here until that has happened (the GPU meanwhile works through the current batch)
@@ -1102,7 +1123,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
     if (via_dma) { FC_TRY(gather_wait(c)); c->gather_pending = false; }
     if (need > 0) {
         if (staged) FC_TRY(evict_staged(c, need, c->list_pin + c->C));
-        else if (c->dma_evict && mv.need <= c->staging_rows) { FC_TRY(gather_block(c, need, mv.buf)); dma_path = send = true; }
+        else if (c->dma_evict && mv.need <= c->staging_rows) { FC_TRY(gather_block(c, need, mv.buf, ahead)); dma_path = send = true; }
         else {
             // more victims than one block holds (or no DMA transmitter): store by kernel, block by block; the
             // block buffer is reused from its start, so nothing may be in transit in it any more: every missing row, also one

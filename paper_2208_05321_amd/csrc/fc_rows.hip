@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void k_copy_rows(float* __restrict__ dst, cons
                                                    unsigned dst_rows, const float* __restrict__ src,
                                                    const int32_t* __restrict__ src_idx, unsigned src_rows, int rows,
                                                    int D, int lpr_shift, int32_t* __restrict__ tag_out,
-                                                   const int32_t* __restrict__ tags) {
+                                                   const int32_t* __restrict__ tags, float* __restrict__ twin, int32_t* __restrict__ tag_twin) {
     using V = typename Vec<VEC>::T;
     const int lpr = 1 << lpr_shift;
     const int gpb = blockDim.x >> lpr_shift;
@@ -25,13 +25,21 @@ __global__ __launch_bounds__(256) void k_copy_rows(float* __restrict__ dst, cons
     for (int j = blockIdx.x * gpb + gl; j < rows; j += gridDim.x * gpb) {
         const int di = dst_idx ? dst_idx[j] : j;
         const int si = src_idx ? src_idx[j] : j;
-        if (KIND == 0 && tag_out && lane == 0) tag_out[j] = tags[j];
+        if (KIND == 0 && tag_out && lane == 0) {
+            const int32_t tag = tags[j];
+            tag_out[j] = tag;
+            if (tag_twin) tag_twin[j] = tag;
+        }
         if ((unsigned)di >= dst_rows || (unsigned)si >= src_rows) continue;   // never true for lists this library builds
         const V* __restrict__ s = reinterpret_cast<const V*>(src + (size_t)si * D);
         V* __restrict__ d = reinterpret_cast<V*>(dst + (size_t)di * D);
         // the evicted rows and the rows of an arrival block are read for the last time here: non-temporal loads keep them
         // from displacing the cached rows in the memory-side cache
-        for (int cidx = lane; cidx < nv; cidx += lpr) d[cidx] = KIND == 1 ? s[cidx] : nt_load_row(&s[cidx]);
+        for (int cidx = lane; cidx < nv; cidx += lpr) {
+            const V v = KIND == 1 ? s[cidx] : nt_load_row(&s[cidx]);
+            d[cidx] = v;
+            if (KIND == 0 && twin) reinterpret_cast<V*>(twin + (size_t)j * D)[cidx] = v;
+        }
     }
 }
 
@@ -63,7 +71,7 @@ __global__ __launch_bounds__(256) void k_fill_rows(RowArgs a) { fill_rows<VEC>(a
 
 int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, const int32_t* dst_idx, int64_t dst_rows,
                      const float* src, const int32_t* src_idx, int64_t src_rows, int64_t rows, int max_blocks, int32_t* tag_out,
-                     const int32_t* tags) {
+                     const int32_t* tags, float* twin, int32_t* tag_twin) {
     if (rows <= 0) return FC_OK;
     const int sh = shift_of(c->lpr);
     const int gpb = 256 >> sh;
@@ -71,7 +79,7 @@ int launch_copy_rows(fc_cache* c, hipStream_t s, int prof_item, float* dst, cons
     if (blocks > max_blocks) blocks = max_blocks;
     ProfScope ps(c, prof_item, s);
 #define FC_LAUNCH_ROWS(V, K) \
-    k_copy_rows<V, K><<<(unsigned)blocks, 256, 0, s>>>(dst, dst_idx, (unsigned)dst_rows, src, src_idx, (unsigned)src_rows, (int)rows, c->D, sh, tag_out, tags)
+    k_copy_rows<V, K><<<(unsigned)blocks, 256, 0, s>>>(dst, dst_idx, (unsigned)dst_rows, src, src_idx, (unsigned)src_rows, (int)rows, c->D, sh, tag_out, tags, twin, tag_twin)
 #define FC_LAUNCH_ROWS_V(K) \
     switch (c->vec) { case 4: FC_LAUNCH_ROWS(4, K); break; case 2: FC_LAUNCH_ROWS(2, K); break; default: FC_LAUNCH_ROWS(1, K); break; }
     if (prof_item == P_EVICT_GATHER) { FC_LAUNCH_ROWS_V(0) }

@@ -1,0 +1,20 @@
+"""`-m gpu`: planned batches with few rows to move: fetched on the index stream up to 1.5 MB (with the sort in the same launch up to
+10240 lookups), their victims stored into the landing block by the gather up to the same size (plain calls: 256 KB).  Sizes on
+either side of each border, blocks with and without room for the ranks behind the rows, both ways to run ahead."""
+import pytest
+
+from tests.parity import run_parity, run_parity_planned
+from tests.tiny_workload import TinyWorkload
+
+pytestmark = pytest.mark.gpu
+
+LIMIT, PLAIN_LIMIT = 3 << 19, 1 << 18
+
+
+@pytest.mark.parametrize("bags", [700, 10_240, 10_241, 30_000])
+@pytest.mark.parametrize("dim,distinct", [(5, 650), (128, LIMIT // 512 - 130), (128, LIMIT // 512 + 260), (130, PLAIN_LIMIT // 520 - 40), (130, PLAIN_LIMIT // 520 + 40)])
+@pytest.mark.parametrize("staging", [0, 300])
+def test_few_rows_to_move(bags, dim, distinct, staging):
+    w = TinyWorkload(num_rows=20 * distinct, dim=dim, cache_rows=distinct + 50, seed=bags + dim, multi_hot=False, bags=bags, distinct_cap=distinct)
+    run_parity_planned(w, 6, warm=True, dma_evict=True, inputs_ready=bags == 10_240, staging_rows=staging)
+    run_parity(w, 5, warm=True, dma_evict=True, staging_rows=staging, values_every=4)
