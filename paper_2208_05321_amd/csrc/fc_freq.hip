@@ -7,6 +7,7 @@
 #include <omp.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -22,50 +23,60 @@ struct fc_freq {
 
 namespace fc {
 
-constexpr int FQ_THREADS = 256;
-constexpr int FQ_ITEMS = 8;
-constexpr int FQ_HASH = 4096;      // twice the ids of a workgroup: open addressing always finds a free entry
-
-// counts[id] += occurrences.  Popular ids repeat thousands of times and same-address device atomics serialise,
-// so each workgroup first aggregates its 2048 ids in an LDS hash table and sends one atomic per distinct id.
-__global__ __launch_bounds__(FQ_THREADS) void k_freq_count(const int64_t* __restrict__ ids, int64_t n, int64_t N,
-                                                           int32_t* counts, uint32_t* flags) {
-    __shared__ int hkey[FQ_HASH];
-    __shared__ int hcnt[FQ_HASH];
-    for (int e = threadIdx.x; e < FQ_HASH; e += FQ_THREADS) { hkey[e] = -1; hcnt[e] = 0; }
+// counts[id] += occurrences.  Popular ids repeat thousands of times and device atomics on one address, or one cache line (the ids of a
+// small column are neighbours), queue up, so each workgroup first aggregates its ids in an LDS hash table and sends one atomic per distinct id.
+template <int NT, int ITEMS>
+__global__ __launch_bounds__(NT) void k_freq_count(const int64_t* __restrict__ ids, int64_t n, int64_t N,
+                                                   int32_t* counts, uint32_t* flags) {
+    constexpr int HASH = 2 * NT * ITEMS;           // twice the ids of a workgroup: open addressing always finds a free entry
+    constexpr int BITS = __builtin_ctz(HASH);
+    __shared__ int hkey[HASH];
+    __shared__ int hcnt[HASH];
+    const int64_t base = (int64_t)blockIdx.x * NT * ITEMS;
+    int64_t id[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t i = base + k * NT + threadIdx.x;
+        id[k] = i < n ? ids[i] : INT64_MAX;
+    }
+    for (int e = threadIdx.x; e < HASH; e += NT) { hkey[e] = -1; hcnt[e] = 0; }
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * FQ_THREADS * FQ_ITEMS;
     bool bad = false;
 #pragma unroll
-    for (int it = 0; it < FQ_ITEMS; ++it) {
-        const int64_t i = base + it * FQ_THREADS + threadIdx.x;
-        if (i < n) {
-            const int64_t id = ids[i];
-            if (id < 0 || id >= N) { bad = true; continue; }
-            const int k = (int)id;
-            unsigned h = ((unsigned)k * 2654435761u) >> 20;          // 12 bits
-            for (;;) {
-                const int prev = atomicCAS(&hkey[h], -1, k);
-                if (prev == -1 || prev == k) { atomicAdd(&hcnt[h], 1); break; }
-                h = (h + 1) & (FQ_HASH - 1);
-            }
+    for (int it = 0; it < ITEMS; ++it) {
+        if ((uint64_t)id[it] >= (uint64_t)N) { bad |= base + it * NT + threadIdx.x < n; continue; }
+        const int k = (int)id[it];
+        unsigned h = ((unsigned)k * 2654435761u) >> (32 - BITS);
+        for (;;) {
+            const int prev = atomicCAS(&hkey[h], -1, k);
+            if (prev == -1 || prev == k) { atomicAdd(&hcnt[h], 1); break; }
+            h = (h + 1) & (HASH - 1);
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < FQ_HASH; e += FQ_THREADS)
+    for (int e = threadIdx.x; e < HASH; e += NT)
         if (hkey[e] >= 0) atomicAdd(&counts[hkey[e]], hcnt[e]);
     if (bad) atomicOr(flags, EF_ID_RANGE);
 }
 
-__global__ __launch_bounds__(256) void k_max_i32(const int32_t* __restrict__ x, int64_t n, int32_t* out) {
-    __shared__ int red[4];
+// 16 bytes a lane, and few workgroups: each ends with an atomic on one address (10 M counters: 23 -> 9.5 us).
+__global__ __launch_bounds__(1024) void k_max_i32(const int32_t* __restrict__ x, int64_t n, int32_t* out) {
+    __shared__ int red[16];
     int m = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) m = max(m, x[i]);
+    const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * 1024, t = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    for (int64_t i = t; i < n4; i += stride) {
+        const int4 v = reinterpret_cast<const int4*>(x)[i];
+        m = max(max(m, max(v.x, v.y)), max(v.z, v.w));
+    }
+    if (t < n - 4 * n4) m = max(m, x[4 * n4 + t]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_down(m, o));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax(out, max(max(red[0], red[1]), max(red[2], red[3])));
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 16; ++k) m = max(m, red[k]);
+        atomicMax(out, m);
+    }
 }
 
 // sorted position r holds id inv[r]; the id's rank is r
@@ -167,7 +178,7 @@ static int freq_build_impl(fc_freq* f, int32_t* freq_rank_host, int32_t* inv_ran
     hipStream_t st = f->stream;
     uint32_t flags = 0;
     FC_HIP(hipMemsetAsync(f->maxc, 0, 4, st));
-    k_max_i32<<<1024, 256, 0, st>>>(f->counts, N, f->maxc);
+    k_max_i32<<<(unsigned)std::min<int64_t>(256, cdiv(N, 4096)), 1024, 0, st>>>(f->counts, N, f->maxc);
     int32_t maxc = 0;
     FC_HIP(hipMemcpyAsync(&maxc, f->maxc, 4, hipMemcpyDeviceToHost, st));
     FC_HIP(hipMemcpyAsync(&flags, f->flags, 4, hipMemcpyDeviceToHost, st));
@@ -252,7 +263,10 @@ int freq_add(fc_freq* f, const int64_t* ids_dev, int64_t n) {
     if (f->total + n > (int64_t)INT32_MAX) return FC_ERR_COUNT_OVERFLOW;
     f->total += n;
     FC_HIP(hipSetDevice(f->device));
-    k_freq_count<<<(unsigned)cdiv(n, FQ_THREADS * FQ_ITEMS), FQ_THREADS, 0, f->stream>>>(ids_dev, n, f->N, f->counts, f->flags);
+    // us a call, 2048 ids a workgroup / 4096 / 8192: 21 k ids 7.9 / 7.2 / 11.3, 65 k 14.0 / 9.7 / 12.8, 130 k 23 / 15 / 14, 426 k 65 / 40 / 28,
+    // 1.7 M 236 / 147 / 93: what grows is the number of workgroups that meet on the popular ids.
+    if (n <= 1 << 17) k_freq_count<1024, 4><<<(unsigned)cdiv(n, 4096), 1024, 0, f->stream>>>(ids_dev, n, f->N, f->counts, f->flags);
+    else k_freq_count<1024, 8><<<(unsigned)cdiv(n, 8192), 1024, 0, f->stream>>>(ids_dev, n, f->N, f->counts, f->flags);
     FC_HIP(hipGetLastError());
     return FC_OK;
 }

@@ -30,7 +30,9 @@ __device__ __forceinline__ int load_key(const int32_t* __restrict__ keys_in, int
     return keys_in[i];
 }
 
-template <int SRC>
+// ALIKE: most keys of a tile have the same digit (occurrence counts: most ids never occur, and the upper digits are alike).  Atomics on one
+// LDS counter queue up, so the lanes that share the first lane's digit are added up first (10 M keys: 37 -> 10 us).
+template <int SRC, bool ALIKE>
 __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restrict__ keys_in, int n, int limit, int shift,
                                                           int radix_bits, int nblk, int32_t* __restrict__ ghist,
                                                           int32_t* __restrict__ stot,
@@ -71,8 +73,16 @@ __global__ __launch_bounds__(RS_THREADS) void k_sort_hist(const int32_t* __restr
     for (int d = threadIdx.x; d < radix; d += RS_THREADS) h[d] = 0;
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it)
-        if (tile0 + it * RS_THREADS + (int)threadIdx.x < n) atomicAdd(&h[(key[it] >> shift) & mask], 1);
+    for (int it = 0; it < ITEMS; ++it) {
+        const bool valid = tile0 + it * RS_THREADS + (int)threadIdx.x < n;
+        const int d = (key[it] >> shift) & mask;
+        if (ALIKE) {
+            const int d0 = __builtin_amdgcn_readfirstlane(d);
+            const int same = __popcll(__ballot(valid && d == d0));
+            if (valid && d != d0) atomicAdd(&h[d], 1);
+            if ((threadIdx.x & 63) == 0) atomicAdd(&h[d0], same);
+        } else if (valid) atomicAdd(&h[d], 1);
+    }
     __syncthreads();
     for (int d = threadIdx.x; d < radix; d += RS_THREADS) {
         const int cnt = h[d];
@@ -320,9 +330,13 @@ static void launch_pass(const SortJob& j, hipStream_t st, const int32_t* kin, co
     {
         ProfScope ps(j.prof, P_SORT_HIST, st);
         const bool first = shift == 0 && j.stot_other && j.other_dirty > 0;
-        k_sort_hist<SRC><<<(unsigned)nblk, RS_THREADS, 0, st>>>(kin, j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : nullptr,
-                                                                     j.flags, j.rank_slot, j.slots_out,
-                                                                     first ? j.stot_other : nullptr, first ? (int)j.other_dirty : 0, j.status);
+#define FC_HIST(A) \
+        k_sort_hist<SRC, A><<<(unsigned)nblk, RS_THREADS, 0, st>>>(kin, j.n, j.limit, shift, rb, nblk, j.ghist, FUSED ? stot : nullptr, \
+                                                                   j.flags, j.rank_slot, j.slots_out, \
+                                                                   first ? j.stot_other : nullptr, first ? (int)j.other_dirty : 0, j.status)
+        if constexpr (!FUSED && (SRC == SORT_SRC_COUNTS || SRC == SORT_SRC_PAIRS)) { if (j.src == SORT_SRC_COUNTS) FC_HIST(true); else FC_HIST(false); }
+        else FC_HIST(false);
+#undef FC_HIST
     }
     if (!FUSED) {
         ProfScope ps(j.prof, P_SORT_SCAN, st);
