@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -122,11 +123,16 @@ static int freq_init(fc_freq* f, int64_t N, void* stream) {
 // Result arrays on their way to the caller's ordinary memory.  The runtime's own copy into such memory moves it through a
 // staging buffer with one thread, which also takes the page faults of arrays nobody has touched yet (10 M ints: 3.9 ms, 2.4 of
 // them the copy); here chunks land in two pinned buffers in turn and several threads carry them on, faults included, while
-// the next chunk crosses the link.  10 M rows, three arrays: build 14.4 -> 6.3 ms (2 MB chunks and 8 threads 8.3, 16 threads 9.1).
+// the next chunk crosses the link.  The threads are the bottleneck (40 MB: 0.9 ms of faults and 0.5 of copying, 0.7 on the link), so they
+// take faults while the GPU still counts and sorts.  10 M rows, counted, ranked and copied out: 6.7 -> 4.5 ms, 4 M 3.1 -> 1.85, 20 M 11.6 -> 8.0.
 struct CopyOut {
     static constexpr size_t CHUNK = 8u << 20;
+    struct Piece { char* dst; const char* src; size_t len; };
     char* pin[2] = {nullptr, nullptr};
     hipEvent_t ev[2] = {nullptr, nullptr};
+    int32_t* dst[3] = {};                      // the arrays, `bytes` long each, one after the other; sources are known later
+    const int32_t* src[3] = {};
+    size_t bytes = 0, arrays = 0, touched = 0;      // touched: bytes, all arrays in a row
     int threads = 1;
     bool ok = false;
 
@@ -148,23 +154,60 @@ struct CopyOut {
     CopyOut(const CopyOut&) = delete;
     CopyOut& operator=(const CopyOut&) = delete;
 
-    // Returns once dst is complete.
-    int copy(void* dst, const void* src, size_t bytes, hipStream_t st) {
-        const size_t chunks = (bytes + CHUNK - 1) / CHUNK;
-        for (size_t i = 0; i <= chunks; ++i) {
-            if (i < chunks) {
-                const size_t off = i * CHUNK, len = bytes - off < CHUNK ? bytes - off : CHUNK;
-                FC_HIP(hipMemcpyAsync(pin[i & 1], (const char*)src + off, len, hipMemcpyDeviceToHost, st));
+    size_t pieces() const { return arrays * cdiv(bytes, CHUNK); }
+    Piece piece(size_t i) const {
+        const size_t per = cdiv(bytes, CHUNK), a = i / per, off = i % per * CHUNK;
+        return {(char*)dst[a] + off, (const char*)src[a] + off, std::min(CHUNK, bytes - off)};
+    }
+
+    // Faults the next pages in, a block of 2 MB to a thread: where pages are that large, threads that met in one would each clear it.  One
+    // instruction reads a byte and writes it back, so that the first access is a write: a read would map the zero page, and the write after it
+    // fault again (arrays of 8 to 80 MB: 10 ms more).
+    void touch_some() {
+        constexpr size_t BLOCK = 2u << 20;
+        const size_t a = touched / bytes, off = touched % bytes;
+        char* const from = (char*)dst[a] + off;
+        char* const first = (char*)((uintptr_t)from & ~(uintptr_t)(BLOCK - 1));
+        char* const to = std::min((char*)dst[a] + bytes, first + threads * BLOCK);
+#pragma omp parallel for schedule(static, 1) num_threads(threads)
+        for (int t = 0; t < threads; ++t)
+            for (char* q = std::max(from, first + t * BLOCK); q < std::min(to, first + (t + 1) * BLOCK); q = (char*)(((uintptr_t)q & ~(uintptr_t)4095) + 4096))
+                __asm__ volatile("orb $0, %0" : "+m"(*q) : : "cc");
+        touched += to - from;
+    }
+
+    // Until what has been enqueued on st is done, pages are faulted in.
+    int wait_touching(hipStream_t st) {
+        FC_HIP(hipEventRecord(ev[0], st));
+        while (touched < arrays * bytes) {
+            const hipError_t q = hipEventQuery(ev[0]);
+            if (q == hipSuccess) return FC_OK;
+            (void)hipGetLastError();
+            if (q != hipErrorNotReady) return FC_ERR_HIP;
+            touch_some();
+        }
+        FC_HIP(hipEventSynchronize(ev[0]));
+        return FC_OK;
+    }
+
+    // Returns once every piece is where it belongs.
+    int run(hipStream_t st) {
+        for (size_t i = 0; i <= pieces(); ++i) {
+            if (i < pieces()) {
+                const Piece q = piece(i);
+                FC_HIP(hipMemcpyAsync(pin[i & 1], q.src, q.len, hipMemcpyDeviceToHost, st));
                 FC_HIP(hipEventRecord(ev[i & 1], st));
             }
             if (i > 0) {
-                const size_t off = (i - 1) * CHUNK, len = bytes - off < CHUNK ? bytes - off : CHUNK;
+                const Piece q = piece(i - 1);
+                const size_t per = cdiv(bytes, CHUNK), end = (i - 1) / per * bytes + (i - 1) % per * CHUNK + q.len;
+                while (touched < end) touch_some();
                 FC_HIP(hipEventSynchronize(ev[(i - 1) & 1]));
-                char* d = (char*)dst + off; const char* p = pin[(i - 1) & 1];
+                const char* p = pin[(i - 1) & 1];
 #pragma omp parallel for schedule(static) num_threads(threads)
                 for (int t = 0; t < threads; ++t) {
-                    const size_t a = len * t / threads, b = len * (t + 1) / threads;
-                    memcpy(d + a, p + a, b - a);
+                    const size_t a = q.len * t / threads, b = q.len * (t + 1) / threads;
+                    memcpy(q.dst + a, p + a, b - a);
                 }
             }
         }
@@ -175,55 +218,68 @@ constexpr size_t COPY_OUT_MIN = 8u << 20;      // 2 M rows: 2.2 -> 1.9 ms; below
 
 static int freq_build_impl(fc_freq* f, int32_t* freq_rank_host, int32_t* inv_rank_host, int32_t* counts_host) {
     const int64_t N = f->N;
+    const size_t bytes = (size_t)N * 4;
     hipStream_t st = f->stream;
+    std::unique_ptr<CopyOut> out;
+    if (bytes >= COPY_OUT_MIN) {                   // set up beside the counting
+        out.reset(new (std::nothrow) CopyOut());
+        if (out && !out->ok) out.reset();
+    }
     uint32_t flags = 0;
     FC_HIP(hipMemsetAsync(f->maxc, 0, 4, st));
     k_max_i32<<<(unsigned)std::min<int64_t>(256, cdiv(N, 4096)), 1024, 0, st>>>(f->counts, N, f->maxc);
+    FC_HIP(hipGetLastError());
     int32_t maxc = 0;
-    FC_HIP(hipMemcpyAsync(&maxc, f->maxc, 4, hipMemcpyDeviceToHost, st));
-    FC_HIP(hipMemcpyAsync(&flags, f->flags, 4, hipMemcpyDeviceToHost, st));
-    FC_HIP(hipStreamSynchronize(st));
-    if (flags & EF_ID_RANGE) return FC_ERR_ID_OUT_OF_RANGE;
-    int bits = 1;
-    while (((int64_t)1 << bits) <= maxc) ++bits;
-    const int64_t nblk = cdiv(N, RS_TILE);
-    int32_t* buf[4] = {nullptr, nullptr, nullptr, nullptr};
-    int32_t *ghist = nullptr, *dtot = nullptr, *rank = nullptr;
-    int rc = FC_OK;
-    auto cleanup = [&]() {
-        for (int32_t* p : buf) if (p) (void)hipFree(p);
-        if (ghist) (void)hipFree(ghist);
-        if (dtot) (void)hipFree(dtot);
-        if (rank) (void)hipFree(rank);
-    };
+    // (into pinned memory the copies do not hold the host up)
+    int32_t* word = out ? reinterpret_cast<int32_t*>(out->pin[1]) : nullptr;
+    FC_HIP(hipMemcpyAsync(word ? word : &maxc, f->maxc, 4, hipMemcpyDeviceToHost, st));
+    FC_HIP(hipMemcpyAsync(word ? (void*)(word + 1) : (void*)&flags, f->flags, 4, hipMemcpyDeviceToHost, st));
+    // One allocation: giving back a large one costs 0.25 ms, whatever its size (10 M rows, seven of them: 1.7 ms of 6.7).  The digit table
+    // is not known yet, so it is laid out for the most digits that a count of all ids so far could take.
+    int most = 1;
+    while (((int64_t)1 << most) <= f->total) ++most;
+    size_t table = 0;
+    for (int b = 1; b <= most; ++b) table = std::max(table, sort_table_ints(N, b));
+    const size_t part = (bytes + 255) & ~(size_t)255;
+    char* mem = nullptr;
     auto body = [&]() -> int {
-        for (int k = 0; k < 4; ++k) FC_HIP(hipMalloc((void**)&buf[k], (size_t)N * 4));
-        FC_HIP(hipMalloc((void**)&ghist, (size_t)(nblk << RS_MAX_BITS) * 4));
-        FC_HIP(hipMalloc((void**)&dtot, (size_t)(1 << RS_MAX_BITS) * 4));
-        FC_HIP(hipMalloc((void**)&rank, (size_t)N * 4));
+        FC_HIP(hipMalloc((void**)&mem, 4 * part + (table + (1 << RS_MAX_BITS)) * 4));
+        int32_t* buf[4];
+        for (int k = 0; k < 4; ++k) buf[k] = reinterpret_cast<int32_t*>(mem + k * part);
+        int32_t* const wanted[3] = {counts_host, inv_rank_host, freq_rank_host};
+        if (out) {
+            out->bytes = bytes;
+            for (int32_t* p : wanted) if (p) out->dst[out->arrays++] = p;
+            FC_TRY(out->wait_touching(st));
+            maxc = word[0]; flags = (uint32_t)word[1];
+        } else FC_HIP(hipStreamSynchronize(st));
+        if (flags & EF_ID_RANGE) return FC_ERR_ID_OUT_OF_RANGE;
+        int bits = 1;
+        while (((int64_t)1 << bits) <= maxc) ++bits;
         SortJob j;
         j.src = SORT_SRC_COUNTS; j.keys_in = f->counts; j.n = (int)N; j.limit = maxc; j.bits = bits;
-        j.keysA = buf[0]; j.valsA = buf[1]; j.keysB = buf[2]; j.valsB = buf[3]; j.ghist = ghist; j.dtot = dtot;
+        j.keysA = buf[0]; j.valsA = buf[1]; j.keysB = buf[2]; j.valsB = buf[3];
+        j.ghist = reinterpret_cast<int32_t*>(mem + 4 * part); j.dtot = j.ghist + table;
         const int32_t *ks, *vs;
         FC_TRY(radix_sort(j, st, &ks, &vs));       // stable: equal counts keep ascending id order
+        int32_t* rank = const_cast<int32_t*>(ks);  // the sorted keys have served
         k_rank_of<<<(unsigned)cdiv(N, 256), 256, 0, st>>>(vs, N, rank);
         FC_HIP(hipGetLastError());
-        const struct { int32_t* dst; const int32_t* src; } outs[3] = {{freq_rank_host, rank}, {inv_rank_host, vs}, {counts_host, f->counts}};
-        const size_t bytes = (size_t)N * 4;
-        if (bytes >= COPY_OUT_MIN) {
-            CopyOut out;                           // set up beside the kernels above
-            if (out.ok) {
-                for (const auto& o : outs) if (o.dst) FC_TRY(out.copy(o.dst, o.src, bytes, st));
-                FC_HIP(hipStreamSynchronize(st));
-                return FC_OK;
-            }
+        if (out) {
+            const int32_t* const from[3] = {f->counts, vs, rank};
+            for (int k = 0, a = 0; k < 3; ++k) if (wanted[k]) out->src[a++] = from[k];
+            FC_TRY(out->wait_touching(st));
+            return out->run(st);
         }
-        for (const auto& o : outs) if (o.dst) FC_HIP(hipMemcpyAsync(o.dst, o.src, bytes, hipMemcpyDeviceToHost, st));
+        if (freq_rank_host) FC_HIP(hipMemcpyAsync(freq_rank_host, rank, bytes, hipMemcpyDeviceToHost, st));
+        if (inv_rank_host) FC_HIP(hipMemcpyAsync(inv_rank_host, vs, bytes, hipMemcpyDeviceToHost, st));
+        if (counts_host) FC_HIP(hipMemcpyAsync(counts_host, f->counts, bytes, hipMemcpyDeviceToHost, st));
         FC_HIP(hipStreamSynchronize(st));
         return FC_OK;
     };
-    rc = body();
-    cleanup();
+    const int rc = body();
+    if (rc != FC_OK) (void)hipStreamSynchronize(st);       // nothing enqueued may still use what is given back
+    if (mem) (void)hipFree(mem);
     return rc;
 }
 

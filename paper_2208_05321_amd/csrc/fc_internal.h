@@ -441,6 +441,7 @@ struct SortJob {
     bool launched = false;                     // a job that went along with the rows (launch_rows_and_sort)
 };
 int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres);
+size_t sort_table_ints(int64_t n, int bits);   // ints of ghist for a job without supertile tables (max_bits 0)
 
 // ---- small batches (fc_small.hip) ----
 bool sort_small_fits(const SortJob& j);

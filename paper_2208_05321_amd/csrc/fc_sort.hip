@@ -389,6 +389,13 @@ static int run_passes(const SortJob& j, hipStream_t st, int passes, int rb, int3
     return FC_OK;
 }
 
+// passes with a scan kernel
+static int scan_passes(int bits, int two) { return bits <= 2 * two ? (bits + two - 1) / two : (bits + 7) / 8; }
+size_t sort_table_ints(int64_t n, int bits) {
+    const int passes = scan_passes(bits, RS_TWO_PASS_BITS);
+    return (size_t)cdiv(n, RS_TILE) << ((bits + passes - 1) / passes);
+}
+
 int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
     // Every pass is a chain of short launches bound by latency rather than by bytes.  Batches of up to FUSE_MAX_TILES
     // tiles take passes of at most 9 bits, each two launches (counts, then offsets and scatter in one kernel; the per-supertile
@@ -412,8 +419,7 @@ int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int
         if ((int64_t)(stot_pass * passes) > j.stot_cap) fused = false;
     }
     if (!fused) {
-        const int two = env_bits ? env_bits : RS_TWO_PASS_BITS;
-        passes = j.bits <= 2 * two ? (j.bits + two - 1) / two : (j.bits + 7) / 8;
+        passes = scan_passes(j.bits, env_bits ? env_bits : RS_TWO_PASS_BITS);
         rb = (j.bits + passes - 1) / passes;
     }
     int32_t* stot = fused ? j.stot : nullptr;
