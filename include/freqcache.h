@@ -112,8 +112,10 @@ enum {
                                Every other result is unchanged.  The call that moves the rows (cache_prepare,
                                cache_prepare_next, or cache_advance after cache_plan_next: what is dirty is only
                                known after the current batch's backward pass) then waits on the host once more, for
-                               the number of dirty victims; after cache_plan_next, bytes_d2h of cache_last_stats is
-                               final only once cache_advance has returned. */
+                               the number of dirty victims (cache_prepare does not with the default transmitter, nor
+                               with FC_EVICT_DMA while victims come out clean and no block is on its way; rows then
+                               change places in one kernel, and cache_last_stats waits for the number); after cache_plan_next, bytes_d2h of
+                               cache_last_stats is final only once cache_advance has returned. */
 };
 
 /* Static module + dynamic module set-up (Sections 4.2, 4.3).

@@ -107,6 +107,8 @@ static int reset_state(fc_cache* c, bool warm) {
     else FC_HIP(hipMemsetAsync(c->cache, 0, (size_t)c->C * c->D * 4, st));   // empty slots read as zeros
     FC_HIP(hipStreamSynchronize(st));
     c->last = fc_stats{};
+    c->dirty_parts = 0;
+    c->dirty_seen = 0;
     c->have_lists = false;
     return FC_OK;
 }
@@ -134,6 +136,7 @@ static void destroy(fc_cache* c) {
     for (auto& set : c->lists) for (int32_t* p : set) if (p) (void)hipFree(p);
     if (c->dirty) (void)hipFree(c->dirty);
     if (c->dcount) (void)hipFree(c->dcount);
+    if (c->dirty_words) (void)hipHostFree(c->dirty_words);
     if (c->dctl) (void)hipHostFree(c->dctl);
     for (int k = 0; k < 2; ++k) {
         if (c->arrive[k]) (void)hipFree(c->arrive[k]);
@@ -255,7 +258,7 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
     c->staging_rows = staging_rows;
     if (const char* e = getenv("FC_EVICT_BLOCKS")) { const int v = atoi(e); if (v >= 1 && v <= 4096) c->evict_blocks = v; }
     if (flags & FC_EVICT_DMA) c->fill_blocks = 40;
-    if (const char* e = getenv("FC_FILL_BLOCKS")) { const int v = atoi(e); if (v >= 1) c->fill_blocks = v; }
+    if (const char* e = getenv("FC_FILL_BLOCKS")) { const int v = atoi(e); if (v >= 1) c->fill_blocks = c->swap_blocks = v; }
     if (const char* e = getenv("FC_FILL_BLOCKS_EARLY")) { const int v = atoi(e); if (v >= 1) { c->fill_blocks_early = v; c->tune_early = false; } }
     if (const char* e = getenv("FC_FILL_BLOCKS_EARLY_START")) { const int v = atoi(e); if (v >= 1) c->fill_blocks_early = v; }   // still tuned
     c->fill_blocks_early_max = c->fill_blocks_early;
@@ -314,6 +317,10 @@ static int create(int64_t N, int32_t D, int64_t C, const int32_t* freq_rank, flo
         FC_HIP(hipMalloc((void**)&c->dcount, (size_t)cdiv(C, 1024) * 4));
         if (hipHostMalloc((void**)&c->dctl, 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); return FC_ERR_OOM_PINNED; }
         c->dctl[0] = c->dctl[1] = 0;
+        if (!(flags & FC_TRANSMIT_STAGED)) {
+            if (hipHostMalloc((void**)&c->dirty_words, (size_t)cdiv(C, 1024) * 8, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); c->dirty_words = nullptr; return FC_ERR_OOM_PINNED; }
+            memset(c->dirty_words, 0, (size_t)cdiv(C, 1024) * 8);
+        }
     }
     if (c->dma_evict) {
         for (int b = 0; b < DMA_BLOCKS; ++b) {
@@ -877,6 +884,7 @@ int cache_destroy(fc_cache* c) {
 
 int cache_last_stats(const fc_cache* c, fc_stats* out) {
     if (!c || !out) return FC_ERR_INVALID_ARG;
+    if (c->dirty_parts) FC_TRY(dirty_total(const_cast<fc_cache*>(c)));
     *out = c->last;
     return FC_OK;
 }

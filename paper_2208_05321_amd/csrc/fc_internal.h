@@ -101,12 +101,13 @@ inline hipStream_t no_stream() { return reinterpret_cast<hipStream_t>(~(uintptr_
 #define FC_DMA_BLOCKS 4
 #endif
 constexpr int DMA_BLOCKS = FC_DMA_BLOCKS;
-struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, transit_base = -1; bool arrived = false; };
+struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, transit_base = -1; bool arrived = false; bool clean_out = false; };   // clean_out: the lists name no clean victims any more
 // An index half that has been enqueued and whose decisions the host has not read yet.
 struct IndexRun {
     int32_t ticket = 0;
     int64_t n = 0, num_bags = 0;
     bool small = false, small_slots = false;
+    bool drop_clean = false;                    // a small batch's kernel has looked its victims' flags up
     int buf = 0, transit_base = -1;
 };
 struct PresortRec {
@@ -180,6 +181,7 @@ struct fc_cache {
     // 64 1216 / 460, 128 1191 / 471, 256 1201 / 452, 512 1223 / 458, 1024 1255 / 468 us a step.
     int fill_blocks = 256;          // 40 with FC_EVICT_DMA:
                                     // ~200 KB of reads in flight fill the link and still let the DMA engine's writes through
+    int swap_blocks = 256;          // and of the kernel in which rows change places
     int fill_blocks_early = 32;     // the same for rows fetched ahead of time by cache_plan_next (tuning: FC_FILL_BLOCKS_EARLY)
     int evict_blocks = 1024;        // workgroups of the host-table store kernel (store_block) (tuning: FC_EVICT_BLOCKS)
     int evict_early = 2;            // when that kernel starts (tuning: FC_EVICT_EARLY): 0 after the miss fill, under
@@ -233,6 +235,12 @@ struct fc_cache {
     int32_t* dcount = nullptr;      // dirty victims per tile of 1024 victims
     int32_t* dctl = nullptr;        // pinned: {dirty victims in all, ticket}
     int32_t dticket = 0;
+    // Plain calls whose rows change places (default transmitter; FC_EVICT_DMA: see drops_clean): the slot assignment looks the victims' flags
+    // up, and nobody waits for their number: every workgroup leaves its count in pinned memory, and who asks for bytes_d2h adds them up.
+    uint64_t* dirty_words = nullptr; // [slot tiles] dirty victims, and (high half) the call they belong to
+    int dirty_parts = 0;             // how many of them make up the latest call's bytes_d2h, not added up yet
+    int32_t dirty_ticket = 0;
+    int64_t dirty_seen = 0;          // dirty victims of the latest call that is known
     const int32_t* out_rank = nullptr;
     const int32_t* out_slot = nullptr;
 
@@ -356,7 +364,8 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
                   int64_t num_bags, int32_t* slots, MovePlan* mv, hipEvent_t before_slots = nullptr, bool defer_slots = false);
 int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids, int64_t n, const int64_t* offsets,
                  int64_t num_bags, int32_t* slots, bool write_slots, IndexRun* run, bool mark_emitted = true);   // mark_emitted: record ev_emit_done
-int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M);
+int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M, bool drop_clean = false);
+int dirty_total(fc_cache* c);               // bytes_d2h of the latest call, where its parts have not been added up yet
 int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv);
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n);
 int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, int64_t* send_rows = nullptr, SortJob* along = nullptr);
@@ -451,7 +460,7 @@ bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags);
 // slots == nullptr: the ranks go to rbuf and the slot write-out is left to the caller
 int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
                          int32_t* slots, int32_t ticket, const int32_t* landed_ranks, int64_t landed, int64_t landed_base,
-                         int transit_base);
+                         int transit_base, bool drop_clean);
 
 // ---- device helpers ----
 // bag of lookup i: the largest b with offsets[b] <= i
@@ -515,6 +524,11 @@ __device__ __forceinline__ int block_excl_scan(int v, int& total, int* lds /* NT
     __syncthreads();
     total = tot;
     return wbase + x - v;
+}
+
+// A count for the host, in pinned memory, with the number of the call it belongs to.
+__device__ __forceinline__ void post_count(uint64_t* word, int count, int ticket) {
+    __hip_atomic_store(word, (uint64_t)(uint32_t)count | (uint64_t)(uint32_t)ticket << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The planning record: lanes 0 .. HOST_REC_WORDS-1 of one wavefront store one word each, 64 consecutive bytes together.

@@ -561,7 +561,9 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_count(const int32_t* __re
 __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount,
                                                               int M, const int32_t* __restrict__ miss_ranks,
                                                               int32_t* __restrict__ fill_slots, int32_t* rank_slot,
-                                                              int32_t* __restrict__ old_rank, const int32_t* __restrict__ plan) {
+                                                              int32_t* __restrict__ old_rank, const int32_t* __restrict__ plan,
+                                                              uint8_t* dirty, uint64_t* __restrict__ dirty_words, int ticket) {
+    // dirty: a row that leaves without having been updated is dropped (old_rank -1); this tile's updated ones are counted
     // plan: the number of missing rows as the device knows it (the host has not seen it yet)
     if (plan) M = plan[PL_STATUS] == FC_OK ? plan[PL_MISS] : 0;
     __shared__ int lds[FREE_THREADS / 64];
@@ -569,21 +571,33 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank
     for (int g = threadIdx.x; g < (int)blockIdx.x; g += FREE_THREADS) part += tcount[g];
     int base;
     (void)block_excl_scan<FREE_THREADS>(part, base, lds);
-    if (base >= M) return;                                   // all missing rows were placed in lower tiles
+    if (base >= M) {                                         // all missing rows were placed in lower tiles
+        if (dirty && threadIdx.x == 0) post_count(dirty_words + blockIdx.x, 0, ticket);
+        return;
+    }
     const int s0 = blockIdx.x * FREE_TILE + threadIdx.x * FREE_PER;
     const unsigned m = empty_mask(slot_rank, s0, C);
     int tot;
-    int j = base + block_excl_scan<FREE_THREADS>(__popc(m), tot, lds);
+    int j = base + block_excl_scan<FREE_THREADS>(__popc(m), tot, lds), written = 0;
     for (int k = 0; k < FREE_PER; ++k) {
         if (!((m >> k) & 1u)) continue;
         if (j >= M) break;
         const int s = s0 + k;
         const int r = miss_ranks[j];
         fill_slots[j] = s;
-        if (old_rank) old_rank[j] = -2 - min(slot_rank[s], -1);     // rank of the row that leaves (-1: the slot was empty)
+        int leaves = -2 - min(slot_rank[s], -1);                    // rank of the row that leaves (-1: the slot was empty)
+        if (dirty && leaves >= 0) {
+            if (dirty[s]) { dirty[s] = 0; ++written; }
+            else leaves = -1;
+        }
+        if (old_rank) old_rank[j] = leaves;
         slot_rank[s] = r;
         rank_slot[r] = s;
         ++j;
+    }
+    if (dirty) {
+        (void)block_excl_scan<FREE_THREADS>(written, tot, lds);
+        if (threadIdx.x == 0) post_count(dirty_words + blockIdx.x, tot, ticket);
     }
 }
 
@@ -884,6 +898,35 @@ static int wait_for_record(const HostCtl* rec, int32_t ticket, hipStream_t st, i
     return FC_OK;
 }
 
+// FC_DIRTY_TRACK: see fc_cache::dirty_words
+int dirty_total(fc_cache* c) {
+    int64_t rows = 0;
+    for (int k = 0; k < c->dirty_parts; ++k) {
+        const volatile uint64_t* word = c->dirty_words + k;
+        FC_TRY(wait_for_ticket(reinterpret_cast<const volatile int32_t*>(word) + 1, c->dirty_ticket, c->stream));
+        rows += (int64_t)(uint32_t)*word;
+    }
+    if (c->dirty_parts) { c->last.bytes_d2h = rows * (int64_t)c->D * 4; c->dirty_seen = rows; }
+    c->dirty_parts = 0;
+    return FC_OK;
+}
+
+// Whether a plain call's rows change places, the clean ones among the victims being dropped (FC_DIRTY_TRACK).  With FC_EVICT_DMA only while
+// victims come out clean (serving) and no block is on its way: then there is nothing for the block and the host threads to do, and a row that
+// does turn out dirty may be stored in its place at once, because no older copy of it is still to arrive there.
+// us a step, victims sorted out by two kernels and the host waiting for their number / this: 426 k lookups of 128 columns 478 / 462, 63 k of 128 133 / 121,
+// 6.6 k of 128 55 / 44, 664 of 32 36 / 23; with FC_EVICT_DMA 30 k of 128 73 / 67, 135 of 10
+// 32 / 20, 1.6 M of 16 203 / 192.
+static bool drops_clean(fc_cache* c, hipStream_t st) {
+    if (!c->dirty_words || st != c->stream) return false;
+    if (!c->dma_evict) return true;
+    for (int64_t rows : c->blk_rows) if (rows > 0) return false;
+    bool there = true;               // the latest call's counts (nearly always: its kernels were enqueued a call ago)
+    for (int k = 0; k < c->dirty_parts && there; ++k) there = (int32_t)(*(const volatile uint64_t*)(c->dirty_words + k) >> 32) == c->dirty_ticket;
+    if (there && c->dirty_parts && dirty_total(c) != FC_OK) return false;
+    return c->dirty_seen == 0;
+}
+
 // Index half of Algorithm 1: every decision (unique rows, misses, victims, slot assignment, both maps, the slots
 // of the batch) and no row movement.  Fills *mv with what prepare_move has to do.
 int launch_slots_out(fc_cache* c, hipStream_t st, int32_t* slots, int64_t n) {
@@ -941,7 +984,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
             c->evict_pending = false;
         }
         FC_TRY(launch_prepare_small(c, st, ids, n, offsets, num_bags, small_slots ? slots : nullptr, ticket, landed_ranks, landed,
-                                    buf * c->staging_rows, transit));
+                                    buf * c->staging_rows, transit, run->drop_clean = drops_clean(c, st)));
     } else {
         const int64_t work = n > num_bags + 1 ? n : num_bags + 1;
         int64_t nmark;
@@ -1003,9 +1046,9 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
 }
 
 // j-th missing rank -> j-th empty slot.  M < 0: the host does not know yet how many there are.
-int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M) {
+int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M, bool drop_clean) {
     if (M == 0 || run.small) return FC_OK;
-    int32_t* old_rank = c->dma_evict ? nullptr : c->fill_src;
+    int32_t* old_rank = c->dma_evict && !drop_clean ? nullptr : c->fill_src;
     const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
     {
         ProfScope ps(c, P_FREE_COUNT, st);
@@ -1013,12 +1056,18 @@ int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M) {
     }
     ProfScope ps(c, P_FREE_PICK, st);
     k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
-                                              c->rank_slot, old_rank, M < 0 ? c->plan[c->lset] : nullptr);
+                                              c->rank_slot, old_rank, M < 0 ? c->plan[c->lset] : nullptr,
+                                              drop_clean ? c->dirty : nullptr, c->dirty_words, run.ticket);
     FC_HIP(hipGetLastError());
     return FC_OK;
 }
 
-// Wait for the decisions (status, counts) and take them over.
+// Wait for the decisions (status, counts) ...
+static int wait_index(fc_cache* c, hipStream_t st, const IndexRun& run) {
+    int32_t h[HOST_REC_WORDS];
+    return wait_for_record(c->hctl, run.ticket, st, h);
+}
+// ... and take them over.
 int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv) {
     int32_t h[HOST_REC_WORDS];
     FC_TRY(wait_for_record(c->hctl, run.ticket, st, h));
@@ -1028,6 +1077,7 @@ int index_result(fc_cache* c, hipStream_t st, const IndexRun& run, MovePlan* mv)
     c->last_one_per_bag = run.n == run.num_bags && !(h[HW_BATCH_FLAGS] & (int32_t)EF_NOT_ONE_PER_BAG);
     const int64_t M = h[HW_MISS], need = h[HW_NEED];
     mv->valid = true; mv->M = M; mv->need = need; mv->buf = run.buf; mv->transit_base = run.transit_base;
+    c->dirty_parts = 0;
     c->last.n_ids = run.n;
     c->last.n_unique = h[HW_UNIQUE];
     c->last.n_hit_unique = h[HW_UNIQUE] - M;
@@ -1047,8 +1097,16 @@ int prepare_index(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* id
     IndexRun run;
     const bool plain = st == c->stream;
     FC_TRY(index_launch(c, st, lookahead, ids, n, offsets, num_bags, slots, !defer_slots && !before_slots, &run));
+    // (a larger batch's by now: the emitting kernel has reported, and the latest call's counts come before it)
+    if (c->dirty_words && plain && !run.small) FC_TRY(wait_index(c, st, run));
+    const bool drop_clean = run.small ? run.drop_clean : drops_clean(c, st);
     FC_TRY(index_result(c, st, run, mv));
-    FC_TRY(index_assign(c, st, run, mv->M));
+    FC_TRY(index_assign(c, st, run, mv->M, drop_clean));
+    if (drop_clean) {
+        mv->clean_out = true;
+        c->dirty_parts = mv->M == 0 ? 0 : run.small ? 1 : (int)cdiv(c->C, FREE_TILE);
+        c->dirty_ticket = run.ticket;
+    }
     if (!plain) { FC_HIP(hipEventRecord(c->ev_assign_done, st)); c->decided = c->ev_assign_done; }
     // every row of the batch has its slot now: write the slots out
     if (before_slots) FC_HIP(hipStreamWaitEvent(st, before_slots, 0));
@@ -1082,7 +1140,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
     int64_t need = mv.need;                    // victims to write back
     const bool staged = (c->flags & FC_TRANSMIT_STAGED) != 0;
     c->out_rank = c->vrank; c->out_slot = c->vslot;
-    if (c->dirty_track && need > 0) {
+    if (c->dirty_track && !mv.clean_out && need > 0) {
         // keep the dirty victims only; their number decides the size of the copies below, so the host waits for it
         const bool dma_block = c->dma_evict && need <= c->staging_rows;
         int32_t* orank = dma_block ? c->vrank_buf[mv.buf] : c->lists[c->lset][5];
@@ -1095,7 +1153,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
         FC_HIP(hipGetLastError());
         const volatile int32_t* dv = reinterpret_cast<const volatile int32_t*>(c->dctl);
         FC_TRY(wait_for_ticket(dv + 1, ticket, st));
-        need = dv[0];
+        need = c->dirty_seen = dv[0];
         c->out_rank = orank; c->out_slot = oslot;
         c->last.bytes_d2h = need * (int64_t)c->D * 4;
     }
@@ -1105,7 +1163,7 @@ int prepare_move(fc_cache* c, hipStream_t st, const MovePlan& mv, bool ahead, in
         FC_HIP(hipStreamSynchronize(st));
     }
     // Default transmitter, rows straight from the host table: they change places with the victims in one kernel.
-    if (!staged && !c->dma_evict && !c->dirty_track && !mv.arrived) {
+    if (mv.clean_out || (!staged && !c->dma_evict && !c->dirty_track && !mv.arrived)) {
         FC_TRY(launch_swap_rows(c, st, M, along));                        // every victim's slot is among those that are filled
         FC_TRY(move_done(c, st, ahead));
         c->pf_dep = c->ev_move_done[c->lset];

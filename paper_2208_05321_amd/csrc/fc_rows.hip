@@ -115,8 +115,8 @@ int launch_swap_rows(fc_cache* c, hipStream_t s, int64_t rows, SortJob* along) {
     if (rows <= 0) return FC_OK;
     const int sh = shift_of(c->lpr);
     const RowArgs a{c->cache, c->fill_slots, (unsigned)c->C, c->host_dev, c->miss_ranks, (unsigned)c->N, c->fill_src, nullptr, 0, (int)rows, c->D, sh, 0, nullptr};
-    if (along) return launch_rows_and_sort(c, s, true, a, c->fill_blocks, along);
-    const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(rows, 256 >> sh), c->fill_blocks);
+    if (along) return launch_rows_and_sort(c, s, true, a, c->swap_blocks, along);
+    const unsigned blocks = (unsigned)std::min<int64_t>(cdiv(rows, 256 >> sh), c->swap_blocks);
     ProfScope ps(c, P_MISS_FILL, s);
     switch (c->vec) {
         case 4: k_swap_rows<4><<<blocks, 256, 0, s>>>(a); break;

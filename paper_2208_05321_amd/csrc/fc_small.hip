@@ -34,6 +34,7 @@ struct SmallArgs {
     int64_t N;
     int n, num_bags, C, words, landed, landed_base, transit_base, transit_rows, ticket, nfree;
     bool dma;
+    uint8_t* dirty; uint64_t* dirty_words;      // see k_free_assign; null: rows leave whether updated or not
 };
 
 // Words of a bitmap over one pair of 16-byte pieces (256 ranks).
@@ -66,7 +67,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     extern __shared__ __align__(16) uint32_t lds_bits[];
     __shared__ int part[SM_WAVES][2], before[SM_WAVES][2], holes[SM_WAVES];
     __shared__ uint32_t s_cand[8];
-    __shared__ int s_hits, s_used, s_threshold, s_queue, s_queue2;
+    __shared__ int s_hits, s_used, s_threshold, s_queue, s_queue2, s_dirty;
     __shared__ uint32_t s_flags;
     uint32_t* ub = lds_bits;                                                   // rows of this batch
     uint32_t* pre = ub + a.words;                                              // missing and (high half) evictable rows before
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     }
     const uint32_t async_flags = a.ctl->async_flags;
     for (int j = tid; j < a.words / 4; j += SM_THREADS) reinterpret_cast<uint4*>(ub)[j] = make_uint4(0, 0, 0, 0);
-    if (tid == 0) { s_hits = s_used = s_queue = s_queue2 = 0; s_flags = 0; s_threshold = 0x7fffffff; }
+    if (tid == 0) { s_hits = s_used = s_queue = s_queue2 = s_dirty = 0; s_flags = 0; s_threshold = 0x7fffffff; }
     // rows of the block that has reached the host table (fill_src below reads what this leaves; who else reads it meanwhile asks
     // only whether it is negative)
     for (int j = tid; j < a.landed; j += SM_THREADS) {
@@ -316,9 +317,18 @@ __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     for (int j = tid; j < M; j += SM_THREADS) {
         const int slot = a.fill_slots[j], rank = a.miss_ranks[j];
         // FC_EVICT_DMA: where the row's newest copy is (-1 the host table, <= -2 in transit); else the row that leaves the slot
-        a.fill_src[j] = a.dma ? a.rank_slot[rank] : a.slot_rank[slot];
+        int src = a.dma && !a.dirty ? a.rank_slot[rank] : a.slot_rank[slot];
+        if (a.dirty && src >= 0) {
+            if (a.dirty[slot]) { a.dirty[slot] = 0; atomicAdd(&s_dirty, 1); }
+            else src = -1;
+        }
+        a.fill_src[j] = src;
         a.slot_rank[slot] = rank;
         a.rank_slot[rank] = slot;
+    }
+    if (a.dirty) {
+        __syncthreads();
+        if (tid == 0) post_count(a.dirty_words, s_dirty, a.ticket);
     }
     if (a.slots_out) {
         __syncthreads();
@@ -358,7 +368,7 @@ bool prepare_small_fits(const fc_cache* c, int64_t n, int64_t num_bags) {
 
 int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_t n, const int64_t* offsets, int64_t num_bags,
                          int32_t* slots, int32_t ticket, const int32_t* landed_ranks, int64_t landed, int64_t landed_base,
-                         int transit_base) {
+                         int transit_base, bool drop_clean) {
     SmallArgs a;
     a.ids = ids; a.offsets = offsets; a.freq_rank = c->freq_rank;
     a.rbits4 = (uint4*)c->rbits; a.pbits4 = (uint4*)c->pbits;
@@ -369,6 +379,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
     a.landed_ranks = landed_ranks; a.landed = (int)landed; a.landed_base = (int)landed_base;
     a.ctl = c->ctl; a.hctl = c->hctl; a.plan = c->plan[c->lset]; a.N = c->N;
     a.n = (int)n; a.num_bags = (int)num_bags; a.C = (int)c->C; a.words = (int)(c->NB * RT_WORDS);
+    a.dirty = drop_clean ? c->dirty : nullptr; a.dirty_words = c->dirty_words;
     a.transit_base = transit_base; a.transit_rows = (int)c->staging_rows; a.ticket = ticket;
     const size_t lds = prepare_small_lds(c, n);
     ProfScope ps(c, P_REMAP_MARK, st);
