@@ -154,7 +154,11 @@ __global__ __launch_bounds__(256) void k_bag_fwd(const float* __restrict__ cache
 // kernel is left with writing the pooled output.  FWD_ROWS lookups per row-group are in flight together; a repeated
 // slot is simply loaded again (it hits the L1 / L2 of the same compute unit).
 constexpr int FWD_ROWS = 8;      // measured at config 4: 4 and 8 alike (188 us), 16 slower (203 us); ordinary stores instead of non-temporal ones 239 us
-template <int VEC>
+// Batches of fewer workgroups than this leave compute units idle, and what counts is how long one row-group takes: one lookup each.
+// us, eight / one: 163 lookups of 226 columns 9.4 / 3.5, 1024 of 16 columns 4.8 / 2.9, 14 k of 128 columns 8.0 / 4.7, 54 k of 64 columns (425 workgroups of eight) 8.5 / 5.3,
+// 426 k of 32 columns (1664) 18.7 / 19.6.
+constexpr int FWD_FEW = 1, FWD_FEW_BLOCKS = 1024;
+template <int VEC, int ROWS>
 __global__ __launch_bounds__(256) void k_bag_fwd_sorted(const float* __restrict__ cache, const int32_t* __restrict__ keys,
                                                         const int32_t* __restrict__ vals, int n, int num_bags, int C, int D,
                                                         int lpr_shift, float* __restrict__ out) {
@@ -163,21 +167,21 @@ __global__ __launch_bounds__(256) void k_bag_fwd_sorted(const float* __restrict_
     const int gpb = blockDim.x >> lpr_shift;
     const int gl = threadIdx.x >> lpr_shift, lane = threadIdx.x & (lpr - 1);
     const int nv = D / VEC;
-    for (int64_t i0 = (int64_t)(blockIdx.x * gpb + gl) * FWD_ROWS; i0 < n; i0 += (int64_t)gridDim.x * gpb * FWD_ROWS) {
-        int k[FWD_ROWS], b[FWD_ROWS];
+    for (int64_t i0 = (int64_t)(blockIdx.x * gpb + gl) * ROWS; i0 < n; i0 += (int64_t)gridDim.x * gpb * ROWS) {
+        int k[ROWS], b[ROWS];
 #pragma unroll
-        for (int j = 0; j < FWD_ROWS; ++j) {
+        for (int j = 0; j < ROWS; ++j) {
             const int64_t i = i0 + j < n ? i0 + j : n - 1;      // the tail repeats the last lookup (same value stored twice)
             k[j] = keys[i];
             b[j] = vals[i];
         }
         for (int cidx = lane; cidx < nv; cidx += lpr) {
-            V v[FWD_ROWS];
+            V v[ROWS];
 #pragma unroll
-            for (int j = 0; j < FWD_ROWS; ++j)     // a slot out of range was sorted under the key C: its bag reads as zeros
+            for (int j = 0; j < ROWS; ++j)     // a slot out of range was sorted under the key C: its bag reads as zeros
                 v[j] = (unsigned)k[j] < (unsigned)C ? reinterpret_cast<const V*>(cache + (size_t)k[j] * D)[cidx] : vzero(V());
 #pragma unroll
-            for (int j = 0; j < FWD_ROWS; ++j)
+            for (int j = 0; j < ROWS; ++j)
                 if ((unsigned)b[j] < (unsigned)num_bags) nt_store(&reinterpret_cast<V*>(out + (size_t)b[j] * D)[cidx], vadd(vzero(V()), v[j]));
         }
     }
@@ -200,14 +204,15 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
         for (PresortRec& r : c->rec) {
             if (r.valid && r.one_per_bag && r.ticket == c->cur_ticket && r.slots == slots && r.n == n && r.offsets == offsets && r.bags == num_bags) {
                 if (!r.caller_waited) { FC_HIP(hipStreamWaitEvent(c->stream, r.done, 0)); r.caller_waited = true; }
-                int64_t blocks = cdiv(n, (int64_t)gpb * FWD_ROWS);
-                if (blocks > (1 << 20)) blocks = 1 << 20;
+                const bool few = cdiv(n, (int64_t)gpb * FWD_ROWS) < FWD_FEW_BLOCKS;
+                const int64_t blocks = std::min<int64_t>(cdiv(n, (int64_t)gpb * (few ? FWD_FEW : FWD_ROWS)), 1 << 20);
                 ProfScope ps(c, P_BAG_FWD, c->stream);
-                switch (c->vec) {
-                    case 4: k_bag_fwd_sorted<4><<<(unsigned)blocks, 256, 0, c->stream>>>(c->cache, r.keys, r.vals, (int)n, (int)num_bags, (int)c->C, c->D, sh, out); break;
-                    case 2: k_bag_fwd_sorted<2><<<(unsigned)blocks, 256, 0, c->stream>>>(c->cache, r.keys, r.vals, (int)n, (int)num_bags, (int)c->C, c->D, sh, out); break;
-                    default: k_bag_fwd_sorted<1><<<(unsigned)blocks, 256, 0, c->stream>>>(c->cache, r.keys, r.vals, (int)n, (int)num_bags, (int)c->C, c->D, sh, out); break;
-                }
+#define FC_SORTED(V, R) k_bag_fwd_sorted<V, R><<<(unsigned)blocks, 256, 0, c->stream>>>(c->cache, r.keys, r.vals, (int)n, (int)num_bags, (int)c->C, c->D, sh, out)
+#define FC_SORTED_V(R) \
+                switch (c->vec) { case 4: FC_SORTED(4, R); break; case 2: FC_SORTED(2, R); break; default: FC_SORTED(1, R); break; }
+                if (few) { FC_SORTED_V(FWD_FEW) } else { FC_SORTED_V(FWD_ROWS) }
+#undef FC_SORTED_V
+#undef FC_SORTED
                 FC_HIP(hipGetLastError());
                 return FC_OK;
             }
@@ -259,7 +264,9 @@ __device__ __forceinline__ V join_pieces(V first, int a, int b, int lpr_shift, P
     for (; q <= b; q += JOIN) {
         V p[JOIN];
 #pragma unroll
-        for (int k = 0; k < JOIN; ++k) p[k] = q + k <= b ? piece(q + k) : vzero(V());
+        for (int k = 0; k < JOIN; ++k) p[k] = piece(min(q + k, b));
+#pragma unroll
+        for (int k = 1; k < JOIN; ++k) if (q + k > b) p[k] = vzero(V());
 #pragma unroll
         for (int k = 1; k < JOIN; ++k) p[0] = vadd(p[0], p[k]);
         if ((q & (span - 1)) == 0) { total = vadd(total, mid); mid = vzero(V()); }
@@ -281,12 +288,13 @@ __global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(
     const int gpb = blockDim.x >> lpr_shift;
     const int gl = threadIdx.x >> lpr_shift, lane = threadIdx.x & (lpr - 1);
     const int nv = D / VEC;
-    // LDS: keys[gpb*CHUNK], vals[gpb*CHUNK], meta[gpb], pieces[gpb][2][D]
+    // LDS: keys[gpb*CHUNK], vals[gpb*CHUNK], kinds[gpb], pieces[gpb][2][D]
     int* skeys = reinterpret_cast<int*>(smem);
     int* svals = skeys + gpb * CHUNK;
-    BwdMeta* smeta = reinterpret_cast<BwdMeta*>(svals + gpb * CHUNK);
-    float* spiece = reinterpret_cast<float*>(smeta + gpb);
+    int* smeta = svals + gpb * CHUNK;                       // kind of each chunk's first piece
+    float* spiece = reinterpret_cast<float*>(smeta + ((gpb + 3) & ~3));
     __shared__ BwdMeta blockmeta;
+    __shared__ uint64_t through[16], ending[16];     // chunks whose first piece lies inside a longer run, ends one begun earlier
 
     const int64_t blk0 = (int64_t)blockIdx.x * gpb * CHUNK;
     for (int t = threadIdx.x; t < gpb * CHUNK; t += blockDim.x) {
@@ -320,6 +328,16 @@ __global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(
                 for (int k = 0; k < BWD_PF; ++k) {
                     const int e = e0 + k;
                     ends[k] = false;
+                    if (CHUNK != BWD_CHUNK) {
+                        // few workgroups: straight-line loads (what lies past the chunk, or within a run, is loaded and not used), so that
+                        // all of them are requested before anything is waited for
+                        const int ec = min(e, cnt - 1), kk = mk[ec];
+                        const V* gp = &reinterpret_cast<const V*>(grad + (size_t)mv[ec] * D)[cidx];
+                        g[k] = STREAM ? nt_load(gp) : *gp;
+                        w[k] = reinterpret_cast<const V*>(cache + (size_t)min(kk, C - 1) * D)[cidx];
+                        ends[k] = (ec + 1 < cnt ? mk[ec + 1] : nextk) != kk;
+                        continue;
+                    }
                     g[k] = vzero(V()); w[k] = vzero(V());
                     if (e < cnt) {
                         const V* gp = &reinterpret_cast<const V*>(grad + (size_t)mv[e] * D)[cidx];
@@ -349,23 +367,45 @@ __global__ __launch_bounds__(CHUNK == BWD_CHUNK ? 256 : 1024) void k_bwd_reduce(
             }
         }
     }
-    if (lane == 0) smeta[gl] = BwdMeta{first_kind, has_head, head_slot, 0};
+    if (lane == 0) smeta[gl] = first_kind;
     __syncthreads();
+    for (int t = threadIdx.x; t < 64 * ((gpb + 63) / 64); t += blockDim.x) {       // whole wavefronts
+        const int kind = t < gpb ? smeta[t] : 0;
+        const uint64_t m2 = __ballot(kind == 2), m1 = __ballot(kind == 1);
+        if ((t & 63) == 0) { through[t >> 6] = m2; ending[t >> 6] = m1; }
+    }
+    __syncthreads();
+    // The last chunk of this workgroup with a piece of the run that goes on after chunk j; whether it ends there.  Read off bit masks: a walk
+    // from chunk to chunk took 0.1 us each, and a popular row's run spans dozens.  (us, loads in branches, the walk and pieces read one
+    // by one -> this, in chunks of 8: 1024 lookups of 16 columns 9.5 -> 7.2, 163 of 226 columns 8.8 -> 6.6, 55 k of 32 columns in bags 10.2 -> 6.6, 426 k of 32 columns 24.5 -> 21.7.)
+    auto last_piece = [&](int j, bool& closed) {
+        int q = j + 1;
+        closed = false;
+        while (q < gpb) {
+            const uint64_t others = ~through[q >> 6] >> (q & 63);
+            if (others) {
+                q += __ffsll((unsigned long long)others) - 1;
+                closed = q < gpb && ((ending[q >> 6] >> (q & 63)) & 1u);
+                break;
+            }
+            q = (q | 63) + 1;
+        }
+        return closed ? q : min(q, gpb) - 1;
+    };
     // join the pieces inside the workgroup, in chunk order (chunks past the end of the batch have no pieces)
     if (gl == 0 && first_kind != 0) {          // a run that entered from the previous workgroup
-        int kind = first_kind, j = 0;
-        while (kind == 2 && j + 1 < gpb && smeta[j + 1].first_kind != 0) { ++j; kind = smeta[j].first_kind; }
-        // chunks 0..j carry pieces of that run; kind says whether it ended (1) or leaves the workgroup (2)
+        bool closed = first_kind == 1;
+        const int j = closed ? 0 : last_piece(0, closed);
+        // chunks 0..j carry pieces of that run; it has ended or leaves the workgroup
         V* __restrict__ out = reinterpret_cast<V*>(part + (size_t)(blockIdx.x * 2) * D);
         for (int cidx = lane; cidx < nv; cidx += lpr) {
             out[cidx] = join_pieces<BWD_CHUNK / CHUNK>(pfirst[cidx], 0, j, lpr_shift, [&](int q) { return reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]; });
         }
-        if (lane == 0) blockmeta.first_kind = kind;
+        if (lane == 0) blockmeta.first_kind = closed ? 1 : 2;
     }
     if (has_head) {                             // a run that starts in this chunk and continues to the right
-        int j = gl, kind = 2;
-        while (kind == 2 && j + 1 < gpb && smeta[j + 1].first_kind != 0) { ++j; kind = smeta[j].first_kind; }
-        const bool closed = kind == 1;          // ended inside the workgroup
+        bool closed;                            // ended inside the workgroup
+        const int j = last_piece(gl, closed);
         V* __restrict__ out = reinterpret_cast<V*>(part + (size_t)(blockIdx.x * 2 + 1) * D);
         for (int cidx = lane; cidx < nv; cidx += lpr) {
             const V acc = join_pieces<BWD_CHUNK / CHUNK>(plast[cidx], gl, j, lpr_shift, [&](int q) { return reinterpret_cast<const V*>(spiece + (size_t)(q * 2) * D)[cidx]; });
@@ -576,7 +616,7 @@ static inline BwdGeom bwd_geometry(const fc_cache* c, int64_t n) {
     else if (cdiv(n, (int64_t)(g.threads / c->lpr) * BWD_SMALL_CHUNK) > bwd_small_blocks(c)) g.chunk = BWD_CHUNK;
     const int gpb = g.threads / c->lpr;                       // chunks per workgroup
     g.blocks = cdiv(n, (int64_t)gpb * g.chunk);
-    g.lds = (size_t)gpb * g.chunk * 8 + (size_t)gpb * sizeof(BwdMeta) + (size_t)gpb * 2 * c->D * 4;
+    g.lds = (size_t)gpb * g.chunk * 8 + (size_t)((gpb + 3) & ~3) * 4 + (size_t)gpb * 2 * c->D * 4;
     return g;
 }
 
