@@ -157,7 +157,7 @@ constexpr int FWD_ROWS = 8;      // measured at config 4: 4 and 8 alike (188 us)
 // Batches of fewer workgroups than this leave compute units idle, and what counts is how long one row-group takes: one lookup each.
 // us, eight / one: 163 lookups of 226 columns 9.4 / 3.5, 1024 of 16 columns 4.8 / 2.9, 14 k of 128 columns 8.0 / 4.7, 54 k of 64 columns (425 workgroups of eight) 8.5 / 5.3,
 // 426 k of 32 columns (1664) 18.7 / 19.6.
-constexpr int FWD_FEW = 1, FWD_FEW_BLOCKS = 1024;
+constexpr int FWD_FEW = 1, FWD_FEW_BLOCKS = 1024, FWD_FOUR_BLOCKS = 128;
 template <int VEC, int ROWS>
 __global__ __launch_bounds__(256) void k_bag_fwd_sorted(const float* __restrict__ cache, const int32_t* __restrict__ keys,
                                                         const int32_t* __restrict__ vals, int n, int num_bags, int C, int D,
@@ -218,7 +218,8 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
             }
         }
     }
-    const int bags_per_group = (n == num_bags && c->fwd_bags > 1) ? c->fwd_bags : 1;
+    // (few workgroups: a bag to a row-group, as in slot order; 3328 lookups of 64 columns, 52 workgroups of four bags, 33.9 -> 32.5 us a step)
+    const int bags_per_group = (n == num_bags && c->fwd_bags > 1 && cdiv(num_bags, (int64_t)gpb * c->fwd_bags) >= FWD_FOUR_BLOCKS) ? c->fwd_bags : 1;
     int64_t blocks = cdiv(num_bags, (int64_t)gpb * bags_per_group);
     if (blocks > (1 << 20)) blocks = 1 << 20;
     ProfScope ps(c, P_BAG_FWD, c->stream);
