@@ -26,6 +26,7 @@ constexpr int64_t ENQUEUE_MAX_IDS = 1 << 20;      // cache_plan_next enqueues ah
 constexpr int64_t ENQUEUE_MAX_FLOATS = 1 << 26;   // and larger batches of up to this many floats of rows
 constexpr int64_t FEW_BYTES = 4 << 20;            // bytes of missing rows up to which the host binds a planned step: plan_enqueued
 constexpr int64_t INLINE_BYTES = 3 << 19;         // bytes of missing rows up to which a planned step fetches them on the index stream: plan_enqueued
+constexpr int64_t ASSIGN_LIST_MOST = 4096;        // victims up to which slots are assigned from their list: index_assign
 constexpr int64_t LAND_BYTES = 1 << 18;           // bytes up to which a gathered block is stored into its landing block by the gather: lands_directly
 constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead, send_block
 // Radix sort of (slot, bag) pairs for the backward pass.
@@ -105,7 +106,7 @@ struct MovePlan { bool valid = false; int64_t M = 0, need = 0; int buf = 0, tran
 // An index half that has been enqueued and whose decisions the host has not read yet.
 struct IndexRun {
     int32_t ticket = 0;
-    int64_t n = 0, num_bags = 0;
+    int64_t n = 0, num_bags = 0, nfree = 0;     // nfree: empty slots before it
     bool small = false, small_slots = false;
     bool drop_clean = false;                    // a small batch's kernel has looked its victims' flags up
     int buf = 0, transit_base = -1;

@@ -558,7 +558,10 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_count(const int32_t* __re
     }
 }
 
-__global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount,
+// LIST: no slot was empty before, so the empty ones are the victims', and each tile picks its own, and counts those of the tiles below it, from the
+// list of victims: no kernel that counts them comes before.
+template <bool LIST>
+__global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount, const int32_t* __restrict__ vslot,
                                                               int M, const int32_t* __restrict__ miss_ranks,
                                                               int32_t* __restrict__ fill_slots, int32_t* rank_slot,
                                                               int32_t* __restrict__ old_rank, const int32_t* __restrict__ plan,
@@ -567,8 +570,23 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank
     // plan: the number of missing rows as the device knows it (the host has not seen it yet)
     if (plan) M = plan[PL_STATUS] == FC_OK ? plan[PL_MISS] : 0;
     __shared__ int lds[FREE_THREADS / 64];
+    __shared__ uint32_t bits[LIST ? FREE_TILE / 32 : 1];
     int part = 0;
-    for (int g = threadIdx.x; g < (int)blockIdx.x; g += FREE_THREADS) part += tcount[g];
+    if (LIST) {
+        if (threadIdx.x < FREE_TILE / 32) bits[threadIdx.x] = 0;
+        __syncthreads();
+        const int tile0 = blockIdx.x * FREE_TILE;
+        auto look = [&](int s) {
+            if (s < tile0) ++part;
+            else if (s < tile0 + FREE_TILE) atomicOr(&bits[(s - tile0) >> 5], 1u << (s & 31));
+        };
+        for (int v = threadIdx.x * 4; v < M; v += FREE_THREADS * 4) {
+            if (v + 4 <= M) {
+                const int4 q = *reinterpret_cast<const int4*>(vslot + v);
+                look(q.x); look(q.y); look(q.z); look(q.w);
+            } else for (int u = v; u < M; ++u) look(vslot[u]);
+        }
+    } else for (int g = threadIdx.x; g < (int)blockIdx.x; g += FREE_THREADS) part += tcount[g];
     int base;
     (void)block_excl_scan<FREE_THREADS>(part, base, lds);
     if (base >= M) {                                         // all missing rows were placed in lower tiles
@@ -576,7 +594,8 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank
         return;
     }
     const int s0 = blockIdx.x * FREE_TILE + threadIdx.x * FREE_PER;
-    const unsigned m = empty_mask(slot_rank, s0, C);
+    static_assert(FREE_TILE % 32 == 0 && FREE_PER == 4, "a thread's four bits lie in one word");
+    const unsigned m = LIST ? (bits[(threadIdx.x * FREE_PER) >> 5] >> ((threadIdx.x * FREE_PER) & 31)) & 15u : empty_mask(slot_rank, s0, C);
     int tot;
     int j = base + block_excl_scan<FREE_THREADS>(__popc(m), tot, lds), written = 0;
     for (int k = 0; k < FREE_PER; ++k) {
@@ -1040,7 +1059,7 @@ int index_launch(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
     // tiles, groups and hits) and the error word, which the next batch's first kernels write
     if (plain) c->due |= DUE_INDEX; else c->due &= ~DUE_INDEX;
     c->last_index_stream = st;
-    run->ticket = ticket; run->n = n; run->num_bags = num_bags;
+    run->ticket = ticket; run->nfree = c->nfree; run->n = n; run->num_bags = num_bags;
     run->small = small; run->small_slots = small_slots; run->buf = buf; run->transit_base = transit_base;
     return FC_OK;
 }
@@ -1050,14 +1069,21 @@ int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M, bo
     if (M == 0 || run.small) return FC_OK;
     int32_t* old_rank = c->dma_evict && !drop_clean ? nullptr : c->fill_src;
     const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
-    {
+    // From the list of victims while reading it costs each tile less than the kernel that it saves, and the host its launch (M < 0: as many as last
+    // time, most likely).  us, counting and assigning / assigning from the list: 11 victims of 935 k slots 6.9 / 4.3, 2.3 k of 5.7 k 6.2 / 5.4, 5.5 k of 60 k
+    // 6.8 / 7.3, 38 k of 150 k 8.8 / 20.
+    const bool list = run.nfree == 0 && (M < 0 ? c->last.n_miss : M) <= ASSIGN_LIST_MOST;
+    if (!list) {
         ProfScope ps(c, P_FREE_COUNT, st);
         k_free_count<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount);
     }
     ProfScope ps(c, P_FREE_PICK, st);
-    k_free_assign<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, (int)M, c->miss_ranks, c->fill_slots,
-                                              c->rank_slot, old_rank, M < 0 ? c->plan[c->lset] : nullptr,
-                                              drop_clean ? c->dirty : nullptr, c->dirty_words, run.ticket);
+#define FC_ASSIGN(L) \
+    k_free_assign<L><<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount, c->vslot, (int)M, c->miss_ranks, c->fill_slots, \
+                                                     c->rank_slot, old_rank, M < 0 ? c->plan[c->lset] : nullptr, \
+                                                     drop_clean ? c->dirty : nullptr, c->dirty_words, run.ticket)
+    if (list) FC_ASSIGN(true); else FC_ASSIGN(false);
+#undef FC_ASSIGN
     FC_HIP(hipGetLastError());
     return FC_OK;
 }
