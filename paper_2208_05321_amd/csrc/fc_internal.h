@@ -52,7 +52,6 @@ constexpr int SMALL_MAX_WORDS = 32768;            // rank bitmap in LDS: up to 1
 constexpr int SMALL_MAX_SLOTS = 65536;            // slot bitmap in LDS: 8 KB
 constexpr size_t SMALL_MAX_LDS = (160 << 10) - 1024;   // all of it, with room for what the kernel declares (4096 ids at the limits of both do not fit)
 constexpr int SMALL_SORT_IDS = 10240;             // the one-workgroup sort
-constexpr int SMALL_POS_BITS = 14, SMALL_KEY_BITS = 32 - SMALL_POS_BITS;
 
 // Sticky device-side flags.
 enum : uint32_t { EF_BAD_OFFSETS = 1u, EF_ID_RANGE = 2u, EF_BAD_SLOT = 4u,

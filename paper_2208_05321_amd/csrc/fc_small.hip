@@ -390,7 +390,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 
 // ---------------------------------------------------------------------------------------------------------
 // Stable sort of up to SMALL_SORT_IDS (slot, bag) pairs by slot in one workgroup: LSD passes of at most 8 bits on words that
-// hold key and lookup number together (a key of up to SMALL_KEY_BITS bits above SMALL_POS_BITS of position), exchanged
+// hold key and lookup number together (see pos_bits), exchanged
 // through LDS; the lookup number becomes its bag at the end.
 // Against the kernels of fc_sort.hip (us a training step, three schedules: backward sorts itself / plain / prepared ahead):
 // 5200 lookups 91, 112, 145 -> 81, 100, 99; 10101 97, 114, 141 -> 97, 100, 127; 15600 99, 117, 139 -> 122, 120, 131, hence
@@ -401,7 +401,7 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 struct SmallSort {
     const int32_t *keys_in, *rank_slot; int32_t* slots_out; const int64_t* offsets; const int32_t* status; uint32_t* flags;
     int32_t *keys_out, *vals_out;
-    int num_bags, one_per_bag, n, limit, passes, radix_bits;
+    int num_bags, one_per_bag, n, limit, passes, radix_bits, pos_bits;
 };
 
 __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
@@ -411,7 +411,7 @@ __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
     int32_t* __restrict__ slots_out = a.slots_out;
     int32_t* __restrict__ keys_out = a.keys_out;
     int32_t* __restrict__ vals_out = a.vals_out;
-    const int num_bags = a.num_bags, one_per_bag = a.one_per_bag, n = a.n, limit = a.limit, passes = a.passes, radix_bits = a.radix_bits;
+    const int num_bags = a.num_bags, one_per_bag = a.one_per_bag, n = a.n, limit = a.limit, passes = a.passes, radix_bits = a.radix_bits, pos_bits = a.pos_bits;
     // two arrays of rounds * SM_THREADS words, the digit counts, and each element's place within its wavefront and digit
     extern __shared__ __align__(16) uint32_t sm_words[];
     const int rounds = (n + SM_THREADS - 1) / SM_THREADS;  // elements per thread
@@ -448,7 +448,7 @@ __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
             if (rank_slot && !refused) slots_out[i] = key[k];
             if ((unsigned)key[k] >= (unsigned)limit) { bad = true; key[k] = limit; }
             other |= check && off[k] != i;
-            from[i] = ((uint32_t)key[k] << SMALL_POS_BITS) | (uint32_t)i;
+            from[i] = ((uint32_t)key[k] << pos_bits) | (uint32_t)i;
         }
     }
     if (refused) return;
@@ -458,7 +458,7 @@ __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
     int* mine = wc + w * radix;
 #pragma unroll 1
     for (int p = 0; p < passes; ++p) {
-        const int shift = SMALL_POS_BITS + p * radix_bits;
+        const int shift = pos_bits + p * radix_bits;
         for (int d = tid; d < SM_WAVES * radix; d += SM_THREADS) wc[d] = 0;
         __syncthreads();
         if (p == 0 && other) s_other = 1;
@@ -504,8 +504,8 @@ __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
 #pragma unroll 4
     for (int e = tid; e < n; e += SM_THREADS) {
         const uint32_t x = from[e];
-        const int i = (int)(x & ((1u << SMALL_POS_BITS) - 1));
-        keys_out[e] = (int)(x >> SMALL_POS_BITS);
+        const int i = (int)(x & ((1u << pos_bits) - 1));
+        keys_out[e] = (int)(x >> pos_bits);
         vals_out[e] = opb ? i : bag_of_lookup(offsets, num_bags, i);
     }
 }
@@ -522,17 +522,23 @@ __global__ __launch_bounds__(SM_THREADS) void k_rows_and_sort(RowArgs r, SmallSo
     else fill_rows<VEC>(r, blockIdx.x - 1, gridDim.x - 1);
 }
 
-static_assert(SMALL_SORT_IDS <= 1 << SMALL_POS_BITS, "a lookup's number has to fit");
+// A word holds key and lookup number: 18 bits of key at the limit of 10240 lookups, 20 at 4096, 22 at 1024.  (At a fixed split of 18 and 14, a small
+// batch with 2^18 or more slots took the general sort, six launches: us a step, 1444 lookups of 32 columns, 935 k slots 58 / 47.)
+static int pos_bits(int n) {
+    int b = 0;
+    while ((1 << b) < n) ++b;
+    return b;
+}
 
 bool sort_small_fits(const SortJob& j) {
-    return (j.src == SORT_SRC_SLOTS || j.src == SORT_SRC_RANKS) && j.n <= SMALL_SORT_IDS && j.bits <= SMALL_KEY_BITS && !j.max_bits && !j.no_fuse;
+    return (j.src == SORT_SRC_SLOTS || j.src == SORT_SRC_RANKS) && j.n <= SMALL_SORT_IDS && j.bits + pos_bits(j.n) <= 32 && !j.max_bits && !j.no_fuse;
 }
 
 static SmallSort small_sort(const SortJob& j, size_t* lds) {
     const int passes = (j.bits + 7) / 8, rb = (j.bits + passes - 1) / passes;
     *lds = 4 * (2 * (size_t)cdiv(j.n, SM_THREADS) * SM_THREADS + ((size_t)SM_WAVES << rb) + (size_t)cdiv(j.n, 2));
     return SmallSort{j.keys_in, j.src == SORT_SRC_RANKS ? j.rank_slot : nullptr, j.slots_out, j.offsets, j.status, j.flags, j.keysA, j.valsA,
-                     j.num_bags, j.one_per_bag && j.n == j.num_bags, j.n, j.limit, passes, rb};
+                     j.num_bags, j.one_per_bag && j.n == j.num_bags, j.n, j.limit, passes, rb, pos_bits(j.n)};
 }
 
 int sort_small(const SortJob& j, hipStream_t st, const int32_t** kres, const int32_t** vres) {
