@@ -76,7 +76,8 @@ enum {
                                Default (flag clear): kernels read / write the mapped pinned table
                                directly, one row-group of lanes per row.  Results are identical. */
     FC_EVICT_DMA = 4,       /* evicted rows only: the block leaves HBM by hipMemcpyAsync on the side stream (DMA
-                               engine, full duplex with the miss fill, no compute units involved) and library-owned
+                               engine, full duplex with the miss fill, no compute units involved; the few rows of a small
+                               batch are stored into the pinned block by the kernel that gathers them) and library-owned
                                host threads scatter it into the host table in the background (block transmitter of
                                Section 4.3 for the device -> host direction).  Misses are still read by kernels.
                                The host table is complete after cache_flush (or cache_check).  Number of threads:
