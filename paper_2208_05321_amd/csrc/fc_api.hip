@@ -466,7 +466,8 @@ static int wait_if_far_ahead(fc_cache* c, bool* landed) {
 
 // cache_plan_next: the planned batch's missing rows into the arrival block of its list set, on the stream pf
 // M < 0: the host does not know the number of rows yet, the kernel reads it (DMA evict transmitter, rows fetched by kernel)
-static int fetch_early(fc_cache* c, int64_t M) {
+// listed: the event that says which rows are missing and where their newest copies are
+static int fetch_early(fc_cache* c, int64_t M, hipEvent_t listed) {
     const int k = c->lset;
     if (!ensure_arrival_block(c, k)) return FC_OK;   // no room for the block: the rows are fetched at cache_advance instead
     if (c->miss_dma) {
@@ -481,7 +482,7 @@ static int fetch_early(fc_cache* c, int64_t M) {
     bool landed;
     FC_TRY(wait_if_far_ahead(c, &landed));
     if (c->tune_early) tune_fetch_grid(c, k, landed);
-    FC_HIP(hipStreamWaitEvent(c->pf, c->ev_emit_done, 0));       // which rows are missing and where their newest copies are
+    FC_HIP(hipStreamWaitEvent(c->pf, listed, 0));
     if (c->pf_dep) FC_HIP(hipStreamWaitEvent(c->pf, c->pf_dep, 0));
     if (c->dma_evict) {
         FC_HIP(hipEventRecord(c->ev_fetch_a[k], c->pf));
@@ -529,6 +530,13 @@ static int record_due_events(fc_cache* c) {
     return FC_OK;
 }
 
+// The most rows that a planned batch fetches on its index stream.  That it has few of them is a guess from the batch before; where many
+// come instead (a hot set that moves), they would hold up its sort and its own victims: plan_enqueued then fetches them on the stream
+// pf, once the host knows.  Twice what the guess goes by, since a batch just beyond it costs less here than a second launch.
+// us, the first batch of many after batches of few, on the index stream whatever their number / this / always on the stream pf:
+// 150 k rows of 64 columns 1640 / 1066 / 998, 300 k 3230 / 2070 / 1923, 40 k 532 / 389 / 370, 7 k of 128 columns (8 k lookups) 242 / 230 / 221.
+static int64_t inline_rows(const fc_cache* c) { return std::min(c->staging_rows, 2 * INLINE_BYTES / ((int64_t)c->D * 4)); }
+
 // The planned batch's missing rows into the arrival block of its list set, on the index stream itself, between the slots and the sort;
 // the event of the decisions then says that they are there, too.
 static int fetch_inline(fc_cache* c, hipStream_t st, SortJob* along) {
@@ -537,7 +545,7 @@ static int fetch_inline(fc_cache* c, hipStream_t st, SortJob* along) {
     bool landed;
     FC_TRY(wait_if_far_ahead(c, &landed));
     if (c->pf_dep) FC_HIP(hipStreamWaitEvent(st, c->pf_dep, 0));
-    FC_TRY(launch_fill_rows(c, st, c->staging_rows, c->arrive[k], c->staging_rows, c->fill_blocks, false, c->plan[k], along));
+    FC_TRY(launch_fill_rows(c, st, inline_rows(c), c->arrive[k], c->staging_rows, c->fill_blocks, false, c->plan[k], along));
     c->arrived_by[k] = c->decided;
     c->fetch_timed[k] = false;
     c->planned.arrived = true;
@@ -596,12 +604,12 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         if (inlined) fetched = fetch_inline(c, st, nullptr);
         FC_HIP(hipEventRecord(c->ev_assign_done, st));
         c->aux = st;
-        if (!few && !inlined) fetched = fetch_early(c, -1);
+        if (!few && !inlined) fetched = fetch_early(c, -1, c->ev_emit_done);
         if (early) FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         c->last_one_per_bag = guess;
         c->pst = st;
         sorted = presort_impl(c, slots, n, offsets, num_bags, slots);
-        if (few && !inlined) fetched = fetch_early(c, -1);
+        if (few && !inlined) fetched = fetch_early(c, -1, c->ev_emit_done);
         rc = index_result(c, st, run, &mv);
     }
     c->pst = c->stream;
@@ -614,9 +622,11 @@ static int plan_enqueued(fc_cache* c, const int64_t* ids, int64_t n, const int64
         FC_HIP(hipEventRecord(c->ev_pre_done, st));
         return rc;
     }
-    mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= c->staging_rows;
+    const int64_t most = inlined ? inline_rows(c) : c->staging_rows;
+    mv.arrived = arrived && fetched == FC_OK && mv.M > 0 && mv.M <= most;
     c->fetch_timed[c->lset] = c->fetch_timed[c->lset] && mv.arrived;
     c->planned = mv;
+    if (fetched == FC_OK && mv.M > most && mv.M <= c->staging_rows) fetched = fetch_early(c, mv.M, c->decided);
     c->pending_ticket = c->ticket;
     bool more = !at_once;                                         // work that ev_pre_done does not stand for yet
     if (sorted == FC_OK && guess && !c->last_one_per_bag) {        // its values are not the bags: once more
@@ -780,7 +790,7 @@ int cache_plan_next(fc_cache* c, const int64_t* ids_dev, int64_t n, const int64_
     // batch changes them; their newest copy is in the host table or in an evicted-row block (transit marks), and the
     // latest row movement, which produced both, is the only thing to wait for.  Victims leave, and these rows enter
     // their slots, at cache_advance.
-    if (mv.M > 0 && mv.M <= c->staging_rows) rc2 = fetch_early(c, mv.M);
+    if (mv.M > 0 && mv.M <= c->staging_rows) rc2 = fetch_early(c, mv.M, c->ev_emit_done);
     if (fold) {
         c->pst = c->pre;
         const int rs = presort_impl(c, slots_dev, n, offsets_dev, num_bags, slots_dev);
