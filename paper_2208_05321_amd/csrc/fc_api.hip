@@ -534,7 +534,7 @@ static int record_due_events(fc_cache* c) {
 // come instead (a hot set that moves), they would hold up its sort and its own victims: plan_enqueued then fetches them on the stream
 // pf, once the host knows.  Twice what the guess goes by, since a batch just beyond it costs less here than a second launch.
 // us, the first batch of many after batches of few, on the index stream whatever their number / this / always on the stream pf:
-// 150 k rows of 64 columns 1640 / 1066 / 998, 300 k 3230 / 2070 / 1923, 40 k 532 / 389 / 370, 7 k of 128 columns (8 k lookups) 242 / 230 / 221.
+// 150 k rows of 64 columns 1640 / 1000 / 1000, 300 k 3230 / 1915 / 1923, 40 k 532 / 370 / 370, 7 k of 128 columns (8 k lookups) 242 / 230 / 221.
 static int64_t inline_rows(const fc_cache* c) { return std::min(c->staging_rows, 2 * INLINE_BYTES / ((int64_t)c->D * 4)); }
 
 // The planned batch's missing rows into the arrival block of its list set, on the index stream itself, between the slots and the sort;

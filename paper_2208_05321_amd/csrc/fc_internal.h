@@ -27,6 +27,7 @@ constexpr int64_t ENQUEUE_MAX_FLOATS = 1 << 26;   // and larger batches of up to
 constexpr int64_t FEW_BYTES = 4 << 20;            // bytes of missing rows up to which the host binds a planned step: plan_enqueued
 constexpr int64_t INLINE_BYTES = 3 << 19;         // bytes of missing rows up to which a planned step fetches them on the index stream: plan_enqueued
 constexpr int64_t ASSIGN_LIST_MOST = 4096;        // victims up to which slots are assigned from their list: index_assign
+constexpr int64_t ASSIGN_LIST_WORDS = 1 << 25;    // and words of the list that all slot tiles together may come to read if there are more
 constexpr int64_t LAND_BYTES = 1 << 18;           // bytes up to which a gathered block is stored into its landing block by the gather: lands_directly
 constexpr float FAR_AHEAD_US = 150.f;             // an evicted block handed over longer ago and still on its way: wait_if_far_ahead, send_block
 // Radix sort of (slot, bag) pairs for the backward pass.

@@ -560,6 +560,7 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_count(const int32_t* __re
 
 // LIST: no slot was empty before, so the empty ones are the victims', and each tile picks its own, and counts those of the tiles below it, from the
 // list of victims: no kernel that counts them comes before.
+constexpr int LIST_LOADS = 8;
 template <bool LIST>
 __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank, int C, const int32_t* __restrict__ tcount, const int32_t* __restrict__ vslot,
                                                               int M, const int32_t* __restrict__ miss_ranks,
@@ -580,7 +581,17 @@ __global__ __launch_bounds__(FREE_THREADS) void k_free_assign(int32_t* slot_rank
             if (s < tile0) ++part;
             else if (s < tile0 + FREE_TILE) atomicOr(&bits[(s - tile0) >> 5], 1u << (s & 31));
         };
-        for (int v = threadIdx.x * 4; v < M; v += FREE_THREADS * 4) {
+        // (a list much longer than the guess it was chosen by is bound by the latency of its loads: several on their way at once; 80 k victims of 100 k
+        // slots 33 -> 18 us)
+        int v = threadIdx.x * 4;
+        for (; v - (int)threadIdx.x * 4 + LIST_LOADS * FREE_THREADS * 4 <= M; v += LIST_LOADS * FREE_THREADS * 4) {
+            int4 q[LIST_LOADS];
+#pragma unroll
+            for (int k = 0; k < LIST_LOADS; ++k) q[k] = *reinterpret_cast<const int4*>(vslot + v + k * FREE_THREADS * 4);
+#pragma unroll
+            for (int k = 0; k < LIST_LOADS; ++k) { look(q[k].x); look(q[k].y); look(q[k].z); look(q[k].w); }
+        }
+        for (; v < M; v += FREE_THREADS * 4) {
             if (v + 4 <= M) {
                 const int4 q = *reinterpret_cast<const int4*>(vslot + v);
                 look(q.x); look(q.y); look(q.z); look(q.w);
@@ -1071,8 +1082,12 @@ int index_assign(fc_cache* c, hipStream_t st, const IndexRun& run, int64_t M, bo
     const unsigned tiles = (unsigned)cdiv(c->C, FREE_TILE);
     // From the list of victims while reading it costs each tile less than the kernel that it saves, and the host its launch (M < 0: as many as last
     // time, most likely).  us, counting and assigning / assigning from the list: 11 victims of 935 k slots 6.9 / 4.3, 2.3 k of 5.7 k 6.2 / 5.4, 5.5 k of 60 k
-    // 6.8 / 7.3, 38 k of 150 k 8.8 / 20.
-    const bool list = run.nfree == 0 && (M < 0 ? c->last.n_miss : M) <= ASSIGN_LIST_MOST;
+    // 6.8 / 7.3, 4 k of 6 M 16 / 10, 4 k of 20 M 73 / 29.
+    // Every tile reads the whole list, so where the number is a guess what a wrong one could cost is bounded: 9 k victims of 935 k slots 9.5 / 9, 80 k of
+    // 100 k (7.8 M words) 10 / 18, 170 k of 180 k (30 M) 10 / 36, and beyond the limit 150 k of 1.5 M (220 M) 11 / 57.
+    const int64_t most = M < 0 ? std::min(run.n, c->C) : M;
+    const bool list = run.nfree == 0 && (M < 0 ? c->last.n_miss : M) <= ASSIGN_LIST_MOST &&
+                      (most <= 2 * ASSIGN_LIST_MOST || most * tiles <= ASSIGN_LIST_WORDS);
     if (!list) {
         ProfScope ps(c, P_FREE_COUNT, st);
         k_free_count<<<tiles, FREE_THREADS, 0, st>>>(c->slot_rank, (int)c->C, c->tcount);

@@ -27,3 +27,36 @@ def test_more_victims_than_the_batch_before_had():
 
     w = Uneven(num_rows=1_100_000, dim=8, cache_rows=20_000, seed=1, multi_hot=False, bags=60_000, distinct_cap=19_000)
     run_parity_planned(w, 8, warm=True, dma_evict=True)
+
+
+@pytest.mark.parametrize("rows,cache,bags,counted", [(300_000, 100_000, 250_000, False), (500_000, 200_000, 250_000, True), (2_500_000, 2_000_000, 8192, False), (2_500_000, 2_000_000, 20_000, True)])
+def test_a_wrong_guess_is_bounded(rows, cache, bags, counted):
+    """Planned batches after one of few victims: the list is read by every slot tile only while that stays bounded if there should be as many
+    victims as lookups or slots.  Either way the slots are the oracle's."""
+    import numpy as np
+    import torch
+    from paper_2208_05321_amd import FreqCache
+    few, many = 40, min(bags, cache) * 4 // 5
+
+    class Shift(TinyWorkload):
+        def batch(self, t):
+            ids = np.arange(bags) % (min(bags, cache) - many)
+            m, first = (many, cache + 10 * few) if t == 2 else (few, cache + t * few)
+            ids[:m] = first + np.arange(m)
+            return self.by_rank[ids].astype(np.int64), np.arange(bags + 1, dtype=np.int64)
+
+    w = Shift(num_rows=rows, dim=4, cache_rows=cache, seed=7, multi_hot=False, bags=bags)
+    w.by_rank = np.argsort(w.freq_rank)
+    run_parity_planned(w, 4, warm=True, dma_evict=True)
+    gpu = FreqCache(rows, 4, cache, w.freq_rank, dma_evict=True)
+    gpu.host_weight()[:] = 0
+    gpu.warm()
+    for t in range(3):
+        ids, off = (torch.from_numpy(x).cuda() for x in w.batch(t))
+        gpu.check()
+        gpu.profile(t > 0)
+        gpu.prepare(ids, off) if t == 0 else gpu.plan_next(ids, off)
+        gpu.advance()
+    rep = gpu.profile_report()
+    gpu.close()
+    assert rep["free_assign"]["launches"] == 1 and ("free_count" in rep) == counted, rep
