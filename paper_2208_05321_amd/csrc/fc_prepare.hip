@@ -783,11 +783,8 @@ static int evict_direct(fc_cache* c, int64_t need, int64_t* last_off, int64_t* l
     return FC_OK;
 }
 
-// DMA evict transmitter: wait until every handed-over block is in the host table and drop all transit marks
-// (afterwards the host table alone is current for every non-resident row, and all blocks are free).
-int dma_quiesce(fc_cache* c, hipStream_t st) {
-    if (!c->dma_evict) return FC_OK;
-    pool_wait(c, pool_published(c));
+// Every handed-over block is in the host table: no row is in transit any more.
+static int drop_transit_marks(fc_cache* c, hipStream_t st) {
     for (int b = 0; b < DMA_BLOCKS; ++b) {
         if (c->blk_rows[b] > 0) {
             k_clear_transit<<<(unsigned)cdiv(c->blk_rows[b], 256), 256, 0, st>>>(c->vrank_buf[b], (int)c->blk_rows[b],
@@ -796,6 +793,15 @@ int dma_quiesce(fc_cache* c, hipStream_t st) {
         }
     }
     FC_HIP(hipGetLastError());
+    return FC_OK;
+}
+
+// DMA evict transmitter: wait until every handed-over block is in the host table and drop all transit marks
+// (afterwards the host table alone is current for every non-resident row, and all blocks are free).
+int dma_quiesce(fc_cache* c, hipStream_t st) {
+    if (!c->dma_evict) return FC_OK;
+    pool_wait(c, pool_published(c));
+    FC_TRY(drop_transit_marks(c, st));
     // the index kernels of a later batch read and write the same map entries, possibly on another stream
     FC_HIP(hipEventRecord(c->ev_quiesce, st));
     c->quiesce_stream = st;
@@ -943,18 +949,22 @@ int dirty_total(fc_cache* c) {
 
 // Whether a plain call's rows change places, the clean ones among the victims being dropped (FC_DIRTY_TRACK).  With FC_EVICT_DMA only while
 // victims come out clean (serving) and no block is on its way: then there is nothing for the block and the host threads to do, and a row that
-// does turn out dirty may be stored in its place at once, because no older copy of it is still to arrive there.
+// does turn out dirty may be stored in its place at once, because no older copy of it is still to arrive there.  (Marks of blocks that have
+// arrived are dropped here: the ring of blocks, which drops them otherwise, comes to a halt with the last dirty victim.  Serving after some training with
+// the marks left in place / this: 30 k lookups of 128 columns 58 / 52.5 us a step, 3.3 k of 64 40 / 30, 664 of 32 34 / 24.5.)
 // us a step, victims sorted out by two kernels and the host waiting for their number / this: 426 k lookups of 128 columns 478 / 462, 63 k of 128 133 / 121,
 // 6.6 k of 128 55 / 44, 664 of 32 36 / 23; with FC_EVICT_DMA 30 k of 128 73 / 67, 135 of 10
 // 32 / 20, 1.6 M of 16 203 / 192.
 static bool drops_clean(fc_cache* c, hipStream_t st) {
     if (!c->dirty_words || st != c->stream) return false;
     if (!c->dma_evict) return true;
-    for (int64_t rows : c->blk_rows) if (rows > 0) return false;
     bool there = true;               // the latest call's counts (nearly always: its kernels were enqueued a call ago)
     for (int k = 0; k < c->dirty_parts && there; ++k) there = (int32_t)(*(const volatile uint64_t*)(c->dirty_words + k) >> 32) == c->dirty_ticket;
     if (there && c->dirty_parts && dirty_total(c) != FC_OK) return false;
-    return c->dirty_seen == 0;
+    if (c->dirty_seen != 0) return false;
+    bool marked = false;
+    for (int64_t rows : c->blk_rows) marked |= rows > 0;
+    return !marked || (pool_completed(c) == pool_published(c) && drop_transit_marks(c, st) == FC_OK);
 }
 
 // Index half of Algorithm 1: every decision (unique rows, misses, victims, slot assignment, both maps, the slots
