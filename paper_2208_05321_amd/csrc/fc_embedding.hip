@@ -627,6 +627,15 @@ static inline int64_t bwd_blocks_most(const fc_cache* c, int64_t n) {
     return std::max(std::min(cdiv(n, gpb * BWD_SMALL_CHUNK), bwd_small_blocks(c)), cdiv(n, gpb * BWD_CHUNK));
 }
 
+// A plain call's sort stays on the caller's stream: on another one it costs two waits for events that have not happened yet (10-15 us
+// of the host each, and a hop between hardware queues), and what it hides beside a saturated link it takes from the link.
+// us a step, on another stream beside the row movement / here: 14 k lookups of 128 columns 125 / 108, 54 k of 64 (FC_EVICT_DMA) 141 / 112, 266 k of 128
+// (FC_EVICT_DMA) 191 / 172, 852 k of 128 1201 / 1172.  Where rows change places on the caller's stream, a sort of more than 2^20 lookups is long enough
+// to pay for that (a step; a call waited for; the first pass): 1.06 M of 64 columns in bags of 20 545; 561; 587 / 557; 571; 579, 1.7 M of 128
+// 1129; 1130; 1153 / 1147; 1164; 1187, of 64 737; 755; 759 / 746; 762; 768, of 32 695; 714; 741 / 707; 720; 760.  With FC_EVICT_DMA it pays in the loop alone: 1.7 M of 128
+// columns 644; 828; 1166 / 655; 794; 1165, of 16 284; 352; 627 / 293; 327; 604.
+bool sorts_beside_rows(const fc_cache* c, int64_t n) { return !c->dma_evict && n > SORT_BESIDE_IDS; }
+
 // Called by cache_prepare / cache_prepare_next / cache_plan_next once the slots of the batch are on their way: the
 // sort needs nothing but the slots and the bag offsets, so that of a batch prepared ahead runs on a library stream (c->aux) while
 // the missing rows are still crossing the host link.  Two records alternate, so that the sort of the next batch does not
@@ -641,11 +650,7 @@ int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* of
     if (c->rec[k ^ 1].valid && c->rec[k ^ 1].ticket != c->cur_ticket) c->rec[k ^ 1].valid = false;
     if (!c->presort || n <= 0 || num_bags <= 0) return slots_out ? FC_ERR_INVALID_ARG : FC_OK;   // the caller then writes the slots out itself
     FC_TRY(ensure_sort(c->sb[k], n));
-    // A plain call's sort stays on the caller's stream: on another one it costs two waits for events that have not happened yet (10-15 us
-    // of the host each, and a hop between hardware queues), and what it hides beside a saturated link it takes from the link.
-    // us a step, on another stream beside the row movement / here: 14 k lookups of 128 columns 125 / 108, 54 k of 64 (FC_EVICT_DMA) 141 / 112, 266 k of 128
-    // (FC_EVICT_DMA) 191 / 172, 852 k of 128 1201 / 1172; of the tried ones only bags of 20 with 53 k missing rows of 64 columns lost (554 / 560).
-    const hipStream_t aux = c->pst == c->stream ? c->stream : c->aux;
+    const hipStream_t aux = c->pst == c->stream && !sorts_beside_rows(c, n) ? c->stream : c->aux;
     if (c->pst != aux) {
         FC_HIP(hipEventRecord(c->ev_slots, c->pst));
         FC_HIP(hipStreamWaitEvent(aux, c->ev_slots, 0));

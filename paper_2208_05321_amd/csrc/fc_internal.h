@@ -53,6 +53,7 @@ constexpr int SMALL_MAX_WORDS = 32768;            // rank bitmap in LDS: up to 1
 constexpr int SMALL_MAX_SLOTS = 65536;            // slot bitmap in LDS: 8 KB
 constexpr size_t SMALL_MAX_LDS = (160 << 10) - 1024;   // all of it, with room for what the kernel declares (4096 ids at the limits of both do not fit)
 constexpr int SMALL_SORT_IDS = 10240;             // the one-workgroup sort
+constexpr int64_t SORT_BESIDE_IDS = 1 << 20;      // lookups beyond which a plain call sorts beside the row movement: sorts_beside_rows
 
 // Sticky device-side flags.
 enum : uint32_t { EF_BAD_OFFSETS = 1u, EF_ID_RANGE = 2u, EF_BAD_SLOT = 4u,
@@ -298,8 +299,8 @@ struct fc_cache {
     int32_t* pmeta = nullptr;       // [groups][4]
     int64_t part_groups = 0;
 
-    // sort of the (slot, bag) pairs started with the batch's index work: on the caller's stream for a plain cache_prepare, else
-    // on the stream `aux` (one of the two above)
+    // sort of the (slot, bag) pairs started with the batch's index work: on the caller's stream for a plain cache_prepare (see
+    // sorts_beside_rows), else on the stream `aux` (one of the two above)
     bool presort = true;            // FC_NO_PRESORT clears it
     hipStream_t aux = nullptr;      // = pf, or pre when cache_plan_next indexes there (pf then fetches rows): the device
                                     // offers four hardware queues, so the library keeps to three streams of its own
@@ -379,6 +380,7 @@ int dma_quiesce(fc_cache* c, hipStream_t st);
 // to `slots_out` on its way (the slot write-out folded into the sort)
 // along: a sort that one workgroup can do is not launched but left in *along (n > 0 then): it goes along with the rows, or by sort_small
 int presort_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offsets, int64_t num_bags, int32_t* slots_out = nullptr, SortJob* along = nullptr);
+bool sorts_beside_rows(const fc_cache* c, int64_t n);     // a plain call's sort goes to a library stream
 bool mark_bytes(fc_cache* c);              // byte marks (allocates them on first use), else bit marks
 int ensure_rbuf(fc_cache* c, int64_t n);  // per-id rank buffer for batches of n ids
 int reserve_bwd(fc_cache* c, int64_t n);   // sort scratch of all three sets and the partial rows for batches of n lookups

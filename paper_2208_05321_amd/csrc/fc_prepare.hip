@@ -1278,7 +1278,8 @@ int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
                  int64_t num_bags, int32_t* slots) {
     MovePlan mv;
     // the slot write-out is folded into the first kernel of the sort, unless the index kernel of a small batch has them in registers
-    const bool fold = !lookahead && c->presort && n > 0 && num_bags > 0 && !prepare_small_fits(c, n, num_bags);
+    const bool beside = !lookahead && sorts_beside_rows(c, n);
+    const bool fold = !lookahead && !beside && c->presort && n > 0 && num_bags > 0 && !prepare_small_fits(c, n, num_bags);
     FC_TRY(prepare_index(c, st, lookahead, ids, n, offsets, num_bags, slots, &mv, nullptr, fold));
     if (lookahead) {
         if (n > 0) (void)presort_impl(c, slots, n, offsets, num_bags);   // on failure the backward pass sorts (and reports) itself
@@ -1287,14 +1288,15 @@ int prepare_impl(fc_cache* c, hipStream_t st, bool lookahead, const int64_t* ids
         FC_HIP(hipStreamWaitEvent(st, c->ev_s_now, 0));
         return prepare_move(c, st, mv, true);
     }
-    // The rows first: while they cross the link the host gets ahead of the GPU.  A sort for one workgroup goes along with them.
+    // The rows first: while they cross the link the host gets ahead of the GPU.  A sort for one workgroup goes along with them, one on
+    // another stream is under way before them.
     SortJob along;
     int64_t send_rows = 0;
-    const bool little = n <= SMALL_SORT_IDS;
+    const bool before = n <= SMALL_SORT_IDS || beside;
     int rs = FC_OK;
-    if (n > 0 && little) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr, &along);
+    if (n > 0 && before) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr, &along);
     FC_TRY(prepare_move(c, st, mv, false, &send_rows, along.n > 0 ? &along : nullptr));
-    if (n > 0 && !little) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr);
+    if (n > 0 && !before) rs = presort_impl(c, slots, n, offsets, num_bags, fold ? slots : nullptr);
     if (along.n > 0 && !along.launched) {
         const int32_t *keys, *vals;
         rs = sort_small(along, st, &keys, &vals);
