@@ -326,7 +326,10 @@ int freq_destroy(fc_freq* f);
 int table_reorder(const float* src_pinned, float* dst_pinned, const int32_t* inv_rank_host, int64_t num_rows,
                   int32_t dim, void* hip_stream);
 
-/* ---- per-kernel timing with HIP events on the handle's own streams (for the benchmark) ---- */
+/* ---- per-kernel timing with HIP events on the handle's own streams (for the benchmark) ----
+ * Each item stands for one kind of work.  While recording, what shares a launch otherwise is launched by itself: the sort of a small batch
+ * ("sort_scatter") apart from its missing rows ("miss_fill"), and with FC_EVICT_DMA the evicted block of a small batch crosses the
+ * link as a copy ("d2h_block"), as larger ones do, and not by the stores of its gather ("evict_gather").  Results are identical. */
 int cache_profile_enable(fc_cache* c, int32_t on);   /* on=1 starts recording, 0 stops; resets totals when turned on */
 int cache_profile_count(void);                        /* number of timed kernels / copies                               */
 const char* cache_profile_name(int32_t k);

@@ -574,7 +574,7 @@ static int sort_pairs(fc_cache* c, SortBufs& sb, hipStream_t st, const int32_t* 
     j.tail_stream = tail; j.tail_event = c->ev_sort_tail; j.last_stream = last;
     j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
     j.prof = c;
-    if (along) {
+    if (along && !c->prof_on) {                  // (a span stands for the sort, or for the rows)
         j.keysA = sb.keysA; j.valsA = sb.valsA;
         if (sort_small_fits(j)) {
             j.last_stream = nullptr;

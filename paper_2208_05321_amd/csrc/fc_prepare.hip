@@ -818,6 +818,7 @@ static bool ranks_travel_along(const fc_cache* c, int64_t need) { return need * 
 // fetched on the index stream), of 96 columns (2.1 MB) 107 / 114, of 128 columns (2.7 MB) 124 / 132; plain, 1024 lookups of 16 columns 60 / 46, 10 k of 32 columns (134 KB)
 // 83 / 79, 18 k of 64 columns (470 KB) 82 / 85.
 static bool lands_directly(const fc_cache* c, int64_t need, bool ahead) {
+    if (c->prof_on) return false;      // a span stands for the gather, or for the block's way over the link
     return ranks_travel_along(c, need) && need * (int64_t)c->D * 4 <= (ahead ? INLINE_BYTES : LAND_BYTES);
 }
 static int gather_block(fc_cache* c, int64_t need, int buf, bool ahead) {
