@@ -157,7 +157,11 @@ constexpr int FWD_ROWS = 8;      // measured at config 4: 4 and 8 alike (188 us)
 // Batches of fewer workgroups than this leave compute units idle, and what counts is how long one row-group takes: one lookup each.
 // us, eight / one: 163 lookups of 226 columns 9.4 / 3.5, 1024 of 16 columns 4.8 / 2.9, 14 k of 128 columns 8.0 / 4.7, 54 k of 64 columns (425 workgroups of eight) 8.5 / 5.3,
 // 426 k of 32 columns (1664) 18.7 / 19.6.
-constexpr int FWD_FEW = 1, FWD_FEW_BLOCKS = 1024, FWD_FOUR_BLOCKS = 128;
+constexpr int FWD_FEW = 1, FWD_FEW_BLOCKS = 1024;
+// In bag order, likewise, four bags to a row-group / one; us by the workgroups of four, 64 columns (16, 128 and 256 alike).  Rows in the caches: 32 4.9 / 2.7,
+// 128 3.8 / 2.8, 256 5.0 / 3.6, 512 5.1 / 3.8, 1024 5.6 / 5.1, 2048 8.9 / 8.7, 4096 16.0 / 17.2, 13312 45 / 52; rows from HBM: 32 4.8 / 4.1, 256 5.6 / 4.4,
+// 512 7.1 / 5.8, 1024 9.3 / 9.8, 2048 16.4 / 17.3, 13312 77 / 92.
+constexpr int FWD_FOUR_BLOCKS = 768;
 template <int VEC, int ROWS>
 __global__ __launch_bounds__(256) void k_bag_fwd_sorted(const float* __restrict__ cache, const int32_t* __restrict__ keys,
                                                         const int32_t* __restrict__ vals, int n, int num_bags, int C, int D,
@@ -218,7 +222,7 @@ int fwd_impl(fc_cache* c, const int32_t* slots, int64_t n, const int64_t* offset
             }
         }
     }
-    // (few workgroups: a bag to a row-group, as in slot order; 3328 lookups of 64 columns, 52 workgroups of four bags, 33.9 -> 32.5 us a step)
+    // (few workgroups: a bag to a row-group, as in slot order)
     const int bags_per_group = (n == num_bags && c->fwd_bags > 1 && cdiv(num_bags, (int64_t)gpb * c->fwd_bags) >= FWD_FOUR_BLOCKS) ? c->fwd_bags : 1;
     int64_t blocks = cdiv(num_bags, (int64_t)gpb * bags_per_group);
     if (blocks > (1 << 20)) blocks = 1 << 20;

@@ -45,3 +45,22 @@ def test_runs_of_many_chunks(dim, head, run):
     """`head` lookups of other rows, the long run, and a tail: 512 chunks of 8 with 8 columns, one workgroup or several."""
     ids = np.concatenate([np.arange(head), np.full(run, 20), 21 + np.arange(max(0, 4096 - head - run)) // 3]).astype(np.int64)
     _check(dim, ids, 1500)
+
+
+@pytest.mark.parametrize("dim,per_workgroup", [(256, 16), (50, 32), (16, 256)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_bag_order_on_either_side_of_the_rule(dim, per_workgroup, over):
+    """Serving without a sort: a bag to a row-group below 768 workgroups of four bags, four from there on."""
+    import torch
+    from paper_2208_05321_amd import FreqCache
+    n, rows = 767 * per_workgroup + over, 900
+    gpu = FreqCache(rows, dim, rows, np.arange(rows, dtype=np.int32), presort=False)
+    table = np.random.default_rng(dim).standard_normal((rows, dim)).astype(np.float32)
+    gpu.host_weight()[:] = table
+    gpu.warm()
+    ids = np.random.default_rng(n).integers(0, rows, n)
+    off_d = torch.arange(n + 1, device="cuda")
+    out = gpu.embedding_bag_fwd(gpu.prepare(torch.from_numpy(ids).cuda(), off_d), off_d)
+    assert np.array_equal(out.cpu().numpy(), table[ids])
+    gpu.check()
+    gpu.close()
