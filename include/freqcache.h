@@ -146,11 +146,12 @@ enum {
  * more, the first handle of a process on a device copies a few dozen blocks of up to 4 MB, about 20 ms, so that the runtime sets up
  * its copy engines here and not among the first training steps).
  * Tuning knobs, read from the environment at this call (defaults suit an MI355X on a PCIe Gen5 x16 link):
- *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256)
- *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch, fixed (default: starts at 32 and follows the
+ *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256), also where cache_plan_next fetches few rows (1.5 MB in
+ *                         the batch before, 3 MB at most) on its index stream
+ *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch on a stream of its own, fixed (default: starts at 32 and follows the
  *                         measured fetch / block-copy durations); FC_FILL_BLOCKS_EARLY_START only moves the start
- *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (without FC_EVICT_DMA: after cache_plan_next
- *                         or with FC_DIRTY_TRACK, otherwise rows change places in the miss fill; with it: more victims than staging_rows)
+ *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (without FC_EVICT_DMA: after cache_plan_next,
+ *                         or cache_prepare_next with FC_DIRTY_TRACK, otherwise rows change places in the miss fill; with it: more victims than staging_rows)
  *   FC_SCATTER_THREADS    host threads of FC_EVICT_DMA (8)
  *   FC_GATHER_THREADS     host threads of FC_MISS_DMA (6)
  *   FC_AHEAD_MISS_PCT     threshold of FC_INPUTS_READY (see there); 0 = never run ahead, 100 = always

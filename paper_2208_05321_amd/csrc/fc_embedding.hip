@@ -700,7 +700,7 @@ static int bwd_run(fc_cache* c, hipStream_t st, const int32_t* slots, int64_t n,
         j.limit = (int)c->C; j.bits = bits; j.flags = &c->ctl->async_flags;
         j.max_bits = c->sort_max_bits; j.no_fuse = c->sort_no_fuse;
         j.prof = prof;
-        FC_TRY(sort_in(j, sb, st, &kin, &vin));      // the scratch of the entry point that allocates nothing has no supertile tables: scan kernels there
+        FC_TRY(sort_in(j, sb, st, &kin, &vin));      // the scratch of the entry point that allocates nothing has no supertile tables: scan kernels beyond 32 tiles (65,536 lookups) there
     }
     const int sh = shift_of(c->lpr);
     if (c->dirty) k_mark_dirty<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(slots, (int)n, (int)c->C, c->dirty);

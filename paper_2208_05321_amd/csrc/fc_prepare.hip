@@ -753,7 +753,7 @@ bool mark_bytes(fc_cache* c) {
 
 // Evicted rows stored by kernel: gather into a device block on the caller's stream (so the slots can be refilled at once); the block
 // is stored into the mapped host table by a kernel on the side stream.  This is how victims leave where the exchange of
-// k_swap_rows does not apply: default transmitter with missing rows that were fetched ahead of time or with FC_DIRTY_TRACK, and
+// k_swap_rows does not apply: default transmitter with missing rows that were fetched ahead of time, or prepared ahead with FC_DIRTY_TRACK, and
 // FC_EVICT_DMA with more victims than a block holds.
 // Measured on MI355X: zero-copy stores that saturate the host link stall the other memory operations of the
 // compute units they run on and starve reads in the other direction, so such a store must not run under small

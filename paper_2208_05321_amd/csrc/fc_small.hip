@@ -61,7 +61,7 @@ __device__ __forceinline__ bool has_lane(uint64_t m) { return __builtin_amdgcn_i
 // times as long here.  The code is kept short: a workgroup that runs once fetches its instructions from memory, too.
 // What bounds it is the chain of dependent reads, a microsecond each, so a thread keeps its ids' ranks and slots in registers, what
 // other threads need goes through LDS wherever it fits, and what a later phase reads is requested before the phase in between.  1024 ids, 100 k rows, 1500 slots: 16.7 -> 10.9 us; 3328 ids,
-// 1 M rows, 15 k slots: 31.4 -> 21.6 (init 2.6, ids to marks 3.6, prefix counts 1.9, threshold 0.7, missing 1.0, slots 3.9, victims and empty
+// 1 M rows, 15 k slots: 31.4 -> 21.6 on one batch again and again, 24.0 in a serving loop (of the 21.6: init 2.6, ids to marks 3.6, prefix counts 1.9, threshold 0.7, missing 1.0, slots 3.9, victims and empty
 // slots 2.4, slots out 1.1, bitmaps 2.4).  A unit runs 16 wavefronts on four SIMDs, so 100 instructions for all are 0.7 us.
 __global__ __launch_bounds__(SM_THREADS) void k_prepare_small(SmallArgs a) {
     extern __shared__ __align__(16) uint32_t lds_bits[];
@@ -392,11 +392,12 @@ int launch_prepare_small(fc_cache* c, hipStream_t st, const int64_t* ids, int64_
 // Stable sort of up to SMALL_SORT_IDS (slot, bag) pairs by slot in one workgroup: LSD passes of at most 8 bits on words that
 // hold key and lookup number together (see pos_bits), exchanged
 // through LDS; the lookup number becomes its bag at the end.
-// Against the kernels of fc_sort.hip (us a training step, three schedules: backward sorts itself / plain / prepared ahead):
-// 5200 lookups 91, 112, 145 -> 81, 100, 99; 10101 97, 114, 141 -> 97, 100, 127; 15600 99, 117, 139 -> 122, 120, 131, hence
-// the limit: one compute unit orders about 400 pairs per microsecond and pass.
-// (Those figures are from before a wavefront's match of a digit came down to four instructions a bit and served for both counting
-// and placing, with no atomics on popular digits: 10101 lookups, 14-bit keys 35 -> 22 us.)
+// Against the kernels of fc_sort.hip (us, rows of 64 columns; those kernels / this).  Beside the missing rows (k_rows_and_sort), a training step, plain: 15 k slots
+// (two passes) 3 k lookups 59 / 45, 7 k 76 / 58, 10.1 k 86 / 67, 13.3 k 99 / 79; 200 k slots (three) 3 k 59 / 50, 7 k 65 / 61, 8.5 k 67 / 66, 10.1 k 69 / 70,
+// 13.3 k 73 / 79: the limit is where the two meet with three passes.  Planned ahead: 15 k slots 5.2 k 82-104 / 73-91, 10.1 k 85-114 / 83-84, 13.3 k 104-119 / 95; 200 k slots 5.2 k
+// 93-97 / 73-87, 10.1 k 98-101 / 77-83, 13.3 k 101-105 / 81-87.  A sort inside the backward call, that call alone: 15 k slots 3 k 26 / 19,
+// 7 k 27 / 24.6, 8.5 k 27.4 / 27, 10.1 k 27.7 / 28.6, 13.3 k 29 / 33; 200 k slots 3 k 27 / 21, 5.2 k 27.4 / 26.9, 7 k 28 / 29.5, 10.1 k 28.4 / 35.3, so that between
+// 9 k lookups (two passes) or 5.5 k (three) and the limit, which is the same for all, a backward call that sorts takes up to 7 us more than it could.
 // ---------------------------------------------------------------------------------------------------------
 struct SmallSort {
     const int32_t *keys_in, *rank_slot; int32_t* slots_out; const int64_t* offsets; const int32_t* status; uint32_t* flags;
@@ -513,7 +514,7 @@ __device__ __forceinline__ void sort_in_workgroup(const SmallSort& a) {
 __global__ __launch_bounds__(SM_THREADS) void k_sort_small(SmallSort a) { sort_in_workgroup(a); }
 
 // The sort in the first workgroup, rows on their way in the others: neither needs the other, the sort keeps one compute unit busy and the
-// rows the link.  (Every workgroup is given the sort's LDS and with it a compute unit of its own; the rows take 64 of them at most.)
+// rows the link.  (Every workgroup is given the sort's LDS, beyond some 7000 lookups more than half of a compute unit's; the rows take 64 workgroups at most.)
 // us a step, one launch after the other / this: 1024 lookups of 16 columns 36.5 / 32.5, 1157 of 128 columns 41.8 / 35.5, 163 of 226 columns 59 / 54.
 template <int VEC, bool SWAP>
 __global__ __launch_bounds__(SM_THREADS) void k_rows_and_sort(RowArgs r, SmallSort a) {

@@ -3,8 +3,8 @@
 // pass is in bounds for any keys, and by the time those on the side stream run, the word may belong to a later batch).
 // Used by the backward pass and the slot-order forward (sort lookups by slot, value = bag) and by the static-module
 // build (sort ids by descending count).  Keys come from one of four sources, see SortSrc.  A pass is either
-// count -> scan -> scatter (up to RS_MAX_BITS bits per digit) or, for batch-sized jobs with many key bits, count -> scatter
-// with per-supertile sums in place of the scan (see radix_sort for which is chosen when).
+// count -> scan -> scatter (up to RS_MAX_BITS bits per digit) or, for batch-sized jobs, count -> scatter: the scatter kernel adds the
+// tiles' counts up itself, beyond SS_TILES tiles with the help of per-supertile sums (see radix_sort for which is chosen when).
 #include "fc_internal.h"
 
 #include <stdlib.h>
@@ -415,8 +415,8 @@ int radix_sort(const SortJob& j, hipStream_t st, const int32_t** kres, const int
     // counts make the scan in between unnecessary; the caller supplies their table).  Up to 18 key bits that is two passes,
     // beyond three of 7 bits, which leave runs of 16 keys per digit and tile.  (Up to 18 bits a scan kernel per pass was kept
     // while a tile's 256 threads added its rows up 8 at a time; with 16 rows together, or with 8 of either kind by 512 threads as now,
-    // the two launches it costs decide: 53 k pairs 143 -> 138 us a step, 852 k 1207 -> 1196, 426 k the same.)  Larger jobs (the static module's ranking) and callers without
-    // a table keep the scan kernel: two passes up to 22 key bits, beyond that passes of at most 8 bits.
+    // the two launches it costs decide: 53 k pairs 143 -> 138 us a step, 852 k 1207 -> 1196, 426 k the same.)  Larger jobs (the static module's ranking) and, beyond
+    // SS_TILES tiles, callers without a table keep the scan kernel: two passes up to 22 key bits, beyond that passes of at most 8 bits.
     // (j.max_bits / j.no_fuse, from FC_SORT_BITS / FC_SORT_FUSED at cache_create, override this for experiments.)
     const int env_bits = (j.max_bits >= 4 && j.max_bits <= RS_TWO_PASS_BITS) ? j.max_bits : 0;
     const bool env_fused = !j.no_fuse;
