@@ -23,3 +23,27 @@ def test_counts_and_ranks(n, rows, skewed):
     order = np.argsort(-want, kind="stable")
     assert np.array_equal(counts, want) and np.array_equal(inv, order)
     assert np.array_equal(rank[order], np.arange(rows))
+
+
+def test_builds_of_one_pass():
+    """Counts of 11 bits on either side of 32 tiles: ranked in one pass on both, so that 65,536 rows do not take longer than 65,537."""
+    import time
+    import torch
+    from paper_2208_05321_amd import FreqCounter
+    best = {}
+    for rows in (65_537, 65_536):
+        ids = (rows ** np.random.default_rng(5).random(20_000)).astype(np.int64) - 1
+        fc = FreqCounter(rows)
+        fc.add(torch.from_numpy(ids).cuda())
+        fr, inv, cnt = fc.build(with_counts=True)
+        want = np.bincount(ids, minlength=rows)
+        assert 1024 <= want.max() < 2048 and np.array_equal(cnt, want)
+        assert np.array_equal(inv, np.argsort(-want, kind="stable")) and np.array_equal(fr[inv], np.arange(rows))
+        times = []
+        for _ in range(60):
+            a = time.perf_counter()
+            fc.build(with_counts=True)
+            times.append(time.perf_counter() - a)
+        best[rows] = min(times)
+        fc.close()
+    assert best[65_536] < 1.08 * best[65_537], best
