@@ -147,7 +147,7 @@ enum {
  * its copy engines here and not among the first training steps).
  * Tuning knobs, read from the environment at this call (defaults suit an MI355X on a PCIe Gen5 x16 link):
  *   FC_FILL_BLOCKS        workgroups of the miss fill (40 with FC_EVICT_DMA, else 256), also where cache_plan_next fetches few rows (1.5 MB in
- *                         the batch before, 3 MB at most) on its index stream
+ *                         the batch before, 3 MB at most) on its index stream (there up to 200 for rows that leave lanes idle)
  *   FC_FILL_BLOCKS_EARLY  workgroups of cache_plan_next's early row fetch on a stream of its own, fixed (default: starts at 32 and follows the
  *                         measured fetch / block-copy durations); FC_FILL_BLOCKS_EARLY_START only moves the start
  *   FC_EVICT_BLOCKS, FC_EVICT_EARLY   width and start of the host-table store kernel (without FC_EVICT_DMA: after cache_plan_next,

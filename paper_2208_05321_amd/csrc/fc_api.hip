@@ -537,6 +537,15 @@ static int record_due_events(fc_cache* c) {
 // 150 k rows of 64 columns 1640 / 1000 / 1000, 300 k 3230 / 1915 / 1923, 40 k 532 / 370 / 370, 7 k of 128 columns (8 k lookups) 242 / 230 / 221.
 static int64_t inline_rows(const fc_cache* c) { return std::min(c->staging_rows, 2 * INLINE_BYTES / ((int64_t)c->D * 4)); }
 
+// Workgroups of that fetch.  It is bound by the reads on their way over the link, so rows that leave lanes idle, or have them read 4 or 8 bytes, get
+// more of them, until as many bytes are on their way as fill_blocks workgroups of 16 bytes a lane have.  fill_blocks whatever the rows / this, us a
+// step and a call waited for: 60 k lookups of 33 columns 165; 200 / 124; 160 (on a stream of its own 143; 215), 30 k of 65 columns 162; 191 / 136; 161, 15 k of
+// 33 columns 107; 135 / 95; 115, 60 k of 9 columns 113; 136 / 110; 129; 30 k of 33 columns, by workgroups: 40 132, 100 122, 200 109, 300 129.
+static int inline_blocks(const fc_cache* c) {
+    const int floats = 256 / c->lpr * std::min(c->D, c->lpr * c->vec);       // on their way in one: 1024 at most
+    return std::min(c->fill_blocks * 1024 / floats, std::max(c->fill_blocks, 200));
+}
+
 // The planned batch's missing rows into the arrival block of its list set, on the index stream itself, between the slots and the sort;
 // the event of the decisions then says that they are there, too.
 static int fetch_inline(fc_cache* c, hipStream_t st, SortJob* along) {
@@ -545,7 +554,7 @@ static int fetch_inline(fc_cache* c, hipStream_t st, SortJob* along) {
     bool landed;
     FC_TRY(wait_if_far_ahead(c, &landed));
     if (c->pf_dep) FC_HIP(hipStreamWaitEvent(st, c->pf_dep, 0));
-    FC_TRY(launch_fill_rows(c, st, inline_rows(c), c->arrive[k], c->staging_rows, c->fill_blocks, false, c->plan[k], along));
+    FC_TRY(launch_fill_rows(c, st, inline_rows(c), c->arrive[k], c->staging_rows, inline_blocks(c), false, c->plan[k], along));
     c->arrived_by[k] = c->decided;
     c->fetch_timed[k] = false;
     c->planned.arrived = true;
